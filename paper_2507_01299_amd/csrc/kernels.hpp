@@ -47,7 +47,7 @@ struct Tuning {
   int fused_max_width = 16384;    // decoder layer: widest block input selected inside every projection workgroup
   int side_g = 0;             // workgroups of that adapter; 0 = by size (both jobs resident at once: at most 512 slots)
   int hinted = 1;             // decoder layer: 1 = the down projection takes its threshold from histograms that the gate|up launch builds
-  int contraction_tiles = 0;  // offline contractions: 0 = workgroup tile by size, 1 = 256 x 128, 2 = 256 x 256
+  int contraction_tiles = 0;  // offline contractions: 0 = workgroup tiles by size, 1 = 128 x 128, 2 = 256 x 256
 };
 Tuning& tuning();
 
@@ -192,7 +192,7 @@ struct ContractionArgs {
   float post_scale;
   int accumulate;           // C32 only: add to what is there
   int symmetric;            // A == B, M == N: compute tiles on or above the diagonal, store both halves
-  int tiles_m, tiles_n, patches_m, patches_n;   // filled in by launch_contraction
+  int tiles_m, tiles_n, tile0, tiles;           // filled in by launch_contraction
   long a_elements, b_elements;                  // extent of each operand over all its terms (filled in as well)
 };
 hipError_t launch_contraction(ContractionArgs a, bool a_kmajor, bool bf16, hipStream_t s);

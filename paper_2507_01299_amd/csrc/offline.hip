@@ -2,23 +2,30 @@
 // calibration tokens, the folded weights Q^T W and W Q, and the residual adapters Q_l^T Q_{l+1}.
 // All four are dense contractions  C[m,n] = sum_k A(k,m) B(k,n)  and share one kernel.
 //
-//  * v_mfma_f32_32x32x16 (f16 / bf16 inputs, fp32 accumulate).  A workgroup of 4 waves owns a 256 x 128
-//    tile of C, each wave a 128 x 64 quarter (4 x 2 instruction tiles, 128 accumulator registers): six
-//    operand reads from LDS feed eight instructions.  The global loads of k-tile i + 2 are in flight
-//    while tile i is multiplied and tile i + 1 moves from registers to the other LDS buffer.
-//  * Operands are stored k-major ([k][m], the layout of X, Q and W), the instruction wants 8 values
-//    along k per lane.  The transposition happens on the way into LDS: a lane loads 8 consecutive
-//    columns of two neighbouring k rows, pairs them into dwords (k, k+1) and writes them to a tile
-//    held as [column][k-pair] with an odd row stride (17 dwords), which makes both the transposing
-//    writes and the operand reads bank-conflict free.  The k-contiguous operand of W Q is copied as is.
+//  * v_mfma_f32_32x32x16 (f16 / bf16 inputs, fp32 accumulate).  A workgroup of 4 waves (one per SIMD) owns a
+//    256 x 256 tile of C, each wave a 128 x 128 quarter (4 x 4 instruction tiles, 256 accumulator registers): eight
+//    operand reads from LDS feed sixteen instructions, half the LDS traffic per flop of the 128 x 64 quarters that eight
+//    waves would own.
+//  * Global loads go straight into LDS (16 bytes per lane, no staging registers) and run three 32-deep k-tiles ahead of
+//    the products: four stages of 32 KiB, one barrier per k-tile, and the loads, the LDS reads and the products of a
+//    k-tile are issued in one fixed interleaved order.
+//  * Operands are stored k-major ([k][m], the layout of X, Q and W), the instruction wants 8 values along k per lane.
+//    The LDS tile keeps the memory's layout and the transposing LDS read does the rest: 16 lanes point at 4 rows x 16
+//    columns and receive 4 k-values of one column each.  A row's 64-byte granules are exchanged by its number
+//    (granule_swizzle; the permutation sits in the addresses of the global loads), so the rows of one read lie in
+//    different banks.  The k-contiguous operand of W Q is read as it is, with its 16-byte pieces exchanged likewise.
 //  * A rotation comes from an eigen-solver in fp32 or better; rounding it to 16 bits before the
 //    product would cost more than the 16-bit rounding of the folded weight itself.  It is therefore
 //    split into 2 (f16) or 3 (bf16) 16-bit terms whose sum carries the fp32 value, and the kernel
 //    adds the products of the listed term pairs into the same accumulators.
-//  * 32 concurrent workgroups of an XCD (workgroup i runs on XCD i % 8) form a 4 x 8 patch of tiles,
-//    so the operand panels they stream are shared through that XCD's L2.
-//  * X^T X is symmetric: tiles that lie entirely below the diagonal are not computed; their elements are
-//    stored by the tile that computes the mirrored position.
+//  * X^T X is symmetric: only tiles on and above the diagonal are computed; a tile above it is stored twice.
+//  * Whole rounds of 256 tiles (one per compute unit) run in 256 x 256 tiles; what is left over runs as 128 x 128 or 64 x 64
+//    parts in a second launch when that is shorter than another round (launch_shape).
+// What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
+// random operands reaches 1.63 PFLOP/s here (2.37 on zeros); the kernel issues 1.26 - 1.29 in whole rounds (4096 x 28672 x
+// 4096 bf16, 3 terms: 2.88 -> 2.22 ms; 5000 x 8192 second moment: 711 -> 338 us, of which 40 us the 16 tiles after the last
+// whole round, and the store of C in 16-byte pieces through LDS saved 45).  The design before it (8 waves of 128 x 64,
+// staging registers, two LDS stages) issued 0.98 and gave the XCDs of a symmetric product uneven shares.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -32,12 +39,13 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bfloat8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef short short4v __attribute__((ext_vector_type(4)));
 
-constexpr int kTileM = 256;        // C tile of a workgroup: 256 rows (A columns) x TN columns, TN = 128 or 256
 constexpr int kKTile = 32;         // k rows per LDS stage
-constexpr int kRowDwords = 17;     // 16 k-pairs + 1 pad: odd stride
-constexpr int kTileDwordsA = kTileM * kRowDwords;
-constexpr int kPatchM = 4, kPatchN = 8;
+// LDS stages: loads run kStages - 1 k-tiles ahead of the products (a k-tile of the smallest workgroup tile is multiplied
+// in a fraction of a memory round trip, so it looks further ahead)
+template <int MI> constexpr int kStagesOf = MI == 1 ? 8 : 4;
+constexpr int kBand = 4;           // tile rows of a band (see tile_of)
 
 template <typename T> struct Mfma;
 template <> struct Mfma<F16> {
@@ -52,41 +60,22 @@ template <> struct Mfma<BF16> {
   }
 };
 
-// Operand loads go through buffer resources that span the whole (multi-term) operand: a 16-byte load whose
-// offset lies at or beyond the operand's size returns zeros, so rows past Kd need no test, and a lane whose
-// columns lie outside the matrix carries the offset kOutside for good.  Per k-tile a load then costs one
-// add (lane offset + the tile's scalar offset) and no branch.
+// Operand loads go through buffer resources that span the whole (multi-term) operand: a 16-byte piece whose
+// offset lies at or beyond the operand's size arrives as zeros, so rows past Kd and columns outside the matrix
+// only need the offset kOutside.
 constexpr uint32_t kOutside = 0x80000000u;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_buffer(const uint16_t* p, long elements) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p), 0, static_cast<int>(elements * 2), 0x00027000);
+__device__ __forceinline__ u32x4 operand_buffer(const uint16_t* p, long elements) {
+  const uint64_t base = reinterpret_cast<uint64_t>(p);
+  return u32x4{static_cast<uint32_t>(base), static_cast<uint32_t>(base >> 32) & 0xFFFFu, static_cast<uint32_t>(elements * 2),
+               0x00027000u};
 }
 
-__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t buf, uint32_t lane_off, uint32_t tile_off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(buf, static_cast<int>(lane_off + tile_off), 0, 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-__device__ __forceinline__ void store_kmajor(uint32_t* tile, const uint4& r0, const uint4& r1, int g, int kp) {
-  const uint32_t a[4] = {r0.x, r0.y, r0.z, r0.w};
-  const uint32_t b[4] = {r1.x, r1.y, r1.z, r1.w};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    tile[(8 * g + 2 * q) * kRowDwords + kp] = __builtin_amdgcn_perm(b[q], a[q], 0x05040100u);       // a.lo | b.lo << 16
-    tile[(8 * g + 2 * q + 1) * kRowDwords + kp] = __builtin_amdgcn_perm(b[q], a[q], 0x07060302u);   // a.hi | b.hi << 16
-  }
-}
-
-__device__ __forceinline__ void store_kcontig(uint32_t* tile, const uint4& r, int row, int kq) {
-  uint32_t* p = tile + row * kRowDwords + 4 * kq;
-  p[0] = r.x; p[1] = r.y; p[2] = r.z; p[3] = r.w;
-}
-
-__device__ __forceinline__ u32x4 read_operand(const uint32_t* tile, int row, int dword0) {
-  const uint32_t* p = tile + row * kRowDwords + dword0;
-  u32x4 v;
-  v.x = p[0]; v.y = p[1]; v.z = p[2]; v.w = p[3];
-  return v;
+// 16 bytes per lane from buffer offset `off` straight to LDS: lane l's piece lands at byte lds_byte + 16 l.  Written as
+// an instruction because the compiler would wait for every outstanding load of this kind before each LDS read; the
+// pipeline below counts them itself.  (The load has no destination register.)
+__device__ __forceinline__ void load_to_lds(u32x4 buf, uint32_t lds_byte, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(off), "s"(buf));
 }
 
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
@@ -98,198 +87,292 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// One k-tile of both operands in a thread's registers: NA / NB 16-byte pieces of A / B.
-template <int NA, int NB>
-struct Staged {
-  uint4 a[NA];
-  uint4 b[NB];
-};
+typedef __attribute__((address_space(3))) char lds_char;
 
-// Is the 256 x TN tile that holds element (row, col) left out of a symmetric product?
-template <int TN>
-__device__ __forceinline__ bool tile_skipped(int row, int col) {
-  return TN * (col / TN + 1) <= kTileM * (row / kTileM);
+// One 64-byte granule (32 columns) of a k-major LDS tile is moved by its row: granule q of row k sits at
+// position q ^ granule_swizzle(k), so that the eight rows a transposing read touches lie in different banks.
+template <int GR>   // granules per row (a power of two)
+__device__ __forceinline__ int granule_swizzle(int k) { return ((k & 3) | (((k >> 3) & 1) << 2)) & (GR - 1); }
+
+// Workgroup barrier once all but the wave's N youngest loads have landed in LDS and its own LDS reads are done.
+template <int N>
+__device__ __forceinline__ void tile_landed() {
+  static_assert(N < 64, "vmcnt is a 6-bit field");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// A workgroup of NW waves owns a 256 x TN tile of C; every wave a 128 x 64 part (4 x 2 instruction tiles):
-// NW = 4, TN = 128 (two workgroups per compute unit) or NW = 8, TN = 256 (one).  The larger tile moves a third
-// fewer operand bytes from the L2 per flop, which is what bounds the product.
-template <typename T, bool A_KMAJOR, int TN, int NW>
-__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void contraction_kernel(ContractionArgs a) {
-  constexpr int NT = NW * 64;
-  constexpr int WN = NW / 2;                     // waves along n (two along m)
-  constexpr int NJ = TN / (32 * WN);             // 32-column instruction tiles of a wave along n
-  static_assert(NJ == 2, "a wave owns 128 x 64");
-  constexpr int GA = 32 * 16 / NT;               // 8-column groups of A per thread (k-major: two rows each)
-  constexpr int GB = (TN / 8) * 16 / NT;         // the same for B
-  constexpr int NA = 2 * GA, NB = 2 * GB;
-  constexpr int kTileN = TN;
-  constexpr int kTileDwordsB = TN * kRowDwords;
-  __shared__ uint32_t lds_a[2][kTileDwordsA];
-  __shared__ uint32_t lds_b[2][kTileDwordsB];
+// LDS writes of a wave before it are seen by its reads after it (the hardware keeps a wave's LDS accesses in order; this
+// keeps the compiler from moving a lane's read in front of another lane's write).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
-  // workgroup -> tile: 32 consecutive workgroups of one XCD take one 4 x 8 patch of tiles
-  const int xcd = blockIdx.x & 7;
-  const int local = blockIdx.x >> 3;
-  const int patch = (local >> 5) * 8 + xcd;
-  const int within = local & 31;
-  if (patch >= a.patches_m * a.patches_n) return;
-  const int tm = (patch / a.patches_n) * kPatchM + (within >> 3);
-  const int tn = (patch % a.patches_n) * kPatchN + (within & 7);
-  if (tm >= a.tiles_m || tn >= a.tiles_n) return;
-  const int m0 = tm * kTileM, n0 = tn * kTileN;
-  if (a.symmetric && tile_skipped<TN>(m0, n0)) return;
+// A tile of the product, as (row, column) of the grid of tiles.  Tiles are numbered band by band (kBand tile rows),
+// column by column inside a band; workgroup b takes number (b % 8) * ceil(tiles / 8) + b / 8, so an XCD
+// (workgroups b % 8) works on consecutive tiles: its 32 compute units on a patch of 4 x 8, sharing the panels of both
+// operands in their L2.  Symmetric products number the tiles on and above the diagonal only.
+struct TileAt { int m, n; };
+__device__ __forceinline__ TileAt tile_of(int number, int tiles_m, int tiles_n, bool symmetric) {
+  int band = 0;
+  for (;;) {
+    const int rows = min(kBand, tiles_m - band * kBand);
+    const int first = symmetric ? band * kBand : 0;          // first column of the band
+    const int head = symmetric ? rows * (rows - 1) / 2 : 0;  // tiles in the columns that meet the diagonal above its last row
+    const int cols = tiles_n - first - (symmetric ? rows - 1 : 0);
+    const int count = head + cols * rows;
+    if (number < count || (band + 1) * kBand >= tiles_m) {
+      if (number < head) {       // column c of the corner holds c + 1 tiles
+        int c = 0;
+        while (number > c) { number -= c + 1; ++c; }
+        return {band * kBand + number, first + c};
+      }
+      number -= head;
+      return {band * kBand + number % rows, first + (symmetric ? rows - 1 : 0) + number / rows};
+    }
+    number -= count;
+    ++band;
+  }
+}
 
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  constexpr int kGroupsPerPass = NT / 16;        // 8-column groups that the workgroup's threads cover at once
-  const int g = (lane & 7) + 8 * (w % (NW / 2));
-  const int kp = (lane >> 3) + 8 * (w / (NW / 2));
-  const int wm = w / WN, wn = w % WN;   // wave tile: rows wm * 128 .. + 127, columns wn * 64 .. + 63
+constexpr int kBigTile = 256;      // tiles are numbered in this size; smaller workgroup tiles are parts of them
 
-  float16v acc[4][NJ];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+// A workgroup of 4 waves (2 x 2) owns a (64 MI) x (64 MI) tile of C, a wave (32 MI) x (32 MI) of it.
+template <typename T, bool A_KMAJOR, int MI>
+__global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(ContractionArgs a) {
+  constexpr int TC = 64 * MI;                    // tile side
+  constexpr int kOperandBytes = TC * kKTile * 2; // one operand of one stage
+  constexpr int kStageBytes = 2 * kOperandBytes;
+  constexpr int CPR = TC / 8;                    // 16-byte pieces per row of a k-major tile
+  constexpr int RPI = 64 / CPR;                  // rows that one wave-load covers
+  constexpr int GR = 2 * MI;                     // granules per row
+  constexpr int kStages = kStagesOf<MI>;
+  constexpr int kParts = 4 / MI;                 // a 256 x 256 tile is kParts x kParts tiles of this kernel
+  __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes];
+
+  const int per_xcd = (a.tiles + 7) >> 3;
+  const int local = static_cast<int>(blockIdx.x & 7) * per_xcd + static_cast<int>(blockIdx.x >> 3);
+  if (local >= a.tiles) return;
+  const TileAt at = tile_of(a.tile0 + local / (kParts * kParts), a.tiles_m, a.tiles_n, a.symmetric != 0);
+  const int part = local % (kParts * kParts);
+  const int m0 = at.m * kBigTile + part / kParts * TC, n0 = at.n * kBigTile + part % kParts * TC;
+  if (m0 >= a.M || n0 >= a.N) return;            // a part of an edge tile that holds nothing (uniform)
+
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int wm = w >> 1, wn = w & 1;
 
   const int ktiles = (a.Kd + kKTile - 1) / kKTile;
   const int iters = ktiles * a.npairs;
 
-  // lane offsets (bytes) into the operands, fixed for the whole kernel
-  const __amdgpu_buffer_rsrc_t bufA = operand_buffer(a.A, a.a_elements);
-  const __amdgpu_buffer_rsrc_t bufB = operand_buffer(a.B, a.b_elements);
-  uint32_t offA[NA], offB[NB];
-  if (A_KMAJOR) {   // rows 2 kp, 2 kp + 1 of the k-tile, columns m0 + 8 (g + h * groups per pass) ..
+  // ---- loads, straight into LDS: wave-load q of wave w fills pieces 64 (4 q + w) .. + 63 of the operand's tile
+  const u32x4 bufA = operand_buffer(a.A, a.a_elements);
+  const u32x4 bufB = operand_buffer(a.B, a.b_elements);
+  uint32_t offA[MI], offB[MI];
+  int kA[MI], kB[MI];                            // k inside the tile of the lane's piece (its first k value)
 #pragma unroll
-    for (int h = 0; h < GA; ++h) {
-      const int c = m0 + 8 * (g + kGroupsPerPass * h);
-      offA[2 * h] = c < a.M ? static_cast<uint32_t>((2 * kp * a.M + c) * 2) : kOutside;
-      offA[2 * h + 1] = c < a.M ? offA[2 * h] + static_cast<uint32_t>(a.M * 2) : kOutside;
-    }
-  } else {          // row m0 + t / 4 + (NT / 4) r, k values 8 (t % 4) .. + 7 of the k-tile
-#pragma unroll
-    for (int r = 0; r < NA; ++r) {
-      const int m = m0 + (t >> 2) + (NT / 4) * r;
-      offA[r] = m < a.M ? static_cast<uint32_t>((m * a.Kd + 8 * (t & 3)) * 2) : kOutside;
-    }
-  }
-#pragma unroll
-  for (int h = 0; h < GB; ++h) {
-    const int c = n0 + 8 * (g + kGroupsPerPass * h);
-    offB[2 * h] = c < a.N ? static_cast<uint32_t>((2 * kp * a.N + c) * 2) : kOutside;
-    offB[2 * h + 1] = c < a.N ? offB[2 * h] + static_cast<uint32_t>(a.N * 2) : kOutside;
-  }
-
-  // iteration it = (term pair p, k-tile kt), kt fastest; the scalar offsets of its tile
-  int f_p = 0, f_kt = 0;
-  auto fetch = [&](Staged<NA, NB>& st) {
-    const int k0 = f_kt * kKTile;
-    const uint32_t ta = static_cast<uint32_t>((a.pa[f_p] * a.a_term_stride + (A_KMAJOR ? static_cast<long>(k0) * a.M : k0)) * 2);
-    const uint32_t tb = static_cast<uint32_t>((a.pb[f_p] * a.b_term_stride + static_cast<long>(k0) * a.N) * 2);
-    // rows of this k-tile at or past Kd are zero (with several terms the bytes behind a term are the next term's)
-    const int kr = a.Kd - k0;
-    const bool row0 = 2 * kp < kr, row1 = 2 * kp + 1 < kr;
+  for (int q = 0; q < MI; ++q) {
+    const int row = (4 * q + w) * RPI + lane / CPR, piece = lane % CPR;
+    const int src = piece ^ (4 * granule_swizzle<GR>(row));
+    kB[q] = row;
+    offB[q] = n0 + 8 * src < a.N ? static_cast<uint32_t>((row * a.N + n0 + 8 * src) * 2) : kOutside;
     if (A_KMAJOR) {
-#pragma unroll
-      for (int r = 0; r < NA; ++r) st.a[r] = load16(bufA, ((r & 1) ? row1 : row0) ? offA[r] : kOutside, ta);
+      kA[q] = row;
+      offA[q] = m0 + 8 * src < a.M ? static_cast<uint32_t>((row * a.M + m0 + 8 * src) * 2) : kOutside;
     } else {
-      // a row's k values past Kd belong to the next row: those lanes read outside instead
-      const bool in = k0 + 8 * (t & 3) < a.Kd;
-#pragma unroll
-      for (int r = 0; r < NA; ++r) st.a[r] = load16(bufA, in ? offA[r] : kOutside, ta);
-    }
-#pragma unroll
-    for (int r = 0; r < NB; ++r) st.b[r] = load16(bufB, ((r & 1) ? row1 : row0) ? offB[r] : kOutside, tb);
-    if (++f_kt == ktiles) { f_kt = 0; ++f_p; }
-  };
-  auto stash = [&](int buf, const Staged<NA, NB>& st) {
-    if (A_KMAJOR) {
-#pragma unroll
-      for (int h = 0; h < GA; ++h) store_kmajor(lds_a[buf], st.a[2 * h], st.a[2 * h + 1], g + kGroupsPerPass * h, kp);
-    } else {
-#pragma unroll
-      for (int r = 0; r < NA; ++r) store_kcontig(lds_a[buf], st.a[r], (t >> 2) + (NT / 4) * r, t & 3);
-    }
-#pragma unroll
-    for (int h = 0; h < GB; ++h) store_kmajor(lds_b[buf], st.b[2 * h], st.b[2 * h + 1], g + kGroupsPerPass * h, kp);
-  };
-  // one 16-deep half (s = 0, 1) of the k-tile in LDS buffer buf
-  auto compute_half = [&](int buf, int s) {
-    const uint32_t* At = lds_a[buf];
-    const uint32_t* Bt = lds_b[buf];
-    const int dw = s * 8 + (lane >> 5) * 4;
-    u32x4 av[4], bv[NJ];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) av[i] = read_operand(At, wm * 128 + i * 32 + (lane & 31), dw);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) bv[j] = read_operand(Bt, wn * 64 + j * 32 + (lane & 31), dw);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j] = Mfma<T>::run(av[i], bv[j], acc[i][j]);
-  };
-
-  // Tile it is computed from LDS buffer it & 1 while the loads of tile it + 2 are in flight and tile
-  // it + 1 (loaded one step earlier) moves from registers to the other buffer: one barrier per tile.
-  Staged<NA, NB> s0, s1;
-  fetch(s0);
-  stash(0, s0);
-  if (iters > 1) fetch(s1);
-  __syncthreads();
-  for (int it = 0; it < iters; it += 2) {
-    // (moving the stash between the two halves of the products, so that its writes complete behind matrix
-    // instructions, measured no faster)
-    if (it + 2 < iters) fetch(s0);
-    compute_half(0, 0);
-    compute_half(0, 1);
-    if (it + 1 < iters) stash(1, s1);
-    __syncthreads();
-    if (it + 1 < iters) {
-      if (it + 3 < iters) fetch(s1);
-      compute_half(1, 0);
-      compute_half(1, 1);
-      if (it + 2 < iters) stash(0, s0);
-      __syncthreads();
+      // [row m][32 k values]: four 16-byte pieces per row, piece p of row m holds k values 8 (p ^ (m / 4 % 4)) ..
+      const int m = (4 * q + w) * 16 + (lane >> 2);
+      kA[q] = 8 * ((lane & 3) ^ ((m >> 2) & 3));
+      offA[q] = m0 + m < a.M ? static_cast<uint32_t>(((m0 + m) * a.Kd + kA[q]) * 2) : kOutside;
     }
   }
+  const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)lds));
+  // The next k-tile to load: its first k, the stage it goes to and the byte offsets of its first element in the
+  // operands.  Past the last tile kr_left is 0: zeros are loaded, so that every step waits for the same count.
+  const uint32_t stepA = static_cast<uint32_t>((A_KMAJOR ? kKTile * a.M : kKTile) * 2), stepB = static_cast<uint32_t>(kKTile * a.N * 2);
+  int f_pair = 0, f_k = a.Kd, f_stage = 0;
+  uint32_t ta = static_cast<uint32_t>(a.pa[0] * a.a_term_stride * 2), tb = static_cast<uint32_t>(a.pb[0] * a.b_term_stride * 2);
+  uint32_t f_lds = lds_base + w * 1024;
+  auto fetch_piece = [&](int q) {                // q < MI: A, else B
+    if (q < MI) load_to_lds(bufA, f_lds + q * 4096, (kA[q & (MI - 1)] < f_k ? offA[q & (MI - 1)] : kOutside) + ta);
+    else load_to_lds(bufB, f_lds + kOperandBytes + (q - MI) * 4096, (kB[q & (MI - 1)] < f_k ? offB[q & (MI - 1)] : kOutside) + tb);
+  };
+  auto fetch_next = [&]() {
+    f_k -= kKTile;
+    ta += stepA;
+    tb += stepB;
+    if (f_k <= 0) {                              // the next term pair (uniform, once per pass over k)
+      ++f_pair;
+      if (f_pair < a.npairs) {
+        f_k = a.Kd;
+        ta = static_cast<uint32_t>(a.pa[f_pair] * a.a_term_stride * 2);
+        tb = static_cast<uint32_t>(a.pb[f_pair] * a.b_term_stride * 2);
+      } else {
+        f_k = 0;
+        ta = tb = 0;
+      }
+    }
+    f_stage = (f_stage + 1) & (kStages - 1);
+    f_lds = lds_base + f_stage * kStageBytes + w * 1024;
+  };
+  auto fetch = [&]() {
+#pragma unroll
+    for (int q = 0; q < 2 * MI; ++q) fetch_piece(q);
+    fetch_next();
+  };
 
-  // accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
-  // The tile indices are compile-time constants (static_for): a run-time index into the accumulator
-  // array would move all of it to scratch memory.
-  static_for<4 * NJ>([&](auto ij) {
-    constexpr int i = decltype(ij)::value / NJ;
-    constexpr int j = decltype(ij)::value % NJ;
-    const int n = n0 + wn * 64 + j * 32 + (lane & 31);
-    if (n < a.N) {
-      static_for<4>([&](auto r4c) {
-        constexpr int r4 = decltype(r4c)::value;
-        const int mb = m0 + wm * 128 + i * 32 + 8 * r4 + 4 * (lane >> 5);
-        float v[4] = {acc[i][j][r4 * 4 + 0] * a.post_scale, acc[i][j][r4 * 4 + 1] * a.post_scale,
-                      acc[i][j][r4 * 4 + 2] * a.post_scale, acc[i][j][r4 * 4 + 3] * a.post_scale};
-        if (a.C16) {
+  // ---- operand reads.  k-major tiles: lane (g, j) = (lane / 16, lane % 16) of a transposing read points at four
+  // columns of row 8 (g / 2) + j / 4 and receives column 16 (g % 2) + j of four rows.
+  const int g = lane >> 4, j = lane & 15;
+  const int rowk = 8 * (g >> 1) + (j >> 2);
+  const int inrow = 32 * (g & 1) + 8 * (j & 3);
+  const int sw = granule_swizzle<GR>(rowk);
+  int adrA[MI], adrB[MI];
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (mb + q < a.M) a.C16[static_cast<long>(mb + q) * a.N + n] = T::from_f32(v[q]);
-        } else {
+  for (int i = 0; i < MI; ++i) {
+    adrA[i] = A_KMAJOR ? rowk * (TC * 2) + ((wm * MI + i) ^ sw) * 64 + inrow
+                       : (wm * MI * 32 + i * 32 + (lane & 31)) * 64 + (((lane >> 5) ^ ((lane >> 2) & 3)) * 16);
+    adrB[i] = kOperandBytes + rowk * (TC * 2) + ((wn * MI + i) ^ sw) * 64 + inrow;
+  }
+  auto read_k = [&](int stage, int adr, int s) -> u32x4 {
+    const lds_char* p = (const lds_char*)lds + stage + adr + s * (16 * TC * 2);
+    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)p));
+    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(p + 4 * TC * 2)));
+    return u32x4{lo.x, lo.y, hi.x, hi.y};
+  };
+  // piece r < 2 MI of a 16-deep slice s: the operand of tile row / column r / 2, alternating A and B
+  auto read_piece = [&](int st, int s, int r, u32x4 (&av)[MI], u32x4 (&bv)[MI]) {
+    const int i = r >> 1;
+    if (r & 1) {
+      bv[i] = read_k(st, adrB[i], s);
+    } else if (A_KMAJOR) {
+      av[i] = read_k(st, adrA[i], s);
+    } else {
+      av[i] = *(const __attribute__((address_space(3))) u32x4*)((const lds_char*)lds + st + (adrA[i] ^ (32 * s)));
+    }
+  };
+
+  float16v acc[MI][MI];
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (mb + q < a.M) {
-              float* c = a.C32 + static_cast<long>(mb + q) * a.N + n;
-              const float o = a.accumulate ? *c + v[q] : v[q];
-              *c = o;
-              v[q] = o;
-            }
-          // element (n, mb .. mb + 3) of a symmetric product, when the tile it falls in is not computed
-          // (M % 4 == 0 and mb % 4 == 0: the four are valid together and share a tile)
-          if (a.symmetric && mb < a.M && tile_skipped<TN>(n, mb)) {
-            float4 o4 = make_float4(v[0], v[1], v[2], v[3]);
-            *reinterpret_cast<float4*>(a.C32 + static_cast<long>(n) * a.N + mb) = o4;
-          }
-        }
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int jj = 0; jj < MI; ++jj)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][jj][r] = 0.0f;
+  // The products of one slice, in a fixed order of instructions: between them the operand reads of the next slice
+  // (stage st, slice s) and, with LOADS, the loads of a later k-tile.
+  auto products = [&](const u32x4 (&av)[MI], const u32x4 (&bv)[MI], int st, int s, u32x4 (&an)[MI], u32x4 (&bn)[MI], auto loads) {
+    static_for<MI * MI>([&](auto ij) {
+      constexpr int x = decltype(ij)::value;
+      constexpr int kEvery = MI * MI / (2 * MI);     // products per operand read and per load
+      if constexpr (kEvery > 0) {
+        if constexpr (x % kEvery == 0) read_piece(st, s, x / kEvery, an, bn);
+        if constexpr (decltype(loads)::value && x % kEvery == kEvery - 1) fetch_piece(x / kEvery);
+      } else {
+        read_piece(st, s, 0, an, bn);
+        read_piece(st, s, 1, an, bn);
+        if constexpr (decltype(loads)::value) { fetch_piece(0); fetch_piece(1); }
+      }
+      acc[x / MI][x % MI] = Mfma<T>::run(av[x / MI], bv[x % MI], acc[x / MI][x % MI]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+
+  // ---- pipeline.  A stage's loads are issued three k-tiles before its products; the second half of tile it is read
+  // while its first half is multiplied, then one barrier, then the first half of tile it + 1 while the second half is
+  // multiplied.  The barrier follows a wait for this wave's own loads of tile it + 1 (the 2 * 2 MI younger ones may
+  // be outstanding) and for its LDS reads of tile it, whose stage the loads issued next overwrite.
+  u32x4 a0[MI], b0[MI], a1[MI], b1[MI];
+  for (int i = 0; i < kStages - 1; ++i) fetch();
+  tile_landed<(kStages - 2) * 2 * MI>();
+  fetch();
+  int stage = 0;
+#pragma unroll
+  for (int r = 0; r < 2 * MI; ++r) read_piece(stage, 0, r, a0, b0);
+  for (int it = 0; it < iters; ++it) {
+    products(a0, b0, stage, 1, a1, b1, std::false_type{});
+    tile_landed<(kStages - 2) * 2 * MI>();
+    stage = (stage + kStageBytes) & (kStages * kStageBytes - 1);
+    products(a1, b1, stage, 0, a0, b0, std::true_type{});
+    fetch_next();
+  }
+  // ---- store.  Accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of its 32 x 32
+  // block.  A strip of 32 rows at a time goes through the wave's own part of the LDS (every load into it has landed and
+  // every wave has left the operands behind), so that memory sees runs of MI * 128 bytes.  The block indices are
+  // compile-time constants (static_for): a run-time index would move the accumulators to scratch memory.
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  constexpr int W = 32 * MI;                     // side of the wave's block
+  constexpr int kPitch32 = W + 4;                // floats per row: 16-byte rows whose pieces fall into different banks
+  constexpr int kPitch16 = W + 8;                // 16-bit values per row
+  static_assert(32 * kPitch32 * 4 * 4 <= kStages * kStageBytes, "the strips of four waves fit the LDS");
+  float* strip = reinterpret_cast<float*>(lds + w * (32 * kPitch32 * 4));
+  const int mw = m0 + wm * W, nw = n0 + wn * W;  // first row and column of the wave's block
+  const int rq = 4 * (lane >> 5), cl = lane & 31;
+  const int M = a.M, N = a.N;
+  uint16_t* const C16 = a.C16;
+  float* const C32 = a.C32;
+  const float post_scale = a.post_scale;
+  const bool mirror = a.symmetric != 0 && at.m != at.n;
+  const bool add = a.accumulate != 0 && C32 != nullptr;
+  // register r of block (i, jj) as it will be stored
+  auto value = [&](float v, int i, int jj, int r) __attribute__((always_inline)) {
+    v *= post_scale;
+    if (add) {
+      const int m = mw + i * 32 + 8 * (r >> 2) + rq + (r & 3), n = nw + jj * 32 + cl;
+      if (m < M && n < N) v = C32[static_cast<long>(m) * N + n] + v;
+    }
+    return v;
+  };
+  // rows r0 .. r0 + 31 of the strip to rows of C, 16 bytes per lane
+  auto store_strip = [&](int row0, int col0) __attribute__((always_inline)) {
+    wave_lds_order();
+    if (C16) {
+      constexpr int kLanes = W / 8;              // lanes per row
+#pragma unroll
+      for (int p = 0; p < 32 * kLanes / 64; ++p) {
+        const int r = p * (64 / kLanes) + lane / kLanes, c = lane % kLanes * 8;
+        const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(strip) + r * kPitch16 + c);
+        if (row0 + r < M && col0 + c < N) *reinterpret_cast<uint4*>(C16 + static_cast<long>(row0 + r) * N + col0 + c) = v;
+      }
+    } else {
+      constexpr int kLanes = W / 4;
+#pragma unroll
+      for (int p = 0; p < 32 * kLanes / 64; ++p) {
+        const int r = p * (64 / kLanes) + lane / kLanes, c = lane % kLanes * 4;
+        const float4 v = *reinterpret_cast<const float4*>(strip + r * kPitch32 + c);
+        if (row0 + r < M && col0 + c < N) *reinterpret_cast<float4*>(C32 + static_cast<long>(row0 + r) * N + col0 + c) = v;
+      }
+    }
+    wave_lds_order();
+  };
+  // a symmetric product's elements below the diagonal: the transposed block (tiles on the diagonal hold both halves).
+  // First, while the elements that are added to still hold their old values.
+  if (mirror) {
+    static_for<MI>([&](auto jc) {                // block columns of the wave
+      constexpr int jj = decltype(jc)::value;
+      static_for<MI>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          *reinterpret_cast<float4*>(strip + cl * kPitch32 + i * 32 + 8 * r4 + rq) =
+              make_float4(value(acc[i][jj][4 * r4], i, jj, 4 * r4), value(acc[i][jj][4 * r4 + 1], i, jj, 4 * r4 + 1),
+                          value(acc[i][jj][4 * r4 + 2], i, jj, 4 * r4 + 2), value(acc[i][jj][4 * r4 + 3], i, jj, 4 * r4 + 3));
       });
-    }
+      store_strip(nw + jj * 32, mw);
+    });
+  }
+  static_for<MI>([&](auto ic) {                  // block rows of the wave
+    constexpr int i = decltype(ic)::value;
+    static_for<MI>([&](auto jc) {
+      constexpr int jj = decltype(jc)::value;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = 8 * (r >> 2) + rq + (r & 3), col = jj * 32 + cl;
+        if (C16) reinterpret_cast<uint16_t*>(strip)[row * kPitch16 + col] = T::from_f32(value(acc[i][jj][r], i, jj, r));
+        else strip[row * kPitch32 + col] = value(acc[i][jj][r], i, jj, r);
+      }
+    });
+    store_strip(mw + i * 32, nw);
   });
 }
 
@@ -323,12 +406,30 @@ hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre
 
 namespace {
 
-template <typename T, bool A_KMAJOR, int TN, int NW>
-hipError_t launch_tiles(ContractionArgs a, hipStream_t s) {
-  a.tiles_m = (a.M + kTileM - 1) / kTileM;
-  a.tiles_n = (a.N + TN - 1) / TN;
-  a.patches_m = (a.tiles_m + kPatchM - 1) / kPatchM;
-  a.patches_n = (a.tiles_n + kPatchN - 1) / kPatchN;
+// Tiles first .. first + count - 1 (numbered in 256 x 256 tiles) by workgroups of (64 MI) x (64 MI) tiles.
+template <typename T, bool A_KMAJOR, int MI>
+hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s) {
+  const long parts = count * (4 / MI) * (4 / MI);
+  const long grid = (parts + 7) / 8 * 8;
+  if (grid > 0x7FFFFFFFL) return hipErrorInvalidValue;
+  a.tile0 = static_cast<int>(first);
+  a.tiles = static_cast<int>(parts);
+  hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// Time of `count` 256 x 256 tiles on the chip by workgroup tiles of 64 mi, in rounds (the time of one 256 x 256 tile per
+// compute unit), from the rates measured on products that fill the chip: 1.25 / 0.9 / 0.5 PFLOP/s for 256 / 128 / 64.
+double tile_rounds(long count, int mi) {
+  if (mi == 4) return static_cast<double>((count + 255) / 256);
+  if (mi == 2) return count <= 64 ? 0.5 : 0.7 * ((count + 127) / 128);   // one, two workgroups per compute unit
+  return 0.1 + 0.16 * ((count + 15) / 16);
+}
+
+template <typename T, bool A_KMAJOR>
+hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
+  a.tiles_m = (a.M + kBigTile - 1) / kBigTile;
+  a.tiles_n = (a.N + kBigTile - 1) / kBigTile;
   // the operands are addressed with 32-bit byte offsets from their first term
   int ta = 0, tb = 0;
   for (int i = 0; i < a.npairs; ++i) {
@@ -338,27 +439,31 @@ hipError_t launch_tiles(ContractionArgs a, hipStream_t s) {
   a.a_elements = ta * a.a_term_stride + static_cast<long>(a.Kd) * a.M;
   a.b_elements = tb * a.b_term_stride + static_cast<long>(a.Kd) * a.N;
   if (a.a_elements * 2 >= 0x7FFFFFF0L || a.b_elements * 2 >= 0x7FFFFFF0L) return hipErrorInvalidValue;
-  const long patches = static_cast<long>(a.patches_m) * a.patches_n;
-  const long grid = (patches + 7) / 8 * 8 * 32;
-  if (grid > 0x7FFFFFFFL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, TN, NW>), dim3(static_cast<unsigned>(grid)), dim3(NW * 64), 0, s, a);
-  return hipGetLastError();
+  const long tiles = a.symmetric ? static_cast<long>(a.tiles_m) * (a.tiles_m + 1) / 2 : static_cast<long>(a.tiles_m) * a.tiles_n;
+  // Whole rounds of 256 x 256 tiles (one per compute unit); what is left over by the tile size that takes least time,
+  // so that a few last tiles do not keep the chip for a whole round.
+  const int forced = tuning().contraction_tiles;   // 0: by size, 1: 128, 2: 256 (tests)
+  long big = forced == 0 ? tiles / 256 * 256 : forced == 2 ? tiles : 0;
+  const long rest = tiles - big;
+  int mi = 2;
+  if (forced == 0) {
+    mi = 4;
+    for (int m : {2, 1})
+      if (tile_rounds(rest, m) < tile_rounds(rest, mi)) mi = m;
+    if (mi == 4) big = tiles;
+  }
+  if (big > 0) {
+    if (hipError_t e = launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s); e != hipSuccess) return e;
+  }
+  if (big == tiles) return hipSuccess;
+  return mi == 2 ? launch_tiles<T, A_KMAJOR, 2>(a, big, rest, s) : launch_tiles<T, A_KMAJOR, 1>(a, big, rest, s);
 }
 
 }  // namespace
 
 hipError_t launch_contraction(ContractionArgs a, bool a_kmajor, bool bf16, hipStream_t s) {
-  // 256 x 256 tiles (8 waves) where the product has enough of them to fill the chip, else 256 x 128 (4 waves)
-  long big_tiles = static_cast<long>((a.M + 255) / 256) * ((a.N + 255) / 256);
-  if (a.symmetric) big_tiles /= 2;               // tiles below the diagonal are not computed
-  const int forced = tuning().contraction_tiles; // 0: by size, 1: 256 x 128, 2: 256 x 256 (tests)
-  const bool big = forced == 2 || (forced == 0 && big_tiles >= 256);
-  if (big) {
-    if (bf16) return a_kmajor ? launch_tiles<BF16, true, 256, 8>(a, s) : launch_tiles<BF16, false, 256, 8>(a, s);
-    return a_kmajor ? launch_tiles<F16, true, 256, 8>(a, s) : launch_tiles<F16, false, 256, 8>(a, s);
-  }
-  if (bf16) return a_kmajor ? launch_tiles<BF16, true, 128, 4>(a, s) : launch_tiles<BF16, false, 128, 4>(a, s);
-  return a_kmajor ? launch_tiles<F16, true, 128, 4>(a, s) : launch_tiles<F16, false, 128, 4>(a, s);
+  if (bf16) return a_kmajor ? launch_shape<BF16, true>(a, s) : launch_shape<BF16, false>(a, s);
+  return a_kmajor ? launch_shape<F16, true>(a, s) : launch_shape<F16, false>(a, s);
 }
 
 }  // namespace larosa

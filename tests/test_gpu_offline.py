@@ -29,7 +29,7 @@ ULP_FRACTION = 0.02
 
 @pytest.fixture(scope="module", params=[0, 2], ids=["tiles-by-size", "tiles-256x256"])
 def api(gpu_device, request):
-    """Every test runs with the workgroup tile chosen by size (256 x 128 at these sizes) and with the 256 x 256
+    """Every test runs with the workgroup tile chosen by size (64 or 128 wide at these sizes) and with the 256 x 256
     tile that large products get forced on."""
     from paper_2507_01299_amd import api as A
     A.lib()
@@ -140,6 +140,45 @@ def test_residual_adapter_matches_oracle(api, dtype, d):
     torch.cuda.synchronize()
     eye = O.decode16(to_bits(out), dtype)
     assert np.abs(eye - np.eye(d)).max() <= 1e-5
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+def test_contraction_tiles_and_left_over_tiles(gpu_device, tile):
+    """Every workgroup tile, and the launch in two parts: 23 x 24 / 2 = 276 and 2 x 129 = 258 tiles of 256 x 256 are one
+    whole round of 256 and a rest that runs in tiles of 64 (tile 0, as do products of a few tiles).  264 x 520 ends inside a tile of every size, 33 and
+    40 tokens inside a k-tile; 45 k-tiles go round all LDS stages."""
+    from paper_2507_01299_amd import api
+    api.set_tuning(10, tile)
+    try:
+        for n, d, dtype in ((40, 5888 - 8, "bf16"), (33, 520, "f16"), (1433, 264, "bf16")):
+            print(f"moment tile={tile} n={n} d={d}", flush=True)
+            xb, x = _calibration(n, d, 23, dtype) if d < 1000 else (lambda b: (b, O.decode16(b, dtype)))(
+                O.encode16(np.random.default_rng(23).standard_normal((n, d)), dtype))
+            C = torch.zeros(d, d, dtype=torch.float32, device="cuda:0")
+            for add in (False, True):
+                api.second_moment(to_dev(xb, dtype), C, dtype, accumulate=add)
+            torch.cuda.synchronize()
+            got = C.cpu().numpy()
+            want = 2 * (x.T @ x)
+            sc = np.sqrt(np.diag(want))
+            assert np.all(np.abs(got - want) <= SM_TOL * sc[:, None] * sc[None, :] + 1e-30)
+            assert np.array_equal(got, got.T)
+        for d, other, dtype in ((264, 33000, "f16"), (264, 520, "bf16")):
+            print(f"folds tile={tile} d={d} other={other}", flush=True)
+            Q = _rotation32(d, 29)
+            Qd, scr = torch.from_numpy(Q).cuda(), api.OfflineScratch(d, dtype)
+            wb = O.encode16(synth.gaussian_weight(d, other, 31), dtype)
+            w64 = O.decode16(wb, dtype)
+            out = torch.zeros(d, other, dtype=api.torch_dtype(dtype), device="cuda:0")
+            api.fold_input(Qd, to_dev(wb, dtype), out, dtype, scr)
+            outT = torch.zeros(other, d, dtype=api.torch_dtype(dtype), device="cuda:0")
+            api.fold_output(to_dev(np.ascontiguousarray(wb.T), dtype), Qd, outT, dtype, scr)
+            torch.cuda.synchronize()
+            wn = np.linalg.norm(w64, axis=0)
+            _check_stored(to_bits(out), O.fold_input_side(Q.astype(np.float64), w64), dtype, "Q^T W", wn[None, :])
+            _check_stored(to_bits(outT), O.fold_output_side(w64.T, Q.astype(np.float64)), dtype, "W Q", wn[:, None])
+    finally:
+        api.set_tuning(10, 0)
 
 
 def test_full_size_llama2_7b_on_sampled_columns(api):
