@@ -43,17 +43,20 @@ size_t gemv_partial_bytes_bound(int B, int d_in_max, int d_out_max) {
   return narrow > wide ? narrow : wide;
 }
 
-size_t batched_partial_bytes(const GemvPlan& p, int B, bool coef_scale) {
-  const int tpg = batched_tokens_per_group(B, coef_scale);
+size_t batched_partial_bytes(const GemvPlan& p, int B, bool coef_scale, int d_in) {
+  const int tpg = batched_tokens_per_group(B, coef_scale, d_in);
   const size_t groups = (B + tpg - 1) / tpg;
   return groups * tpg * p.partial_floats * sizeof(float);
 }
 
 // One launch of the batched kernels (B > 1): C holds the tokens' coefficients over all rows.  An
 // optional side product (side.W != nullptr: same token count, no coefficient scale) shares the launch.
-int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t st, BatchArgs side = BatchArgs{}) {
+// Wide outputs take 256-column strips where their partial sums fit the workspace, else 128-column ones.
+int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t st, BatchArgs side = BatchArgs{},
+                bool may_widen = true) {
   const bool cs = a.coef_scale != nullptr;
-  const bool has_side = side.W != nullptr && batched_uses_mfma(a.B, cs);
+  const bool mfma = batched_uses_mfma(a.B, cs, a.d_in);
+  const bool has_side = side.W != nullptr && mfma && batched_uses_mfma(a.B, false, side.d_in);
   // two products in one launch share the chip in proportion to the bytes each has to read
   int g_main = 0, g_side = 0;
   if (has_side) {
@@ -63,39 +66,47 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
     if (g_side < 1) g_side = 1;
     g_main = total - g_side > 0 ? total - g_side : 1;
   }
-  const GemvPlan p = plan_batched(a.d_in, a.d_out, batched_uses_mfma(a.B, cs), g_main);
-  const int tpg = batched_tokens_per_group(a.B, cs);
-  const size_t groups = (a.B + tpg - 1) / tpg;
-  size_t slots = groups * p.nstrips;
-  size_t pbytes = batched_partial_bytes(p, a.B, cs);
+  const size_t groups = (a.B + batched_tokens_per_group(a.B, cs, a.d_in) - 1) / batched_tokens_per_group(a.B, cs, a.d_in);
+  size_t slots = 0, pbytes = 0;
   unsigned* counters = static_cast<unsigned*>(ws);
   char* partial = static_cast<char*>(ws) + kCounterBytes;
+  auto place = [&](BatchArgs& x, int g_hint, bool scaled) {
+    const GemvPlan p = plan_batched(x.d_in, x.d_out, mfma, g_hint, may_widen && a.B > 16);
+    x.chunk = p.chunk;
+    x.G = p.G;
+    x.nstrips = p.nstrips;
+    x.wps = p.wps;
+    x.strip_cols = p.strip_cols;
+    x.counters = counters + slots * kCounterStride;
+    x.partial = reinterpret_cast<float*>(partial + pbytes);
+    slots += groups * p.nstrips;
+    pbytes += batched_partial_bytes(p, x.B, scaled, x.d_in);
+  };
   BatchPair pr{};
+  place(a, g_main, cs);
   if (has_side) {
-    const GemvPlan ps = plan_batched(side.d_in, side.d_out, true, g_side);
-    side.chunk = ps.chunk;
-    side.G = ps.G;
-    side.nstrips = ps.nstrips;
-    side.wps = ps.wps;
-    side.counters = counters + slots * kCounterStride;
-    side.partial = reinterpret_cast<float*>(partial + pbytes);
-    slots += groups * ps.nstrips;
-    pbytes += batched_partial_bytes(ps, a.B, false);
+    place(side, g_side, false);
     pr.side = side;
-    pr.side_G = ps.G;
+    pr.side_G = side.G;
   }
+  const bool fits = ws && aligned(ws, 256) && ws_bytes >= kCounterBytes + pbytes;
+  if (may_widen && (slots > kCounterSlots || !fits)) return run_batched(a, bf16, ws, ws_bytes, st, side, false);
   if (slots > kCounterSlots) return LAROSA_EUNSUPPORTED;
-  if (!ws || !aligned(ws, 256) || ws_bytes < kCounterBytes + pbytes) return LAROSA_EWORKSPACE;
-  a.chunk = p.chunk;
-  a.G = p.G;
-  a.nstrips = p.nstrips;
-  a.wps = p.wps;
-  a.counters = counters;
-  a.partial = reinterpret_cast<float*>(partial);
+  if (!fits) return LAROSA_EWORKSPACE;
   pr.main = a;
   if (launch_batched_pair(pr, bf16, st) != hipSuccess) return LAROSA_EHIP;
   if (side.W != nullptr && !has_side) return run_batched(side, bf16, ws, ws_bytes, st);   // FMA path: two launches
   return LAROSA_OK;
+}
+
+// Bytes at the head of a workspace that a batched product of B tokens takes, in strips of 256 columns if that leaves
+// `behind` bytes after it, else of 128.
+size_t batched_head_bytes(int B, int d_in, int d_out, size_t ws_bytes, size_t behind) {
+  const bool mfma = batched_uses_mfma(B, false, d_in);
+  auto head = [&](bool wide) {
+    return round_up(kCounterBytes + batched_partial_bytes(plan_batched(d_in, d_out, mfma, 0, wide && B > 16), B, false, d_in), 256);
+  };
+  return head(true) + behind <= ws_bytes ? head(true) : head(false);
 }
 
 struct Carver {
@@ -266,9 +277,8 @@ int larosa_sparse_gemv(const void* Wp, const void* h, const int32_t* idx, void* 
   if (int rc = check_gemv_shapes(B, d_in, d_out, K)) return rc;
   if (B > 1) {
     // masked coefficient matrix in the tail of the workspace, then one pass over the weight
-    const GemvPlan p = plan_batched(d_in, d_out, batched_uses_mfma(B, false));
-    const size_t head = round_up(kCounterBytes + batched_partial_bytes(p, B, false), 256);
     const size_t cbytes = static_cast<size_t>(B) * d_in * 2;
+    const size_t head = batched_head_bytes(B, d_in, d_out, ws_bytes, cbytes);
     if (!ws || !aligned(ws, 256) || ws_bytes < head + cbytes) return LAROSA_EWORKSPACE;
     uint16_t* C = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + head);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -345,9 +355,9 @@ static size_t layer_gemv_ws(const larosa_layer* L, int B) {
       const GemvPlan bp[] = {plan_batched(L->d, L->d, m), plan_batched(L->d, L->d_q + 2 * L->d_kv, m),
                              plan_batched(L->d_q, L->d, m), plan_batched(L->d, 2 * L->d_ff, m),
                              plan_batched(L->d_ff, L->d, m)};
-      const size_t side_bytes = (m && (L->shortcut_attn || L->shortcut_mlp)) ? batched_partial_bytes(bp[0], B, false) : 0;
+      const size_t side_bytes = (m && (L->shortcut_attn || L->shortcut_mlp)) ? batched_partial_bytes(bp[0], B, false, L->d) : 0;
       for (const GemvPlan& p : bp) {
-        const size_t need = round_up(kCounterBytes + batched_partial_bytes(p, B, m ? false : cs) + side_bytes, 256);
+        const size_t need = round_up(kCounterBytes + batched_partial_bytes(p, B, m ? false : cs, L->d) + side_bytes, 256);
         if (need > s) s = need;
       }
     }
@@ -902,8 +912,8 @@ int larosa_sparse_gemv_static(const void* Wp, const void* h, const int32_t* idx,
   // the same scratch need as larosa_sparse_gemv's workspace, against the fixed size of the array
   size_t need;
   if (B > 1) {
-    const GemvPlan p = plan_batched(d_in, d_out, batched_uses_mfma(B, false));
-    need = round_up(kCounterBytes + batched_partial_bytes(p, B, false), 256) + static_cast<size_t>(B) * d_in * 2;
+    const size_t cbytes = static_cast<size_t>(B) * d_in * 2;
+    need = batched_head_bytes(B, d_in, d_out, LAROSA_STATIC_SCRATCH_BYTES, cbytes) + cbytes;
   } else {
     need = kCounterBytes + plan_gemv(d_out, K).partial_floats * sizeof(float);
   }

@@ -6,13 +6,15 @@
 // The same kernels serve the batched rotation / adapter / dense baseline (C = x).
 //
 //   * the product is a skinny dense contraction (all rows x B tokens), so it runs on the matrix
-//     cores (v_mfma_f32_16x16x16 f16/bf16): M = 16 output columns, N = 16 tokens, K = 16 rows,
-//     token blocks padded to 16.  A lane loads 8 consecutive columns of 4 rows (16 lanes x 16 bytes
-//     = 256 contiguous bytes per row), and a byte permute regroups those registers into the K-runs
-//     the instruction wants; the weight never passes through LDS.  Measured on MI355X this kernel is
-//     the fastest for every B >= 2 (the fp32-FMA kernel needed 205 us per LLaMA3-8B layer at B = 4 where
-//     this one needed 160 us), because the kernel is HBM-bound and the FMA variant spends its issue slots
-//     on B x 8 multiply-adds and coefficient reads per 16 bytes loaded;
+//     cores (f16/bf16, fp32 accumulate): M = 16 output columns, N = 16 tokens, token blocks padded to 16.
+//     Measured on MI355X this is the fastest for every B >= 2 (the fp32-FMA kernel needed 205 us per LLaMA3-8B layer at
+//     B = 4 where the first matrix-core kernel needed 160 us), because the product is HBM-bound and the FMA variant spends
+//     its issue slots on B x 8 multiply-adds and coefficient reads per 16 bytes loaded.  Two kernels:
+//     up to 16 tokens (skinny16) a lane loads 8 consecutive columns of 4 rows (16 lanes x 16 bytes = 256 contiguous bytes
+//     per row), and a byte permute regroups those registers into the K-runs the instruction wants; the weight never
+//     passes through LDS.  More tokens (skinny32, groups of 32) keep the matrix cores busy longer per row, so the
+//     loads go straight to LDS, ahead of the products and without registers of their own, and transposing LDS reads make
+//     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 149 us);
 //   * an fp32-FMA kernel (2 or 4 tokens per workgroup) remains for the one case the 16-bit B
 //     operand cannot express: a per-channel coefficient scale applied in fp32 (learned pre-norm
 //     scale in front of an explicit rotation).
@@ -20,6 +22,7 @@
 // stores and loads, arrival counter, the last arrival finishes) and epilogue follow the single-token
 // kernel (gemv_core.hpp), with one arrival per workgroup for all its tokens.
 #include "gemv_core.hpp"
+#include "lds_load.hpp"
 
 namespace larosa {
 
@@ -95,6 +98,24 @@ __device__ __forceinline__ void store_out8(const BatchArgs& a, int tok, int col,
     for (int k = 0; k < 8; ++k) v[k] = r[k] + round_store<T>(v[k]);
   }
   *reinterpret_cast<uint4*>(a.y + off) = pack8<T>(v);
+}
+
+// the same for 4 consecutive columns (d_out % 4 == 0: all four are inside)
+template <typename T>
+__device__ __forceinline__ void store_out4(const BatchArgs& a, int tok, int col, const float __attribute__((ext_vector_type(4))) & sum,
+                                           float scale) {
+  const size_t off = static_cast<size_t>(tok) * a.d_out + col;
+  float v[4] = {sum.x * scale, sum.y * scale, sum.z * scale, sum.w * scale};
+  if (a.residual) {
+    if (a.y_pre) *reinterpret_cast<uint2*>(a.y_pre + off) = pack4<T>(v);
+    const uint2 r = *reinterpret_cast<const uint2*>(a.residual + off);
+    float f[4];
+    T::unpack2(r.x, f[0], f[1]);
+    T::unpack2(r.y, f[2], f[3]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = f[k] + round_store<T>(v[k]);
+  }
+  *reinterpret_cast<uint2*>(a.y + off) = pack4<T>(v);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -288,9 +309,11 @@ __global__ __launch_bounds__(kBThreads) void skinny_fma_kernel(BatchArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// matrix-core kernel, NTB blocks of 16 tokens per workgroup
+// matrix-core kernels: up to 16 tokens (skinny16), groups of 32 tokens (skinny32)
 // ------------------------------------------------------------------------------------------------
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bfloat8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
@@ -306,18 +329,18 @@ __device__ __forceinline__ float4_t mfma16<BF16>(uint2 a, uint2 b, float4_t c) {
                                                    0, 0);
 }
 
-constexpr int kMStrip = 128;        // output columns per workgroup of the matrix-core kernel
-constexpr int kMRW = 8;             // its row-waves
-constexpr int kMTileStride = 130;   // floats per token row of an LDS tile (8-byte aligned, spreads tokens over banks)
+constexpr int k16Strip = 128;        // output columns per workgroup of the kernel for up to 16 tokens
+constexpr int k16Waves = 8;             // its row-waves
+constexpr int k16Pitch = 130;   // floats per token row of an LDS tile (8-byte aligned, spreads tokens over banks)
 
-// Geometry: a workgroup is 8 waves on ONE strip of 128 columns (256 contiguous bytes per row), each
+// Up to 16 tokens.  Geometry: a workgroup is 8 waves on ONE strip of 128 columns (256 contiguous bytes per row), each
 // wave taking its own run of 16-row tiles, two tiles (8 row loads of 16 bytes per lane) in flight.
 // Narrow strips keep the number of workgroups that share a strip -- and with it the partial-sum
 // traffic, which grows with the token count -- small.
-template <typename T, int NTB>
-__device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int grp) {
-  __shared__ float tile[4][16][kMTileStride];
-  __shared__ float scale_s[NTB * 16];
+template <typename T>
+__device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp) {
+  __shared__ float tile[4][16][k16Pitch];
+  __shared__ float scale_s[16];
   __shared__ int s_last;
 
   const int tid = threadIdx.x;
@@ -325,7 +348,7 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
   const int rw = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kgrp = lane >> 4;    // K-run of 4 rows inside a 16-row tile
   const int m = lane & 15;       // column group (A operand) / token (B operand)
-  const int b0 = grp * NTB * 16;
+  const int b0 = grp * 16;
   const int K = a.d_in;
   const int chunk = a.chunk;
 
@@ -334,22 +357,20 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
     const Geometry ge = strip_geometry(g, a.wps, K, chunk);
     const int s = ge.s, t0 = ge.t0, t1 = ge.t1;
     const int n = t1 - t0;
-    const int colbase = s * kMStrip + 8 * m;   // this lane's 8 columns (A operand)
+    const int colbase = s * k16Strip + 8 * m;   // this lane's 8 columns (A operand)
     const bool colv = colbase < a.d_out;
 
-    float4_t acc[NTB][8];
+    float4_t acc[8];
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 8; ++i) acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     const int ntiles = (n + 15) / 16;
-    const int per = (ntiles + kMRW - 1) / kMRW;
+    const int per = (ntiles + k16Waves - 1) / k16Waves;
     const int tl0 = rw * per;
     const int tl1 = min(ntiles, tl0 + per);
     for (int tl = tl0; tl < tl1; tl += 2) {
       uint4 v[2][4];
-      uint2 bf[2][NTB];
+      uint2 bf[2];
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
         // first of this lane's 4 rows; t0 % 8 == 0, so j0 % 4 == 0.  A tile past this wave's run
@@ -362,22 +383,19 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int r = min(j0 + q, t1 - 1);
-          v[h2][q] = load_stream16(a.W + static_cast<size_t>(r) * a.d_out + (colv ? colbase : s * kMStrip));
+          v[h2][q] = load_stream16(a.W + static_cast<size_t>(r) * a.d_out + (colv ? colbase : s * k16Strip));
         }
-        // B operand: 4 consecutive rows of token (b0 + tb*16 + m); rows at or past t1 belong to
+        // B operand: 4 consecutive rows of token b0 + m; rows at or past t1 belong to
         // another workgroup (or do not exist) and must contribute nothing
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-          const int tok = b0 + tb * 16 + m;
-          // j0 % 4 == 0 and K % 8 == 0, so min(j0, K - 4) keeps the four rows inside the token's vector
-          uint2 c = *reinterpret_cast<const uint2*>(a.C + static_cast<size_t>(min(tok, a.B - 1)) * K + min(j0, K - 4));
-          if (j0 + 1 >= t1) c.x &= 0x0000FFFFu;
-          if (j0 + 2 >= t1) c.y = 0u;
-          if (j0 + 3 >= t1) c.y &= 0x0000FFFFu;
-          if (j0 >= t1 || tok >= a.B) c.x = 0u;
-          if (tok >= a.B) c.y = 0u;
-          bf[h2][tb] = c;
-        }
+        const int tok = b0 + m;
+        // j0 % 4 == 0 and K % 8 == 0, so min(j0, K - 4) keeps the four rows inside the token's vector
+        uint2 c = *reinterpret_cast<const uint2*>(a.C + static_cast<size_t>(min(tok, a.B - 1)) * K + min(j0, K - 4));
+        if (j0 + 1 >= t1) c.x &= 0x0000FFFFu;
+        if (j0 + 2 >= t1) c.y = 0u;
+        if (j0 + 3 >= t1) c.y &= 0x0000FFFFu;
+        if (j0 >= t1 || tok >= a.B) c.x = 0u;
+        if (tok >= a.B) c.y = 0u;
+        bf[h2] = c;
       }
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
@@ -392,29 +410,28 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
           uint2 af;
           af.x = __builtin_amdgcn_perm(vw1[i >> 1], vw0[i >> 1], sel);
           af.y = __builtin_amdgcn_perm(vw3[i >> 1], vw2[i >> 1], sel);
-#pragma unroll
-          for (int tb = 0; tb < NTB; ++tb) acc[tb][i] = mfma16<T>(af, bf[h2][tb], acc[tb][i]);
+          acc[i] = mfma16<T>(af, bf[h2], acc[i]);
         }
       }
     }
 
     LAROSA_STAMP(1);
     const int n_s = ge.g_last - ge.g_first + 1;
-    const size_t slot_floats = static_cast<size_t>(NTB) * 16 * kMStrip;
+    const size_t slot_floats = static_cast<size_t>(16) * k16Strip;
     unsigned* ctr = a.counters + (static_cast<size_t>(grp) * a.nstrips + s) * kCounterStride;
-    // every partial of this token group as one buffer (slot of workgroup w at byte w * slot bytes; a thread's 16 bytes of token block tb at tb * 8 KiB + tid * 16 within it);
+    // every partial of this token group as one buffer (slot of workgroup w at byte w * slot bytes; a thread's 16 bytes at tid * 16 within it);
     // 16-byte accesses with the sc1 cache policy are coherent across the chip, see gemv_core.hpp
-    const int slot_bytes = NTB * 8192;
+    constexpr int slot_bytes = 8192;
     const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(
         a.partial + static_cast<size_t>(grp) * a.G * slot_floats, 0, a.G * slot_bytes, 0x00027000);
     constexpr int kCoherent = 16;
     const int my_slot = g * slot_bytes;
 
-    // Sum the 8 row-waves of token block tb: waves 0-3 write their tiles, waves 4-7 add theirs on
+    // Sum the 8 row-waves: waves 0-3 write their tiles, waves 4-7 add theirs on
     // top, then every thread adds the four tiles for its two float pairs (pair q: token q / 64,
     // columns 2*(q % 64), +1).  D element e of MFMA i in lane (kgrp, m) is column 32*kgrp + 8*e + i
     // of token m.  The order of the additions is fixed.
-    auto reduce_tb = [&](int tb, float2 (&sm)[2]) {
+    auto reduce_waves = [&](float2 (&sm)[2]) {
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         if ((rw >> 2) == r) {
@@ -423,7 +440,7 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               float* p = &tile[rw & 3][m][32 * kgrp + 8 * e + i];
-              *p = (r == 0) ? acc[tb][i][e] : *p + acc[tb][i][e];
+              *p = (r == 0) ? acc[i][e] : *p + acc[i][e];
             }
         }
         __syncthreads();
@@ -442,8 +459,8 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
       }
       __syncthreads();
     };
-    // epilogue of one token block: its 16 x 128 sums (pairs held as in reduce_tb) go through tile[0]
-    auto tile_out = [&](int tb, const float2 (&sm)[2]) {
+    // epilogue: the 16 x 128 sums (pairs held as in reduce_waves) go through tile[0]
+    auto tile_out = [&](const float2 (&sm)[2]) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int q = tid + k * kBThreads;
@@ -451,37 +468,31 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
       }
       __syncthreads();
       if (tid < 256) {
-        const int tok = b0 + tb * 16 + (tid >> 4);
-        const int col = s * kMStrip + (tid & 15) * 8;
+        const int tok = b0 + (tid >> 4);
+        const int col = s * k16Strip + (tid & 15) * 8;
         if (tok < a.B && col < a.d_out) {
           float v[8];
           const float* p = &tile[0][tid >> 4][(tid & 15) * 8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = p[e];
-          store_out8<T>(a, tok, col, v, scale_s[tb * 16 + (tid >> 4)]);
+          store_out8<T>(a, tok, col, v, scale_s[tid >> 4]);
         }
       }
       __syncthreads();
     };
 
     if (n_s == 1) {
-      token_scales<T, kMRW>(a, b0, NTB * 16, scale_s, lane, rw);
+      token_scales<T, k16Waves>(a, b0, 16, scale_s, lane, rw);
       __syncthreads();
-#pragma unroll
-      for (int tb = 0; tb < NTB; ++tb) {
-        float2 sm[2];
-        reduce_tb(tb, sm);
-        tile_out(tb, sm);
-      }
+      float2 sm[2];
+      reduce_waves(sm);
+      tile_out(sm);
     } else {
-#pragma unroll
-      for (int tb = 0; tb < NTB; ++tb) {
-        float2 sm[2];
-        reduce_tb(tb, sm);
-        // the thread's two float pairs of the block as one 16-byte chip-coherent store
-        const u32x4 v = {__float_as_uint(sm[0].x), __float_as_uint(sm[0].y), __float_as_uint(sm[1].x), __float_as_uint(sm[1].y)};
-        __builtin_amdgcn_raw_buffer_store_b128(v, slots, my_slot + tb * 8192 + tid * 16, 0, kCoherent);
-      }
+      float2 sm[2];
+      reduce_waves(sm);
+      // the thread's two float pairs as one 16-byte chip-coherent store
+      const u32x4 v = {__float_as_uint(sm[0].x), __float_as_uint(sm[0].y), __float_as_uint(sm[1].x), __float_as_uint(sm[1].y)};
+      __builtin_amdgcn_raw_buffer_store_b128(v, slots, my_slot + tid * 16, 0, kCoherent);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
       LAROSA_STAMP(2);
@@ -493,33 +504,274 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
       LAROSA_STAMP(3);
       if (s_last != 0) {   // uniform over the workgroup
         if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        token_scales<T, kMRW>(a, b0, NTB * 16, scale_s, lane, rw);
-        for (int tb = 0; tb < NTB; ++tb) {
-          // each thread owns 2 float pairs of the block and adds the partials in workgroup order
-          float2 sum[2];
-          sum[0] = sum[1] = make_float2(0.f, 0.f);
-          for (int gg = ge.g_first; gg <= ge.g_last; gg += 8) {
-            u32x4 v[8];
+        token_scales<T, k16Waves>(a, b0, 16, scale_s, lane, rw);
+        // each thread owns 2 float pairs of the block and adds the partials in workgroup order
+        float2 sum[2];
+        sum[0] = sum[1] = make_float2(0.f, 0.f);
+        for (int gg = ge.g_first; gg <= ge.g_last; gg += 8) {
+          u32x4 v[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              if (gg + q <= ge.g_last) {          // uniform over the workgroup: no partial is read twice
-                v[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, (gg + q) * slot_bytes + tb * 8192 + tid * 16, 0, kCoherent);
-              }
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              if (gg + q <= ge.g_last) {
-                sum[0].x += __uint_as_float(v[q].x);
-                sum[0].y += __uint_as_float(v[q].y);
-                sum[1].x += __uint_as_float(v[q].z);
-                sum[1].y += __uint_as_float(v[q].w);
-              }
+          for (int q = 0; q < 8; ++q) {
+            if (gg + q <= ge.g_last) {          // uniform over the workgroup: no partial is read twice
+              v[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, (gg + q) * slot_bytes + tid * 16, 0, kCoherent);
             }
           }
-          tile_out(tb, sum);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            if (gg + q <= ge.g_last) {
+              sum[0].x += __uint_as_float(v[q].x);
+              sum[0].y += __uint_as_float(v[q].y);
+              sum[1].x += __uint_as_float(v[q].z);
+              sum[1].y += __uint_as_float(v[q].w);
+            }
+          }
         }
+        tile_out(sum);
       }
     }
+  }
+  LAROSA_STAMP(5);
+}
+
+template <typename T>
+__device__ __forceinline__ float4_t mfma32(u32x4 a, u32x4 b, float4_t c);
+template <>
+__device__ __forceinline__ float4_t mfma32<F16>(u32x4 a, u32x4 b, float4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ float4_t mfma32<BF16>(u32x4 a, u32x4 b, float4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfloat8_t, a), __builtin_bit_cast(bfloat8_t, b), c, 0, 0, 0);
+}
+
+// More than 16 tokens, in groups of 32.  What bounded the kernel above here: with two blocks of tokens a wave spends twice
+// as long between its batches of loads, so fewer are in flight (4096 x 22016, 32 tokens: 47.8 us on 172 workgroups; this
+// one 41.5).  For 16 tokens the two are level, and the one above keeps its smaller hand-off.
+constexpr int kMRW = 4;             // row-waves of a workgroup
+constexpr int kMThreads = kMRW * 64;
+constexpr int kMRows = 32;          // rows of a tile: one step of a wave
+
+// Sizes of the kernel for strips of SC columns.
+constexpr int kMTokens = 32;
+template <int SC>
+struct SkinnyShape {
+  static constexpr int kTokens = kMTokens;
+  static constexpr int kStages = SC == 128 ? 4 : 2;              // tiles in a wave's ring
+  static constexpr int kTileBytes = kMRows * SC * 2;
+  static constexpr int kStage = kTileBytes + kMTokens * kMRows * 2;   // a tile and the tokens' coefficients of its rows
+  static constexpr int kRing = kStages * kStage;
+  static constexpr int kLds = kMRW * kRing;
+  static constexpr int kPitch = SC + 4;                          // floats per token row of a wave's sums in LDS
+  static_assert(kLds <= 160 * 1024, "a compute unit's LDS");
+  static_assert(sizeof(float) * (kMRW * kTokens * kPitch + kTokens + 1) <= kLds, "sums, scales and flag reuse the rings");
+};
+
+// Position of row k's 32-byte granules in a tile with G of them per row: granule q sits at q ^ granule_swap(k), so that
+// the sixteen rows of one transposing read lie in different banks.
+template <int G>
+__device__ __forceinline__ int granule_swap(int k) { return ((k & 3) | (((k >> 3) & 3) << 2)) & (G - 1); }
+
+// Geometry: a workgroup is 4 waves on ONE strip of SC columns (2 SC contiguous bytes per row).  Each wave streams its own
+// run of 32-row tiles through a ring of its own in LDS: the loads go straight to LDS and run ahead of the products by
+// what the ring holds (at least 16 KiB a wave), and no wave waits for another until the sums meet.
+//   W tile    [32 rows][SC columns] as in memory, granules exchanged as above.  16 lanes of a transposing read point at
+//             4 rows x 16 columns and receive 4 consecutive rows of one column each: the A operand (M = 16 columns,
+//             K = 32 rows).
+//   C tile    [16 tokens][32 rows], 16-byte piece p of token m at position p ^ (m / 4 % 4): the B operand.
+// Rows past the workgroup's range arrive as zeros (beyond the end of the buffer the tile's loads go through), and so do
+// columns past d_out, tokens past B and the coefficients of rows past the range.
+template <typename T, int SC>
+__device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp) {
+  typedef SkinnyShape<SC> Sh;
+  constexpr int NTB = kMTokens / 16;             // blocks of 16 tokens
+  constexpr int kTokens = Sh::kTokens, kStage = Sh::kStage, kRing = Sh::kRing, kPitch = Sh::kPitch;
+  constexpr int kGroups = SC / 16;               // 16-column groups of the strip
+  constexpr int kLoadsW = Sh::kTileBytes / 1024; // wave-loads per tile
+  constexpr int kLoads = kLoadsW + NTB;
+  constexpr int kRowLanes = SC / 8;              // lanes that load one row
+  constexpr int kLoadRows = 64 / kRowLanes;
+  // sized at the launch: with the size in sight the compiler plans for one wave per SIMD, moves the accumulators to the
+  // upper register file and copies them around every product
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int rw = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b0 = grp * kTokens;
+  const int K = a.d_in, d_out = a.d_out;
+
+  LAROSA_STAMP(0);
+  Geometry ge = strip_geometry(g, a.wps, K, a.chunk);
+  ge.t0 = __builtin_amdgcn_readfirstlane(ge.t0);   // uniform, but the division leaves it in vector registers
+  ge.t1 = __builtin_amdgcn_readfirstlane(ge.t1);
+  const int s = ge.s;
+
+  // this wave's rows [r0, r1): whole tiles, the last one possibly short
+  const int ntiles = (ge.t1 - ge.t0 + kMRows - 1) / kMRows;
+  const int per = (ntiles + kMRW - 1) / kMRW;
+  const int tl0 = min(rw * per, ntiles), tl1 = min(tl0 + per, ntiles);
+  const int r0 = ge.t0 + tl0 * kMRows, r1 = min(ge.t1, ge.t0 + tl1 * kMRows);
+
+  // ---- loads.  Wave-load q covers kLoadRows rows of the tile; a lane's place in the row is lane % kRowLanes pieces.
+  uint32_t offW[kLoadsW];
+#pragma unroll
+  for (int q = 0; q < kLoadsW; ++q) {
+    const int row = q * kLoadRows + lane / kRowLanes, pos = lane % kRowLanes;
+    const int col = (((pos >> 1) ^ granule_swap<kGroups>(row)) << 4) + (pos & 1) * 8;
+    offW[q] = s * SC + col < d_out ? (static_cast<uint32_t>(row) * d_out + s * SC + col) * 2u : kOutside;
+  }
+  uint32_t offC[NTB];
+  const int kC = 8 * ((lane & 3) ^ ((lane >> 4) & 3));           // first row of the lane's piece: token lane / 4, position lane % 4
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb) {
+    const int tok = tb * 16 + (lane >> 2);
+    offC[tb] = b0 + tok < a.B ? (static_cast<uint32_t>(tok) * K + kC) * 2u : kOutside;
+  }
+  const uint32_t ring = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)lds)) + rw * kRing;
+  const char* nextW = reinterpret_cast<const char*>(a.W) + static_cast<size_t>(r0) * d_out * 2;
+  const char* nextC = reinterpret_cast<const char*>(a.C) + (static_cast<size_t>(b0) * K + r0) * 2;
+  int left = r1 - r0;                            // rows of the wave not yet asked for
+  uint32_t in_stage = 0;
+  const uint32_t bytesC = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(min(kTokens, a.B - b0)) * K * 2u);
+  auto fetch = [&]() __attribute__((always_inline)) {
+    const int rows = __builtin_amdgcn_readfirstlane(max(0, min(kMRows, left)));   // (the clamp is a vector instruction)
+    const u32x4 bufW = raw_buffer(nextW, static_cast<uint32_t>(rows) * d_out * 2u);
+    const u32x4 bufC = raw_buffer(nextC, bytesC);
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb)
+      load_to_lds(bufC, ring + in_stage + Sh::kTileBytes + tb * 1024, kC < rows ? offC[tb] : kOutside);
+#pragma unroll
+    for (int q = 0; q < kLoadsW; ++q) load_to_lds_stream(bufW, ring + in_stage + q * 1024, offW[q]);
+    left -= kMRows;
+    nextW += static_cast<size_t>(kMRows) * d_out * 2;
+    nextC += kMRows * 2;
+    in_stage = in_stage == (Sh::kStages - 1) * kStage ? 0 : in_stage + kStage;
+  };
+
+  // ---- operand reads
+  const int grp16 = lane >> 4, j = lane & 15;
+  const int rowk = 8 * grp16 + (j >> 2);
+  const int sw = granule_swap<kGroups>(rowk);    // of the four rows from rowk on, and of the four after them
+  const uint32_t rdW = ring + rowk * (SC * 2) + 8 * (j & 3);
+  const uint32_t rdC = ring + Sh::kTileBytes + j * 64 + ((grp16 ^ ((j >> 2) & 3)) * 16);
+  float4_t acc[NTB][kGroups];
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) acc[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+  for (int i = 0; i < Sh::kStages; ++i) fetch();
+  uint32_t stage = 0;
+  for (int t = tl0; t < tl1; ++t) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((Sh::kStages - 1) * kLoads) : "memory");   // this tile has landed
+    u32x4 av[kGroups], bv[NTB];
+#pragma unroll
+    for (int tb = 0; tb < NTB; ++tb) bv[tb] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(rdC + stage + tb * 1024);
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+      const uint32_t p = rdW + stage + ((i ^ sw) * 32);
+      const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4_t*>(p)));
+      const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4_t*>(p + 4 * SC * 2)));
+      av[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // it is in registers: its stage takes the next loads
+    fetch();
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i)
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) acc[tb][i] = mfma32<T>(av[i], bv[tb], acc[tb][i]);
+    stage = stage == (Sh::kStages - 1) * kStage ? 0 : stage + kStage;
+  }
+  // every load has landed and every wave has left its ring: the LDS is free for the sums
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+  LAROSA_STAMP(1);
+
+  float* sums = reinterpret_cast<float*>(lds);                         // [wave][token][kPitch]
+  float* scale_s = sums + kMRW * kTokens * kPitch;                     // [token]
+  int* s_last = reinterpret_cast<int*>(scale_s + kTokens);
+  // D element e of product i in lane (grp16, j) is column 16 i + 4 grp16 + e of token j
+#pragma unroll
+  for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i)
+      *reinterpret_cast<float4_t*>(sums + (rw * kTokens + tb * 16 + j) * kPitch + 16 * i + 4 * grp16) = acc[tb][i];
+  const int n_s = ge.g_last - ge.g_first + 1;
+  if (n_s == 1) token_scales<T, kMRW>(a, b0, kTokens, scale_s, lane, rw);
+  __syncthreads();
+  // a thread owns pieces tid + 256 p: columns 4 (piece % (SC / 4)) .. + 3 of token piece / (SC / 4)
+  constexpr int kPieces = kTokens * (SC / 4) / kMThreads;
+  constexpr int kPass = kPieces < 8 ? kPieces : 8;                     // pieces a finisher holds at a time
+  auto wave_sum_of = [&](int piece) __attribute__((always_inline)) {   // the four waves' sums, in order
+    const float* q = sums + piece / (SC / 4) * kPitch + piece % (SC / 4) * 4;
+    float4_t v = *reinterpret_cast<const float4_t*>(q);
+#pragma unroll
+    for (int w = 1; w < kMRW; ++w) v += *reinterpret_cast<const float4_t*>(q + w * kTokens * kPitch);
+    return v;
+  };
+  auto store_piece = [&](int piece, const float4_t& v) __attribute__((always_inline)) {
+    const int tok = piece / (SC / 4), col = s * SC + piece % (SC / 4) * 4;
+    if (b0 + tok < a.B && col < d_out) store_out4<T>(a, b0 + tok, col, v, scale_s[tok]);
+  };
+  if (n_s == 1) {
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) store_piece(tid + p * kMThreads, wave_sum_of(tid + p * kMThreads));
+    LAROSA_STAMP(5);
+    return;
+  }
+
+  // every partial of this strip as one buffer: slot of workgroup w at byte w * slot bytes, piece i of it at 16 i; 16-byte
+  // accesses with the sc1 cache policy are coherent across the chip, see gemv_core.hpp
+  constexpr int kSlotBytes = kTokens * SC * 4;
+  constexpr int kCoherent = 16;
+  unsigned* ctr = a.counters + (static_cast<size_t>(grp) * a.nstrips + s) * kCounterStride;
+  const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(
+      a.partial + (static_cast<size_t>(grp) * a.G + ge.g_first) * (kTokens * SC), 0, n_s * kSlotBytes, 0x00027000);
+  const int mine = (g - ge.g_first) * kSlotBytes;
+#pragma unroll
+  for (int p = 0; p < kPieces; ++p)
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wave_sum_of(tid + p * kMThreads)), slots,
+                                           mine + (tid + p * kMThreads) * 16, 0, kCoherent);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  LAROSA_STAMP(2);
+  if (tid == 0) {
+    const unsigned old = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_last = (old == static_cast<unsigned>(n_s - 1)) ? 1 : 0;
+  }
+  __syncthreads();
+  LAROSA_STAMP(3);
+  if (*s_last == 0) {                            // uniform over the workgroup
+    LAROSA_STAMP(5);
+    return;
+  }
+  if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  token_scales<T, kMRW>(a, b0, kTokens, scale_s, lane, rw);
+  __syncthreads();
+  // the thread's pieces of every partial, added in workgroup order
+  constexpr int kAhead = 16 / kPass;             // partials in flight
+  for (int p0 = 0; p0 < kPieces; p0 += kPass) {
+    float4_t sm[kPass];
+#pragma unroll
+    for (int p = 0; p < kPass; ++p) sm[p] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < n_s; w += kAhead) {
+      u32x4 v[kAhead][kPass];
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q)
+        if (w + q < n_s) {                       // uniform over the workgroup: no partial is read twice
+#pragma unroll
+          for (int p = 0; p < kPass; ++p)
+            v[q][p] = __builtin_amdgcn_raw_buffer_load_b128(slots, (w + q) * kSlotBytes + (tid + (p0 + p) * kMThreads) * 16, 0, kCoherent);
+        }
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q)
+        if (w + q < n_s) {
+#pragma unroll
+          for (int p = 0; p < kPass; ++p) sm[p] += __builtin_bit_cast(float4_t, v[q][p]);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < kPass; ++p) store_piece(tid + (p0 + p) * kMThreads, sm[p]);
   }
   LAROSA_STAMP(5);
 }
@@ -528,22 +780,32 @@ __device__ __forceinline__ void skinny_mfma_body(const BatchArgs& a, int g, int 
 // One launch, up to two independent products: workgroups [0, side_G) of the grid run the side product
 // (a residual adapter on a block's shortcut, which needs only the block's input), the others the main
 // one.  Both use the same token grouping (blockIdx.y).
-template <typename T, int NTB>
-__global__ __launch_bounds__(kBThreads) void skinny_mfma_kernel(BatchPair p) {
+template <typename T>
+__global__ __launch_bounds__(k16Waves * 64) void skinny16_kernel(BatchPair p) {
   const int g = blockIdx.x;
   const bool side = g < p.side_G;                       // uniform over the workgroup
-  skinny_mfma_body<T, NTB>(side ? p.side : p.main, side ? g : g - p.side_G, blockIdx.y);
+  skinny16_body<T>(side ? p.side : p.main, side ? g : g - p.side_G, blockIdx.y);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kMThreads, 2) void skinny32_kernel(BatchPair p) {
+  const int g = blockIdx.x;
+  const bool side = g < p.side_G;
+  const BatchArgs& a = side ? p.side : p.main;
+  const int own = side ? g : g - p.side_G;
+  if (a.strip_cols == 256) skinny32_body<T, 256>(a, own, blockIdx.y);
+  else skinny32_body<T, 128>(a, own, blockIdx.y);
 }
 
 }  // namespace
-bool batched_uses_mfma(int B, bool coef_scale);
+bool batched_uses_mfma(int B, bool coef_scale, int d_in);
 namespace {
 
 template <typename T>
 hipError_t launch_batched_t(const BatchPair& p, hipStream_t st) {
   const BatchArgs& a = p.main;
   const dim3 block(kBThreads);
-  if (!batched_uses_mfma(a.B, a.coef_scale != nullptr)) {
+  if (!batched_uses_mfma(a.B, a.coef_scale != nullptr, a.d_in)) {
     if (p.side_G > 0) return hipErrorInvalidValue;   // the FMA kernel carries no side product
     // (a per-channel coefficient scale is applied in fp32, which only the FMA kernel does)
     if (a.B <= 2) {
@@ -552,35 +814,43 @@ hipError_t launch_batched_t(const BatchPair& p, hipStream_t st) {
       hipLaunchKernelGGL((skinny_fma_kernel<T, 4>), dim3(a.G, (a.B + 3) / 4), block, 0, st, a);
     }
   } else if (a.B <= 16) {
-    hipLaunchKernelGGL((skinny_mfma_kernel<T, 1>), dim3(a.G + p.side_G, 1), block, 0, st, p);
+    hipLaunchKernelGGL((skinny16_kernel<T>), dim3(a.G + p.side_G), dim3(k16Waves * 64), 0, st, p);
   } else {
-    hipLaunchKernelGGL((skinny_mfma_kernel<T, 2>), dim3(a.G + p.side_G, (a.B + 31) / 32), block, 0, st, p);
+    const bool wide = a.strip_cols == 256 || (p.side_G > 0 && p.side.strip_cols == 256);
+    hipLaunchKernelGGL((skinny32_kernel<T>), dim3(a.G + p.side_G, (a.B + kMTokens - 1) / kMTokens), dim3(kMThreads),
+                       max(SkinnyShape<128>::kLds, wide ? SkinnyShape<256>::kLds : 0), st, p);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-bool batched_uses_mfma(int B, bool coef_scale) { return B >= 2 && !coef_scale; }
+// (a token group's coefficients are addressed with 32-bit byte offsets: 32 tokens of d_in values below 2 GiB)
+bool batched_uses_mfma(int B, bool coef_scale, int d_in) { return B >= 2 && !coef_scale && d_in < (1 << 25); }
 
 int batched_g_total() { return tuning().g_target > 0 ? tuning().g_target : 256; }
 
-int batched_tokens_per_group(int B, bool coef_scale) {
-  if (batched_uses_mfma(B, coef_scale)) return B <= 16 ? 16 : 32;
+int batched_tokens_per_group(int B, bool coef_scale, int d_in) {
+  if (batched_uses_mfma(B, coef_scale, d_in)) return B <= 16 ? 16 : 32;
   return B <= 2 ? 2 : 4;
 }
 
-GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint) {
+GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool may_widen) {
   GemvPlan p;
-  p.strip_cols = 128;   // both batched kernels work on 128-column strips
+  // 512 contiguous bytes per row instead of 256 stream faster (8192 x 57344, 32 tokens: 150 against 170 us) but a strip's
+  // partial sums are twice as large: worth it where at most four workgroups share a strip (22016 outputs: 41.5 against
+  // 42.5 us; 12288, five to a strip: 26.8 against 26.3)
+  const bool wide = mfma && may_widen && (d_out + 255) / 256 > 51;
+  p.strip_cols = wide ? 256 : 128;
   p.nstrips = (d_out + p.strip_cols - 1) / p.strip_cols;
   // one workgroup per compute unit: each strip gets the same number of workgroups, each of those an equal run
-  // of whole 16-row tiles (keeps row starts 8-aligned), so a workgroup never works on two strips
+  // of whole tiles (32 rows; 16 in the FMA kernel), so a workgroup never works on two strips
   long G = g_hint > 0 ? g_hint : batched_g_total();
   long wps = G / p.nstrips;
   if (wps < 1) wps = 1;
+  const long rows = mfma ? 32 : 16;
   long chunk = (d_in + wps - 1) / wps;
-  chunk = (chunk + 15) / 16 * 16;
+  chunk = (chunk + rows - 1) / rows * rows;
   if (!mfma && chunk > kBatchChunkMax) chunk = kBatchChunkMax;   // LDS staging of the coefficients
   wps = (d_in + chunk - 1) / chunk;
   p.chunk = static_cast<int>(chunk);

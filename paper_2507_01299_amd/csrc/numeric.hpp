@@ -78,6 +78,14 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   return v;
 }
 
+template <typename T>
+__device__ __forceinline__ uint2 pack4(const float (&f)[4]) {
+  uint2 v;
+  v.x = static_cast<uint32_t>(T::from_f32(f[0])) | (static_cast<uint32_t>(T::from_f32(f[1])) << 16);
+  v.y = static_cast<uint32_t>(T::from_f32(f[2])) | (static_cast<uint32_t>(T::from_f32(f[3])) << 16);
+  return v;
+}
+
 // value after one storage rounding
 template <typename T>
 __device__ __forceinline__ float round_store(float f) { return T::to_f32(T::from_f32(f)); }

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "lds_load.hpp"
 #include "numeric.hpp"
 
 namespace larosa {
@@ -60,22 +61,10 @@ template <> struct Mfma<BF16> {
   }
 };
 
-// Operand loads go through buffer resources that span the whole (multi-term) operand: a 16-byte piece whose
-// offset lies at or beyond the operand's size arrives as zeros, so rows past Kd and columns outside the matrix
-// only need the offset kOutside.
-constexpr uint32_t kOutside = 0x80000000u;
-
+// Operand loads go through buffer resources that span the whole (multi-term) operand: rows past Kd and columns outside
+// the matrix only need the offset kOutside.
 __device__ __forceinline__ u32x4 operand_buffer(const uint16_t* p, long elements) {
-  const uint64_t base = reinterpret_cast<uint64_t>(p);
-  return u32x4{static_cast<uint32_t>(base), static_cast<uint32_t>(base >> 32) & 0xFFFFu, static_cast<uint32_t>(elements * 2),
-               0x00027000u};
-}
-
-// 16 bytes per lane from buffer offset `off` straight to LDS: lane l's piece lands at byte lds_byte + 16 l.  Written as
-// an instruction because the compiler would wait for every outstanding load of this kind before each LDS read; the
-// pipeline below counts them itself.  (The load has no destination register.)
-__device__ __forceinline__ void load_to_lds(u32x4 buf, uint32_t lds_byte, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(off), "s"(buf));
+  return raw_buffer(p, static_cast<uint32_t>(elements * 2));
 }
 
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
@@ -86,8 +75,6 @@ __device__ __forceinline__ void static_for(F&& f) {
     f(std::integral_constant<int, N - 1>{});
   }
 }
-
-typedef __attribute__((address_space(3))) char lds_char;
 
 // One 64-byte granule (32 columns) of a k-major LDS tile is moved by its row: granule q of row k sits at
 // position q ^ granule_swizzle(k), so that the eight rows a transposing read touches lie in different banks.

@@ -248,3 +248,33 @@ def test_config0_single_linear_by_its_recipe(api, ws):
             got = O.decode16(to_bits(y), dtype)[0]
             # three 16-bit roundings separate the two (Q, h, W'): each is 2^-11 relative per entry
             assert rel_l2(got, dense) <= 3e-3
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,d_in,d_out", [(17, 8, 8), (32, 40, 136), (31, 1000, 4096), (33, 72, 13064), (17, 520, 13312),
+                                          (48, 4120, 1032)])
+def test_more_than_16_tokens_in_both_strip_widths(api, dtype, B, d_in, d_out):
+    """The kernel for groups of 32 tokens: fewer rows than one tile, ragged rows and columns, a last group with one or
+    16 tokens, strips of 128 columns and (more than 13056 outputs) of 256; and wide outputs on a workspace that only
+    holds the partial sums of 128-column strips."""
+    print(f"B={B} d_in={d_in} d_out={d_out} {dtype}", flush=True)
+    rng = np.random.default_rng(1700 + B)
+    xb = O.encode16(rng.standard_normal((B, d_in)), dtype)
+    wb = O.encode16(synth.gaussian_weight(d_in, d_out, B), dtype)
+    want = O.decode16(xb, dtype) @ O.decode16(wb, dtype)
+    x, W = to_dev(xb, dtype), to_dev(wb, dtype)
+    sizes = [api.workspace_bytes(B, d_in, d_out, d_in)]
+    if (d_out + 255) // 256 > 51:
+        groups, wps = (B + 31) // 32, max(1, 256 // ((d_out + 127) // 128))
+        chunk = (-(-d_in // wps) + 15) // 16 * 16
+        sizes.append((1 << 20) + groups * 32 * ((d_out + 127) // 128) * -(-d_in // chunk) * 128 * 4)
+    outs = []
+    for nbytes in sizes:
+        w = api.Workspace(nbytes)
+        y = torch.full((B, d_out), 7.0, dtype=x.dtype, device="cuda:0")
+        for _ in range(2):                                    # the arrival counters are left at zero
+            api.dense_gemv(W, x, y, dtype, w)
+        torch.cuda.synchronize()
+        stored_close(to_bits(y), want, dtype, f"workspace {nbytes}")
+        outs.append(to_bits(y))
+    assert all(rel_l2(O.decode16(o, dtype), O.decode16(outs[0], dtype)) <= REL_L2_TOL for o in outs)
