@@ -14,6 +14,8 @@
 // accumulators per lane.  Narrow (anything else): the 16-bit kernel's 512-column strips, one dword
 // per lane and row, 16 rows in flight.  The -8 offset is applied once per lane as -8 * sum of
 // coefficients.  Reductions, cross-workgroup hand-off and epilogue are shared with the 16-bit kernel.
+#include <type_traits>
+
 #include "gemv_core.hpp"
 
 namespace larosa {
@@ -195,35 +197,69 @@ __global__ __launch_bounds__(RW * 64) void gemv_rows_w4_kernel(W4Args w) {
   reduce_and_finish<T, RW>(acc, sg.s, b, g, a.G, a.wps, a.partial, a.counters, a.nstrips, ep, sh, lane, rw);
 }
 
-// Round-to-nearest quantiser: one wave per row and 512 columns, a lane holds 8 columns, 16 lanes
-// share a group.  s = max|w| / 7 rounded to 16 bits, q = clip(rint(w / s), -8, 7) + 8.
+// Maximum over each 16 lanes of a wave (non-negative values), in every lane: four row rotations on the vector unit.
+__device__ __forceinline__ float row16_max(float v) {
+  auto turned = [](float x, auto by) __attribute__((always_inline)) {
+    const int i = static_cast<int>(__float_as_uint(x));
+    return __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_update_dpp(i, i, 0x120 + decltype(by)::value, 0xF, 0xF, false)));   // row_ror
+  };
+  v = fmaxf(v, turned(v, std::integral_constant<int, 8>{}));
+  v = fmaxf(v, turned(v, std::integral_constant<int, 4>{}));
+  v = fmaxf(v, turned(v, std::integral_constant<int, 2>{}));
+  return fmaxf(v, turned(v, std::integral_constant<int, 1>{}));
+}
+
+// Round-to-nearest quantiser: a wave takes 512 columns of kQuantRows rows (all loaded first), a lane 8 columns of each,
+// 16 lanes share a group.  s = max|w| / 7 rounded to 16 bits, q = clip(rint(w / s), -8, 7) + 8.
+// HBM-bound (2.5 bytes per weight) once the quotients are cheap: a correctly rounded fp32 division is about ten
+// instructions, and eight of them per 16 bytes kept the vector unit busy longer than memory (4096 x 22016: 61 us with one
+// row per 64-lane workgroup and divisions).  The quotient is therefore w r + (w - (w r) s) r with r = 1 / s: within an ulp
+// of the true one, and exact where that is representable.  Only ties need more than that: w and s are 16-bit values, so a
+// quotient that is no tie (half-integer, representable) is at least 2^-16 of its size away from one.
+constexpr int kQuantRows = 4, kQuantWaves = 4;
+
 template <typename T>
-__global__ __launch_bounds__(64) void quantize_w4_kernel(const uint16_t* __restrict__ W, int d_out, int ng,
-                                                         uint32_t* __restrict__ Wq, uint16_t* __restrict__ scales) {
-  const int lane = threadIdx.x;
-  const int row = blockIdx.y;
+__global__ __launch_bounds__(kQuantWaves * 64) void quantize_w4_kernel(const uint16_t* __restrict__ W, int d_in, int d_out, int ng,
+                                                                       uint32_t* __restrict__ Wq, uint16_t* __restrict__ scales) {
+  const int lane = threadIdx.x & 63;
+  const int row0 = (blockIdx.y * kQuantWaves + (threadIdx.x >> 6)) * kQuantRows;
   const int col = blockIdx.x * kStripCols + lane * 8;
-  float w[8];
+  const bool in = col < d_out;
+  uint4 v[kQuantRows];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = 0.f;
-  if (col < d_out) unpack8<T>(*reinterpret_cast<const uint4*>(W + static_cast<size_t>(row) * d_out + col), w);
-  float m = 0.f;
+  for (int r = 0; r < kQuantRows; ++r)
+    v[r] = in && row0 + r < d_in ? load_stream16(W + static_cast<size_t>(row0 + r) * d_out + col) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(w[k]));
+  for (int r = 0; r < kQuantRows; ++r) {
+    float w[8];
+    unpack8<T>(v[r], w);
+    float m = 0.f;
 #pragma unroll
-  for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
-  const uint16_t sb = T::from_f32(m / 7.0f);
-  const float s = T::to_f32(sb);
-  uint32_t packed = 0;
+    for (int k = 0; k < 8; ++k) m = fmaxf(m, fabsf(w[k]));
+    m = row16_max(m);
+    const uint16_t sb = T::from_f32(m / 7.0f);
+    const float s = T::to_f32(sb);
+    uint32_t packed = 0;
+    if (__all(s == 0.f || (s > 0x1p-100f && s < 0x1p100f))) {
+      const float r1 = s > 0.f ? __frcp_rn(s) : 0.f;             // a scale of zero: all codes 8
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    float q = 0.f;
-    if (s > 0.f) q = fminf(fmaxf(rintf(w[k] / s), -8.f), 7.f);
-    packed |= static_cast<uint32_t>(static_cast<int>(q) + 8) << (4 * k);
-  }
-  if (col < d_out) {
-    Wq[static_cast<size_t>(row) * (d_out / 8) + col / 8] = packed;
-    if ((lane & 15) == 0) scales[static_cast<size_t>(row) * ng + col / kW4Group] = sb;
+      for (int k = 0; k < 8; ++k) {
+        const float q0 = w[k] * r1;
+        const float q = fminf(fmaxf(rintf(fmaf(fmaf(-q0, s, w[k]), r1, q0)), -8.f), 7.f);
+        packed |= static_cast<uint32_t>(static_cast<int>(q) + 8) << (4 * k);
+      }
+    } else {                                                     // reciprocals out of range, infinities, NaN
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        float q = 0.f;
+        if (s > 0.f) q = fminf(fmaxf(rintf(w[k] / s), -8.f), 7.f);
+        packed |= static_cast<uint32_t>(static_cast<int>(q) + 8) << (4 * k);
+      }
+    }
+    if (in && row0 + r < d_in) {
+      Wq[static_cast<size_t>(row0 + r) * (d_out / 8) + col / 8] = packed;
+      if ((lane & 15) == 0) scales[static_cast<size_t>(row0 + r) * ng + col / kW4Group] = sb;
+    }
   }
 }
 
@@ -257,11 +293,12 @@ int w4_strip_cols(int d_out) {
 hipError_t launch_quantize_w4(const uint16_t* W, int d_in, int d_out, uint32_t* Wq, uint16_t* scales, bool bf16,
                               hipStream_t s) {
   const int ng = (d_out + kW4Group - 1) / kW4Group;
-  dim3 grid((d_out + kStripCols - 1) / kStripCols, d_in), block(64);
+  constexpr int kRows = kQuantRows * kQuantWaves;
+  dim3 grid((d_out + kStripCols - 1) / kStripCols, (d_in + kRows - 1) / kRows), block(kQuantWaves * 64);
   if (bf16)
-    hipLaunchKernelGGL(quantize_w4_kernel<BF16>, grid, block, 0, s, W, d_out, ng, Wq, scales);
+    hipLaunchKernelGGL(quantize_w4_kernel<BF16>, grid, block, 0, s, W, d_in, d_out, ng, Wq, scales);
   else
-    hipLaunchKernelGGL(quantize_w4_kernel<F16>, grid, block, 0, s, W, d_out, ng, Wq, scales);
+    hipLaunchKernelGGL(quantize_w4_kernel<F16>, grid, block, 0, s, W, d_in, d_out, ng, Wq, scales);
   return hipGetLastError();
 }
 

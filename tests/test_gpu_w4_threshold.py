@@ -192,3 +192,24 @@ def test_threshold_then_projection_is_the_masked_product(api, ws):
     torch.cuda.synchronize()
     masked = np.where(np.abs(h[0]) > float(eps), h[0], 0.0)
     assert rel_l2(O.decode16(to_bits(y), dtype)[0], O.round16(masked @ W, dtype)) <= REL_L2_TOL
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("d_in,d_out", [(1, 8), (15, 512), (17, 520), (33, 1032)])
+def test_quantiser_on_ties_and_extreme_groups(api, dtype, d_in, d_out):
+    """Quotients that are exact half-integers (the rounding decides), groups of zeros, and groups whose scale is at
+    the ends of the storage type's range; row counts around the 16 rows of a workgroup."""
+    rng = np.random.default_rng(41 * d_in + d_out)
+    k = rng.integers(-14, 15, size=(d_in, d_out)).astype(np.float64)          # w / s = k / 2: every odd k is a tie
+    ng = (d_out + 127) // 128
+    exps = rng.integers(-10, 4, size=(d_in, ng)) if dtype == "f16" else rng.integers(-118, 100, size=(d_in, ng))
+    for g in range(ng):
+        k[:, g * 128] = 14.0                                                    # the scale is 2^e exactly
+        k[:, g * 128:(g + 1) * 128] *= 2.0 ** exps[:, g:g + 1] / 2
+    k[d_in // 2, :min(128, d_out)] = 0.0
+    wb = O.encode16(k, dtype)
+    codes, sbits = O.quantize_rtn_w4(O.decode16(wb, dtype), dtype)
+    q, s = api.quantize_w4(to_dev(wb, dtype), dtype)
+    torch.cuda.synchronize()
+    assert np.array_equal(q.cpu().numpy().view(np.uint32), O.pack_w4(codes))
+    assert np.array_equal(to_bits(s), sbits)
