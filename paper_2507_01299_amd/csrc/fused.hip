@@ -14,6 +14,7 @@
 // while the projection's workgroups are still selecting, and the adapter leaves the layer's
 // critical path.
 #include "gemv_core.hpp"
+#include "lds_load.hpp"
 #include "topk_core.hpp"
 
 namespace larosa {
@@ -76,12 +77,39 @@ struct LdsRowsOfVector {
   }
 };
 
+// While a workgroup selects, memory is idle.  Each of its waves asks for a few weight rows that it will probably stream:
+// the MLP vector is not sorted by a rotation, so its channels are kept about evenly, rank t of K lies near row
+// t d_in / K, and K / d_in of the rows around there are kept.  The loads go to an LDS piece that nobody reads; what counts
+// is that the rows are in this XCD's L2 when the row loop asks for them.  Six rows a wave measured best (layers at 40 %:
+// 7B 76.8 -> 76.4 us, 8B 84.0 -> 83.0, 70B 240.4 -> 239.0, 5120 wide 109.6 -> 108.2; 3 rows half of that, 16 rows and
+// more a loss, and the o projection, whose waves stream two batches of rows in all, only loses).  With few workgroups
+// there is memory to spare in the row loop as well and the extra rows only cost: 2944 wide (168 workgroups) level, 2048
+// wide (112) 52.2 -> 52.5, 1024 wide (30) 45.7 -> 46.2; so from three quarters of the compute units on.
+constexpr int kAheadRows = 6, kAheadMinGroups = 192;
+__device__ __forceinline__ void ask_ahead(const FusedArgs& a, const Segment& sg, int rw, int lane, const char* sink) {
+  bool valid;
+  const int col = strip_lane_col(sg.s, lane, a.g.d_out, a.pair_cols, valid);
+  int ra, re;
+  wave_run<8>(sg.t0, sg.t1, rw, ra, re);
+  const float per_rank = static_cast<float>(a.g.d_in) / static_cast<float>(a.g.K);
+  const int first = __builtin_amdgcn_readfirstlane(min(static_cast<int>(static_cast<float>(ra) * per_rank), a.g.d_in - 1));
+  const int n = __builtin_amdgcn_readfirstlane(min(min(kAheadRows, re - ra), a.g.d_in - first));   // (below 1 for a wave without ranks)
+  const uint32_t to = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)sink));
+  const uint32_t off = valid ? static_cast<uint32_t>(col) * 2u : kOutside;
+  const char* row = reinterpret_cast<const char*>(a.g.W) + static_cast<size_t>(first) * a.g.d_out * 2;
+  for (int i = 0; i < n; ++i) {
+    load_to_lds(raw_buffer(row, static_cast<uint32_t>(a.g.d_out) * 2u), to, off);   // a row ends its buffer
+    row += static_cast<size_t>(a.g.d_out) * 2;
+  }
+}
+
 template <typename T, int NS>   // NS slabs (2048 elements each) cover the vector
 __global__ __launch_bounds__(512) void fused_hinted_gemv_kernel(FusedArgs a) {
   constexpr int RW = 8, NT = RW * 64;
   __shared__ HintShared hs;
   __shared__ GemvShared<RW> sh;
   __shared__ int lst_idx[kFusedChunkMax];
+  __shared__ __attribute__((aligned(16))) char sink[1024];
 
   LAROSA_STAMP(0);
   const int tid = threadIdx.x;
@@ -129,6 +157,8 @@ __global__ __launch_bounds__(512) void fused_hinted_gemv_kernel(FusedArgs a) {
       hs.r = r;
     }
   }
+  const Segment sg = segment_of(g, a.g.wps, a.g.chunk, K);
+  if (a.g.G >= kAheadMinGroups) ask_ahead(a, sg, rw, lane, sink);
   __syncthreads();
   LAROSA_STAMP(1);
   const unsigned Tk = hs.T, r = hs.r;
@@ -175,7 +205,6 @@ __global__ __launch_bounds__(512) void fused_hinted_gemv_kernel(FusedArgs a) {
   // ---- this workgroup's ranks: row indices into LDS; workgroup 0 also writes the whole index list.
   // A wave's share of a slab holds a contiguous run of ranks: waves whose run misses the workgroup's
   // range skip the slab (all but one or two of the wave-slab pairs).
-  const Segment sg = segment_of(g, a.g.wps, a.g.chunk, K);
   const int n = sg.t1 - sg.t0;
   int32_t* idx_out = (a.idx_out && g == 0) ? a.idx_out + static_cast<size_t>(b) * K : nullptr;
 #pragma unroll
