@@ -810,7 +810,7 @@ def main():
                                      "(5 launches; the step time is still divided by the 4 projections)")
                                     if shortcut_form else "timed by HIP events recorded inside larosa_layer_forward"))
                                 if B == 1 else
-                                "skinny_mfma_kernel: the 4 batched projections of a layer (union of kept rows)"),
+                                "skinny16_kernel / skinny32_kernel: the 4 batched projections of a layer (union of kept rows)"),
                      "bytes_per_launch": sel_bytes_launch, "us_per_launch": round(sparse_launch_us, 3)},
         "cpu_baseline": cpu,
         "extra": {

@@ -43,8 +43,8 @@ size_t gemv_partial_bytes_bound(int B, int d_in_max, int d_out_max) {
   return narrow > wide ? narrow : wide;
 }
 
-size_t batched_partial_bytes(const GemvPlan& p, int B, bool coef_scale, int d_in) {
-  const int tpg = batched_tokens_per_group(B, coef_scale, d_in);
+size_t batched_partial_bytes(const GemvPlan& p, int B, bool coef_scale, int d_in, int d_out) {
+  const size_t tpg = batched_tokens_per_group(B, coef_scale, d_in, d_out);
   const size_t groups = (B + tpg - 1) / tpg;
   return groups * tpg * p.partial_floats * sizeof(float);
 }
@@ -66,12 +66,14 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
     if (g_side < 1) g_side = 1;
     g_main = total - g_side > 0 ? total - g_side : 1;
   }
-  const size_t groups = (a.B + batched_tokens_per_group(a.B, cs, a.d_in) - 1) / batched_tokens_per_group(a.B, cs, a.d_in);
+  const int tpg = batched_tokens_per_group(a.B, cs, a.d_in, a.d_out);   // (a side product goes with the main one)
+  const size_t groups = (a.B + tpg - 1) / tpg;
   size_t slots = 0, pbytes = 0;
   unsigned* counters = static_cast<unsigned*>(ws);
   char* partial = static_cast<char*>(ws) + kCounterBytes;
-  auto place = [&](BatchArgs& x, int g_hint, bool scaled) {
-    const GemvPlan p = plan_batched(x.d_in, x.d_out, mfma, g_hint, may_widen && a.B > 16);
+  auto place = [&](BatchArgs& x, int g_hint) {
+    const GemvPlan p = plan_batched(x.d_in, x.d_out, mfma, g_hint, tpg == 32, may_widen);
+    x.group_tokens = tpg;
     x.chunk = p.chunk;
     x.G = p.G;
     x.nstrips = p.nstrips;
@@ -80,12 +82,12 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
     x.counters = counters + slots * kCounterStride;
     x.partial = reinterpret_cast<float*>(partial + pbytes);
     slots += groups * p.nstrips;
-    pbytes += batched_partial_bytes(p, x.B, scaled, x.d_in);
+    pbytes += groups * tpg * p.partial_floats * sizeof(float);
   };
   BatchPair pr{};
-  place(a, g_main, cs);
+  place(a, g_main);
   if (has_side) {
-    place(side, g_side, false);
+    place(side, g_side);
     pr.side = side;
     pr.side_G = side.G;
   }
@@ -103,8 +105,9 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
 // `behind` bytes after it, else of 128.
 size_t batched_head_bytes(int B, int d_in, int d_out, size_t ws_bytes, size_t behind) {
   const bool mfma = batched_uses_mfma(B, false, d_in);
+  const bool many = batched_tokens_per_group(B, false, d_in, d_out) == 32;
   auto head = [&](bool wide) {
-    return round_up(kCounterBytes + batched_partial_bytes(plan_batched(d_in, d_out, mfma, 0, wide && B > 16), B, false, d_in), 256);
+    return round_up(kCounterBytes + batched_partial_bytes(plan_batched(d_in, d_out, mfma, 0, many, wide), B, false, d_in, d_out), 256);
   };
   return head(true) + behind <= ws_bytes ? head(true) : head(false);
 }
@@ -355,9 +358,9 @@ static size_t layer_gemv_ws(const larosa_layer* L, int B) {
       const GemvPlan bp[] = {plan_batched(L->d, L->d, m), plan_batched(L->d, L->d_q + 2 * L->d_kv, m),
                              plan_batched(L->d_q, L->d, m), plan_batched(L->d, 2 * L->d_ff, m),
                              plan_batched(L->d_ff, L->d, m)};
-      const size_t side_bytes = (m && (L->shortcut_attn || L->shortcut_mlp)) ? batched_partial_bytes(bp[0], B, false, L->d) : 0;
+      const size_t side_bytes = (m && (L->shortcut_attn || L->shortcut_mlp)) ? batched_partial_bytes(bp[0], B, false, L->d, L->d) : 0;
       for (const GemvPlan& p : bp) {
-        const size_t need = round_up(kCounterBytes + batched_partial_bytes(p, B, m ? false : cs, L->d) + side_bytes, 256);
+        const size_t need = round_up(kCounterBytes + batched_partial_bytes(p, B, m ? false : cs, L->d, L->d) + side_bytes, 256);
         if (need > s) s = need;
       }
     }

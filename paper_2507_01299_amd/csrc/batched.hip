@@ -12,7 +12,7 @@
 //     its issue slots on B x 8 multiply-adds and coefficient reads per 16 bytes loaded.  Two kernels:
 //     up to 16 tokens (skinny16) a lane loads 8 consecutive columns of 4 rows (16 lanes x 16 bytes = 256 contiguous bytes
 //     per row), and a byte permute regroups those registers into the K-runs the instruction wants; the weight never
-//     passes through LDS.  More tokens (skinny32, groups of 32) keep the matrix cores busy longer per row, so the
+//     passes through LDS.  More tokens (skinny32, groups of 32; small weights stay with groups of 16) keep the matrix cores busy longer per row, so the
 //     loads go straight to LDS, ahead of the products and without registers of their own, and transposing LDS reads make
 //     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 149 us);
 //   * an fp32-FMA kernel (2 or 4 tokens per workgroup) remains for the one case the 16-bit B
@@ -361,14 +361,15 @@ constexpr int k16Strip = 128;        // output columns per workgroup of the kern
 constexpr int k16Waves = 8;             // its row-waves
 constexpr int k16Pitch = 130;   // floats per token row of an LDS tile (8-byte aligned, spreads tokens over banks)
 
-// Up to 16 tokens.  Geometry: a workgroup is 8 waves on ONE strip of 128 columns (256 contiguous bytes per row), each
+// Up to 16 tokens per group.  Geometry: a workgroup is 8 waves on ONE strip of 128 columns (256 contiguous bytes per row), each
 // wave taking its own run of 16-row tiles, two tiles (8 row loads of 16 bytes per lane) in flight.
 // Narrow strips keep the number of workgroups that share a strip -- and with it the partial-sum
 // traffic, which grows with the token count -- small.
 template <typename T>
 __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp) {
+  constexpr int NTB = 1;         // blocks of 16 tokens
   __shared__ float tile[4][16][k16Pitch];
-  __shared__ float scale_s[16];
+  __shared__ float scale_s[NTB * 16];
   __shared__ int s_last;
 
   const int tid = threadIdx.x;
@@ -376,7 +377,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
   const int rw = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kgrp = lane >> 4;    // K-run of 4 rows inside a 16-row tile
   const int m = lane & 15;       // column group (A operand) / token (B operand)
-  const int b0 = grp * 16;
+  const int b0 = grp * NTB * 16;
   const int K = a.d_in;
   const int chunk = a.chunk;
 
@@ -388,9 +389,11 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
     const int colbase = s * k16Strip + 8 * m;   // this lane's 8 columns (A operand)
     const bool colv = colbase < a.d_out;
 
-    float4_t acc[8];
+    float4_t acc[NTB][8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     const int ntiles = (n + 15) / 16;
     const int per = (ntiles + k16Waves - 1) / k16Waves;
@@ -398,7 +401,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
     const int tl1 = min(ntiles, tl0 + per);
     for (int tl = tl0; tl < tl1; tl += 2) {
       uint4 v[2][4];
-      uint2 bf[2];
+      uint2 bf[2][NTB];
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
         // first of this lane's 4 rows; t0 % 8 == 0, so j0 % 4 == 0.  A tile past this wave's run
@@ -413,17 +416,20 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
           const int r = min(j0 + q, t1 - 1);
           v[h2][q] = load_stream16(a.W + static_cast<size_t>(r) * a.d_out + (colv ? colbase : s * k16Strip));
         }
-        // B operand: 4 consecutive rows of token b0 + m; rows at or past t1 belong to
+        // B operand: 4 consecutive rows of token (b0 + tb*16 + m); rows at or past t1 belong to
         // another workgroup (or do not exist) and must contribute nothing
-        const int tok = b0 + m;
-        // j0 % 4 == 0 and K % 8 == 0, so min(j0, K - 4) keeps the four rows inside the token's vector
-        uint2 c = *reinterpret_cast<const uint2*>(a.C + static_cast<size_t>(min(tok, a.B - 1)) * K + min(j0, K - 4));
-        if (j0 + 1 >= t1) c.x &= 0x0000FFFFu;
-        if (j0 + 2 >= t1) c.y = 0u;
-        if (j0 + 3 >= t1) c.y &= 0x0000FFFFu;
-        if (j0 >= t1 || tok >= a.B) c.x = 0u;
-        if (tok >= a.B) c.y = 0u;
-        bf[h2] = c;
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+          const int tok = b0 + tb * 16 + m;
+          // j0 % 4 == 0 and K % 8 == 0, so min(j0, K - 4) keeps the four rows inside the token's vector
+          uint2 c = *reinterpret_cast<const uint2*>(a.C + static_cast<size_t>(min(tok, a.B - 1)) * K + min(j0, K - 4));
+          if (j0 + 1 >= t1) c.x &= 0x0000FFFFu;
+          if (j0 + 2 >= t1) c.y = 0u;
+          if (j0 + 3 >= t1) c.y &= 0x0000FFFFu;
+          if (j0 >= t1 || tok >= a.B) c.x = 0u;
+          if (tok >= a.B) c.y = 0u;
+          bf[h2][tb] = c;
+        }
       }
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
@@ -438,28 +444,29 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
           uint2 af;
           af.x = __builtin_amdgcn_perm(vw1[i >> 1], vw0[i >> 1], sel);
           af.y = __builtin_amdgcn_perm(vw3[i >> 1], vw2[i >> 1], sel);
-          acc[i] = mfma16<T>(af, bf[h2], acc[i]);
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) acc[tb][i] = mfma16<T>(af, bf[h2][tb], acc[tb][i]);
         }
       }
     }
 
     LAROSA_STAMP(1);
     const int n_s = ge.g_last - ge.g_first + 1;
-    const size_t slot_floats = static_cast<size_t>(16) * k16Strip;
+    const size_t slot_floats = static_cast<size_t>(NTB) * 16 * k16Strip;
     unsigned* ctr = a.counters + (static_cast<size_t>(grp) * a.nstrips + s) * kCounterStride;
-    // every partial of this token group as one buffer (slot of workgroup w at byte w * slot bytes; a thread's 16 bytes at tid * 16 within it);
+    // every partial of this token group as one buffer (slot of workgroup w at byte w * slot bytes; a thread's 16 bytes of token block tb at tb * 8 KiB + tid * 16 within it);
     // 16-byte accesses with the sc1 cache policy are coherent across the chip, see gemv_core.hpp
-    constexpr int slot_bytes = 8192;
+    const int slot_bytes = NTB * 8192;
     const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(
         a.partial + static_cast<size_t>(grp) * a.G * slot_floats, 0, a.G * slot_bytes, 0x00027000);
     constexpr int kCoherent = 16;
     const int my_slot = g * slot_bytes;
 
-    // Sum the 8 row-waves: waves 0-3 write their tiles, waves 4-7 add theirs on
+    // Sum the 8 row-waves of token block tb: waves 0-3 write their tiles, waves 4-7 add theirs on
     // top, then every thread adds the four tiles for its two float pairs (pair q: token q / 64,
     // columns 2*(q % 64), +1).  D element e of MFMA i in lane (kgrp, m) is column 32*kgrp + 8*e + i
     // of token m.  The order of the additions is fixed.
-    auto reduce_waves = [&](float2 (&sm)[2]) {
+    auto reduce_tb = [&](int tb, float2 (&sm)[2]) {
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         if ((rw >> 2) == r) {
@@ -468,7 +475,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               float* p = &tile[rw & 3][m][32 * kgrp + 8 * e + i];
-              *p = (r == 0) ? acc[i][e] : *p + acc[i][e];
+              *p = (r == 0) ? acc[tb][i][e] : *p + acc[tb][i][e];
             }
         }
         __syncthreads();
@@ -487,8 +494,8 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
       }
       __syncthreads();
     };
-    // epilogue: the 16 x 128 sums (pairs held as in reduce_waves) go through tile[0]
-    auto tile_out = [&](const float2 (&sm)[2]) {
+    // epilogue of one token block: its 16 x 128 sums (pairs held as in reduce_tb) go through tile[0]
+    auto tile_out = [&](int tb, const float2 (&sm)[2]) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int q = tid + k * kBThreads;
@@ -496,31 +503,37 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
       }
       __syncthreads();
       if (tid < 256) {
-        const int tok = b0 + (tid >> 4);
+        const int tok = b0 + tb * 16 + (tid >> 4);
         const int col = s * k16Strip + (tid & 15) * 8;
         if (tok < a.B && col < a.d_out) {
           float v[8];
           const float* p = &tile[0][tid >> 4][(tid & 15) * 8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = p[e];
-          store_out8<T>(a, tok, col, v, scale_s[tid >> 4]);
+          store_out8<T>(a, tok, col, v, scale_s[tb * 16 + (tid >> 4)]);
         }
       }
       __syncthreads();
     };
 
     if (n_s == 1) {
-      token_scales<T, k16Waves>(a, b0, 16, scale_s, lane, rw);
+      token_scales<T, k16Waves>(a, b0, NTB * 16, scale_s, lane, rw);
       __syncthreads();
-      float2 sm[2];
-      reduce_waves(sm);
-      tile_out(sm);
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) {
+        float2 sm[2];
+        reduce_tb(tb, sm);
+        tile_out(tb, sm);
+      }
     } else {
-      float2 sm[2];
-      reduce_waves(sm);
-      // the thread's two float pairs as one 16-byte chip-coherent store
-      const u32x4 v = {__float_as_uint(sm[0].x), __float_as_uint(sm[0].y), __float_as_uint(sm[1].x), __float_as_uint(sm[1].y)};
-      __builtin_amdgcn_raw_buffer_store_b128(v, slots, my_slot + tid * 16, 0, kCoherent);
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) {
+        float2 sm[2];
+        reduce_tb(tb, sm);
+        // the thread's two float pairs of the block as one 16-byte chip-coherent store
+        const u32x4 v = {__float_as_uint(sm[0].x), __float_as_uint(sm[0].y), __float_as_uint(sm[1].x), __float_as_uint(sm[1].y)};
+        __builtin_amdgcn_raw_buffer_store_b128(v, slots, my_slot + tb * 8192 + tid * 16, 0, kCoherent);
+      }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
       LAROSA_STAMP(2);
@@ -532,29 +545,31 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
       LAROSA_STAMP(3);
       if (s_last != 0) {   // uniform over the workgroup
         if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        token_scales<T, k16Waves>(a, b0, 16, scale_s, lane, rw);
-        // each thread owns 2 float pairs of the block and adds the partials in workgroup order
-        float2 sum[2];
-        sum[0] = sum[1] = make_float2(0.f, 0.f);
-        for (int gg = ge.g_first; gg <= ge.g_last; gg += 8) {
-          u32x4 v[8];
+        token_scales<T, k16Waves>(a, b0, NTB * 16, scale_s, lane, rw);
+        for (int tb = 0; tb < NTB; ++tb) {
+          // each thread owns 2 float pairs of the block and adds the partials in workgroup order
+          float2 sum[2];
+          sum[0] = sum[1] = make_float2(0.f, 0.f);
+          for (int gg = ge.g_first; gg <= ge.g_last; gg += 8) {
+            u32x4 v[8];
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            if (gg + q <= ge.g_last) {          // uniform over the workgroup: no partial is read twice
-              v[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, (gg + q) * slot_bytes + tid * 16, 0, kCoherent);
+            for (int q = 0; q < 8; ++q) {
+              if (gg + q <= ge.g_last) {          // uniform over the workgroup: no partial is read twice
+                v[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, (gg + q) * slot_bytes + tb * 8192 + tid * 16, 0, kCoherent);
+              }
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              if (gg + q <= ge.g_last) {
+                sum[0].x += __uint_as_float(v[q].x);
+                sum[0].y += __uint_as_float(v[q].y);
+                sum[1].x += __uint_as_float(v[q].z);
+                sum[1].y += __uint_as_float(v[q].w);
+              }
             }
           }
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            if (gg + q <= ge.g_last) {
-              sum[0].x += __uint_as_float(v[q].x);
-              sum[0].y += __uint_as_float(v[q].y);
-              sum[1].x += __uint_as_float(v[q].z);
-              sum[1].y += __uint_as_float(v[q].w);
-            }
-          }
+          tile_out(tb, sum);
         }
-        tile_out(sum);
       }
     }
   }
@@ -573,8 +588,8 @@ __device__ __forceinline__ float4_t mfma32<BF16>(u32x4 a, u32x4 b, float4_t c) {
 }
 
 // More than 16 tokens, in groups of 32.  What bounded the kernel above here: with two blocks of tokens a wave spends twice
-// as long between its batches of loads, so fewer are in flight (4096 x 22016, 32 tokens: 47.8 us on 172 workgroups; this
-// one 41.5).  For 16 tokens the two are level, and the one above keeps its smaller hand-off.
+// as long between its batches of loads, so fewer are in flight (4096 x 22016, 32 tokens: 47.5 us on 172 workgroups; this
+// one 42.3).  For 16 tokens the two are level, and the one above keeps its smaller hand-off.
 constexpr int kMRW = 4;             // row-waves of a workgroup
 constexpr int kMThreads = kMRW * 64;
 constexpr int kMRows = 32;          // rows of a tile: one step of a wave
@@ -841,8 +856,8 @@ hipError_t launch_batched_t(const BatchPair& p, hipStream_t st) {
     } else {
       hipLaunchKernelGGL((skinny_fma_kernel<T, 4>), dim3(a.G, (a.B + 3) / 4), block, 0, st, a);
     }
-  } else if (a.B <= 16) {
-    hipLaunchKernelGGL((skinny16_kernel<T>), dim3(a.G + p.side_G), dim3(k16Waves * 64), 0, st, p);
+  } else if (a.group_tokens <= 16) {
+    hipLaunchKernelGGL((skinny16_kernel<T>), dim3(a.G + p.side_G, (a.B + 15) / 16), dim3(k16Waves * 64), 0, st, p);
   } else {
     const bool wide = a.strip_cols == 256 || (p.side_G > 0 && p.side.strip_cols == 256);
     hipLaunchKernelGGL((skinny32_kernel<T>), dim3(a.G + p.side_G, (a.B + kMTokens - 1) / kMTokens), dim3(kMThreads),
@@ -858,27 +873,29 @@ bool batched_uses_mfma(int B, bool coef_scale, int d_in) { return B >= 2 && !coe
 
 int batched_g_total() { return tuning().g_target > 0 ? tuning().g_target : 256; }
 
-int batched_tokens_per_group(int B, bool coef_scale, int d_in) {
-  if (batched_uses_mfma(B, coef_scale, d_in)) return B <= 16 ? 16 : 32;
-  return B <= 2 ? 2 : 4;
+int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out) {
+  if (!batched_uses_mfma(B, coef_scale, d_in)) return B <= 2 ? 2 : 4;
+  // 17 .. 32 tokens on a small weight: reading it twice, out of the caches, costs less than the larger hand-off of a group
+  // of 32 (32 tokens: 1024 x 1024 11.4 against 15.8 us, 2048 x 2048 10.1 against 11.7; 2048 x 5632: 14.2 against 11.3)
+  const bool small = B <= 32 && d_out <= 32768 && static_cast<long>(d_in) * d_out <= 5L << 20;
+  return B <= 16 || small ? 16 : 32;
 }
 
-GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool may_widen) {
+GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool many, bool may_widen) {
   GemvPlan p;
-  // 512 contiguous bytes per row instead of 256 stream faster (8192 x 57344, 32 tokens: 150 against 170 us) but a strip's
-  // partial sums are twice as large: worth it where at most four workgroups share a strip (22016 outputs: 41.5 against
-  // 42.5 us; 12288, five to a strip: 26.8 against 26.3)
-  const bool wide = mfma && may_widen && (d_out + 255) / 256 > 51;
+  // 512 contiguous bytes per row instead of 256 stream faster (8192 x 57344, 32 tokens: 149 against 170 us), but where the
+  // narrow strips fill the chip once, wide ones need a hand-off that those do not (512 x 22016: 13.5 against 10 us): wide
+  // from more than one narrow strip per compute unit on
+  const bool wide = mfma && many && may_widen && (d_out + 127) / 128 > 256;
   p.strip_cols = wide ? 256 : 128;
   p.nstrips = (d_out + p.strip_cols - 1) / p.strip_cols;
   // one workgroup per compute unit: each strip gets the same number of workgroups, each of those an equal run
-  // of whole tiles (32 rows; 16 in the FMA kernel), so a workgroup never works on two strips
+  // of whole 16-row tiles (keeps row starts 8-aligned), so a workgroup never works on two strips
   long G = g_hint > 0 ? g_hint : batched_g_total();
   long wps = G / p.nstrips;
   if (wps < 1) wps = 1;
-  const long rows = mfma ? 32 : 16;
   long chunk = (d_in + wps - 1) / wps;
-  chunk = (chunk + rows - 1) / rows * rows;
+  chunk = (chunk + 15) / 16 * 16;
   if (!mfma && chunk > kBatchChunkMax) chunk = kBatchChunkMax;   // LDS staging of the coefficients
   wps = (d_in + chunk - 1) / chunk;
   p.chunk = static_cast<int>(chunk);

@@ -22,7 +22,7 @@
 #include <numeric>
 #define CK(x) do { hipError_t e = (x); if (e != hipSuccess) { printf("HIP error %s at %d\n", hipGetErrorString(e), __LINE__); exit(1); } } while (0)
 using namespace larosa;
-namespace larosa { int batched_tokens_per_group(int, bool, int) { return 0; } }
+namespace larosa { int batched_tokens_per_group(int, bool, int, int) { return 0; } }
 
 static inline uint32_t hashu(uint32_t x) { x ^= x >> 15; x *= 2246822519u; x ^= x >> 13; x *= 3266489917u; x ^= x >> 16; return x; }
 static inline float wval(size_t i, unsigned seed) { uint32_t x = hashu((uint32_t)i * 2654435761u + seed); return ((x & 0xFFFF) / 65536.0f - 0.5f) * 0.07f; }

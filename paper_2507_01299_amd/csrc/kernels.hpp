@@ -121,7 +121,8 @@ struct BatchArgs {
   uint16_t* y;                // [B, d_out]
   int d_in, d_out, B;
   int chunk, G, nstrips, wps; // strip g / wps, rows [(g % wps) * chunk, + chunk) of all d_in
-  int strip_cols;             // 128, or 256 (kernel for more than 16 tokens)
+  int strip_cols;             // 128, or 256 (kernel for groups of 32 tokens)
+  int group_tokens;           // tokens per group: 16 or 32 on the matrix cores, 2 or 4 else
   float* partial;             // [groups][G][tokens per group][strip_cols] fp32
   unsigned* counters;         // [groups][nstrips] arrival counters
   const uint16_t* coef_scale; // as in GemvArgs
@@ -132,11 +133,11 @@ struct BatchArgs {
 };
 constexpr int kBatchChunkMax = 4096;   // rows per workgroup segment (LDS coefficient staging)
 // g_hint > 0: number of workgroups to aim for (a product that shares its launch takes its share of the chip)
-// may_widen: strips of 256 columns for wide outputs (more than 16 tokens only; twice the scratch per token), else 128
-GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint = 0, bool may_widen = true);
+// many: groups of 32 tokens; may_widen: then strips of 256 columns for wide outputs, else 128
+GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint = 0, bool many = false, bool may_widen = false);
 int batched_g_total();      // workgroups a whole batched launch aims for
 bool batched_uses_mfma(int B, bool coef_scale, int d_in);
-int batched_tokens_per_group(int B, bool coef_scale, int d_in);
+int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out);
 hipError_t launch_batched(const BatchArgs& a, bool bf16, hipStream_t s);
 // Two independent batched products in one launch of the matrix-core kernel (same token count, no
 // fp32 coefficient scale): the first side_G workgroups of the grid run `side`.

@@ -251,11 +251,11 @@ def test_config0_single_linear_by_its_recipe(api, ws):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("B,d_in,d_out", [(17, 8, 8), (32, 40, 136), (31, 1000, 4096), (33, 72, 13064), (17, 520, 13312),
+@pytest.mark.parametrize("B,d_in,d_out", [(17, 8, 8), (32, 40, 136), (31, 1000, 4096), (32, 4120, 1544), (17, 1032, 5128), (33, 72, 33032), (17, 520, 33024),
                                           (48, 4120, 1032)])
 def test_more_than_16_tokens_in_both_strip_widths(api, dtype, B, d_in, d_out):
-    """The kernel for groups of 32 tokens: fewer rows than one tile, ragged rows and columns, a last group with one or
-    16 tokens, strips of 128 columns and (more than 13056 outputs) of 256; and wide outputs on a workspace that only
+    """Groups of 32 tokens, and (17 .. 32 tokens, small weights) two groups of 16 instead: fewer rows than one tile, ragged
+    rows and columns, a last group with one or 16 tokens, strips of 128 columns and (more than 32768 outputs) of 256; and wide outputs on a workspace that only
     holds the partial sums of 128-column strips."""
     print(f"B={B} d_in={d_in} d_out={d_out} {dtype}", flush=True)
     rng = np.random.default_rng(1700 + B)
@@ -264,10 +264,8 @@ def test_more_than_16_tokens_in_both_strip_widths(api, dtype, B, d_in, d_out):
     want = O.decode16(xb, dtype) @ O.decode16(wb, dtype)
     x, W = to_dev(xb, dtype), to_dev(wb, dtype)
     sizes = [api.workspace_bytes(B, d_in, d_out, d_in)]
-    if (d_out + 255) // 256 > 51:
-        groups, wps = (B + 31) // 32, max(1, 256 // ((d_out + 127) // 128))
-        chunk = (-(-d_in // wps) + 15) // 16 * 16
-        sizes.append((1 << 20) + groups * 32 * ((d_out + 127) // 128) * -(-d_in // chunk) * 128 * 4)
+    if d_out > 32768:
+        sizes.append((1 << 20) + (B + 31) // 32 * 32 * ((d_out + 127) // 128) * 128 * 4)
     outs = []
     for nbytes in sizes:
         w = api.Workspace(nbytes)
