@@ -14,7 +14,7 @@
 //     per row), and a byte permute regroups those registers into the K-runs the instruction wants; the weight never
 //     passes through LDS.  More tokens (skinny32, groups of 32; small weights stay with groups of 16) keep the matrix cores busy longer per row, so the
 //     loads go straight to LDS, ahead of the products and without registers of their own, and transposing LDS reads make
-//     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 149 us);
+//     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 151 us);
 //   * an fp32-FMA kernel (2 or 4 tokens per workgroup) remains for the one case the 16-bit B
 //     operand cannot express: a per-channel coefficient scale applied in fp32 (learned pre-norm
 //     scale in front of an explicit rotation).
