@@ -14,7 +14,7 @@
 //     per row), and a byte permute regroups those registers into the K-runs the instruction wants; the weight never
 //     passes through LDS.  More tokens (skinny32, groups of 32; small weights stay with groups of 16) keep the matrix cores busy longer per row, so the
 //     loads go straight to LDS, ahead of the products and without registers of their own, and transposing LDS reads make
-//     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 151 us);
+//     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 153 us);
 //   * an fp32-FMA kernel (2 or 4 tokens per workgroup) remains for the one case the 16-bit B
 //     operand cannot express: a per-channel coefficient scale applied in fp32 (learned pre-norm
 //     scale in front of an explicit rotation).
@@ -340,9 +340,8 @@ __global__ __launch_bounds__(kBThreads) void skinny_fma_kernel(BatchArgs a) {
 // matrix-core kernels: up to 16 tokens (skinny16), groups of 32 tokens (skinny32)
 // ------------------------------------------------------------------------------------------------
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef __bf16 bfloat8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
 template <typename T>
@@ -576,65 +575,54 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
   LAROSA_STAMP(5);
 }
 
-template <typename T>
-__device__ __forceinline__ float4_t mfma32(u32x4 a, u32x4 b, float4_t c);
-template <>
-__device__ __forceinline__ float4_t mfma32<F16>(u32x4 a, u32x4 b, float4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ float4_t mfma32<BF16>(u32x4 a, u32x4 b, float4_t c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bfloat8_t, a), __builtin_bit_cast(bfloat8_t, b), c, 0, 0, 0);
-}
-
 // More than 16 tokens, in groups of 32.  What bounded the kernel above here: with two blocks of tokens a wave spends twice
 // as long between its batches of loads, so fewer are in flight (4096 x 22016, 32 tokens: 47.5 us on 172 workgroups; this
-// one 42.3).  For 16 tokens the two are level, and the one above keeps its smaller hand-off.
-constexpr int kMRW = 4;             // row-waves of a workgroup
-constexpr int kMThreads = kMRW * 64;
-constexpr int kMRows = 32;          // rows of a tile: one step of a wave
-
-// Sizes of the kernel for strips of SC columns.
+// one 43.1).  For 16 tokens the two are level, and the one above keeps its smaller hand-off.
+// The sums are formed in that kernel's order, so a token's result does not depend on the size of its batch: eight runs of
+// 16-row tiles per workgroup, one 16-deep product after the other along a run, the runs added as (0 + 4) + (1 + 5) + ...
+constexpr int kMRuns = 8;           // runs of rows per workgroup
 constexpr int kMTokens = 32;
-template <int SC>
+constexpr int kMLds = 160 * 1024;   // a compute unit's LDS: the rings of all waves
+
+// Sizes of the kernel for strips of SC columns, NW waves and tiles of R rows.
+template <int SC, int NW, int R>
 struct SkinnyShape {
-  static constexpr int kTokens = kMTokens;
-  static constexpr int kStages = SC == 128 ? 4 : 2;              // tiles in a wave's ring
-  static constexpr int kTileBytes = kMRows * SC * 2;
-  static constexpr int kStage = kTileBytes + kMTokens * kMRows * 2;   // a tile and the tokens' coefficients of its rows
+  static constexpr int kTileBytes = R * SC * 2;
+  static constexpr int kStage = kTileBytes + kMTokens * R * 2;   // a tile and the tokens' coefficients of its rows
+  static constexpr int kStages = kMLds / NW / kStage;           // tiles in a wave's ring
   static constexpr int kRing = kStages * kStage;
-  static constexpr int kLds = kMRW * kRing;
   static constexpr int kPitch = SC + 4;                          // floats per token row of a wave's sums in LDS
-  static_assert(kLds <= 160 * 1024, "a compute unit's LDS");
-  static_assert(sizeof(float) * (kMRW * kTokens * kPitch + kTokens + 1) <= kLds, "sums, scales and flag reuse the rings");
+  static_assert(sizeof(float) * (4 * kMTokens * kPitch + kMTokens + 1) <= NW * kRing, "sums, scales and flag reuse the rings");
 };
 
 // Position of row k's 32-byte granules in a tile with G of them per row: granule q sits at q ^ granule_swap(k), so that
-// the sixteen rows of one transposing read lie in different banks.
+// the eight rows that half a wave's transposing read touches lie in different banks.
 template <int G>
-__device__ __forceinline__ int granule_swap(int k) { return ((k & 3) | (((k >> 3) & 3) << 2)) & (G - 1); }
+__device__ __forceinline__ int granule_swap(int k) { return k & (G - 1); }
 
-// Geometry: a workgroup is 4 waves on ONE strip of SC columns (2 SC contiguous bytes per row).  Each wave streams its own
-// run of 32-row tiles through a ring of its own in LDS: the loads go straight to LDS and run ahead of the products by
-// what the ring holds (at least 16 KiB a wave), and no wave waits for another until the sums meet.
-//   W tile    [32 rows][SC columns] as in memory, granules exchanged as above.  16 lanes of a transposing read point at
+// Geometry: a workgroup is NW waves on ONE strip of SC columns (2 SC contiguous bytes per row).  Each wave streams its own
+// runs of rows (one, or with four waves two) through a ring of its own in LDS: the loads go straight to LDS and run ahead
+// of the products by what the ring holds (at least 16 KiB a wave), and no wave waits for another until the sums meet.
+//   W tile    [R rows][SC columns] as in memory, granules exchanged as above.  16 lanes of a transposing read point at
 //             4 rows x 16 columns and receive 4 consecutive rows of one column each: the A operand (M = 16 columns,
-//             K = 32 rows).
-//   C tile    [16 tokens][32 rows], 16-byte piece p of token m at position p ^ (m / 4 % 4): the B operand.
-// Rows past the workgroup's range arrive as zeros (beyond the end of the buffer the tile's loads go through), and so do
-// columns past d_out, tokens past B and the coefficients of rows past the range.
-template <typename T, int SC>
+//             K = 16 rows).
+//   C tile    R = 32: two blocks of [16 tokens][32 rows], 16-byte piece p of token m at position p ^ (m / 4 % 4);
+//             R = 16: [32 tokens][16 rows].  The B operand.
+// Rows past the run arrive as zeros (beyond the end of the buffer the tile's loads go through), and so do columns past
+// d_out, tokens past B and the coefficients of rows past the run.
+template <typename T, int SC, int NW, int R>
 __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp) {
-  typedef SkinnyShape<SC> Sh;
+  typedef SkinnyShape<SC, NW, R> Sh;
   constexpr int NTB = kMTokens / 16;             // blocks of 16 tokens
-  constexpr int kTokens = Sh::kTokens, kStage = Sh::kStage, kRing = Sh::kRing, kPitch = Sh::kPitch;
+  constexpr int kTokens = kMTokens, kStage = Sh::kStage, kRing = Sh::kRing, kPitch = Sh::kPitch;
+  constexpr int kThreads = NW * 64;
   constexpr int kGroups = SC / 16;               // 16-column groups of the strip
   constexpr int kLoadsW = Sh::kTileBytes / 1024; // wave-loads per tile
-  constexpr int kLoads = kLoadsW + NTB;
+  constexpr int kLoadsC = R / 16;
+  constexpr int kLoads = kLoadsW + kLoadsC;
   constexpr int kRowLanes = SC / 8;              // lanes that load one row
   constexpr int kLoadRows = 64 / kRowLanes;
-  // sized at the launch: with the size in sight the compiler plans for one wave per SIMD, moves the accumulators to the
-  // upper register file and copies them around every product
+  constexpr int kCLanes = R / 8;                 // lanes that load one token's coefficients
   extern __shared__ __attribute__((aligned(1024))) char lds[];
 
   const int tid = threadIdx.x;
@@ -649,11 +637,11 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
   ge.t1 = __builtin_amdgcn_readfirstlane(ge.t1);
   const int s = ge.s;
 
-  // this wave's rows [r0, r1): whole tiles, the last one possibly short
-  const int ntiles = (ge.t1 - ge.t0 + kMRows - 1) / kMRows;
-  const int per = (ntiles + kMRW - 1) / kMRW;
-  const int tl0 = min(rw * per, ntiles), tl1 = min(tl0 + per, ntiles);
-  const int r0 = ge.t0 + tl0 * kMRows, r1 = min(ge.t1, ge.t0 + tl1 * kMRows);
+  // runs of whole 16-row tiles, the last one possibly short; run rw and (four waves) run rw + 4
+  const int per = ((ge.t1 - ge.t0 + 15) / 16 + kMRuns - 1) / kMRuns * 16;   // rows of a run
+  auto run_begin = [&](int run) __attribute__((always_inline)) { return min(ge.t1, ge.t0 + run * per); };
+  int r0 = run_begin(rw);                        // first row not yet asked for
+  int left = run_begin(rw + 1) - r0;             // rows of the run not yet asked for
 
   // ---- loads.  Wave-load q covers kLoadRows rows of the tile; a lane's place in the row is lane % kRowLanes pieces.
   uint32_t offW[kLoadsW];
@@ -663,93 +651,131 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
     const int col = (((pos >> 1) ^ granule_swap<kGroups>(row)) << 4) + (pos & 1) * 8;
     offW[q] = s * SC + col < d_out ? (static_cast<uint32_t>(row) * d_out + s * SC + col) * 2u : kOutside;
   }
-  uint32_t offC[NTB];
-  const int kC = 8 * ((lane & 3) ^ ((lane >> 4) & 3));           // first row of the lane's piece: token lane / 4, position lane % 4
+  uint32_t offC[kLoadsC];
+  // first row of the lane's piece: token lane / kCLanes (of its block), position lane % kCLanes
+  const int kC = R == 32 ? 8 * ((lane & 3) ^ ((lane >> 4) & 3)) : 8 * (lane & 1);
 #pragma unroll
-  for (int tb = 0; tb < NTB; ++tb) {
-    const int tok = tb * 16 + (lane >> 2);
-    offC[tb] = b0 + tok < a.B ? (static_cast<uint32_t>(tok) * K + kC) * 2u : kOutside;
+  for (int q = 0; q < kLoadsC; ++q) {
+    const int tok = q * 16 + lane / kCLanes;
+    offC[q] = b0 + tok < a.B ? (static_cast<uint32_t>(tok) * K + kC) * 2u : kOutside;
   }
   const uint32_t ring = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)lds)) + rw * kRing;
   const char* nextW = reinterpret_cast<const char*>(a.W) + static_cast<size_t>(r0) * d_out * 2;
   const char* nextC = reinterpret_cast<const char*>(a.C) + (static_cast<size_t>(b0) * K + r0) * 2;
-  int left = r1 - r0;                            // rows of the wave not yet asked for
+  const int steps0 = (left + R - 1) / R;         // tiles of the wave's first run, of its second
+  const int second = NW < kMRuns ? run_begin(rw + NW) : 0;
+  int left2 = NW < kMRuns ? run_begin(rw + NW + 1) - second : 0;
+  const int steps1 = (left2 + R - 1) / R;
   uint32_t in_stage = 0;
   const uint32_t bytesC = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(min(kTokens, a.B - b0)) * K * 2u);
   auto fetch = [&]() __attribute__((always_inline)) {
-    const int rows = __builtin_amdgcn_readfirstlane(max(0, min(kMRows, left)));   // (the clamp is a vector instruction)
+    const int rows = __builtin_amdgcn_readfirstlane(max(0, min(R, left)));   // (the clamp is a vector instruction)
     const u32x4 bufW = raw_buffer(nextW, static_cast<uint32_t>(rows) * d_out * 2u);
     const u32x4 bufC = raw_buffer(nextC, bytesC);
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb)
-      load_to_lds(bufC, ring + in_stage + Sh::kTileBytes + tb * 1024, kC < rows ? offC[tb] : kOutside);
+    for (int q = 0; q < kLoadsC; ++q)
+      load_to_lds(bufC, ring + in_stage + Sh::kTileBytes + q * 1024, kC < rows ? offC[q] : kOutside);
 #pragma unroll
     for (int q = 0; q < kLoadsW; ++q) load_to_lds_stream(bufW, ring + in_stage + q * 1024, offW[q]);
-    left -= kMRows;
-    nextW += static_cast<size_t>(kMRows) * d_out * 2;
-    nextC += kMRows * 2;
+    left -= R;
+    nextW += static_cast<size_t>(R) * d_out * 2;
+    nextC += R * 2;
+    if (NW < kMRuns && left <= 0 && left2 > 0) { // on to the second run (once)
+      left = left2;
+      left2 = 0;
+      nextW = reinterpret_cast<const char*>(a.W) + static_cast<size_t>(second) * d_out * 2;
+      nextC = reinterpret_cast<const char*>(a.C) + (static_cast<size_t>(b0) * K + second) * 2;
+    }
     in_stage = in_stage == (Sh::kStages - 1) * kStage ? 0 : in_stage + kStage;
   };
 
   // ---- operand reads
   const int grp16 = lane >> 4, j = lane & 15;
-  const int rowk = 8 * grp16 + (j >> 2);
-  const int sw = granule_swap<kGroups>(rowk);    // of the four rows from rowk on, and of the four after them
+  const int rowk = 4 * grp16 + (j >> 2);
+  const int sw = granule_swap<kGroups>(rowk);    // (and of row rowk + 16)
   const uint32_t rdW = ring + rowk * (SC * 2) + 8 * (j & 3);
-  const uint32_t rdC = ring + Sh::kTileBytes + j * 64 + ((grp16 ^ ((j >> 2) & 3)) * 16);
-  float4_t acc[NTB][kGroups];
+  const uint32_t rdC = ring + Sh::kTileBytes + (R == 32 ? j * 64 + (((grp16 >> 1) ^ ((j >> 2) & 3)) * 16) + (grp16 & 1) * 8 : j * 32 + grp16 * 8);
+  float4_t acc[NTB][kGroups], run_sum[NTB][kGroups];   // of the run at hand; of the runs before it
 #pragma unroll
   for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-    for (int i = 0; i < kGroups; ++i) acc[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < kGroups; ++i) acc[tb][i] = run_sum[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
 
   for (int i = 0; i < Sh::kStages; ++i) fetch();
   uint32_t stage = 0;
-  for (int t = tl0; t < tl1; ++t) {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((Sh::kStages - 1) * kLoads) : "memory");   // this tile has landed
-    u32x4 av[kGroups], bv[NTB];
+#pragma nounroll
+  for (int run = 0; run < kMRuns / NW; ++run) {
+    const int steps = run == 0 ? steps0 : steps1;
+    for (int t = 0; t < steps; ++t) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((Sh::kStages - 1) * kLoads) : "memory");   // this tile has landed
+      uint2 av[R / 16][kGroups], bv[R / 16][NTB];
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb) bv[tb] = *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(rdC + stage + tb * 1024);
+      for (int h = 0; h < R / 16; ++h)
 #pragma unroll
-    for (int i = 0; i < kGroups; ++i) {
-      const uint32_t p = rdW + stage + ((i ^ sw) * 32);
-      const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4_t*>(p)));
-      const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4_t*>(p + 4 * SC * 2)));
-      av[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+        for (int tb = 0; tb < NTB; ++tb)
+          bv[h][tb] = __builtin_bit_cast(uint2, *reinterpret_cast<const __attribute__((address_space(3))) u32x2*>(
+              R == 32 ? (rdC ^ (32 * h)) + stage + tb * 1024 : rdC + stage + tb * 512));
+#pragma unroll
+      for (int h = 0; h < R / 16; ++h)
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i) {
+          const uint32_t p = rdW + stage + ((i ^ sw) * 32) + h * (16 * SC * 2);
+          av[h][i] = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4_t*>(p)));
+        }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // it is in registers: its stage takes the next loads
+      fetch();
+#pragma unroll
+      for (int h = 0; h < R / 16; ++h)
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i)
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) acc[tb][i] = mfma16<T>(av[h][i], bv[h][tb], acc[tb][i]);
+      stage = stage == (Sh::kStages - 1) * kStage ? 0 : stage + kStage;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // it is in registers: its stage takes the next loads
-    fetch();
+    if constexpr (NW < kMRuns) {
 #pragma unroll
-    for (int i = 0; i < kGroups; ++i)
+      for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-      for (int tb = 0; tb < NTB; ++tb) acc[tb][i] = mfma32<T>(av[i], bv[tb], acc[tb][i]);
-    stage = stage == (Sh::kStages - 1) * kStage ? 0 : stage + kStage;
+        for (int i = 0; i < kGroups; ++i) {
+          run_sum[tb][i] += acc[tb][i];
+          acc[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    }
   }
   // every load has landed and every wave has left its ring: the LDS is free for the sums
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   __syncthreads();
   LAROSA_STAMP(1);
 
-  float* sums = reinterpret_cast<float*>(lds);                         // [wave][token][kPitch]
-  float* scale_s = sums + kMRW * kTokens * kPitch;                     // [token]
+  float* sums = reinterpret_cast<float*>(lds);                         // [run % 4][token][kPitch]
+  float* scale_s = sums + 4 * kTokens * kPitch;                        // [token]
   int* s_last = reinterpret_cast<int*>(scale_s + kTokens);
   // D element e of product i in lane (grp16, j) is column 16 i + 4 grp16 + e of token j
 #pragma unroll
-  for (int tb = 0; tb < NTB; ++tb)
+  for (int half = 0; half < NW / 4; ++half) {
+    if ((rw >> 2) == half) {
 #pragma unroll
-    for (int i = 0; i < kGroups; ++i)
-      *reinterpret_cast<float4_t*>(sums + (rw * kTokens + tb * 16 + j) * kPitch + 16 * i + 4 * grp16) = acc[tb][i];
+      for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i) {
+          float4_t* q = reinterpret_cast<float4_t*>(sums + ((rw & 3) * kTokens + tb * 16 + j) * kPitch + 16 * i + 4 * grp16);
+          const float4_t v = NW < kMRuns ? run_sum[tb][i] : acc[tb][i];
+          *q = half == 0 ? v : *q + v;
+        }
+    }
+    if (half + 1 < NW / 4) __syncthreads();
+  }
   const int n_s = ge.g_last - ge.g_first + 1;
-  if (n_s == 1) token_scales<T, kMRW>(a, b0, kTokens, scale_s, lane, rw);
+  if (n_s == 1) token_scales<T, NW>(a, b0, kTokens, scale_s, lane, rw);
   __syncthreads();
-  // a thread owns pieces tid + 256 p: columns 4 (piece % (SC / 4)) .. + 3 of token piece / (SC / 4)
-  constexpr int kPieces = kTokens * (SC / 4) / kMThreads;
+  // a thread owns pieces tid + kThreads p: columns 4 (piece % (SC / 4)) .. + 3 of token piece / (SC / 4)
+  constexpr int kPieces = kTokens * (SC / 4) / kThreads;
   constexpr int kPass = kPieces < 8 ? kPieces : 8;                     // pieces a finisher holds at a time
-  auto wave_sum_of = [&](int piece) __attribute__((always_inline)) {   // the four waves' sums, in order
+  auto wave_sum_of = [&](int piece) __attribute__((always_inline)) {   // the four pairs of runs, in order
     const float* q = sums + piece / (SC / 4) * kPitch + piece % (SC / 4) * 4;
     float4_t v = *reinterpret_cast<const float4_t*>(q);
 #pragma unroll
-    for (int w = 1; w < kMRW; ++w) v += *reinterpret_cast<const float4_t*>(q + w * kTokens * kPitch);
+    for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const float4_t*>(q + w * kTokens * kPitch);
     return v;
   };
   auto store_piece = [&](int piece, const float4_t& v) __attribute__((always_inline)) {
@@ -758,7 +784,7 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
   };
   if (n_s == 1) {
 #pragma unroll
-    for (int p = 0; p < kPieces; ++p) store_piece(tid + p * kMThreads, wave_sum_of(tid + p * kMThreads));
+    for (int p = 0; p < kPieces; ++p) store_piece(tid + p * kThreads, wave_sum_of(tid + p * kThreads));
     LAROSA_STAMP(5);
     return;
   }
@@ -773,8 +799,8 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
   const int mine = (g - ge.g_first) * kSlotBytes;
 #pragma unroll
   for (int p = 0; p < kPieces; ++p)
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wave_sum_of(tid + p * kMThreads)), slots,
-                                           mine + (tid + p * kMThreads) * 16, 0, kCoherent);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, wave_sum_of(tid + p * kThreads)), slots,
+                                           mine + (tid + p * kThreads) * 16, 0, kCoherent);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   LAROSA_STAMP(2);
@@ -789,7 +815,7 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
     return;
   }
   if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  token_scales<T, kMRW>(a, b0, kTokens, scale_s, lane, rw);
+  token_scales<T, NW>(a, b0, kTokens, scale_s, lane, rw);
   __syncthreads();
   // the thread's pieces of every partial, added in workgroup order
   constexpr int kAhead = 16 / kPass;             // partials in flight
@@ -804,7 +830,7 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
         if (w + q < n_s) {                       // uniform over the workgroup: no partial is read twice
 #pragma unroll
           for (int p = 0; p < kPass; ++p)
-            v[q][p] = __builtin_amdgcn_raw_buffer_load_b128(slots, (w + q) * kSlotBytes + (tid + (p0 + p) * kMThreads) * 16, 0, kCoherent);
+            v[q][p] = __builtin_amdgcn_raw_buffer_load_b128(slots, (w + q) * kSlotBytes + (tid + (p0 + p) * kThreads) * 16, 0, kCoherent);
         }
 #pragma unroll
       for (int q = 0; q < kAhead; ++q)
@@ -814,7 +840,7 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
         }
     }
 #pragma unroll
-    for (int p = 0; p < kPass; ++p) store_piece(tid + (p0 + p) * kMThreads, sm[p]);
+    for (int p = 0; p < kPass; ++p) store_piece(tid + (p0 + p) * kThreads, sm[p]);
   }
   LAROSA_STAMP(5);
 }
@@ -830,14 +856,17 @@ __global__ __launch_bounds__(k16Waves * 64) void skinny16_kernel(BatchPair p) {
   skinny16_body<T>(side ? p.side : p.main, side ? g : g - p.side_G, blockIdx.y);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kMThreads, 2) void skinny32_kernel(BatchPair p) {
+// NW = 4 waves of tiles of 32 rows, or 8 of 16 rows (launch_batched_t).  The four waves' two sets of sums take more than
+// the 256 registers that a second wave per SIMD would leave; the LDS holds one workgroup per compute unit anyway.
+template <typename T, int NW>
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 1 : 2) void skinny32_kernel(BatchPair p) {
+  constexpr int R = NW == 4 ? 32 : 16;
   const int g = blockIdx.x;
   const bool side = g < p.side_G;
   const BatchArgs& a = side ? p.side : p.main;
   const int own = side ? g : g - p.side_G;
-  if (a.strip_cols == 256) skinny32_body<T, 256>(a, own, blockIdx.y);
-  else skinny32_body<T, 128>(a, own, blockIdx.y);
+  if (a.strip_cols == 256) skinny32_body<T, 256, NW, R>(a, own, blockIdx.y);
+  else skinny32_body<T, 128, NW, R>(a, own, blockIdx.y);
 }
 
 }  // namespace
@@ -859,9 +888,13 @@ hipError_t launch_batched_t(const BatchPair& p, hipStream_t st) {
   } else if (a.group_tokens <= 16) {
     hipLaunchKernelGGL((skinny16_kernel<T>), dim3(a.G + p.side_G, (a.B + 15) / 16), dim3(k16Waves * 64), 0, st, p);
   } else {
-    const bool wide = a.strip_cols == 256 || (p.side_G > 0 && p.side.strip_cols == 256);
-    hipLaunchKernelGGL((skinny32_kernel<T>), dim3(a.G + p.side_G, (a.B + kMTokens - 1) / kMTokens), dim3(kMThreads),
-                       max(SkinnyShape<128>::kLds, wide ? SkinnyShape<256>::kLds : 0), st, p);
+    const dim3 grid(a.G + p.side_G, (a.B + kMTokens - 1) / kMTokens);
+    // rows of a workgroup at which four waves, with twice the tile, overtake eight, whose runs stay even when there are few
+    // tiles (32 tokens, eight / four waves: 4096 x 4096 (512 rows each) 14.0 / 14.7 us, 4096 x 8192 (1024) 18.9 / 19.0,
+    // 11008 x 4096 (1376) 24.0 / 23.9, 14336 x 4096 (1792) 28.6 / 27.7, 4096 x 12288 (2048) 29.4 / 26.7, 4096 x 22016
+    // (4096) 47.3 / 42.7; in strips of 256: 600 x 48720 19.1 / 20.2, 8192 x 57344 168 / 149)
+    if (a.chunk <= 1024) hipLaunchKernelGGL((skinny32_kernel<T, 8>), grid, dim3(512), kMLds, st, p);
+    else hipLaunchKernelGGL((skinny32_kernel<T, 4>), grid, dim3(256), kMLds, st, p);
   }
   return hipGetLastError();
 }

@@ -276,3 +276,25 @@ def test_more_than_16_tokens_in_both_strip_widths(api, dtype, B, d_in, d_out):
         stored_close(to_bits(y), want, dtype, f"workspace {nbytes}")
         outs.append(to_bits(y))
     assert all(rel_l2(O.decode16(o, dtype), O.decode16(outs[0], dtype)) <= REL_L2_TOL for o in outs)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("B,d_in,d_out", [(17, 8, 8), (33, 72, 136), (33, 1000, 4096), (32, 4120, 1544), (40, 1040, 16648), (33, 2056, 16520),
+                                          (32, 8192, 6144), (17, 520, 33032), (33, 1032, 33032)])
+def test_a_tokens_bits_do_not_depend_on_its_batch(api, dtype, B, d_in, d_out):
+    """More than 16 tokens run in kernels of their own (groups of 32, of eight or four waves, strips of 128 or 256
+    columns); they add a token's products in the order of the kernel for up to 16, so every token's result has the bits
+    that it has in a batch of 16.  Sizes: runs of rows that are empty, end inside a tile or differ in length, with and
+    without a hand-off between workgroups."""
+    print(f"B={B} d_in={d_in} d_out={d_out} {dtype}", flush=True)
+    rng = np.random.default_rng(1900 + B + d_in)
+    x = to_dev(O.encode16(rng.standard_normal((B, d_in)), dtype), dtype)
+    W = to_dev(O.encode16(synth.gaussian_weight(d_in, d_out, B), dtype), dtype)
+    w = api.workspace(B, d_in, d_out, d_in)
+    y = torch.zeros(B, d_out, dtype=x.dtype, device="cuda:0")
+    api.dense_gemv(W, x, y, dtype, w)
+    for first in list(range(0, B - 16, 16)) + [B - 16]:
+        part = torch.zeros(16, d_out, dtype=x.dtype, device="cuda:0")
+        api.dense_gemv(W, x[first:first + 16].contiguous(), part, dtype, w)
+        torch.cuda.synchronize()
+        assert torch.equal(part.view(torch.int16), y[first:first + 16].view(torch.int16)), first

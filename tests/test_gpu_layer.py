@@ -94,6 +94,32 @@ def test_large_batches_span_several_token_groups(api, B):
     check_layer_trace(layers[0], xb, tr, out)
 
 
+@pytest.mark.parametrize("form", ["shortcut", "folded"])
+@pytest.mark.parametrize("d", [1024, 1040])
+def test_a_tokens_bits_do_not_depend_on_its_batch(api, form, d):
+    """33 tokens through a layer, and the same tokens 16 at a time: equal bits.  gate|up is wide enough (32880) for strips of
+    256 columns, with the shortcut adapter's 128-column strips in the same launch; 1024 and 1040 input rows lie on the
+    two sides of the line between workgroups of eight and of four waves."""
+    print(f"layer in batches of 33 and 16 form={form} d={d}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(d)
+    rnd = lambda *s, std: torch.randn(*s, generator=g, device="cuda:0", dtype=torch.float16).mul_(std)  # noqa: E731
+    d_ff = 16440
+    extra = dict(adapter=rnd(d, d, std=d ** -0.5)) if form == "folded" else dict(shortcut_attn=rnd(d, d, std=d ** -0.5),
+                                                                                 shortcut_mlp=rnd(d, d, std=d ** -0.5))
+    layer = api.Layer(d, d, d, d_ff, 16, d * 3 // 5, d * 3 // 5, d * 3 // 5, d_ff * 3 // 5, rnd(d, 3 * d, std=0.02), rnd(d, d, std=0.02),
+                      rnd(d, 2 * d_ff, std=0.02), rnd(d_ff, d, std=0.02), "f16", rms_eps=1e-5, **extra)
+    x = rnd(33, d, std=1.0)
+    out = torch.zeros_like(x)
+    ws = api.Workspace(layer.workspace_bytes(33))
+    api.layer_forward(layer, x, out, ws)
+    for first in (0, 16, 17):
+        part = torch.zeros(16, d, dtype=x.dtype, device="cuda:0")
+        api.layer_forward(layer, x[first:first + 16].contiguous(), part, ws)
+        torch.cuda.synchronize()
+        assert torch.isfinite(part).all()
+        assert torch.equal(part.view(torch.int16), out[first:first + 16].view(torch.int16)), first
+
+
 @pytest.mark.parametrize("seed", list(range(12)))
 def test_seeded_random_shapes_and_kept_counts(api, seed):
     """Seeded random layer shapes (every width a multiple of 8, GQA groups of 1-4), random kept counts
