@@ -51,9 +51,8 @@ size_t batched_partial_bytes(const GemvPlan& p, int B, bool coef_scale, int d_in
 
 // One launch of the batched kernels (B > 1): C holds the tokens' coefficients over all rows.  An
 // optional side product (side.W != nullptr: same token count, no coefficient scale) shares the launch.
-// Wide outputs take 256-column strips where their partial sums fit the workspace, else 128-column ones.
-int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t st, BatchArgs side = BatchArgs{},
-                bool may_widen = true) {
+// Counters and partial sums are laid out, and refused, by strips of 128 columns, whatever the launch takes (plan_batched).
+int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t st, BatchArgs side = BatchArgs{}) {
   const bool cs = a.coef_scale != nullptr;
   const bool mfma = batched_uses_mfma(a.B, cs, a.d_in);
   const bool has_side = side.W != nullptr && mfma && batched_uses_mfma(a.B, false, side.d_in);
@@ -72,7 +71,7 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
   unsigned* counters = static_cast<unsigned*>(ws);
   char* partial = static_cast<char*>(ws) + kCounterBytes;
   auto place = [&](BatchArgs& x, int g_hint) {
-    const GemvPlan p = plan_batched(x.d_in, x.d_out, mfma, g_hint, tpg == 32, may_widen);
+    const GemvPlan p = plan_batched(x.d_in, x.d_out, mfma, g_hint, tpg == 32);
     x.group_tokens = tpg;
     x.chunk = p.chunk;
     x.G = p.G;
@@ -81,7 +80,7 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
     x.strip_cols = p.strip_cols;
     x.counters = counters + slots * kCounterStride;
     x.partial = reinterpret_cast<float*>(partial + pbytes);
-    slots += groups * p.nstrips;
+    slots += groups * ((x.d_out + kBatchStrip - 1) / kBatchStrip);
     pbytes += groups * tpg * p.partial_floats * sizeof(float);
   };
   BatchPair pr{};
@@ -91,25 +90,18 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
     pr.side = side;
     pr.side_G = side.G;
   }
-  const bool fits = ws && aligned(ws, 256) && ws_bytes >= kCounterBytes + pbytes;
-  if (may_widen && (slots > kCounterSlots || !fits)) return run_batched(a, bf16, ws, ws_bytes, st, side, false);
   if (slots > kCounterSlots) return LAROSA_EUNSUPPORTED;
-  if (!fits) return LAROSA_EWORKSPACE;
+  if (!ws || !aligned(ws, 256) || ws_bytes < kCounterBytes + pbytes) return LAROSA_EWORKSPACE;
   pr.main = a;
   if (launch_batched_pair(pr, bf16, st) != hipSuccess) return LAROSA_EHIP;
   if (side.W != nullptr && !has_side) return run_batched(side, bf16, ws, ws_bytes, st);   // FMA path: two launches
   return LAROSA_OK;
 }
 
-// Bytes at the head of a workspace that a batched product of B tokens takes, in strips of 256 columns if that leaves
-// `behind` bytes after it, else of 128.
-size_t batched_head_bytes(int B, int d_in, int d_out, size_t ws_bytes, size_t behind) {
-  const bool mfma = batched_uses_mfma(B, false, d_in);
-  const bool many = batched_tokens_per_group(B, false, d_in, d_out) == 32;
-  auto head = [&](bool wide) {
-    return round_up(kCounterBytes + batched_partial_bytes(plan_batched(d_in, d_out, mfma, 0, many, wide), B, false, d_in, d_out), 256);
-  };
-  return head(true) + behind <= ws_bytes ? head(true) : head(false);
+// Bytes at the head of a workspace that a batched product of B tokens takes.
+size_t batched_head_bytes(int B, int d_in, int d_out) {
+  const GemvPlan p = plan_batched(d_in, d_out, batched_uses_mfma(B, false, d_in));
+  return round_up(kCounterBytes + batched_partial_bytes(p, B, false, d_in, d_out), 256);
 }
 
 struct Carver {
@@ -281,7 +273,7 @@ int larosa_sparse_gemv(const void* Wp, const void* h, const int32_t* idx, void* 
   if (B > 1) {
     // masked coefficient matrix in the tail of the workspace, then one pass over the weight
     const size_t cbytes = static_cast<size_t>(B) * d_in * 2;
-    const size_t head = batched_head_bytes(B, d_in, d_out, ws_bytes, cbytes);
+    const size_t head = batched_head_bytes(B, d_in, d_out);
     if (!ws || !aligned(ws, 256) || ws_bytes < head + cbytes) return LAROSA_EWORKSPACE;
     uint16_t* C = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + head);
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -915,8 +907,7 @@ int larosa_sparse_gemv_static(const void* Wp, const void* h, const int32_t* idx,
   // the same scratch need as larosa_sparse_gemv's workspace, against the fixed size of the array
   size_t need;
   if (B > 1) {
-    const size_t cbytes = static_cast<size_t>(B) * d_in * 2;
-    need = batched_head_bytes(B, d_in, d_out, LAROSA_STATIC_SCRATCH_BYTES, cbytes) + cbytes;
+    need = batched_head_bytes(B, d_in, d_out) + static_cast<size_t>(B) * d_in * 2;
   } else {
     need = kCounterBytes + plan_gemv(d_out, K).partial_floats * sizeof(float);
   }

@@ -765,7 +765,7 @@ __device__ __forceinline__ void skinny32_body(const BatchArgs& a, int g, int grp
     }
     if (half + 1 < NW / 4) __syncthreads();
   }
-  const int n_s = ge.g_last - ge.g_first + 1;
+  const int n_s = SC == kBatchStrip ? ge.g_last - ge.g_first + 1 : 1;   // workgroups of the strip; wide strips have one (plan_batched)
   if (n_s == 1) token_scales<T, NW>(a, b0, kTokens, scale_s, lane, rw);
   __syncthreads();
   // a thread owns pieces tid + kThreads p: columns 4 (piece % (SC / 4)) .. + 3 of token piece / (SC / 4)
@@ -914,13 +914,9 @@ int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out) {
   return B <= 16 || small ? 16 : 32;
 }
 
-GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool many, bool may_widen) {
+GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool many) {
   GemvPlan p;
-  // 512 contiguous bytes per row instead of 256 stream faster (8192 x 57344, 32 tokens: 149 against 170 us), but where the
-  // narrow strips fill the chip once, wide ones need a hand-off that those do not (512 x 22016: 13.5 against 10 us): wide
-  // from more than one narrow strip per compute unit on
-  const bool wide = mfma && many && may_widen && (d_out + 127) / 128 > 256;
-  p.strip_cols = wide ? 256 : 128;
+  p.strip_cols = kBatchStrip;
   p.nstrips = (d_out + p.strip_cols - 1) / p.strip_cols;
   // one workgroup per compute unit: each strip gets the same number of workgroups, each of those an equal run
   // of whole 16-row tiles (keeps row starts 8-aligned), so a workgroup never works on two strips
@@ -935,6 +931,15 @@ GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool many, boo
   p.wps = static_cast<int>(wps);
   p.G = static_cast<int>(p.nstrips * wps);
   p.partial_floats = static_cast<size_t>(p.G) * p.strip_cols;  // per token
+  // 512 contiguous bytes per row instead of 256 stream faster (8192 x 57344, 32 tokens: 149 against 168 us), but where the
+  // narrow strips fill the chip once, wide ones need a hand-off that those do not (512 x 22016: 13.5 against 10 us): wide
+  // from more than one narrow strip per compute unit on, one workgroup each, so without a hand-off (and without the
+  // counters and partial sums that the narrow plan provides)
+  if (mfma && many && wps == 1 && p.nstrips > 256) {
+    p.strip_cols = 256;
+    p.nstrips = (d_out + 255) / 256;
+    p.G = p.nstrips;
+  }
   return p;
 }
 

@@ -59,7 +59,7 @@ int main(int argc, char** argv) {
     uint16_t *C, *y; CK(hipMalloc(&C, (size_t)32 * sh.d_in * 2)); CK(hipMalloc(&y, (size_t)32 * sh.d_out * 2));
     hipLaunchKernelGGL(fill_bf16, dim3(256), dim3(256), 0, 0, C, (size_t)32 * sh.d_in, 999u);
     CK(hipDeviceSynchronize());
-    const GemvPlan p = plan_batched(sh.d_in, sh.d_out, true, G, B > 16, true);
+    const GemvPlan p = plan_batched(sh.d_in, sh.d_out, true, G, B > 16);
     BatchArgs a{}; a.C = C; a.y = y; a.d_in = sh.d_in; a.d_out = sh.d_out; a.B = B;
     a.chunk = p.chunk; a.G = p.G; a.nstrips = p.nstrips; a.wps = p.wps; a.strip_cols = p.strip_cols; a.group_tokens = B > 16 ? 32 : 16; a.counters = ctr; a.partial = partial;
     const size_t need = (size_t)32 * p.partial_floats * sizeof(float);

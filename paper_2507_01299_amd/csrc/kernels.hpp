@@ -121,7 +121,7 @@ struct BatchArgs {
   uint16_t* y;                // [B, d_out]
   int d_in, d_out, B;
   int chunk, G, nstrips, wps; // strip g / wps, rows [(g % wps) * chunk, + chunk) of all d_in
-  int strip_cols;             // 128, or 256 (kernel for groups of 32 tokens)
+  int strip_cols;             // kBatchStrip, or 256 (kernel for groups of 32 tokens, one workgroup per strip)
   int group_tokens;           // tokens per group: 16 or 32 on the matrix cores, 2 or 4 else
   float* partial;             // [groups][G][tokens per group][strip_cols] fp32
   unsigned* counters;         // [groups][nstrips] arrival counters
@@ -131,10 +131,11 @@ struct BatchArgs {
   const uint16_t* residual;
   uint16_t* y_pre;
 };
+constexpr int kBatchStrip = 128;       // columns of a strip
 constexpr int kBatchChunkMax = 4096;   // rows per workgroup segment (LDS coefficient staging)
 // g_hint > 0: number of workgroups to aim for (a product that shares its launch takes its share of the chip)
-// many: groups of 32 tokens; may_widen: then strips of 256 columns for wide outputs, else 128
-GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint = 0, bool many = false, bool may_widen = false);
+// many: groups of 32 tokens, whose wide outputs take strips of 256 columns; partial_floats is the same without it
+GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint = 0, bool many = false);
 int batched_g_total();      // workgroups a whole batched launch aims for
 bool batched_uses_mfma(int B, bool coef_scale, int d_in);
 int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out);

@@ -298,3 +298,23 @@ def test_a_tokens_bits_do_not_depend_on_its_batch(api, dtype, B, d_in, d_out):
         api.dense_gemv(W, x[first:first + 16].contiguous(), part, dtype, w)
         torch.cuda.synchronize()
         assert torch.equal(part.view(torch.int16), y[first:first + 16].view(torch.int16)), first
+
+
+def test_many_workgroups_per_strip_of_a_wide_output(api):
+    """Asked for more workgroups than strips, a wide output keeps 128-column strips, whose workgroups hand over to each
+    other (strips of 256 columns have one workgroup each)."""
+    rng = np.random.default_rng(2000)
+    B, d_in, d_out, dtype = 33, 1000, 33032, "f16"
+    xb = O.encode16(rng.standard_normal((B, d_in)), dtype)
+    wb = O.encode16(synth.gaussian_weight(d_in, d_out, B), dtype)
+    x, W, y = to_dev(xb, dtype), to_dev(wb, dtype), torch.zeros(B, d_out, dtype=torch.float16, device="cuda:0")
+    api.set_tuning(0, 1024)
+    try:
+        w = api.workspace(B, d_in, d_out, d_in)
+        for _ in range(2):                                    # the arrival counters are left at zero
+            y.fill_(7.0)
+            api.dense_gemv(W, x, y, dtype, w)
+            torch.cuda.synchronize()
+            stored_close(to_bits(y), O.decode16(xb, dtype) @ O.decode16(wb, dtype), dtype, "wide output")
+    finally:
+        api.set_tuning(0, 0)

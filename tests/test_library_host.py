@@ -73,6 +73,20 @@ def test_invalid_arguments_are_rejected_on_the_host(lib):
         assert lib.larosa_set_tuning(key, good) == api.OK
 
 
+@pytest.mark.parametrize("B", [17, 33])
+def test_wide_batched_outputs_are_refused_as_ever(lib, B):
+    """More than 32768 outputs of more than 16 tokens may run in wider strips; a call is accepted and sized by the
+    strips of 128 columns all the same: one arrival counter per strip and group of 32 tokens, 4096 in all."""
+    from paper_2507_01299_amd import api
+    fake = ctypes.c_void_p(0x1000)        # never dereferenced: every call below is refused
+    groups = (B + 31) // 32
+    too_wide = (4096 // groups) * 128 + 8
+    assert lib.larosa_dense_gemv(fake, fake, fake, B, 8, too_wide, 0, fake, 1 << 40, None) == api.EUNSUPPORTED
+    widest = too_wide - 8
+    need = (1 << 20) + groups * 32 * widest * 4
+    assert lib.larosa_dense_gemv(fake, fake, fake, B, 8, widest, 0, fake, need - 1, None) == api.EWORKSPACE
+
+
 def test_layer_struct_validation(lib):
     from paper_2507_01299_amd import api
     L = api._Layer(256, 256, 128, 704, 32, 100, 100, 100, 300, 0x1000, 0x1000, 0x1000, 0x1000,
