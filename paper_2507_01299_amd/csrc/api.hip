@@ -54,8 +54,8 @@ size_t batched_partial_bytes(const GemvPlan& p, int B, bool coef_scale, int d_in
 // Counters and partial sums are laid out, and refused, by strips of 128 columns, whatever the launch takes (plan_batched).
 int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t st, BatchArgs side = BatchArgs{}) {
   const bool cs = a.coef_scale != nullptr;
-  const bool mfma = batched_uses_mfma(a.B, cs, a.d_in);
-  const bool has_side = side.W != nullptr && mfma && batched_uses_mfma(a.B, false, side.d_in);
+  const bool mfma = batched_uses_mfma(a.B, cs);
+  const bool has_side = side.W != nullptr && mfma;
   // two products in one launch share the chip in proportion to the bytes each has to read
   int g_main = 0, g_side = 0;
   if (has_side) {
@@ -100,7 +100,7 @@ int run_batched(BatchArgs a, bool bf16, void* ws, size_t ws_bytes, hipStream_t s
 
 // Bytes at the head of a workspace that a batched product of B tokens takes.
 size_t batched_head_bytes(int B, int d_in, int d_out) {
-  const GemvPlan p = plan_batched(d_in, d_out, batched_uses_mfma(B, false, d_in));
+  const GemvPlan p = plan_batched(d_in, d_out, batched_uses_mfma(B, false));
   return round_up(kCounterBytes + batched_partial_bytes(p, B, false, d_in, d_out), 256);
 }
 

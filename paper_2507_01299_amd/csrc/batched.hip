@@ -870,14 +870,14 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 1 : 2) void skinny32_kernel(Batc
 }
 
 }  // namespace
-bool batched_uses_mfma(int B, bool coef_scale, int d_in);
+bool batched_uses_mfma(int B, bool coef_scale);
 namespace {
 
 template <typename T>
 hipError_t launch_batched_t(const BatchPair& p, hipStream_t st) {
   const BatchArgs& a = p.main;
   const dim3 block(kBThreads);
-  if (!batched_uses_mfma(a.B, a.coef_scale != nullptr, a.d_in)) {
+  if (!batched_uses_mfma(a.B, a.coef_scale != nullptr)) {
     if (p.side_G > 0) return hipErrorInvalidValue;   // the FMA kernel carries no side product
     // (a per-channel coefficient scale is applied in fp32, which only the FMA kernel does)
     if (a.B <= 2) {
@@ -901,17 +901,17 @@ hipError_t launch_batched_t(const BatchPair& p, hipStream_t st) {
 
 }  // namespace
 
-// (a token group's coefficients are addressed with 32-bit byte offsets: 32 tokens of d_in values below 2 GiB)
-bool batched_uses_mfma(int B, bool coef_scale, int d_in) { return B >= 2 && !coef_scale && d_in < (1 << 25); }
+bool batched_uses_mfma(int B, bool coef_scale) { return B >= 2 && !coef_scale; }
 
 int batched_g_total() { return tuning().g_target > 0 ? tuning().g_target : 256; }
 
 int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out) {
-  if (!batched_uses_mfma(B, coef_scale, d_in)) return B <= 2 ? 2 : 4;
+  if (!batched_uses_mfma(B, coef_scale)) return B <= 2 ? 2 : 4;
   // 17 .. 32 tokens on a small weight: reading it twice, out of the caches, costs less than the larger hand-off of a group
   // of 32 (32 tokens: 1024 x 1024 11.4 against 15.8 us, 2048 x 2048 10.1 against 11.7; 2048 x 5632: 14.2 against 11.3)
   const bool small = B <= 32 && d_out <= 32768 && static_cast<long>(d_in) * d_out <= 5L << 20;
-  return B <= 16 || small ? 16 : 32;
+  // groups of 32 address their coefficients with 32-bit byte offsets: below 2 GiB a group
+  return B <= 16 || small || d_in >= 1 << 25 ? 16 : 32;
 }
 
 GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool many) {

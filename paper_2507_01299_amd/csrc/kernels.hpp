@@ -137,7 +137,7 @@ constexpr int kBatchChunkMax = 4096;   // rows per workgroup segment (LDS coeffi
 // many: groups of 32 tokens, whose wide outputs take strips of 256 columns; partial_floats is the same without it
 GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint = 0, bool many = false);
 int batched_g_total();      // workgroups a whole batched launch aims for
-bool batched_uses_mfma(int B, bool coef_scale, int d_in);
+bool batched_uses_mfma(int B, bool coef_scale);
 int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out);
 hipError_t launch_batched(const BatchArgs& a, bool bf16, hipStream_t s);
 // Two independent batched products in one launch of the matrix-core kernel (same token count, no

@@ -318,3 +318,21 @@ def test_many_workgroups_per_strip_of_a_wide_output(api):
             stored_close(to_bits(y), O.decode16(xb, dtype) @ O.decode16(wb, dtype), dtype, "wide output")
     finally:
         api.set_tuning(0, 0)
+
+
+@pytest.mark.parametrize("B", [2, 17])
+def test_inputs_of_2_to_the_25_channels_stay_on_the_matrix_cores(api, B):
+    """32 tokens of 2^25 channels are 2 GiB of coefficients, past the 32-bit offsets of the kernel for groups of 32: the one
+    for 16 tokens takes them, on the workspace of its 256 workgroups (the vector-unit kernel would need 8192)."""
+    print(f"B={B} d_in=2^25", flush=True)
+    d_in, d_out, dtype = 1 << 25, 8, "f16"
+    g = torch.Generator(device="cuda:0").manual_seed(B)
+    x = torch.randn(B, d_in, generator=g, device="cuda:0", dtype=torch.float16)
+    W = torch.randn(d_in, d_out, generator=g, device="cuda:0", dtype=torch.float16)
+    y = torch.zeros(B, d_out, dtype=torch.float16, device="cuda:0")
+    ws = api.Workspace((1 << 20) + (B + 15) // 16 * 16 * 256 * 128 * 4)
+    api.dense_gemv(W, x, y, dtype, ws)
+    torch.cuda.synchronize()
+    W64 = W.double()
+    want = torch.stack([x[b].double() @ W64 for b in range(B)]).cpu().numpy()
+    stored_close(to_bits(y), want, dtype, "2^25 channels")
