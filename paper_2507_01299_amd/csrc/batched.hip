@@ -34,22 +34,24 @@ constexpr int kBThreads = 512;
 // ------------------------------------------------------------------------------------------------
 // masked coefficient matrix from (h, idx): C[b,:] = 0, then C[b, idx[b,t]] = h[b, idx[b,t]]
 // ------------------------------------------------------------------------------------------------
-// A workgroup fills kPrepSlice channels of one token: it reads the token's whole index list (it need not be sorted),
+// A workgroup fills a slice of one token's channels: it reads the token's whole index list (it need not be sorted),
 // marks the kept channels of its slice in LDS and writes the slice once.  Latency-bound (under 1 MB moved): with one
 // workgroup per token, its scattered stores and the barrier between them, 5 tokens of 14336 channels took 6.9 us, so
 // slices of several workgroups per token and 16 index loads in flight per lane; now 3.9 us (5.2 with 8 in flight and 256
-// lanes).
-constexpr int kPrepSlice = 4096, kPrepThreads = 512;
+// lanes).  Every slice reads the list again, so from 64 slices of 4096 on the slices grow instead of their number (16
+// tokens of 2^22 channels, whole call: 0.70 ms; 5.9 ms in slices of 4096, 3.6 with one workgroup per token).
+constexpr int kPrepThreads = 512, kPrepPass = kPrepThreads * 8;   // channels per pass of the workgroup over its slice
+constexpr int kPrepSlices = 64, kPrepSliceMax = 1 << 17;
 __global__ __launch_bounds__(kPrepThreads) void batch_prep_kernel(const uint16_t* __restrict__ h, const int32_t* __restrict__ idx,
-                                                                  uint16_t* __restrict__ C, int d_in, int K) {
-  __shared__ __attribute__((aligned(8))) unsigned char kept[kPrepSlice];
+                                                                  uint16_t* __restrict__ C, int d_in, int K, int slice) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char kept[];   // [slice]
   const int b = blockIdx.y;
-  const int c0 = blockIdx.x * kPrepSlice;
-  const int i = c0 + threadIdx.x * 8;            // the lane's 8 channels (d_in % 8 == 0: all inside or none)
-  const size_t row = static_cast<size_t>(b) * d_in;
-  uint4 v = make_uint4(0u, 0u, 0u, 0u);
-  if (i < d_in) v = *reinterpret_cast<const uint4*>(h + row + i);
-  *reinterpret_cast<uint2*>(kept + threadIdx.x * 8) = make_uint2(0u, 0u);
+  const int c0 = blockIdx.x * slice, n = min(slice, d_in - c0);   // the slice's channels
+  const size_t at = static_cast<size_t>(b) * d_in + c0;
+  const int i0 = threadIdx.x * 8;                // the lane's 8 channels of the first pass (d_in % 8 == 0: all inside or none)
+  uint4 first = make_uint4(0u, 0u, 0u, 0u);
+  if (i0 < n) first = *reinterpret_cast<const uint4*>(h + at + i0);
+  for (int i = i0; i < n; i += kPrepPass) *reinterpret_cast<uint2*>(kept + i) = make_uint2(0u, 0u);
   __syncthreads();
   const int32_t* ib = idx + static_cast<size_t>(b) * K;
   constexpr int kAhead = 16;
@@ -60,19 +62,20 @@ __global__ __launch_bounds__(kPrepThreads) void batch_prep_kernel(const uint16_t
 #pragma unroll
     for (int q = 0; q < kAhead; ++q) {
       const unsigned e = static_cast<unsigned>(j[q] - c0);
-      if (e < static_cast<unsigned>(kPrepSlice)) kept[e] = 1;
+      if (e < static_cast<unsigned>(n)) kept[e] = 1;
     }
   }
   __syncthreads();
-  if (i < d_in) {
-    const uint2 k = *reinterpret_cast<const uint2*>(kept + threadIdx.x * 8);
+  for (int i = i0; i < n; i += kPrepPass) {
+    uint4 v = i == i0 ? first : *reinterpret_cast<const uint4*>(h + at + i);
+    const uint2 k = *reinterpret_cast<const uint2*>(kept + i);
     // bytes 0 / 1 of a channel pair to the two halves of its dword
     const auto mask2 = [](uint32_t bytes, int sh) { return ((bytes >> sh) & 1u) * 0xFFFFu | ((bytes >> (sh + 8)) & 1u) * 0xFFFF0000u; };
     v.x &= mask2(k.x, 0);
     v.y &= mask2(k.x, 16);
     v.z &= mask2(k.y, 0);
     v.w &= mask2(k.y, 16);
-    *reinterpret_cast<uint4*>(C + row + i) = v;
+    *reinterpret_cast<uint4*>(C + at + i) = v;
   }
 }
 
@@ -944,7 +947,11 @@ GemvPlan plan_batched(int d_in, int d_out, bool mfma, int g_hint, bool many) {
 }
 
 hipError_t launch_batch_prep(const uint16_t* h, const int32_t* idx, uint16_t* C, int B, int d_in, int K, hipStream_t s) {
-  hipLaunchKernelGGL(batch_prep_kernel, dim3((d_in + kPrepSlice - 1) / kPrepSlice, B), dim3(kPrepThreads), 0, s, h, idx, C, d_in, K);
+  const long passes = (static_cast<long>(d_in) + kPrepPass - 1) / kPrepPass;
+  const long even = (passes + kPrepSlices - 1) / kPrepSlices * kPrepPass;
+  const int slice = even < kPrepSliceMax ? static_cast<int>(even) : kPrepSliceMax;
+  const unsigned slices = static_cast<unsigned>((static_cast<long>(d_in) + slice - 1) / slice);
+  hipLaunchKernelGGL(batch_prep_kernel, dim3(slices, B), dim3(kPrepThreads), slice, s, h, idx, C, d_in, K, slice);
   return hipGetLastError();
 }
 

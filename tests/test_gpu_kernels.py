@@ -336,3 +336,24 @@ def test_inputs_of_2_to_the_25_channels_stay_on_the_matrix_cores(api, B):
     W64 = W.double()
     want = torch.stack([x[b].double() @ W64 for b in range(B)]).cpu().numpy()
     stored_close(to_bits(y), want, dtype, "2^25 channels")
+
+
+@pytest.mark.parametrize("d_in", [8, 4096, 4104, 64 * 4096 + 8, (1 << 23) + 4096 + 8])
+def test_masked_coefficients_of_every_slice(api, d_in):
+    """Several tokens with unsorted index lists: the masked coefficients are written in slices of 4096 channels, of more than
+    that past 64 slices, and of 131072 past 2^23 channels.  The result has the bits of the dense product of the masked
+    tokens."""
+    print(f"d_in={d_in}", flush=True)
+    B, d_out, dtype = 3, 8, "f16"
+    K = max(1, d_in * 3 // 7)
+    g = torch.Generator(device="cuda:0").manual_seed(d_in)
+    h = torch.randn(B, d_in, generator=g, device="cuda:0", dtype=torch.float16)
+    W = torch.randn(d_in, d_out, generator=g, device="cuda:0", dtype=torch.float16)
+    idx = torch.stack([torch.randperm(d_in, generator=g, device="cuda:0")[:K] for _ in range(B)])
+    masked = torch.zeros_like(h).scatter_(1, idx, h.gather(1, idx))
+    ws = api.workspace(B, d_in, d_out, K)
+    got, want = (torch.zeros(B, d_out, dtype=torch.float16, device="cuda:0") for _ in range(2))
+    api.sparse_gemv(W, h, idx.int().contiguous(), got, dtype, ws)
+    api.dense_gemv(W, masked, want, dtype, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
