@@ -241,14 +241,15 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_w4_kernel(const uin
     const float s = T::to_f32(sb);
     uint32_t packed = 0;
     if (__all(s == 0.f || (s > 0x1p-100f && s < 0x1p100f))) {
-      const float r1 = s > 0.f ? __frcp_rn(s) : 0.f;             // a scale of zero: all codes 8
+      const float r1 = s > 0.f ? __frcp_rn(s) : 0.f;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const float q0 = w[k] * r1;
         const float q = fminf(fmaxf(rintf(fmaf(fmaf(-q0, s, w[k]), r1, q0)), -8.f), 7.f);
         packed |= static_cast<uint32_t>(static_cast<int>(q) + 8) << (4 * k);
       }
-    } else {                                                     // reciprocals out of range, infinities, NaN
+      if (!(s > 0.f)) packed = 0x88888888u;                      // a scale of zero: all codes 8, those of NaN too
+    } else {                                                     // reciprocals out of range, infinities
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         float q = 0.f;

@@ -213,3 +213,28 @@ def test_quantiser_on_ties_and_extreme_groups(api, dtype, d_in, d_out):
     torch.cuda.synchronize()
     assert np.array_equal(q.cpu().numpy().view(np.uint32), O.pack_w4(codes))
     assert np.array_equal(to_bits(s), sbits)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_quantiser_on_nan_and_infinite_groups(api, dtype):
+    """A NaN does not count for its group's scale; its code is 8 where the scale is zero, else 0 (the lowest).  An infinite
+    group has an infinite scale: code 0 for the infinities themselves, 8 for the rest."""
+    rng = np.random.default_rng(47)
+    W = rng.standard_normal((6, 512))
+    W[:, :128] = 0.0
+    W[0, 5] = W[0, 127] = W[3, 64] = np.nan                       # zeros and NaN: scale 0
+    W[1, 128:256] = np.nan                                        # nothing but NaN: scale 0
+    W[2, 256:384:3] = np.nan                                      # NaN among numbers
+    W[4, 384], W[4, 390], W[4, 400] = np.inf, -np.inf, np.nan
+    wb = np.where(np.isnan(W), np.uint16(0x7E00 if dtype == "f16" else 0x7FC0), O.encode16(np.nan_to_num(W, posinf=np.inf, neginf=-np.inf), dtype))
+    w64 = O.decode16(wb, dtype)
+    finite = np.where(np.isfinite(w64), w64, 0.0)
+    codes, sbits = O.quantize_rtn_w4(finite, dtype)
+    codes = np.where(np.isnan(w64) & (np.repeat(O.decode16(sbits, dtype), 128, axis=1) > 0), 0, codes)
+    codes[4, 384:] = 8
+    codes[4, [384, 390, 400]] = 0
+    sbits[4, 3] = O.encode16(np.array([np.inf]), dtype)[0]
+    q, s = api.quantize_w4(to_dev(wb.astype(np.uint16), dtype), dtype)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_bits(s), sbits)
+    assert np.array_equal(q.cpu().numpy().view(np.uint32), O.pack_w4(codes.astype(np.uint8)))
