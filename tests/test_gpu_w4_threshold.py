@@ -238,3 +238,33 @@ def test_quantiser_on_nan_and_infinite_groups(api, dtype):
     torch.cuda.synchronize()
     assert np.array_equal(to_bits(s), sbits)
     assert np.array_equal(q.cpu().numpy().view(np.uint32), O.pack_w4(codes.astype(np.uint8)))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_quantiser_on_ties_of_scales_with_rounded_reciprocals(api, dtype):
+    """Scales S 2^e with S odd: 1 / S is not representable, so w times the rounded reciprocal misses some of the exact
+    half-integers w / s = k / 2 and rounds them to the other neighbour (worked out here in 32 bits: the inputs hold such
+    pairs).  The codes are those of the division."""
+    bits, exps = (11, range(-12, 4)) if dtype == "f16" else (8, range(-90, 91, 12))
+    rng = np.random.default_rng(53)
+    odd = np.arange(3, 2 ** bits // 7, 2)                         # 7 S, the group's largest value, is representable
+    S = np.tile(odd, 3)
+    W = np.zeros((len(S), 128))
+    missed = 0
+    for r, s in enumerate(S):
+        ks = np.array([k for k in range(-13, 14) if abs(k) * s < 2 ** bits])
+        k = rng.choice(ks, 128)
+        k[:len(ks)] = ks                                          # every tie of this scale that is representable
+        w = k * (s / 2.0)
+        plain = np.rint((w.astype(np.float32) * (np.float32(1.0) / np.float32(s))).astype(np.float32))
+        missed += int((plain != np.rint(k / 2.0)).sum())
+        w[127] = 7.0 * s
+        W[r] = w * 2.0 ** rng.choice(exps)
+    assert missed > 0
+    wb = O.encode16(W, dtype)
+    assert np.array_equal(O.decode16(wb, dtype), W)               # nothing was rounded on the way in
+    codes, sbits = O.quantize_rtn_w4(W, dtype)
+    q, sc = api.quantize_w4(to_dev(wb, dtype), dtype)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_bits(sc), sbits)
+    assert np.array_equal(q.cpu().numpy().view(np.uint32), O.pack_w4(codes))
