@@ -102,7 +102,11 @@ _DTYPE_CODES = {F16: F16, "f16": F16, torch.float16: F16, BF16: BF16, "bf16": BF
 def dtype_code(t) -> int:
     try:
         return _DTYPE_CODES[t]
-    except (KeyError, TypeError):
+    except (KeyError, TypeError):        # not found by hash: a 0-d array or tensor equal to a code is one too
+        if t in (F16, "f16", torch.float16):
+            return F16
+        if t in (BF16, "bf16", torch.bfloat16):
+            return BF16
         raise ValueError(f"unsupported dtype {t}") from None
 
 

@@ -38,6 +38,19 @@ def test_status_strings_and_version(lib):
     assert len(seen) == 6 and api.status_string(0) == "ok"
 
 
+def test_dtype_codes():
+    import numpy as np
+    import torch
+    from paper_2507_01299_amd import api
+    for t in (0, False, np.int64(0), np.array(0), torch.tensor(0), "f16", torch.float16):
+        assert api.dtype_code(t) == api.F16
+    for t in (1, True, 1.0, np.int32(1), np.array(1), torch.tensor(1), "bf16", torch.bfloat16):
+        assert api.dtype_code(t) == api.BF16
+    for t in (2, -1, None, "f32", torch.float32, [0], np.array(2), torch.tensor(2)):
+        with pytest.raises(ValueError):
+            api.dtype_code(t)
+
+
 def test_workspace_bytes_is_pure_and_monotone(lib):
     a = lib.larosa_workspace_bytes(1, 4096, 4096, 2457)
     b = lib.larosa_workspace_bytes(1, 4096, 22016, 2457)
