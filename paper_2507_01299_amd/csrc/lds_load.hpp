@@ -20,14 +20,15 @@ __device__ __forceinline__ uint32_t __attribute__((ext_vector_type(4))) raw_buff
 
 // 16 bytes per lane from buffer offset `off`: lane l's piece lands at LDS byte lds_byte + 16 l.  Written as an
 // instruction because the compiler would wait for every outstanding load of this kind before each LDS read; the callers
-// count them themselves (s_waitcnt vmcnt).  m0 is not used for anything else in these kernels.
+// count them themselves (s_waitcnt vmcnt).  m0 is declared as
+// overwritten; what a load writes to LDS is ordered by those waits, which are memory barriers to the compiler.
 __device__ __forceinline__ void load_to_lds(uint32_t __attribute__((ext_vector_type(4))) buf, uint32_t lds_byte, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(off), "s"(buf));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_byte), "v"(off), "s"(buf) : "m0");
 }
 
 // The same for data that is read once (non-temporal).
 __device__ __forceinline__ void load_to_lds_stream(uint32_t __attribute__((ext_vector_type(4))) buf, uint32_t lds_byte, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds_byte), "v"(off), "s"(buf));
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds" ::"s"(lds_byte), "v"(off), "s"(buf) : "m0");
 }
 
 }  // namespace larosa
