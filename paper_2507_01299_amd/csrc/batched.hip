@@ -911,8 +911,12 @@ int batched_g_total() { return tuning().g_target > 0 ? tuning().g_target : 256; 
 int batched_tokens_per_group(int B, bool coef_scale, int d_in, int d_out) {
   if (!batched_uses_mfma(B, coef_scale)) return B <= 2 ? 2 : 4;
   // 17 .. 32 tokens on a small weight: reading it twice, out of the caches, costs less than the larger hand-off of a group
-  // of 32 (32 tokens: 1024 x 1024 11.4 against 15.8 us, 2048 x 2048 10.1 against 11.7; 2048 x 5632: 14.2 against 11.3)
-  const bool small = B <= 32 && d_out <= 32768 && static_cast<long>(d_in) * d_out <= 5L << 20;
+  // of 32.  Measured from 0.5 to 15 M values, tall and flat (two groups of 16 / one of 32, 32 tokens): 1024 x 1024 11.8 /
+  // 14.6 us, 8192 x 512 15.1 / 20.1, 512 x 8192 8.6 / 9.4, 2560 x 2560 11.0 / 12.4, 2048 x 4096 11.5 / 12.5, 8192 x 1024
+  // 14.3 / 16.5, 1024 x 8192 10.7 / 10.9 (512 x 16384, the flattest, 10.5 / 10.2); level at 9.4 M (3072 x 3072 13.3 / 13.0);
+  // then 2560 x 4096 13.7 / 13.1, 2048 x 5632 14.8 / 12.0, 1024 x 11008 14.7 / 11.6.  A side product shares the
+  // main one's launch and with it the size of its groups.
+  const bool small = B <= 32 && d_out <= 32768 && static_cast<long>(d_in) * d_out <= 8L << 20;
   // groups of 32 address their coefficients with 32-bit byte offsets: below 2 GiB a group
   return B <= 16 || small || d_in >= 1 << 25 ? 16 : 32;
 }

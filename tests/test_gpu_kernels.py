@@ -280,7 +280,7 @@ def test_more_than_16_tokens_in_both_strip_widths(api, dtype, B, d_in, d_out):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("B,d_in,d_out", [(17, 8, 8), (33, 72, 136), (33, 1000, 4096), (32, 4120, 1544), (40, 1040, 16648), (33, 2056, 16520),
-                                          (32, 8192, 6144), (17, 520, 33032), (33, 1032, 33032)])
+                                          (31, 2120, 4104), (32, 2048, 4096), (32, 8192, 6144), (17, 520, 33032), (33, 1032, 33032)])
 def test_a_tokens_bits_do_not_depend_on_its_batch(api, dtype, B, d_in, d_out):
     """More than 16 tokens run in kernels of their own (groups of 32, of eight or four waves, strips of 128 or 256
     columns); they add a token's products in the order of the kernel for up to 16, so every token's result has the bits
