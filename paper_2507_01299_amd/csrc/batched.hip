@@ -369,9 +369,11 @@ constexpr int k16Pitch = 130;   // floats per token row of an LDS tile (8-byte a
 // traffic, which grows with the token count -- small.
 template <typename T>
 __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp) {
-  constexpr int NTB = 1;         // blocks of 16 tokens
   __shared__ float tile[4][16][k16Pitch];
-  __shared__ float scale_s[NTB * 16];
+  // blocks of 16 tokens.  The three loops over it stay: written straight, the compiler lays this kernel's tail out
+  // differently and its launches take 0.3 - 0.4 % longer (8B-shaped halves of 13 tokens 129.5 -> 129.9 us)
+  constexpr int NTB = 1;
+  __shared__ float scale_s[16];
   __shared__ int s_last;
 
   const int tid = threadIdx.x;
@@ -379,7 +381,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
   const int rw = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kgrp = lane >> 4;    // K-run of 4 rows inside a 16-row tile
   const int m = lane & 15;       // column group (A operand) / token (B operand)
-  const int b0 = grp * NTB * 16;
+  const int b0 = grp * 16;
   const int K = a.d_in;
   const int chunk = a.chunk;
 
@@ -391,11 +393,9 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
     const int colbase = s * k16Strip + 8 * m;   // this lane's 8 columns (A operand)
     const bool colv = colbase < a.d_out;
 
-    float4_t acc[NTB][8];
+    float4_t acc[8];
 #pragma unroll
-    for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[tb][i] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 8; ++i) acc[i] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     const int ntiles = (n + 15) / 16;
     const int per = (ntiles + k16Waves - 1) / k16Waves;
@@ -403,7 +403,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
     const int tl1 = min(ntiles, tl0 + per);
     for (int tl = tl0; tl < tl1; tl += 2) {
       uint4 v[2][4];
-      uint2 bf[2][NTB];
+      uint2 bf[2];
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
         // first of this lane's 4 rows; t0 % 8 == 0, so j0 % 4 == 0.  A tile past this wave's run
@@ -418,20 +418,17 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
           const int r = min(j0 + q, t1 - 1);
           v[h2][q] = load_stream16(a.W + static_cast<size_t>(r) * a.d_out + (colv ? colbase : s * k16Strip));
         }
-        // B operand: 4 consecutive rows of token (b0 + tb*16 + m); rows at or past t1 belong to
-        // another workgroup (or do not exist) and must contribute nothing
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-          const int tok = b0 + tb * 16 + m;
-          // j0 % 4 == 0 and K % 8 == 0, so min(j0, K - 4) keeps the four rows inside the token's vector
-          uint2 c = *reinterpret_cast<const uint2*>(a.C + static_cast<size_t>(min(tok, a.B - 1)) * K + min(j0, K - 4));
-          if (j0 + 1 >= t1) c.x &= 0x0000FFFFu;
-          if (j0 + 2 >= t1) c.y = 0u;
-          if (j0 + 3 >= t1) c.y &= 0x0000FFFFu;
-          if (j0 >= t1 || tok >= a.B) c.x = 0u;
-          if (tok >= a.B) c.y = 0u;
-          bf[h2][tb] = c;
-        }
+        // B operand: 4 consecutive rows of token b0 + m; rows at or past t1 belong to another workgroup
+        // (or do not exist) and must contribute nothing
+        const int tok = b0 + m;
+        // j0 % 4 == 0 and K % 8 == 0, so min(j0, K - 4) keeps the four rows inside the token's vector
+        uint2 c = *reinterpret_cast<const uint2*>(a.C + static_cast<size_t>(min(tok, a.B - 1)) * K + min(j0, K - 4));
+        if (j0 + 1 >= t1) c.x &= 0x0000FFFFu;
+        if (j0 + 2 >= t1) c.y = 0u;
+        if (j0 + 3 >= t1) c.y &= 0x0000FFFFu;
+        if (j0 >= t1 || tok >= a.B) c.x = 0u;
+        if (tok >= a.B) c.y = 0u;
+        bf[h2] = c;
       }
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
@@ -446,29 +443,28 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
           uint2 af;
           af.x = __builtin_amdgcn_perm(vw1[i >> 1], vw0[i >> 1], sel);
           af.y = __builtin_amdgcn_perm(vw3[i >> 1], vw2[i >> 1], sel);
-#pragma unroll
-          for (int tb = 0; tb < NTB; ++tb) acc[tb][i] = mfma16<T>(af, bf[h2][tb], acc[tb][i]);
+          acc[i] = mfma16<T>(af, bf[h2], acc[i]);
         }
       }
     }
 
     LAROSA_STAMP(1);
     const int n_s = ge.g_last - ge.g_first + 1;
-    const size_t slot_floats = static_cast<size_t>(NTB) * 16 * k16Strip;
+    const size_t slot_floats = 16 * k16Strip;
     unsigned* ctr = a.counters + (static_cast<size_t>(grp) * a.nstrips + s) * kCounterStride;
-    // every partial of this token group as one buffer (slot of workgroup w at byte w * slot bytes; a thread's 16 bytes of token block tb at tb * 8 KiB + tid * 16 within it);
+    // every partial of this token group as one buffer (slot of workgroup w at byte w * slot bytes; a thread's 16 bytes at tid * 16 within it);
     // 16-byte accesses with the sc1 cache policy are coherent across the chip, see gemv_core.hpp
-    const int slot_bytes = NTB * 8192;
+    const int slot_bytes = 8192;
     const __amdgpu_buffer_rsrc_t slots = __builtin_amdgcn_make_buffer_rsrc(
         a.partial + static_cast<size_t>(grp) * a.G * slot_floats, 0, a.G * slot_bytes, 0x00027000);
     constexpr int kCoherent = 16;
     const int my_slot = g * slot_bytes;
 
-    // Sum the 8 row-waves of token block tb: waves 0-3 write their tiles, waves 4-7 add theirs on
+    // Sum the 8 row-waves: waves 0-3 write their tiles, waves 4-7 add theirs on
     // top, then every thread adds the four tiles for its two float pairs (pair q: token q / 64,
     // columns 2*(q % 64), +1).  D element e of MFMA i in lane (kgrp, m) is column 32*kgrp + 8*e + i
     // of token m.  The order of the additions is fixed.
-    auto reduce_tb = [&](int tb, float2 (&sm)[2]) {
+    auto reduce = [&](float2 (&sm)[2]) {
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         if ((rw >> 2) == r) {
@@ -477,7 +473,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               float* p = &tile[rw & 3][m][32 * kgrp + 8 * e + i];
-              *p = (r == 0) ? acc[tb][i][e] : *p + acc[tb][i][e];
+              *p = (r == 0) ? acc[i][e] : *p + acc[i][e];
             }
         }
         __syncthreads();
@@ -496,8 +492,8 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
       }
       __syncthreads();
     };
-    // epilogue of one token block: its 16 x 128 sums (pairs held as in reduce_tb) go through tile[0]
-    auto tile_out = [&](int tb, const float2 (&sm)[2]) {
+    // epilogue: the 16 x 128 sums (pairs held as in reduce) go through tile[0]
+    auto tile_out = [&](const float2 (&sm)[2]) {
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int q = tid + k * kBThreads;
@@ -505,33 +501,33 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
       }
       __syncthreads();
       if (tid < 256) {
-        const int tok = b0 + tb * 16 + (tid >> 4);
+        const int tok = b0 + (tid >> 4);
         const int col = s * k16Strip + (tid & 15) * 8;
         if (tok < a.B && col < a.d_out) {
           float v[8];
           const float* p = &tile[0][tid >> 4][(tid & 15) * 8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = p[e];
-          store_out8<T>(a, tok, col, v, scale_s[tb * 16 + (tid >> 4)]);
+          store_out8<T>(a, tok, col, v, scale_s[tid >> 4]);
         }
       }
       __syncthreads();
     };
 
     if (n_s == 1) {
-      token_scales<T, k16Waves>(a, b0, NTB * 16, scale_s, lane, rw);
+      token_scales<T, k16Waves>(a, b0, 16, scale_s, lane, rw);
       __syncthreads();
 #pragma unroll
       for (int tb = 0; tb < NTB; ++tb) {
         float2 sm[2];
-        reduce_tb(tb, sm);
-        tile_out(tb, sm);
+        reduce(sm);
+        tile_out(sm);
       }
     } else {
 #pragma unroll
       for (int tb = 0; tb < NTB; ++tb) {
         float2 sm[2];
-        reduce_tb(tb, sm);
+        reduce(sm);
         // the thread's two float pairs of the block as one 16-byte chip-coherent store
         const u32x4 v = {__float_as_uint(sm[0].x), __float_as_uint(sm[0].y), __float_as_uint(sm[1].x), __float_as_uint(sm[1].y)};
         __builtin_amdgcn_raw_buffer_store_b128(v, slots, my_slot + tb * 8192 + tid * 16, 0, kCoherent);
@@ -547,7 +543,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
       LAROSA_STAMP(3);
       if (s_last != 0) {   // uniform over the workgroup
         if (tid == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        token_scales<T, k16Waves>(a, b0, NTB * 16, scale_s, lane, rw);
+        token_scales<T, k16Waves>(a, b0, 16, scale_s, lane, rw);
         for (int tb = 0; tb < NTB; ++tb) {
           // each thread owns 2 float pairs of the block and adds the partials in workgroup order
           float2 sum[2];
@@ -557,7 +553,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
               if (gg + q <= ge.g_last) {          // uniform over the workgroup: no partial is read twice
-                v[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, (gg + q) * slot_bytes + tb * 8192 + tid * 16, 0, kCoherent);
+                v[q] = __builtin_amdgcn_raw_buffer_load_b128(slots, (gg + q) * slot_bytes + tid * 16, 0, kCoherent);
               }
             }
 #pragma unroll
@@ -570,7 +566,7 @@ __device__ __forceinline__ void skinny16_body(const BatchArgs& a, int g, int grp
               }
             }
           }
-          tile_out(tb, sum);
+          tile_out(sum);
         }
       }
     }
