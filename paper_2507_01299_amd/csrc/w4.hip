@@ -240,15 +240,22 @@ __global__ __launch_bounds__(kQuantWaves * 64) void quantize_w4_kernel(const uin
     const uint16_t sb = T::from_f32(m / 7.0f);
     const float s = T::to_f32(sb);
     uint32_t packed = 0;
-    if (__all(s == 0.f || (s > 0x1p-100f && s < 0x1p100f))) {
-      const float r1 = s > 0.f ? __frcp_rn(s) : 0.f;
+    // Three ways, chosen by the wave: scales in the reciprocal's range (lanes outside the matrix do not count); zeros
+    // among them, which need two selects (as the only way 1 - 3 % of the kernel's time); else divisions.
+    const bool plain = s > 0x1p-100f && s < 0x1p100f;
+    auto by_reciprocal = [&](float r1) __attribute__((always_inline)) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const float q0 = w[k] * r1;
         const float q = fminf(fmaxf(rintf(fmaf(fmaf(-q0, s, w[k]), r1, q0)), -8.f), 7.f);
         packed |= static_cast<uint32_t>(static_cast<int>(q) + 8) << (4 * k);
       }
-      if (!(s > 0.f)) packed = 0x88888888u;                      // a scale of zero: all codes 8, those of NaN too
+    };
+    if (__all(plain || !in)) {
+      by_reciprocal(__frcp_rn(s));
+    } else if (__all(plain || s == 0.f)) {
+      by_reciprocal(plain ? __frcp_rn(s) : 0.f);
+      if (!plain) packed = 0x88888888u;                          // a scale of zero: all codes 8, those of NaN too
     } else {                                                     // reciprocals out of range, infinities
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
