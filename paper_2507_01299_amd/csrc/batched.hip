@@ -42,16 +42,22 @@ constexpr int kBThreads = 512;
 // tokens of 2^22 channels, whole call: 0.70 ms; 5.9 ms in slices of 4096, 3.6 with one workgroup per token).
 constexpr int kPrepThreads = 512, kPrepPass = kPrepThreads * 8;   // channels per pass of the workgroup over its slice
 constexpr int kPrepSlices = 64, kPrepSliceMax = 1 << 17;
+template <bool ONE_PASS>   // slices of kPrepPass channels, 0.06 us a call faster than with the loops and LDS sized at the launch
 __global__ __launch_bounds__(kPrepThreads) void batch_prep_kernel(const uint16_t* __restrict__ h, const int32_t* __restrict__ idx,
-                                                                  uint16_t* __restrict__ C, int d_in, int K, int slice) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char kept[];   // [slice]
+                                                                  uint16_t* __restrict__ C, int d_in, int K, int any_slice) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char any_kept[];
+  __shared__ __attribute__((aligned(16))) unsigned char pass_kept[ONE_PASS ? kPrepPass : 16];
+  unsigned char* const kept = ONE_PASS ? pass_kept : any_kept;   // [slice]
+  const int slice = ONE_PASS ? kPrepPass : any_slice;
   const int b = blockIdx.y;
   const int c0 = blockIdx.x * slice, n = min(slice, d_in - c0);   // the slice's channels
   const size_t at = static_cast<size_t>(b) * d_in + c0;
   const int i0 = threadIdx.x * 8;                // the lane's 8 channels of the first pass (d_in % 8 == 0: all inside or none)
   uint4 first = make_uint4(0u, 0u, 0u, 0u);
   if (i0 < n) first = *reinterpret_cast<const uint4*>(h + at + i0);
-  for (int i = i0; i < n; i += kPrepPass) *reinterpret_cast<uint2*>(kept + i) = make_uint2(0u, 0u);
+  if (ONE_PASS) *reinterpret_cast<uint2*>(kept + i0) = make_uint2(0u, 0u);
+  else
+    for (int i = i0; i < n; i += kPrepPass) *reinterpret_cast<uint2*>(kept + i) = make_uint2(0u, 0u);
   __syncthreads();
   const int32_t* ib = idx + static_cast<size_t>(b) * K;
   constexpr int kAhead = 16;
@@ -62,7 +68,7 @@ __global__ __launch_bounds__(kPrepThreads) void batch_prep_kernel(const uint16_t
 #pragma unroll
     for (int q = 0; q < kAhead; ++q) {
       const unsigned e = static_cast<unsigned>(j[q] - c0);
-      if (e < static_cast<unsigned>(n)) kept[e] = 1;
+      if (e < static_cast<unsigned>(slice)) kept[e] = 1;
     }
   }
   __syncthreads();
@@ -951,7 +957,8 @@ hipError_t launch_batch_prep(const uint16_t* h, const int32_t* idx, uint16_t* C,
   const long even = (passes + kPrepSlices - 1) / kPrepSlices * kPrepPass;
   const int slice = even < kPrepSliceMax ? static_cast<int>(even) : kPrepSliceMax;
   const unsigned slices = static_cast<unsigned>((static_cast<long>(d_in) + slice - 1) / slice);
-  hipLaunchKernelGGL(batch_prep_kernel, dim3(slices, B), dim3(kPrepThreads), slice, s, h, idx, C, d_in, K, slice);
+  if (slice == kPrepPass) hipLaunchKernelGGL(batch_prep_kernel<true>, dim3(slices, B), dim3(kPrepThreads), 0, s, h, idx, C, d_in, K, slice);
+  else hipLaunchKernelGGL(batch_prep_kernel<false>, dim3(slices, B), dim3(kPrepThreads), slice, s, h, idx, C, d_in, K, slice);
   return hipGetLastError();
 }
 
