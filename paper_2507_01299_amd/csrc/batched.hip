@@ -6,15 +6,16 @@
 // The same kernels serve the batched rotation / adapter / dense baseline (C = x).
 //
 //   * the product is a skinny dense contraction (all rows x B tokens), so it runs on the matrix
-//     cores (f16/bf16, fp32 accumulate): M = 16 output columns, N = 16 tokens, token blocks padded to 16.
+//     cores (f16/bf16, fp32 accumulate): M = 16 output columns, N = 16 tokens, K = 16 rows, token blocks padded to 16.
 //     Measured on MI355X this is the fastest for every B >= 2 (the fp32-FMA kernel needed 205 us per LLaMA3-8B layer at
 //     B = 4 where the first matrix-core kernel needed 160 us), because the product is HBM-bound and the FMA variant spends
-//     its issue slots on B x 8 multiply-adds and coefficient reads per 16 bytes loaded.  Two kernels:
+//     its issue slots on B x 8 multiply-adds and coefficient reads per 16 bytes loaded.  Two kernels, which add a token's
+//     products in the same order (its bits do not depend on the size of its batch):
 //     up to 16 tokens (skinny16) a lane loads 8 consecutive columns of 4 rows (16 lanes x 16 bytes = 256 contiguous bytes
 //     per row), and a byte permute regroups those registers into the K-runs the instruction wants; the weight never
-//     passes through LDS.  More tokens (skinny32, groups of 32; small weights stay with groups of 16) keep the matrix cores busy longer per row, so the
-//     loads go straight to LDS, ahead of the products and without registers of their own, and transposing LDS reads make
-//     the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 153 us);
+//     passes through LDS.  More tokens (skinny32, groups of 32; small weights stay with groups of 16) keep the matrix
+//     cores busy longer per row, so the loads go straight to LDS, ahead of the products and without registers of their
+//     own, and transposing LDS reads make the K-runs (LLaMA2-7B layer, 32 tokens: 161 -> 152 us);
 //   * an fp32-FMA kernel (2 or 4 tokens per workgroup) remains for the one case the 16-bit B
 //     operand cannot express: a per-channel coefficient scale applied in fp32 (learned pre-norm
 //     scale in front of an explicit rotation).

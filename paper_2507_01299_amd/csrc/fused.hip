@@ -80,11 +80,14 @@ struct LdsRowsOfVector {
 // While a workgroup selects, memory is idle.  Each of its waves asks for a few weight rows that it will probably stream:
 // the MLP vector is not sorted by a rotation, so its channels are kept about evenly, rank t of K lies near row
 // t d_in / K, and K / d_in of the rows around there are kept.  The loads go to an LDS piece that nobody reads; what counts
-// is that the rows are in this XCD's L2 when the row loop asks for them.  Six rows a wave measured best (layers at 40 %:
-// 7B 76.8 -> 76.4 us, 8B 84.0 -> 83.0, 70B 240.4 -> 239.0, 5120 wide 109.6 -> 108.2; 3 rows half of that, 16 rows and
-// more a loss, and the o projection, whose waves stream two batches of rows in all, only loses).  With few workgroups
-// there is memory to spare in the row loop as well and the extra rows only cost: 2944 wide (168 workgroups) level, 2048
-// wide (112) 52.2 -> 52.5, 1024 wide (30) 45.7 -> 46.2; so from three quarters of the compute units on.
+// is that the rows are in this XCD's L2 when the row loop asks for them.  Six rows a wave measured best (layers at 40 %
+// without / with, two runs of one side within 0.1 %: 7B 76.9 / 76.4 us, 70B in two halves 236.4 / 235.2, 5120 wide 109.7 /
+// 108.4, 6656 wide 161.8 / 160.9, 7B at 25 % 91.7 / 91.1; 3 rows half of that, 16 rows and more a loss, and the o
+// projection, whose waves stream two batches of rows in all, only loses).  The price is traffic: of the 7B layer's 11.0 MB
+// asked for, 40 % are rows that are not kept, and its down projection fetches 60.0 instead of 55.1 MB (counters: 4.4 MB not
+// kept, so all but 0.5 MB of the kept ones are found in the L2).  With few workgroups there is memory to spare in the row
+// loop as well and the extra rows only cost: 2944 wide (168 workgroups) level, 2048 wide (112) 52.2 -> 52.5, 1024 wide (30)
+// 45.7 -> 46.2; so from three quarters of the compute units on.
 constexpr int kAheadRows = 6, kAheadMinGroups = 192;
 __device__ __forceinline__ void ask_ahead(const FusedArgs& a, const Segment& sg, int rw, int lane, const char* sink) {
   bool valid;

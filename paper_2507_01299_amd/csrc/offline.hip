@@ -4,11 +4,11 @@
 //
 //  * v_mfma_f32_32x32x16 (f16 / bf16 inputs, fp32 accumulate).  A workgroup of 4 waves (one per SIMD) owns a
 //    256 x 256 tile of C, each wave a 128 x 128 quarter (4 x 4 instruction tiles, 256 accumulator registers): eight
-//    operand reads from LDS feed sixteen instructions, half the LDS traffic per flop of the 128 x 64 quarters that eight
-//    waves would own.
+//    operand reads from LDS feed sixteen instructions, two thirds of the LDS traffic per flop of the 128 x 64 quarters that
+//    eight waves would own.
 //  * Global loads go straight into LDS (16 bytes per lane, no staging registers) and run three 32-deep k-tiles ahead of
-//    the products: four stages of 32 KiB, one barrier per k-tile, and the loads, the LDS reads and the products of a
-//    k-tile are issued in one fixed interleaved order.
+//    the products: four stages of 32 KiB (the smallest tile: eight of 8 KiB, seven ahead), one barrier per k-tile, and the
+//    loads, the LDS reads and the products of a k-tile are issued in one fixed interleaved order.
 //  * Operands are stored k-major ([k][m], the layout of X, Q and W), the instruction wants 8 values along k per lane.
 //    The LDS tile keeps the memory's layout and the transposing LDS read does the rest: 16 lanes point at 4 rows x 16
 //    columns and receive 4 k-values of one column each.  A row's 64-byte granules are exchanged by its number
@@ -22,10 +22,12 @@
 //  * Whole rounds of 256 tiles (one per compute unit) run in 256 x 256 tiles; what is left over runs as 128 x 128 or 64 x 64
 //    parts in a second launch when that is shorter than another round (launch_shape).
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
-// random operands reaches 1.63 PFLOP/s here (2.37 on zeros); the kernel issues 1.26 - 1.29 in whole rounds (4096 x 28672 x
-// 4096 bf16, 3 terms: 2.88 -> 2.22 ms; 5000 x 8192 second moment: 711 -> 338 us, of which 40 us the 16 tiles after the last
-// whole round, and the store of C in 16-byte pieces through LDS saved 45).  The design before it (8 waves of 128 x 64,
-// staging registers, two LDS stages) issued 0.98 and gave the XCDs of a symmetric product uneven shares.
+// random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace, before -> now): 4096 x
+// 28672 x 4096 bf16, 3 terms, 2957 -> 2174 - 2235 us = 1.29 - 1.33 PFLOP/s; f16 folds of a 4096-wide layer 1.15 - 1.18, its adapter 1.24;
+// second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 321 + 36 us = 1.04 (36 for the 16 tiles after
+// the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
+// 64 - 73 % of the cycles; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
+// staging registers, two LDS stages) kept them busy 34 % and gave the XCDs of a symmetric product uneven shares.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   }
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)lds));
   // The next k-tile to load: its first k, the stage it goes to and the byte offsets of its first element in the
-  // operands.  Past the last tile kr_left is 0: zeros are loaded, so that every step waits for the same count.
+  // operands.  Past the last tile f_k is 0: zeros are loaded, so that every step waits for the same count.
   const uint32_t stepA = static_cast<uint32_t>((A_KMAJOR ? kKTile * a.M : kKTile) * 2), stepB = static_cast<uint32_t>(kKTile * a.N * 2);
   int f_pair = 0, f_k = a.Kd, f_stage = 0;
   uint32_t ta = static_cast<uint32_t>(a.pa[0] * a.a_term_stride * 2), tb = static_cast<uint32_t>(a.pb[0] * a.b_term_stride * 2);
@@ -265,10 +267,10 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
     });
   };
 
-  // ---- pipeline.  A stage's loads are issued three k-tiles before its products; the second half of tile it is read
+  // ---- pipeline.  A stage's loads are issued kStages - 1 k-tiles before its products; the second half of tile it is read
   // while its first half is multiplied, then one barrier, then the first half of tile it + 1 while the second half is
-  // multiplied.  The barrier follows a wait for this wave's own loads of tile it + 1 (the 2 * 2 MI younger ones may
-  // be outstanding) and for its LDS reads of tile it, whose stage the loads issued next overwrite.
+  // multiplied.  The barrier follows a wait for this wave's own loads of tile it + 1 (the kStages - 2 tiles of 2 MI loads
+  // after it may be outstanding) and for its LDS reads of tile it, whose stage the loads issued next overwrite.
   u32x4 a0[MI], b0[MI], a1[MI], b1[MI];
   for (int i = 0; i < kStages - 1; ++i) fetch();
   tile_landed<(kStages - 2) * 2 * MI>();
