@@ -33,8 +33,8 @@ __device__ __forceinline__ void clear_words(const FusedArgs& a, int g) {
 __device__ __forceinline__ uint2 load_source4(const FusedArgs& a, int b, int i) {
   if (a.src_mode == kSrcGqa) {
     // context-length-1 attention: query head i/head_dim outputs the value head of its group
-    const int head = i / a.head_dim;
-    const int src = (head / a.group) * a.head_dim + (i - head * a.head_dim);
+    const int head = quotient_by(i, a.head_magic);
+    const int src = quotient_by(head, a.group_magic) * a.head_dim + (i - head * a.head_dim);
     return *reinterpret_cast<const uint2*>(a.src + static_cast<size_t>(b) * (a.d_q + 2 * a.d_kv) + a.d_q + a.d_kv + src);
   }
   return *reinterpret_cast<const uint2*>(a.src + static_cast<size_t>(b) * a.g.d_in + i);
@@ -272,8 +272,7 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   constexpr int kFusedRW = RW;
   __shared__ TopkShared<RW> tk;
   __shared__ GemvShared<RW> sh;
-  __shared__ int lst_idx[kFusedChunkMax];
-  __shared__ float lst_val[kFusedChunkMax];
+  __shared__ RowCoef lst[kFusedChunkMax + 64];   // the last 64 take what is not this workgroup's, and are not read
 
   LAROSA_STAMP(0);
   const int tid = threadIdx.x;
@@ -283,8 +282,8 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   int g = blockIdx.x;
   if (a.side_G > 0) {                     // uniform over the workgroup
     if (g < a.side_G) {
-      static_assert(kFusedChunkMax >= kRowListMax, "the side job stages its coefficients in lst_val");
-      gemv_rows_body<T, RW, false>(a.side, g, b, sh, nullptr, lst_val);
+      static_assert(sizeof(lst) >= kRowListMax * sizeof(float), "the side job stages its coefficients in lst");
+      gemv_rows_body<T, RW, false>(a.side, g, b, sh, nullptr, reinterpret_cast<float*>(lst));
       return;
     }
     g -= a.side_G;
@@ -293,18 +292,18 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   const int d_in = a.g.d_in;
   const int K = a.g.K;
   const int base = tid * E;
-  const int nvalid = max(0, min(E, d_in - base));
   topk_clear<kFusedRW>(tk);               // made visible by the first barrier below, while the loads are in flight
 
-  // ---- the block's input vector, this lane's E elements as stored 16-bit values
-  uint16_t raw[E];
+  // ---- the block's input vector: this lane's E elements as stored, two to a register (zeros past its end)
+  uint32_t raw[E / 2];
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
     const int i = base + q * 4;
     const uint2 v = i < d_in ? load_source4(a, b, i) : make_uint2(0u, 0u);
-    raw[q * 4 + 0] = static_cast<uint16_t>(v.x & 0xFFFFu); raw[q * 4 + 1] = static_cast<uint16_t>(v.x >> 16);
-    raw[q * 4 + 2] = static_cast<uint16_t>(v.y & 0xFFFFu); raw[q * 4 + 3] = static_cast<uint16_t>(v.y >> 16);
+    raw[2 * q] = v.x;
+    raw[2 * q + 1] = v.y;
   }
+  const Segment sg = segment_of(g, a.g.wps, a.g.chunk, K);
   if (a.src_mode == kSrcNorm) {
     // h = R(x * rsqrt(mean(x^2) + eps) * scale)
     // the lane's slice of the learned scale, fetched with x (loads at each use would each wait for memory)
@@ -316,22 +315,32 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     }
     float ss = 0.f;
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-      const float xv = (q < nvalid) ? T::to_f32(raw[q]) : 0.f;
-      ss = fmaf(xv, xv, ss);
+    for (int q = 0; q < E / 2; ++q) {
+      float x0, x1;
+      T::unpack2(raw[q], x0, x1);
+      ss = fmaf(x0, x0, ss);
+      ss = fmaf(x1, x1, ss);
     }
     ss = wave_sum(ss);
     if (lane == 0) sh.blockred[rw] = ss;
     __syncthreads();
     float tot = 0.f;
+#pragma unroll
     for (int w2 = 0; w2 < kFusedRW; ++w2) tot += sh.blockred[w2];
     const float rinv = 1.0f / sqrtf(tot / static_cast<float>(d_in) + a.norm_eps);
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-      float xv = T::to_f32(raw[q]) * rinv;
-      const uint32_t w = (q & 2) ? sc2[q >> 2].y : sc2[q >> 2].x;
-      if (a.norm_scale) xv *= T::to_f32(static_cast<uint16_t>((q & 1) ? (w >> 16) : (w & 0xFFFFu)));
-      raw[q] = (q < nvalid) ? T::from_f32(xv) : static_cast<uint16_t>(0);   // padding stays zero
+    for (int q = 0; q < E / 2; ++q) {
+      float x0, x1;
+      T::unpack2(raw[q], x0, x1);
+      x0 *= rinv;
+      x1 *= rinv;
+      if (a.norm_scale) {
+        float s0, s1;
+        T::unpack2((q & 1) ? sc2[q >> 1].y : sc2[q >> 1].x, s0, s1);
+        x0 *= s0;
+        x1 *= s1;
+      }
+      raw[q] = base + 2 * q < d_in ? T::from_f32(x0) | (static_cast<uint32_t>(T::from_f32(x1)) << 16) : 0u;   // past the end: zeros
     }
   } else {
     __syncthreads();
@@ -340,34 +349,38 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
       const int i = base + q * 4;
-      if (i < d_in) {
-        uint2 v;
-        v.x = raw[q * 4 + 0] | (static_cast<uint32_t>(raw[q * 4 + 1]) << 16);
-        v.y = raw[q * 4 + 2] | (static_cast<uint32_t>(raw[q * 4 + 3]) << 16);
-        *reinterpret_cast<uint2*>(a.h_out + static_cast<size_t>(b) * d_in + i) = v;
-      }
+      if (i < d_in) *reinterpret_cast<uint2*>(a.h_out + static_cast<size_t>(b) * d_in + i) = make_uint2(raw[2 * q], raw[2 * q + 1]);
     }
   }
 
   // ---- Top-K select; keep the (row, coefficient) pairs of this workgroup's ranks in LDS
   LAROSA_STAMP(1);
-  const auto st = block_select<kFusedRW, E>(raw, K, tk);
+  uint32_t key[E / 2];
+#pragma unroll
+  for (int q = 0; q < E / 2; ++q) key[q] = raw[q] & kPairKeys;
+  const auto st = block_select<kFusedRW, E>(key, K, tk);
   LAROSA_STAMP(2);
-  const Segment sg = segment_of(g, a.g.wps, a.g.chunk, K);
   const int n = sg.t1 - sg.t0;            // <= the list capacity by the plan
-  int32_t* idx_out = (a.idx_out && g == 0) ? a.idx_out + static_cast<size_t>(b) * K : nullptr;
-  // only lanes whose ranks meet this workgroup's rank range (a few percent) walk their elements
-  const int p0 = static_cast<int>(st.first_rank()), p1 = static_cast<int>(st.end_rank());
-  if (idx_out || (p0 < sg.t1 && p1 > sg.t0)) {
-    for_each_kept<E>(st, [&](int q, unsigned upos, bool kept) {
-      const int pos = static_cast<int>(upos);
-      if (idx_out && kept) idx_out[pos] = base + q;          // idx_out is uniform over the workgroup
-      const int e = pos - sg.t0;
-      if (kept && static_cast<unsigned>(e) < static_cast<unsigned>(n)) {
-        lst_idx[e] = base + q;
-        lst_val[e] = T::to_f32(raw[q]);
-      }
-    });
+  if (a.idx_out && g == 0) {
+    int32_t* idx_out = a.idx_out + static_cast<size_t>(b) * K;
+    unsigned pos = st.first;
+    for (int q = 0; q < E; ++q) {
+      if (kept_bit(st, q)) idx_out[pos++] = base + q;
+    }
+  }
+  // only lanes whose ranks meet this workgroup's rank range (a few percent) walk their elements, without a branch per element:
+  // a wave that has such lanes is what the others wait for
+  if (static_cast<int>(st.first) < sg.t1 && static_cast<int>(st.first + st.n) > sg.t0) {
+    unsigned pos = st.first - static_cast<unsigned>(sg.t0);     // (wraps for ranks in front of the range)
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      const unsigned is = kept_bit(st, q);
+      const unsigned at = pos | (is - 1u);                      // all ones unless it is kept
+      float f[2];
+      T::unpack2(raw[q >> 1], f[0], f[1]);
+      lst[at < static_cast<unsigned>(n) ? at : static_cast<unsigned>(kFusedChunkMax + lane)] = RowCoef{base + q, f[q & 1]};
+      pos += is;
+    }
   }
   LAROSA_STAMP(3);
   __syncthreads();
@@ -376,10 +389,7 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   // ---- stream the kept rows of this workgroup's ranks
   const Epilogue ep{a.g.y, a.g.rms_src, a.g.rms_eps, a.g.residual, a.g.y_pre, d_in, a.g.d_out, a.pair_cols, a.pair_out,
                     a.hist_out, a.hist_col0, a.hist_col1, a.hist_weight};
-  LdsRows rows;
-  rows.idx = lst_idx;
-  rows.val = lst_val;
-  rows.base = sg.t0;
+  const LdsPairs rows{lst, sg.t0};
   bool col_valid;
   const int col = strip_lane_col(sg.s, lane, a.g.d_out, a.pair_cols, col_valid);
   float acc[8];
@@ -428,7 +438,9 @@ hipError_t launch_hinted(const FusedArgs& a, hipStream_t st) {
 }
 
 template <typename T>
-hipError_t launch_rw(const FusedArgs& a, hipStream_t st) {
+hipError_t launch_rw(FusedArgs a, hipStream_t st) {
+  a.head_magic = quotient_magic(a.head_dim);
+  a.group_magic = quotient_magic(a.group);
   if (a.hist_in) return launch_hinted<T>(a, st);
   return launch_nv<T, 8>(a, st);
 }

@@ -74,6 +74,26 @@ struct LdsRows {
   }
 };
 
+// The same with a pair to an entry, one LDS access each way.
+struct RowCoef {
+  int row;
+  float coef;
+};
+struct LdsPairs {
+  const RowCoef* list;
+  int base;                  // rank of entry 0
+  __device__ __forceinline__ void batch(int t, int re, int lane, int (&j)[kUnroll], float (&c)[kUnroll]) const {
+    const int u0 = lane & (kUnroll - 1);
+    const RowCoef e = list[min(t + u0, re - 1) - base];
+    const float myc = (t + u0 < re) ? e.coef : 0.f;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      j[u] = __builtin_amdgcn_readlane(e.row, u);
+      c[u] = __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(myc)), u)));
+    }
+  }
+};
+
 // The identity row list with its coefficients staged in LDS (dense mat-vec: row t is rank t).
 struct LdsCoefs {
   const float* val;

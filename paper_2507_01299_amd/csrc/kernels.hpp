@@ -74,6 +74,10 @@ int w4_strip_cols(int d_out);
 hipError_t launch_quantize_w4(const uint16_t* W, int d_in, int d_out, uint32_t* Wq, uint16_t* scales, bool bf16,
                               hipStream_t s);
 
+// i / n = the upper half of i * quotient_magic(n), for 0 <= i < 2^16 and 2 <= n <= 2^16 (n = 1: quotient_by returns i): the
+// factor exceeds 2^32 / n by less than 1, so the product exceeds the quotient by less than i / 2^32 < 1 / n.
+inline unsigned quotient_magic(int n) { return n > 1 ? 0xFFFFFFFFu / static_cast<unsigned>(n) + 1u : 0u; }
+
 // Column-sparse projection with the Top-K select fused into its prologue: the kept list is
 // built inside every workgroup from the block's input vector.
 enum : int { kSrcPlain = 0, kSrcGqa = 1, kSrcSilu = 2, kSrcNorm = 3 };
@@ -84,6 +88,7 @@ struct FusedArgs {
   const uint16_t* src;        //   kSrcPlain: [B, d_in];  kSrcNorm: x [B, d_in] to be RMS-normed;
                               //   kSrcGqa: q|k|v [B, d_q+2d_kv]  (kSrcSilu is a Top-K kernel source only)
   int d_q, d_kv, head_dim, group;
+  unsigned head_magic, group_magic;   // filled in at the launch (quotient_magic)
   const uint16_t* norm_scale; // kSrcNorm: [d_in] or nullptr
   float norm_eps;
   uint16_t* h_out;            // nullable: receives the input vector [B, d_in]
@@ -160,6 +165,7 @@ struct TopkSource {
   int mode;
   const uint16_t* src;
   int d_q, d_kv, head_dim, group;   // kSrcGqa
+  unsigned head_magic, group_magic; // filled in at the launch (quotient_magic)
   const uint16_t* norm_scale;       // kSrcNorm: [d] or nullptr
   float norm_eps;
   uint16_t* h_out;

@@ -86,6 +86,11 @@ __device__ __forceinline__ uint2 pack4(const float (&f)[4]) {
   return v;
 }
 
+// i / n with the factor from quotient_magic(n): an integer division is about 40 instructions
+__device__ __forceinline__ int quotient_by(int i, unsigned magic) {
+  return magic ? static_cast<int>(__umulhi(static_cast<unsigned>(i), magic)) : i;
+}
+
 // value after one storage rounding
 template <typename T>
 __device__ __forceinline__ float round_store(float f) { return T::to_f32(T::from_f32(f)); }
@@ -96,17 +101,31 @@ __device__ __forceinline__ float silu_f32(float g) {
   return g * __frcp_rn(1.0f + __expf(-g));
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// Sums over lanes, the same value in every lane.  A butterfly over lane distances 32, 16, 8, 4, 2, 1, in this order,
+// without LDS round trips: the two wide steps exchange halves and rows of 16 lanes, and as every step leaves the value
+// periodic in the distance it has covered, a rotation of the row by 8, 4, 2, 1 is the exchange at that distance.
+template <int ROR>
+__device__ __forceinline__ float row_rotated(float v) {
+  const int i = static_cast<int>(__float_as_uint(v));
+  return __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_update_dpp(i, i, 0x120 + ROR, 0xF, 0xF, false)));
 }
-
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+template <int N>   // over each N = 16, 32 or 64 consecutive lanes
+__device__ __forceinline__ float lanes_sum(float v) {
+  static_assert(N == 16 || N == 32 || N == 64, "rows of 16 lanes, pairs of them, the wave");
+  if constexpr (N == 64) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  }
+  if constexpr (N >= 32) {
+    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  }
+  v += row_rotated<8>(v);
+  v += row_rotated<4>(v);
+  v += row_rotated<2>(v);
+  return v + row_rotated<1>(v);
 }
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum<64>(v); }
 
 // inclusive prefix sum across the 64 lanes of a wave, on the data-parallel-primitive path of the
 // VALU (no LDS round trips): Hillis-Steele steps of 1, 2, 4, 8 lanes inside each row of 16, then

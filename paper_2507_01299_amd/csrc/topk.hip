@@ -1,5 +1,7 @@
 // Stand-alone Top-K sparsifier kernel (Sec. 4.3, Eq. 8): one workgroup of 1024 lanes per token;
 // the selection itself is in topk_core.hpp.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "topk_core.hpp"
 
@@ -7,27 +9,30 @@ namespace larosa {
 
 namespace {
 
-#ifndef LAROSA_TOPK_KERNEL_COPIES
-#define LAROSA_TOPK_KERNEL_COPIES kTopkCopiesWide
-#endif
-constexpr int kTopkThreads = 1024;
+constexpr int kTopkThreads = 1024;        // (threshold kernel)
 constexpr int kTopkWaves = kTopkThreads / 64;
 
+// Copies of pass 1's histogram: 32 where the workgroup can sum them by itself (topk_core.hpp), else 8.
+template <int NW> constexpr int kTopkKernelCopies = NW % 4 == 0 ? kTopkCopiesWide : kTopkCopies;
+
+// One workgroup of NW waves per token, E elements per lane (a multiple of 4).
 // Where the selected vector comes from (batched decoder layer): the plain vector, the context-length-1
 // attention output read straight from q|k|v (value head of the query head's group), or
 // R(SiLU(gate) * up) computed from gate|up.  The vector itself can be written out as well.
-template <typename T, int E>   // E elements per lane, multiple of 4
-__global__ __launch_bounds__(kTopkThreads) void topk_kernel(const uint16_t* __restrict__ h, int d, int K,
-                                                            int32_t* __restrict__ idx,
-                                                            uint16_t* __restrict__ vals,
-                                                            uint16_t* __restrict__ masked, TopkSource sc) {
-  __shared__ TopkShared<kTopkWaves, LAROSA_TOPK_KERNEL_COPIES> sm;
+// RUN: the sum of squares of kSrcNorm is formed from the squares of runs of RUN elements, 64 runs by halves, the sums of
+// 64 runs one after the other -- whatever NW is, so that the choice of NW changes no bit.
+template <typename T, int NW, int E, int RUN>
+__global__ __launch_bounds__(NW * 64) void topk_kernel(const uint16_t* __restrict__ h, int d, int K,
+                                                       int32_t* __restrict__ idx,
+                                                       uint16_t* __restrict__ vals,
+                                                       uint16_t* __restrict__ masked, TopkSource sc) {
+  __shared__ TopkShared<NW, kTopkKernelCopies<NW>> sm;
   const int b = blockIdx.x;
   const uint16_t* hb = h + static_cast<size_t>(b) * d;
   const int base = threadIdx.x * E;
 
   LAROSA_STAMP(0);
-  topk_clear<kTopkWaves>(sm);             // made visible by the first barrier below
+  topk_clear<NW>(sm);                     // made visible by the first barrier below
   // All of the lane's loads are issued first, unconditionally and from addresses clamped into the
   // vector (d % 4 == 0: a group of four is all valid or all past the end; groups past the end re-read
   // the last group and are ignored).  Loads under a lane or mode condition sit in branches of their
@@ -37,8 +42,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const uint16_t* __re
 #pragma unroll
     for (int q = 0; q < E / 4; ++q) {
       const int i = min(base + q * 4, d - 4);
-      const int head = i / sc.head_dim;
-      const int src = (head / sc.group) * sc.head_dim + (i - head * sc.head_dim);
+      const int head = quotient_by(i, sc.head_magic);
+      const int src = quotient_by(head, sc.group_magic) * sc.head_dim + (i - head * sc.head_dim);
       ld0[q] = *reinterpret_cast<const uint2*>(sc.src + static_cast<size_t>(b) * (sc.d_q + 2 * sc.d_kv) + sc.d_q +
                                                sc.d_kv + src);
       ld1[q] = make_uint2(0u, 0u);
@@ -58,31 +63,31 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const uint16_t* __re
       ld1[q] = make_uint2(0u, 0u);
     }
   }
-  uint16_t raw[E];
+  uint32_t raw[E / 2];                    // the lane's elements as stored, two to a register (zeros past the end)
 #pragma unroll
   for (int q = 0; q < E / 4; ++q) {
     const int i = base + q * 4;
     uint2 v = ld0[q];
     if (sc.mode == kSrcSilu) {
-      float g[4], u[4];
+      float g[4], u[4], o[4];
       T::unpack2(ld0[q].x, g[0], g[1]);
       T::unpack2(ld0[q].y, g[2], g[3]);
       T::unpack2(ld1[q].x, u[0], u[1]);
       T::unpack2(ld1[q].y, u[2], u[3]);
-      uint16_t o[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) o[k] = T::from_f32(silu_f32(g[k]) * u[k]);
-      v.x = o[0] | (static_cast<uint32_t>(o[1]) << 16);
-      v.y = o[2] | (static_cast<uint32_t>(o[3]) << 16);
+      for (int k = 0; k < 4; ++k) {
+        o[k] = silu_f32(g[k]) * u[k];
+        // rounded to fp32 before the storage rounding; left to itself the compiler does both in one for some sizes and not
+        // for others, and a batched layer's bits would change with the width (above 16384 it always has done both in one)
+        if constexpr (RUN <= 16) asm("" : "+v"(o[k]));
+      }
+      v = pack4<T>(o);
     }
     if (i >= d) v = make_uint2(0u, 0u);
     if (i < d && sc.h_out && sc.mode != kSrcNorm) *reinterpret_cast<uint2*>(sc.h_out + static_cast<size_t>(b) * d + i) = v;
-    raw[q * 4 + 0] = static_cast<uint16_t>(v.x & 0xFFFFu);
-    raw[q * 4 + 1] = static_cast<uint16_t>(v.x >> 16);
-    raw[q * 4 + 2] = static_cast<uint16_t>(v.y & 0xFFFFu);
-    raw[q * 4 + 3] = static_cast<uint16_t>(v.y >> 16);
+    raw[2 * q] = v.x;
+    raw[2 * q + 1] = v.y;
   }
-  const int nvalid = max(0, min(E, d - base));
   if (sc.mode == kSrcNorm) {
     // h = R(x * rsqrt(mean(x^2) + eps) * scale): the pre-norm of a block whose rotation is absorbed
     // the lane's slice of the learned scale, fetched up front (loads at each use would each wait for memory)
@@ -92,68 +97,96 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const uint16_t* __re
       const int i = base + q * 4;
       sc2[q] = (sc.norm_scale && i < d) ? *reinterpret_cast<const uint2*>(sc.norm_scale + i) : make_uint2(0u, 0u);
     }
-    float ss = 0.f;
+    constexpr int kRuns = E / RUN;        // runs per lane; 64 / kRuns lanes hold 64 of them
+    static_assert(E % RUN == 0 && (kRuns == 1 || kRuns == 2 || kRuns == 4), "lane exchanges of kRuns runs");
+    __shared__ float tot_w[NW * kRuns];
+    float ss[kRuns];
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-      const float xv = (q < nvalid) ? T::to_f32(raw[q]) : 0.f;
-      ss = fmaf(xv, xv, ss);
+    for (int k = 0; k < kRuns; ++k) {
+      ss[k] = 0.f;
+#pragma unroll
+      for (int q = k * (RUN / 2); q < (k + 1) * (RUN / 2); ++q) {
+        float x0, x1;
+        T::unpack2(raw[q], x0, x1);
+        ss[k] = fmaf(x0, x0, ss[k]);
+        ss[k] = fmaf(x1, x1, ss[k]);
+      }
+      ss[k] = lanes_sum<64 / kRuns>(ss[k]);
     }
-    ss = wave_sum(ss);
-    float* tot_w = reinterpret_cast<float*>(sm.wave_tot);
-    if ((threadIdx.x & 63) == 0) tot_w[threadIdx.x >> 6] = ss;
+#pragma unroll
+    for (int o = kRuns / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < o; ++k) ss[k] += ss[k + o];
+    if ((threadIdx.x & (64 / kRuns - 1)) == 0) tot_w[threadIdx.x / (64 / kRuns)] = ss[0];
     __syncthreads();
     float tot = 0.f;
-    for (int w2 = 0; w2 < kTopkWaves; ++w2) tot += tot_w[w2];   // the select writes wave_tot only after further barriers
+#pragma unroll
+    for (int w2 = 0; w2 < NW * kRuns; ++w2) tot += tot_w[w2];
     const float rinv = 1.0f / sqrtf(tot / static_cast<float>(d) + sc.norm_eps);
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-      float xv = T::to_f32(raw[q]) * rinv;
-      const uint32_t w = (q & 2) ? sc2[q >> 2].y : sc2[q >> 2].x;
-      if (sc.norm_scale) xv *= T::to_f32(static_cast<uint16_t>((q & 1) ? (w >> 16) : (w & 0xFFFFu)));
-      raw[q] = (q < nvalid) ? T::from_f32(xv) : static_cast<uint16_t>(0);   // padding stays zero
+    for (int q = 0; q < E / 2; ++q) {
+      float x0, x1;
+      T::unpack2(raw[q], x0, x1);
+      x0 *= rinv;
+      x1 *= rinv;
+      if (sc.norm_scale) {
+        float s0, s1;
+        T::unpack2((q & 1) ? sc2[q >> 1].y : sc2[q >> 1].x, s0, s1);
+        x0 *= s0;
+        x1 *= s1;
+      }
+      raw[q] = base + 2 * q < d ? T::from_f32(x0) | (static_cast<uint32_t>(T::from_f32(x1)) << 16) : 0u;   // past the end: zeros
     }
     if (sc.h_out) {
 #pragma unroll
       for (int q = 0; q < E / 4; ++q) {
         const int i = base + q * 4;
-        if (i < d) {
-          uint2 v;
-          v.x = raw[q * 4 + 0] | (static_cast<uint32_t>(raw[q * 4 + 1]) << 16);
-          v.y = raw[q * 4 + 2] | (static_cast<uint32_t>(raw[q * 4 + 3]) << 16);
-          *reinterpret_cast<uint2*>(sc.h_out + static_cast<size_t>(b) * d + i) = v;
-        }
+        if (i < d) *reinterpret_cast<uint2*>(sc.h_out + static_cast<size_t>(b) * d + i) = make_uint2(raw[2 * q], raw[2 * q + 1]);
       }
     }
   }
   if (sc.mode != kSrcNorm) __syncthreads();
   LAROSA_STAMP(1);
-  const auto st = block_select<kTopkWaves, E>(raw, K, sm);
+  uint32_t key[E / 2];
+#pragma unroll
+  for (int q = 0; q < E / 2; ++q) key[q] = raw[q] & kPairKeys;
+  const auto st = block_select<NW, E>(key, K, sm);
   LAROSA_STAMP(2);
 
-  int32_t* idxb = idx ? idx + static_cast<size_t>(b) * K : nullptr;   // the index list is optional
-  uint16_t* valb = vals ? vals + static_cast<size_t>(b) * K : nullptr;
-  uint16_t mk[E];
+  // The index list goes through LDS, so that memory sees whole lines: written from the lanes that hold the elements, a wave's
+// stores touch a line per lane or two (14336 wide, 8601 kept: whole kernel 8.2 -> 7.1 us, 28672: 15.5 -> 11.5).  Not kept: to a slot that nobody reads.
+  if (idx) {
+    constexpr int kList = NW * 64 * E;
+    __shared__ uint16_t list[kList + 64];
+    unsigned pos = st.first;
 #pragma unroll
-  for (int q = 0; q < E; ++q) mk[q] = 0;
-  for_each_kept<E>(st, [&](int q, unsigned pos, bool kept) {
-    if (kept) {
-      if (idxb) idxb[pos] = base + q;
-      if (valb) valb[pos] = raw[q];
+    for (int q = 0; q < E; ++q) {
+      const unsigned is = kept_bit(st, q);
+      list[is ? pos : static_cast<unsigned>(kList + (threadIdx.x & 63))] = static_cast<uint16_t>(base + q);
+      pos += is;
     }
-    mk[q] = kept ? raw[q] : static_cast<uint16_t>(0);
-  });
+    __syncthreads();
+    int32_t* idxb = idx + static_cast<size_t>(b) * K;
+    for (int i = threadIdx.x; i < K; i += NW * 64) idxb[i] = list[i];
+  }
+  if (vals) {
+    uint16_t* valb = vals + static_cast<size_t>(b) * K;
+    unsigned pos = st.first;
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      if (kept_bit(st, q)) valb[pos++] = static_cast<uint16_t>(raw[q >> 1] >> (16 * (q & 1)));
+    }
+  }
   LAROSA_STAMP(3);
   if (masked) {
     uint16_t* mb = masked + static_cast<size_t>(b) * d;
+    // bits 15 and 31 spread over their halves
+    auto mask = [](uint32_t signs) __attribute__((always_inline)) { return ((signs >> 15) & 1u) * 0xFFFFu | (signs >> 31) * 0xFFFF0000u; };
 #pragma unroll
     for (int q = 0; q < E / 4; ++q) {
       const int i = base + q * 4;
-      if (i < d) {
-        uint2 v;
-        v.x = mk[q * 4 + 0] | (static_cast<uint32_t>(mk[q * 4 + 1]) << 16);
-        v.y = mk[q * 4 + 2] | (static_cast<uint32_t>(mk[q * 4 + 3]) << 16);
-        *reinterpret_cast<uint2*>(mb + i) = v;
-      }
+      if (i < d)
+        *reinterpret_cast<uint2*>(mb + i) = make_uint2(raw[2 * q] & mask(st.kept[2 * q]), raw[2 * q + 1] & mask(st.kept[2 * q + 1]));
     }
   }
   LAROSA_STAMP(4);
@@ -230,24 +263,33 @@ hipError_t launch_threshold_select(const uint16_t* h, int B, int d, float eps, i
   return bf16 ? launch_threshold_t<BF16>(h, B, d, eps, idx, count, s) : launch_threshold_t<F16>(h, B, d, eps, idx, count, s);
 }
 
+// Waves and elements per lane by width: what a wave executes is mostly fixed, and two waves or more share a SIMD, so narrow vectors
+// take few waves; but element by element a wave is slower than two.  Whole kernel, us, one token, f16 (with index list):
+// 512 wide 2 waves 2.8, 1 wave 3.1 (16: 4.1); 1024: 2 waves 3.2, 4 waves 3.3; 2048: 8 waves 3.4, 4 waves 3.6; 4096: 8 waves
+// 4.0, 4 waves 4.6, 16 waves 4.3; 8192: 16 waves 5.2, 8 waves 5.9 (before the index list went through LDS);
+// 14336: 16 waves 7.1, 8 waves 9.6 (likewise).  With 16 waves at every width and the index list written directly:
+// 4.1 (512) 4.5 (4096) 5.5 (8192) 8.7 (14336) 16.4 (28672, now 11.5).
 template <typename T>
 hipError_t launch_topk_t(const uint16_t* h, int B, int d, int K, int32_t* idx, uint16_t* vals, uint16_t* masked,
-                         const TopkSource& sc, hipStream_t s) {
-  dim3 grid(B), block(kTopkThreads);
-  const int e = (d + kTopkThreads - 1) / kTopkThreads;
-  if (e <= 4)
-    hipLaunchKernelGGL((topk_kernel<T, 4>), grid, block, 0, s, h, d, K, idx, vals, masked, sc);
-  else if (e <= 8)
-    hipLaunchKernelGGL((topk_kernel<T, 8>), grid, block, 0, s, h, d, K, idx, vals, masked, sc);
-  else if (e <= 16)
-    hipLaunchKernelGGL((topk_kernel<T, 16>), grid, block, 0, s, h, d, K, idx, vals, masked, sc);
-  else if (e <= 24)
-    hipLaunchKernelGGL((topk_kernel<T, 24>), grid, block, 0, s, h, d, K, idx, vals, masked, sc);
-  else if (e <= 32)
-    hipLaunchKernelGGL((topk_kernel<T, 32>), grid, block, 0, s, h, d, K, idx, vals, masked, sc);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+                         TopkSource sc, hipStream_t s) {
+  sc.head_magic = quotient_magic(sc.head_dim);
+  sc.group_magic = quotient_magic(sc.group);
+  auto launch = [&](auto nw, auto e, auto run) {
+    hipLaunchKernelGGL((topk_kernel<T, decltype(nw)::value, decltype(e)::value, decltype(run)::value>), dim3(B), dim3(64 * decltype(nw)::value),
+                       0, s, h, d, K, idx, vals, masked, sc);
+    return hipGetLastError();
+  };
+#define LAROSA_TOPK(NW, E, RUN) launch(std::integral_constant<int, NW>{}, std::integral_constant<int, E>{}, std::integral_constant<int, RUN>{})
+  if (d <= 512) return LAROSA_TOPK(2, 4, 4);
+  if (d <= 1024) return LAROSA_TOPK(2, 8, 4);
+  if (d <= 2048) return LAROSA_TOPK(8, 4, 4);
+  if (d <= 4096) return LAROSA_TOPK(8, 8, 4);
+  if (d <= 8192) return LAROSA_TOPK(16, 8, 8);
+  if (d <= 16384) return LAROSA_TOPK(16, 16, 16);
+  if (d <= 24576) return LAROSA_TOPK(16, 24, 24);
+  if (d <= 32768) return LAROSA_TOPK(16, 32, 32);
+#undef LAROSA_TOPK
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_topk(const uint16_t* h, int B, int d, int K, int32_t* idx, uint16_t* vals, uint16_t* masked,

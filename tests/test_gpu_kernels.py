@@ -72,6 +72,26 @@ def test_topk_indices_are_exact(api, dtype, B, d, K):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("d", [504, 512, 520, 1024, 1032, 2048, 2056, 4096, 4104, 8192, 8200, 16384, 16392, 24576, 24584, 32768])
+def test_topk_where_its_workgroup_changes(api, dtype, d):
+    """Widths at which another number of waves, elements per lane or copies of the histogram takes over, the last lanes full
+    or empty; vectors of 40 magnitudes (hundreds of ties at every threshold, the quota ending inside lanes) with zeros."""
+    print(f"topk dtype={dtype} d={d}", flush=True)
+    rng = np.random.default_rng(d)
+    v = rng.choice(np.concatenate([[0.0], 2.0 ** rng.uniform(-9, 9, 39)]), (2, d)) * rng.choice([-1.0, 1.0], (2, d))
+    hb = O.encode16(v, dtype)
+    for K in (1, 2, d // 3, (3 * d) // 5, d - 1, d):
+        idx = torch.full((2, K), -1, dtype=torch.int32, device="cuda:0")
+        vals = torch.zeros(2, K, dtype=api.torch_dtype(dtype), device="cuda:0")
+        api.topk(to_dev(hb, dtype), K, idx, dtype, vals=vals)
+        torch.cuda.synchronize()
+        for b in range(2):
+            want = O.topk_indices(hb[b], K)
+            assert np.array_equal(idx.cpu().numpy()[b], want), (K, b)
+            assert np.array_equal(to_bits(vals)[b], hb[b][want]), (K, b)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_topk_ties_and_special_values(api, dtype):
     d = 4096
     rng = np.random.default_rng(3)
