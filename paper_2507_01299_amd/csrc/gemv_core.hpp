@@ -27,6 +27,12 @@ __device__ __forceinline__ uint4 load_stream16(const uint16_t* p) {
 // Row sources.  batch(t, re, lane, j, c) gives the rows and coefficients of the kUnroll ranks
 // t .. t + kUnroll - 1 of the kept list (ranks >= re: any valid row with coefficient zero).
 
+// A rank's row and coefficient.
+struct RowCoef {
+  int row;
+  float coef;
+};
+
 // Read from global memory: indexed (idx != nullptr) or the identity list.
 template <typename T, bool INDEXED>
 struct GlobalRows {
@@ -38,6 +44,11 @@ struct GlobalRows {
     float c = T::to_f32(h[j]);
     if (coef_scale) c *= T::to_f32(coef_scale[j]);
     return c;
+  }
+  __device__ __forceinline__ RowCoef entry(int t, int re) const {
+    const int tc = min(t, re - 1), j = row(tc);
+    const float c = coef(tc, j);
+    return RowCoef{j, t < re ? c : 0.f};
   }
   __device__ __forceinline__ void batch(int t, int re, int /*lane*/, int (&j)[kUnroll], float (&c)[kUnroll]) const {
 #pragma unroll
@@ -75,13 +86,15 @@ struct LdsRows {
 };
 
 // The same with a pair to an entry, one LDS access each way.
-struct RowCoef {
-  int row;
-  float coef;
-};
 struct LdsPairs {
   const RowCoef* list;
   int base;                  // rank of entry 0
+  // rank t, or a valid row with coefficient zero at or past re
+  __device__ __forceinline__ RowCoef entry(int t, int re) const {
+    RowCoef e = list[min(t, re - 1) - base];
+    if (t >= re) e.coef = 0.f;
+    return e;
+  }
   __device__ __forceinline__ void batch(int t, int re, int lane, int (&j)[kUnroll], float (&c)[kUnroll]) const {
     const int u0 = lane & (kUnroll - 1);
     const RowCoef e = list[min(t + u0, re - 1) - base];
@@ -423,6 +436,18 @@ __device__ __forceinline__ bool stage_row_list(const Rows& rows, int t0, int cou
     const int j = rows.row(t0 + e);
     if (lst_idx) lst_idx[e] = j;          // the identity list needs no indices
     lst_val[e] = rows.coef(t0 + e, j);
+  }
+  __syncthreads();
+  return true;
+}
+
+// The same into one list of pairs.
+template <int NT, typename Rows>
+__device__ __forceinline__ bool stage_row_pairs(const Rows& rows, int t0, int count, RowCoef* lst) {
+  if (count > kRowListMax) return false;
+  for (int e = threadIdx.x; e < count; e += NT) {
+    const int j = rows.row(t0 + e);
+    lst[e] = RowCoef{j, rows.coef(t0 + e, j)};
   }
   __syncthreads();
   return true;

@@ -73,6 +73,64 @@ __device__ __forceinline__ void stream_rows_w4(const uint32_t* __restrict__ wcol
   for (int k = 0; k < 8; ++k) acc[k] = fmaf(-8.0f, csum, acc[k]);
 }
 
+// The same with two batches of 16 rows in flight: while one is multiplied the next is on its way.
+// What bounds a call is the chain of memory round trips (four batches a wave at 4096 x 22016, 2457 kept).  Lanes without
+// columns pass any valid ones.
+template <typename T, typename Rows>
+__device__ __forceinline__ void stream_rows_w4_ahead(const uint32_t* __restrict__ wcol, int row_dwords,
+                                               const uint16_t* __restrict__ scol, int ng, const Rows& rows, int ra,
+                                               int re, float (&acc)[8]) {
+  const int lane = threadIdx.x & 63;
+  float csum = 0.f;
+  struct Batch { uint32_t v[kW4Unroll]; uint32_t s[kW4Unroll]; float c; };
+  auto ask = [&](Batch& q, int t) __attribute__((always_inline)) {
+    const RowCoef e = rows.entry(t + (lane & (kW4Unroll - 1)), re);
+    q.c = e.coef;
+#pragma unroll
+    for (int u = 0; u < kW4Unroll; ++u) {
+      const size_t j = static_cast<unsigned>(__builtin_amdgcn_readlane(e.row, u));
+      q.s[u] = scol[j * ng];
+      q.v[u] = load_stream4(wcol + j * row_dwords);
+    }
+  };
+  auto add = [&](const Batch& q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kW4Unroll; ++u) {
+      const float h = __uint_as_float(static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(q.c)), u)));
+      const float c = h * T::to_f32(static_cast<uint16_t>(q.s[u]));
+      csum += c;
+      fma_codes8(q.v[u], c * kW4CodeScale, acc);
+    }
+  };
+  // no load stands under a condition of its own: the compiler would wait for all loads where the paths meet
+  const int batches = (re - ra + kW4Unroll - 1) / kW4Unroll;
+  Batch q0, q1;
+  if (batches == 1) {
+    ask(q0, ra);
+    add(q0);
+  } else if (batches > 1) {
+    ask(q0, ra);
+    ask(q1, ra + kW4Unroll);
+    int t = ra;
+    for (; t + 3 * kW4Unroll < re; t += 2 * kW4Unroll) {
+      add(q0);
+      ask(q0, t + 2 * kW4Unroll);
+      add(q1);
+      ask(q1, t + 3 * kW4Unroll);
+    }
+    add(q0);
+    if (t + 2 * kW4Unroll < re) {
+      ask(q0, t + 2 * kW4Unroll);
+      add(q1);
+      add(q0);
+    } else {
+      add(q1);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) acc[k] = fmaf(-8.0f, csum, acc[k]);
+}
+
 // Wide geometry: a lane reads 16 bytes (32 codes, one scale group) per kept row, a wave 2048 columns.
 constexpr int kW4WideAcc = 32;
 constexpr int kW4WideCols = 64 * kW4WideAcc;
@@ -156,11 +214,13 @@ __global__ __launch_bounds__(RW * 64, 2) void gemv_rows_w4_wide_kernel(W4Args w)
   reduce_and_finish<T, RW, kW4WideAcc>(acc, sg.s, b, g, a.G, a.wps, a.partial, a.counters, a.nstrips, ep, sh, lane, rw);
 }
 
-template <typename T, int RW, bool INDEXED>
+// AHEAD: two batches of rows in flight, for launches of at most one workgroup per compute unit (two batches take 166
+// registers, so a second workgroup would not fit; with two, one batch each does as well).  us without / with, f16:
+// 4096 x 4096 7.0 / 6.3, 4096 x 22016 13.5 / 12.5, 28672 x 8192 24.8 / 22.4; two tokens of 1632 x 27560 12.4 / 16.2.
+template <typename T, int RW, bool INDEXED, bool AHEAD>
 __global__ __launch_bounds__(RW * 64) void gemv_rows_w4_kernel(W4Args w) {
   __shared__ GemvShared<RW> sh;
-  __shared__ int lst_idx[INDEXED ? kRowListMax : 1];
-  __shared__ float lst_val[INDEXED ? kRowListMax : 1];
+  __shared__ RowCoef lst[INDEXED ? kRowListMax : 1];          // without AHEAD: the rows, then the coefficients
   const GemvArgs& a = w.g;
   const int lane = threadIdx.x & 63;
   const int rw = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -176,23 +236,27 @@ __global__ __launch_bounds__(RW * 64) void gemv_rows_w4_kernel(W4Args w) {
   const int row_dwords = a.d_out / 8;
 
   const Segment sg = segment_of(g, a.wps, a.chunk, K);
-  const bool staged = INDEXED && stage_row_list<RW * 64>(rows, sg.t0, sg.t1 - sg.t0, lst_idx, lst_val);
+  int* const lst_idx = reinterpret_cast<int*>(lst);
+  float* const lst_val = reinterpret_cast<float*>(lst) + (INDEXED ? kRowListMax : 1);
+  const bool staged = INDEXED && (AHEAD ? stage_row_pairs<RW * 64>(rows, sg.t0, sg.t1 - sg.t0, lst)
+                                        : stage_row_list<RW * 64>(rows, sg.t0, sg.t1 - sg.t0, lst_idx, lst_val));
   const int col = sg.s * kStripCols + lane * 8;
   float acc[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) acc[k] = 0.f;
   int ra, re;
   wave_run<RW>(sg.t0, sg.t1, rw, ra, re);
-  if (col < a.d_out) {
-    if (staged) {
-      LdsRows lr;
-      lr.idx = lst_idx;
-      lr.val = lst_val;
-      lr.base = sg.t0;
-      stream_rows_w4<T>(w.Wq + col / 8, row_dwords, w.scales + col / kW4Group, w.ng, lr, ra, re, acc);
-    } else {
-      stream_rows_w4<T>(w.Wq + col / 8, row_dwords, w.scales + col / kW4Group, w.ng, rows, ra, re, acc);
-    }
+  if constexpr (AHEAD) {
+    const int vcol = col < a.d_out ? col : sg.s * kStripCols;   // (lines that the others read)
+    const uint32_t* wcol = w.Wq + vcol / 8;
+    const uint16_t* scol = w.scales + vcol / kW4Group;
+    if (staged) stream_rows_w4_ahead<T>(wcol, row_dwords, scol, w.ng, LdsPairs{lst, sg.t0}, ra, re, acc);
+    else stream_rows_w4_ahead<T>(wcol, row_dwords, scol, w.ng, rows, ra, re, acc);
+  } else if (col < a.d_out) {
+    const uint32_t* wcol = w.Wq + col / 8;
+    const uint16_t* scol = w.scales + col / kW4Group;
+    if (staged) stream_rows_w4<T>(wcol, row_dwords, scol, w.ng, LdsRows{lst_idx, lst_val, sg.t0}, ra, re, acc);
+    else stream_rows_w4<T>(wcol, row_dwords, scol, w.ng, rows, ra, re, acc);
   }
   reduce_and_finish<T, RW>(acc, sg.s, b, g, a.G, a.wps, a.partial, a.counters, a.nstrips, ep, sh, lane, rw);
 }
@@ -282,10 +346,11 @@ hipError_t launch_w4_t(const W4Args& w, hipStream_t st) {
       hipLaunchKernelGGL((gemv_rows_w4_wide_kernel<T, RW, false>), grid, block, 0, st, w);
     return hipGetLastError();
   }
-  if (w.g.idx)
-    hipLaunchKernelGGL((gemv_rows_w4_kernel<T, RW, true>), grid, block, 0, st, w);
-  else
-    hipLaunchKernelGGL((gemv_rows_w4_kernel<T, RW, false>), grid, block, 0, st, w);
+  const bool ahead = static_cast<long>(w.g.G) * w.g.B <= 256;
+  if (w.g.idx && ahead) hipLaunchKernelGGL((gemv_rows_w4_kernel<T, RW, true, true>), grid, block, 0, st, w);
+  else if (w.g.idx) hipLaunchKernelGGL((gemv_rows_w4_kernel<T, RW, true, false>), grid, block, 0, st, w);
+  else if (ahead) hipLaunchKernelGGL((gemv_rows_w4_kernel<T, RW, false, true>), grid, block, 0, st, w);
+  else hipLaunchKernelGGL((gemv_rows_w4_kernel<T, RW, false, false>), grid, block, 0, st, w);
   return hipGetLastError();
 }
 

@@ -89,6 +89,35 @@ def test_w4_projection_matches_oracle(api, ws, w4_geometry, dtype, B, d_in, d_ou
     assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("per_wave", [1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81])
+def test_w4_row_batches_in_flight(api, ws, dtype, per_wave):
+    """One workgroup per strip with `per_wave` rows for each of its waves (the last one fewer): every way the pipeline of
+    16-row batches can begin and end, against one launch for many tokens, which takes the loop of single batches (the sums
+    are formed in the same order: same bits), and against the oracle.  The second strip holds 8 columns."""
+    d_in, d_out, K, many = 704, 520, 8 * per_wave - 3, 200
+    print(f"sparse_gemv_w4 batches dtype={dtype} per_wave={per_wave}", flush=True)
+    rng = np.random.default_rng(per_wave)
+    codes, sbits = O.quantize_rtn_w4(synth.gaussian_weight(d_in, d_out, 31), dtype)
+    Wq, sc = _dev_w4(codes, sbits, dtype)
+    hb, h = _heavy(rng, 1, d_in, dtype)
+    idx = O.topk_batch(hb, K)
+    api.set_tuning(1, 1 << 20)
+    try:
+        ys = []
+        for B in (1, many):
+            y = torch.zeros(B, d_out, dtype=api.torch_dtype(dtype), device="cuda:0")
+            api.sparse_gemv_w4(Wq, sc, to_dev(np.repeat(hb, B, 0), dtype), torch.from_numpy(np.repeat(idx, B, 0)).cuda(), y, dtype,
+                               ws if B == 1 else api.workspace(B, d_in, d_out, K))
+            torch.cuda.synchronize()
+            ys.append(to_bits(y))
+    finally:
+        api.set_tuning(1, 112)
+    assert (ys[1] == ys[0][0]).all()
+    want = O.round16(O.sparse_project_w4(h[0], idx[0], codes, sbits, dtype), dtype)
+    assert rel_l2(O.decode16(ys[0], dtype)[0], want) <= REL_L2_TOL
+
+
 def test_w4_projection_full_size_gate_up(api, ws, w4_geometry):
     """gate|up of the 7B-shaped layer (4096 x 22016, 40 % sparsity) in the launch shape the bench times."""
     dtype, d_in, d_out, K = "f16", 4096, 22016, 2458
