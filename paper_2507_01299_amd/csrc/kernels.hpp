@@ -202,13 +202,13 @@ struct ContractionArgs {
   float post_scale;
   int accumulate;           // C32 only: add to what is there
   int symmetric;            // A == B, M == N: compute tiles on or above the diagonal, store both halves
+  int tiles_m, tiles_n, tile0, tiles;           // filled in by launch_contraction
+  long a_elements, b_elements;                  // extent of each operand over all its terms (filled in as well)
   // bf16 on the f16 units, or null: exponent fields of the rows and columns of C by which the f16 operands are scaled; C16
   // (bf16) then has rows of ldc elements, and C32, post_scale, accumulate and symmetric are not looked at
   const int* exp_m;
   const int* exp_n;
   int ldc;
-  int tiles_m, tiles_n, tile0, tiles;           // filled in by launch_contraction
-  long a_elements, b_elements;                  // extent of each operand over all its terms (filled in as well)
 };
 hipError_t launch_contraction(ContractionArgs a, bool a_kmajor, bool bf16, hipStream_t s);
 // An operand of that form: f16 terms of src [rows][cols] (rows of `pitch` elements), each line scaled by its own power of two.

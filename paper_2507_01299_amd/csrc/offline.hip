@@ -20,13 +20,16 @@
 //    adds the products of the listed term pairs into the same accumulators.  Larger bf16 products run on the f16 units
 //    all the same (BF16OnF16): two f16 terms carry the fp32 value too once every line of an operand is scaled by a power of two
 //    of its own, and a bf16 weight is an f16 number then.  A third of a fold's products and half of an adapter's go, for
-//    scaled copies of the operands (4096 x 28672: 2257 -> 1737 us, 1490 of them products at 1.29 PFLOP/s, 240 copies).
+//    scaled copies of the operands (4096 x 28672: 2257 -> 1737 us, 240 of them copies).
+//  * The two terms of a fold go through k together (TWO): the weight's tile is loaded, and read from LDS, once for both, three
+//    operands a k-tile instead of four.  4096 x 28672 bf16 1737 -> 1640 us (1.37 PFLOP/s issued), 4096 x 22016 f16 1315 -> 1233,
+//    11008 x 4096 (W Q) f16 698 -> 646, 1024 x 16384 76 -> 72.
 //  * X^T X is symmetric: only tiles on and above the diagonal are computed; a tile above it is stored twice.
 //  * Whole rounds of 256 tiles (one per compute unit) run in 256 x 256 tiles; what is left over runs as 128 x 128 or 64 x 64
 //    parts in a second launch when that is shorter than another round (launch_shape).
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
 // random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace): 4096 x
-// 28672 x 4096 bf16, in 3 terms 1.29 - 1.33 PFLOP/s, scaled 1.29; f16 folds of a 4096-wide layer 1.15 - 1.18, its adapter 1.24;
+// 28672 x 4096 bf16, in 3 terms 1.29 - 1.33 PFLOP/s, scaled in 2 1.37; f16 folds of a 4096-wide layer 1.23 - 1.25, its adapter 1.24;
 // second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 321 + 36 us = 1.04 (36 for the 16 tiles after
 // the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
 // 64 - 73 % of the cycles; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
@@ -139,15 +142,20 @@ constexpr int kExpTop = 141;
 constexpr int kBigTile = 256;      // tiles are numbered in this size; smaller workgroup tiles are parts of them
 
 // A workgroup of 4 waves (2 x 2) owns a (64 MI) x (64 MI) tile of C, a wave (32 MI) x (32 MI) of it.
-template <typename T, bool A_KMAJOR, int MI>
+// TWO: both term pairs of a fold in one pass over k.  The operand that has two terms (A if it is k-major, else B: the
+// rotation) brings both of a k-tile, the weight comes once for both: three operands are loaded and read from LDS where two
+// passes take four.
+template <typename T, bool A_KMAJOR, int MI, bool TWO>
 __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(ContractionArgs a) {
   constexpr int TC = 64 * MI;                    // tile side
   constexpr int kOperandBytes = TC * kKTile * 2; // one operand of one stage
-  constexpr int kStageBytes = 2 * kOperandBytes;
+  constexpr int kStageBytes = (TWO ? 3 : 2) * kOperandBytes;   // A, B, second term
   constexpr int CPR = TC / 8;                    // 16-byte pieces per row of a k-major tile
   constexpr int RPI = 64 / CPR;                  // rows that one wave-load covers
   constexpr int GR = 2 * MI;                     // granules per row
-  constexpr int kStages = kStagesOf<MI>;
+  constexpr int kStages = TWO ? 3 : kStagesOf<MI>;
+  static_assert(!TWO || MI == 4, "two terms at once: the large tile only");
+  constexpr int kLoads = kStageBytes / 4096;     // of a wave per stage
   constexpr int kParts = 4 / MI;                 // a 256 x 256 tile is kParts x kParts tiles of this kernel
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes];
 
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   const int wm = w >> 1, wn = w & 1;
 
   const int ktiles = (a.Kd + kKTile - 1) / kKTile;
-  const int iters = ktiles * a.npairs;
+  const int iters = TWO ? ktiles : ktiles * a.npairs;
 
   // ---- loads, straight into LDS: wave-load q of wave w fills pieces 64 (4 q + w) .. + 63 of the operand's tile
   const u32x4 bufA = operand_buffer(a.A, a.a_elements);
@@ -194,8 +202,12 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   int f_pair = 0, f_k = a.Kd, f_stage = 0;
   uint32_t ta = static_cast<uint32_t>(a.pa[0] * a.a_term_stride * 2), tb = static_cast<uint32_t>(a.pb[0] * a.b_term_stride * 2);
   uint32_t f_lds = lds_base + w * 1024;
-  auto fetch_piece = [&](int q) {                // q < MI: A, else B
-    if (q < MI) load_to_lds(bufA, f_lds + q * 4096, (kA[q & (MI - 1)] < f_k ? offA[q & (MI - 1)] : kOutside) + ta);
+  const uint32_t term2 = static_cast<uint32_t>((A_KMAJOR ? a.a_term_stride : a.b_term_stride) * 2);
+  auto fetch_piece = [&](int q) {                // q < MI: A, then B, then the second term of one of them
+    if (q >= 2 * MI) {
+      if (A_KMAJOR) load_to_lds(bufA, f_lds + 2 * kOperandBytes + (q - 2 * MI) * 4096, (kA[q & (MI - 1)] < f_k ? offA[q & (MI - 1)] : kOutside) + (ta + term2));
+      else load_to_lds(bufB, f_lds + 2 * kOperandBytes + (q - 2 * MI) * 4096, (kB[q & (MI - 1)] < f_k ? offB[q & (MI - 1)] : kOutside) + (tb + term2));
+    } else if (q < MI) load_to_lds(bufA, f_lds + q * 4096, (kA[q & (MI - 1)] < f_k ? offA[q & (MI - 1)] : kOutside) + ta);
     else load_to_lds(bufB, f_lds + kOperandBytes + (q - MI) * 4096, (kB[q & (MI - 1)] < f_k ? offB[q & (MI - 1)] : kOutside) + tb);
   };
   auto fetch_next = [&]() {
@@ -204,7 +216,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
     tb += stepB;
     if (f_k <= 0) {                              // the next term pair (uniform, once per pass over k)
       ++f_pair;
-      if (f_pair < a.npairs) {
+      if (!TWO && f_pair < a.npairs) {
         f_k = a.Kd;
         ta = static_cast<uint32_t>(a.pa[f_pair] * a.a_term_stride * 2);
         tb = static_cast<uint32_t>(a.pb[f_pair] * a.b_term_stride * 2);
@@ -213,12 +225,12 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
         ta = tb = 0;
       }
     }
-    f_stage = (f_stage + 1) & (kStages - 1);
+    f_stage = f_stage == kStages - 1 ? 0 : f_stage + 1;
     f_lds = lds_base + f_stage * kStageBytes + w * 1024;
   };
   auto fetch = [&]() {
 #pragma unroll
-    for (int q = 0; q < 2 * MI; ++q) fetch_piece(q);
+    for (int q = 0; q < kLoads; ++q) fetch_piece(q);
     fetch_next();
   };
 
@@ -283,19 +295,74 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   // while its first half is multiplied, then one barrier, then the first half of tile it + 1 while the second half is
   // multiplied.  The barrier follows a wait for this wave's own loads of tile it + 1 (the kStages - 2 tiles of 2 MI loads
   // after it may be outstanding) and for its LDS reads of tile it, whose stage the loads issued next overwrite.
-  u32x4 a0[MI], b0[MI], a1[MI], b1[MI];
-  for (int i = 0; i < kStages - 1; ++i) fetch();
-  tile_landed<(kStages - 2) * 2 * MI>();
-  fetch();
-  int stage = 0;
-#pragma unroll
-  for (int r = 0; r < 2 * MI; ++r) read_piece(stage, 0, r, a0, b0);
-  for (int it = 0; it < iters; ++it) {
-    products(a0, b0, stage, 1, a1, b1, std::false_type{});
+  if constexpr (!TWO) {
+    u32x4 a0[MI], b0[MI], a1[MI], b1[MI];
+    for (int i = 0; i < kStages - 1; ++i) fetch();
     tile_landed<(kStages - 2) * 2 * MI>();
-    stage = (stage + kStageBytes) & (kStages * kStageBytes - 1);
-    products(a1, b1, stage, 0, a0, b0, std::true_type{});
-    fetch_next();
+    fetch();
+    int stage = 0;
+  #pragma unroll
+    for (int r = 0; r < 2 * MI; ++r) read_piece(stage, 0, r, a0, b0);
+    for (int it = 0; it < iters; ++it) {
+      products(a0, b0, stage, 1, a1, b1, std::false_type{});
+      tile_landed<(kStages - 2) * 2 * MI>();
+      stage = (stage + kStageBytes) & (kStages * kStageBytes - 1);
+      products(a1, b1, stage, 0, a0, b0, std::true_type{});
+      fetch_next();
+    }
+  } else {
+    // The same with four groups of products per k-tile: first term, second term of its first half, then of its second.
+    // The barrier stands before the last group, which reads the next tile's first operands; a tile's twelve loads are
+    // issued half in that group, half in the one after.
+    u32x4 p0[MI], p1[MI], s0[MI], s1[MI];        // first term, second term; the shared operand of each half
+    auto read_term = [&](int st, int s, int term, int i) -> u32x4 {
+      return A_KMAJOR ? read_k(st + term * 2 * kOperandBytes, adrA[i], s) : read_k(st + term * kOperandBytes, adrB[i], s);
+    };
+    auto read_shared = [&](int st, int s, int i) -> u32x4 {
+      if constexpr (A_KMAJOR) return read_k(st, adrB[i], s);
+      else return *(const __attribute__((address_space(3))) u32x4*)((const lds_char*)lds + st + (adrA[i] ^ (32 * s)));
+    };
+    auto group = [&](const u32x4 (&p)[MI], const u32x4 (&sh)[MI], auto between) {
+      static_for<MI * MI>([&](auto ij) {
+        constexpr int x = decltype(ij)::value;
+        between(x);
+        acc[x / MI][x % MI] = A_KMAJOR ? Mfma<T>::run(p[x / MI], sh[x % MI], acc[x / MI][x % MI])
+                                       : Mfma<T>::run(sh[x / MI], p[x % MI], acc[x / MI][x % MI]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    fetch();
+    fetch();
+    tile_landed<kLoads>();
+#pragma unroll
+    for (int q = 0; q < kLoads / 2; ++q) fetch_piece(q);
+    int stage = 0;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      p0[i] = read_term(stage, 0, 0, i);
+      s0[i] = read_shared(stage, 0, i);
+    }
+    for (int it = 0; it < iters; ++it) {
+      group(p0, s0, [&](int x) __attribute__((always_inline)) {
+        if (x % 4 == 0) p1[x / 4] = read_term(stage, 0, 1, x / 4);
+        if (x % 2 == 1 && x / 2 < kLoads / 2) fetch_piece(kLoads / 2 + x / 2);
+      });
+      fetch_next();
+      group(p1, s0, [&](int x) __attribute__((always_inline)) {
+        if (x % 4 == 0) p0[x / 4] = read_term(stage, 1, 0, x / 4);
+        if (x % 4 == 2) s1[x / 4] = read_shared(stage, 1, x / 4);
+      });
+      group(p0, s1, [&](int x) __attribute__((always_inline)) {
+        if (x % 4 == 0) p1[x / 4] = read_term(stage, 1, 1, x / 4);
+      });
+      tile_landed<kLoads>();                     // of the three tiles under way, the youngest may be outstanding
+      stage = stage == (kStages - 1) * kStageBytes ? 0 : stage + kStageBytes;
+      group(p1, s1, [&](int x) __attribute__((always_inline)) {
+        if (x % 4 == 0) p0[x / 4] = read_term(stage, 0, 0, x / 4);
+        if (x % 4 == 2) s0[x / 4] = read_shared(stage, 0, x / 4);
+        if (x % 2 == 1 && x / 2 < kLoads / 2) fetch_piece(x / 2);
+      });
+    }
   }
   // ---- store.  Accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of its 32 x 32
   // block.  A strip of 32 rows at a time goes through the wave's own part of the LDS (every load into it has landed and
@@ -621,14 +688,14 @@ hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre
 namespace {
 
 // Tiles first .. first + count - 1 (numbered in 256 x 256 tiles) by workgroups of (64 MI) x (64 MI) tiles.
-template <typename T, bool A_KMAJOR, int MI>
+template <typename T, bool A_KMAJOR, int MI, bool TWO = false>
 hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s) {
   const long parts = count * (4 / MI) * (4 / MI);
   const long grid = (parts + 7) / 8 * 8;
   if (grid > 0x7FFFFFFFL) return hipErrorInvalidValue;
   a.tile0 = static_cast<int>(first);
   a.tiles = static_cast<int>(parts);
-  hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TWO>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -667,7 +734,14 @@ hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
     if (mi == 4) big = tiles;
   }
   if (big > 0) {
-    if (hipError_t e = launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s); e != hipSuccess) return e;
+    // a fold's two term pairs: the rotation's first and second term with the weight
+    bool two = a.npairs == 2 && (A_KMAJOR ? a.pa[0] == 0 && a.pa[1] == 1 && a.pb[0] == 0 && a.pb[1] == 0
+                                          : a.pb[0] == 0 && a.pb[1] == 1 && a.pa[0] == 0 && a.pa[1] == 0);
+    hipError_t e;
+    if constexpr (std::is_same_v<T, BF16>) two = false;   // (bf16 terms come in threes)
+    else if (two) e = launch_tiles<T, A_KMAJOR, 4, true>(a, 0, big, s);
+    if (!two) e = launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s);
+    if (e != hipSuccess) return e;
   }
   if (big == tiles) return hipSuccess;
   return mi == 2 ? launch_tiles<T, A_KMAJOR, 2>(a, big, rest, s) : launch_tiles<T, A_KMAJOR, 1>(a, big, rest, s);
