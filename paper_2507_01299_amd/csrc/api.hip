@@ -729,7 +729,7 @@ inline size_t terms_bytes(int d, bool bf16) {
 // The copies cost a launch and three passes over the operands, so small products stay with three terms.  Measured, three
 // terms / scaled (us, input fold): 1280 x 512 27.5 / 30.0, 1800 x 512 38.3 / 41.0, 1024 x 4096 42.6 / 42.0, 1280 x 2048 42.5 / 42.3,
 // 1536 x 1536 49.8 / 46.5, 1536 x 28672 386 / 346; from 2048 on at every width: 2048 x 256 42.2 / 39.4, 2048 x 8192 188 / 159,
-// 4096 x 128 110 / 92, 4096 x 4096 376 / 293, 4096 x 28672 2257 / 1737.  Adapters: 256 15.5 / 17.5, 512 24.3 / 22.8, 1024 41.3 /
+// 4096 x 128 110 / 92, 4096 x 4096 374 / 281, 2048 x 28672 (panels) 637 / 546, 4096 x 28672 2260 / 1625.  Adapters: 256 15.5 / 17.5, 512 24.3 / 22.8, 1024 41.3 /
 // 31.6, 4096 716 / 423.
 constexpr int kScaledFoldMin = 1152, kScaledFoldAll = 2048, kScaledAdapterMin = 512;
 constexpr double kScaledFoldWork = 3e9;          // d * d * other, below kScaledFoldAll
@@ -745,7 +745,6 @@ struct ScaledFold {
   ScaleJob q, w;
   int lines;                                     // columns (input fold) or rows (output fold) of a panel; 0: not taken
 };
-inline long panel_round(int d) { return 256 / std::min(256, (d + 255) / 256) * 256L; }
 inline size_t exponent_parts(int d) { return (static_cast<size_t>(d) + kScaleRows - 1) / kScaleRows; }
 ScaledFold scaled_fold(const float* Q, int d, int other, bool bf16, void* ws, size_t ws_bytes) {
   ScaledFold f{};
@@ -759,10 +758,15 @@ ScaledFold scaled_fold(const float* Q, int d, int other, bool bf16, void* ws, si
   const size_t fixed = terms + exp_q + part_q + 512;   // (512: roundings of the panel's exponents and their parts)
   if (ws_bytes < fixed) return f;
   const long fit = static_cast<long>((ws_bytes - fixed) / (2 * static_cast<size_t>(d) + 4 + parts)) / 8 * 8;
-  // the whole weight, or panels of whole rounds of 256 tiles (256 x 256) of the result
-  const long round = panel_round(d);
-  const long lines = fit >= other ? other : fit / round * round;
-  if (lines < 8) return f;
+  // The whole weight, or panels of whole rounds of 256 tiles (256 x 256) of the result.  The usual workspace (twice three
+  // terms) holds a little less than 4 d lines: below d = 2056 less than a round, taken if it fills 7/8 of one (from d = 1800
+  // on; three terms in one go are faster than rounds that are half empty).
+  const long tiles = std::min(256, (d + 255) / 256), round = 256 / tiles * 256;
+  long lines = other;
+  if (fit < other) {
+    lines = fit >= round ? fit / round * round : fit / 256 * 256;
+    if (tiles * (lines / 256) < 224) return f;
+  }
   char* p = static_cast<char*>(ws);
   auto take = [&](size_t bytes) { char* at = p; p += round_up(bytes, 256); return at; };
   f.q.kind = kRotationColumns;
@@ -790,14 +794,7 @@ int check_offline(const void* a, const void* b, const void* c, int d, larosa_dty
 
 size_t larosa_offline_workspace_bytes(int d, larosa_dtype t) {
   if (d < 8 || !dtype_ok(t)) return 0;
-  const bool bf16 = t == LAROSA_BF16;
-  // bf16: room for a panel of a whole round in a scaled fold (from d = 2048 on, twice three terms hold that anyway), for
-  // its exponents and their parts
-  const size_t plain = 2 * terms_bytes(d, bf16);
-  if (!bf16 || d < kScaledFoldMin) return plain;
-  const size_t parts = exponent_parts(d), line = 2 * static_cast<size_t>(d) + 4 + parts;
-  const size_t lines = std::max(4 * static_cast<size_t>(d), static_cast<size_t>(panel_round(d)));
-  return round_up(std::max(plain, 4 * static_cast<size_t>(d) * d + d * (4 + parts) + 1280 + lines * line), 256);
+  return 2 * terms_bytes(d, t == LAROSA_BF16);
 }
 
 int larosa_second_moment(const void* X, int n_tokens, int d, larosa_dtype t, float* C, int accumulate,

@@ -418,7 +418,7 @@ def test_bf16_contractions_hold_any_exponents(gpu_device, tile, d, other):
 
 @pytest.mark.parametrize("d,other", [(2048, 8192 + 264), (2056, 7168 + 8)])
 def test_bf16_folds_in_panels(gpu_device, d, other):
-    """More columns (rows) than the workspace holds scaled copies of: a second panel of 264 or 8 lines."""
+    """More columns (rows) than the workspace holds scaled copies of: panels of 7936 and 520 lines, 7168 and 8."""
     from paper_2507_01299_amd import api
     rng = np.random.default_rng(d)
     print(f"bf16 panels d={d} other={other}", flush=True)
@@ -430,8 +430,8 @@ def test_bf16_folds_in_panels(gpu_device, d, other):
     outT = torch.zeros(other, d, dtype=torch.bfloat16, device="cuda:0")
     api.fold_output(to_dev(np.ascontiguousarray(wb.T), "bf16"), Qd, outT, "bf16", sc)
     torch.cuda.synchronize()
-    first = other // 256 * 256 - 256
-    cols = np.unique(np.concatenate([rng.choice(other, 32), np.arange(other - 16, other), np.arange(first, first + 8)]))
+    first = 7936 if d == 2048 else 7168
+    cols = np.unique(np.concatenate([rng.choice(other, 32), np.arange(other - 16, other), np.arange(first - 8, first + 8)]))
     w64 = O.decode16(wb[:, cols], "bf16")
     want = O.fold_input_side(Q.astype(np.float64), w64)
     wn = np.linalg.norm(w64, axis=0)
