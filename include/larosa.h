@@ -201,9 +201,7 @@ int larosa_layer_after_attention(const larosa_layer* L, const void* residual, co
  * LAROSA_EINVAL for null/misaligned pointers or bad sizes, LAROSA_EWORKSPACE for a workspace that is
  * too small, LAROSA_EHIP when a launch fails. */
 
-/* Bytes of workspace the three folding calls below need for d x d rotations of type t (host only).  In bf16 the
- * folds also keep scaled copies of the weight there, panel by panel; one that gets less (three terms of the rotation, half
- * of this, suffice) may take a slower way. */
+/* Bytes of workspace the three folding calls below need for d x d rotations of type t (host only). */
 size_t larosa_offline_workspace_bytes(int d, larosa_dtype t);
 
 /* Second-moment accumulation (Sec. 4.2): C (+)= X^T X for n_tokens calibration rows X [n_tokens, d]

@@ -4,7 +4,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "kernels.hpp"
@@ -719,70 +718,6 @@ inline size_t terms_bytes(int d, bool bf16) {
   return round_up(static_cast<size_t>(contraction_terms(bf16)) * d * d * 2, 256);
 }
 
-// ---- bf16 contractions on the f16 units.  An fp32 rotation takes three bf16 terms but only two f16 ones, and a bf16 weight
-// is an f16 number exactly once its exponent fits: two passes of products instead of three for a fold, three instead of six
-// for an adapter.  Every column (row) is scaled by a power of two of its own, so an element within 2^-31 of its column's
-// largest is held to the last bit of a bf16, or to 2^-23 of itself of an fp32, and a smaller one to 2^-40 of that largest.
-// The scaled copy of the weight lives in the workspace, panel by panel.
-
-//
-// The copies cost a launch and three passes over the operands, so small products stay with three terms.  Measured, three
-// terms / scaled (us, input fold): 1280 x 512 27.5 / 30.0, 1800 x 512 38.3 / 41.0, 1024 x 4096 42.6 / 42.0, 1280 x 2048 42.5 / 42.3,
-// 1536 x 1536 49.8 / 46.5, 1536 x 28672 386 / 346; from 2048 on at every width: 2048 x 256 42.2 / 39.4, 2048 x 8192 188 / 159,
-// 4096 x 128 110 / 92, 4096 x 4096 374 / 281, 2048 x 28672 (panels) 637 / 546, 4096 x 28672 2260 / 1625.  Adapters: 256 15.5 / 17.5, 512 24.3 / 22.8, 1024 41.3 /
-// 31.6, 4096 716 / 423.
-constexpr int kScaledFoldMin = 1152, kScaledFoldAll = 2048, kScaledAdapterMin = 512;
-constexpr double kScaledFoldWork = 3e9;          // d * d * other, below kScaledFoldAll
-
-// What the kernels' 32-bit byte offsets refuse in three bf16 terms stays refused.
-inline bool terms_addressable(int d, int other) {
-  const long n = static_cast<long>(d) * d, w = static_cast<long>(d) * other;
-  return 3 * n * 2 < 0x7FFFFFF0L && w * 2 < 0x7FFFFFF0L;
-}
-
-// Workspace of a scaled fold: two f16 terms of Q, exponents (rotation, panel) and their parts, the panel of the weight.
-struct ScaledFold {
-  ScaleJob q, w;
-  int lines;                                     // columns (input fold) or rows (output fold) of a panel; 0: not taken
-};
-inline size_t exponent_parts(int d) { return (static_cast<size_t>(d) + kScaleRows - 1) / kScaleRows; }
-ScaledFold scaled_fold(const float* Q, int d, int other, bool bf16, void* ws, size_t ws_bytes) {
-  ScaledFold f{};
-  if (!bf16 || !terms_addressable(d, other)) return f;
-  // (a tile that is asked for takes the scaled form at any size: tests)
-  if (tuning().contraction_tiles == 0 && d < kScaledFoldAll &&
-      (d < kScaledFoldMin || static_cast<double>(d) * d * other < kScaledFoldWork)) return f;
-  const size_t parts = exponent_parts(d);
-  const size_t terms = round_up(static_cast<size_t>(d) * d * 4, 256), exp_q = round_up(static_cast<size_t>(d) * 4, 256);
-  const size_t part_q = round_up(d * parts, 256);
-  const size_t fixed = terms + exp_q + part_q + 512;   // (512: roundings of the panel's exponents and their parts)
-  if (ws_bytes < fixed) return f;
-  const long fit = static_cast<long>((ws_bytes - fixed) / (2 * static_cast<size_t>(d) + 4 + parts)) / 8 * 8;
-  // The whole weight, or panels of whole rounds of 256 tiles (256 x 256) of the result.  The usual workspace (twice three
-  // terms) holds a little less than 4 d lines: below d = 2056 less than a round, taken if it fills 7/8 of one (from d = 1800
-  // on; three terms in one go are faster than rounds that are half empty).
-  const long tiles = std::min(256, (d + 255) / 256), round = 256 / tiles * 256;
-  long lines = other;
-  if (fit < other) {
-    lines = fit >= round ? fit / round * round : fit / 256 * 256;
-    if (tiles * (lines / 256) < 224) return f;
-  }
-  char* p = static_cast<char*>(ws);
-  auto take = [&](size_t bytes) { char* at = p; p += round_up(bytes, 256); return at; };
-  f.q.kind = kRotationColumns;
-  f.q.src = Q;
-  f.q.rows = f.q.cols = d;
-  f.q.pitch = d;
-  f.q.dst = reinterpret_cast<uint16_t*>(take(terms));
-  f.q.exps = reinterpret_cast<int*>(take(exp_q));
-  f.q.part = reinterpret_cast<uint8_t*>(take(part_q));
-  f.w.exps = reinterpret_cast<int*>(take(static_cast<size_t>(lines) * 4));
-  f.w.part = reinterpret_cast<uint8_t*>(take(lines * parts));
-  f.w.dst = reinterpret_cast<uint16_t*>(p);
-  f.lines = static_cast<int>(lines);
-  return f;
-}
-
 int check_offline(const void* a, const void* b, const void* c, int d, larosa_dtype t) {
   if (!a || !b || !c || !dtype_ok(t)) return LAROSA_EINVAL;
   if (!aligned(a, 16) || !aligned(b, 16) || !aligned(c, 16)) return LAROSA_EINVAL;
@@ -820,31 +755,8 @@ int larosa_fold_input(const float* Q, const void* W, int d, int d_out, larosa_dt
   const bool bf16 = t == LAROSA_BF16;
   if (!ws || !aligned(ws, 256) || ws_bytes < terms_bytes(d, bf16)) return LAROSA_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const long n = static_cast<long>(d) * d;
-  if (const ScaledFold f = scaled_fold(Q, d, d_out, bf16, ws, ws_bytes); f.lines) {
-    ScaleJob jobs[2] = {f.w, f.q};
-    jobs[0].kind = kWeightColumns;
-    jobs[0].rows = d;
-    jobs[0].pitch = d_out;
-    for (int c = 0; c < d_out; c += f.lines) {
-      const int cols = std::min(f.lines, d_out - c);
-      jobs[0].src = static_cast<const uint16_t*>(W) + c;
-      jobs[0].cols = cols;
-      if (launch_scale(jobs, c == 0 ? 2 : 1, st) != hipSuccess) return LAROSA_EHIP;
-      ContractionArgs a{};
-      a.A = f.q.dst; a.B = f.w.dst;
-      a.M = d; a.N = cols; a.Kd = d;
-      a.a_term_stride = n;
-      a.npairs = 2;
-      a.pa[1] = 1;
-      a.C16 = static_cast<uint16_t*>(W_out) + c;
-      a.exp_m = f.q.exps; a.exp_n = f.w.exps;
-      a.ldc = d_out;
-      if (launch_contraction(a, true, true, st) != hipSuccess) return LAROSA_EHIP;
-    }
-    return LAROSA_OK;
-  }
   uint16_t* terms = static_cast<uint16_t*>(ws);
+  const long n = static_cast<long>(d) * d;
   if (launch_split_terms(Q, terms, n, term_pre_scale(bf16), bf16, st) != hipSuccess) return LAROSA_EHIP;
   ContractionArgs a{};
   a.A = terms; a.B = static_cast<const uint16_t*>(W);
@@ -864,31 +776,8 @@ int larosa_fold_output(const void* W, const float* Q, int d_in, int d, larosa_dt
   const bool bf16 = t == LAROSA_BF16;
   if (!ws || !aligned(ws, 256) || ws_bytes < terms_bytes(d, bf16)) return LAROSA_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const long n = static_cast<long>(d) * d;
-  if (const ScaledFold f = scaled_fold(Q, d, d_in, bf16, ws, ws_bytes); f.lines) {
-    ScaleJob jobs[2] = {f.w, f.q};
-    jobs[0].kind = kWeightRows;
-    jobs[0].cols = d;
-    jobs[0].pitch = d;
-    for (int r = 0; r < d_in; r += f.lines) {
-      const int rows = std::min(f.lines, d_in - r);
-      jobs[0].src = static_cast<const uint16_t*>(W) + static_cast<long>(r) * d;
-      jobs[0].rows = rows;
-      if (launch_scale(jobs, r == 0 ? 2 : 1, st) != hipSuccess) return LAROSA_EHIP;
-      ContractionArgs a{};
-      a.A = f.w.dst; a.B = f.q.dst;
-      a.M = rows; a.N = d; a.Kd = d;
-      a.b_term_stride = n;
-      a.npairs = 2;
-      a.pb[1] = 1;
-      a.C16 = static_cast<uint16_t*>(W_out) + static_cast<long>(r) * d;
-      a.exp_m = f.w.exps; a.exp_n = f.q.exps;
-      a.ldc = d;
-      if (launch_contraction(a, false, true, st) != hipSuccess) return LAROSA_EHIP;
-    }
-    return LAROSA_OK;
-  }
   uint16_t* terms = static_cast<uint16_t*>(ws);
+  const long n = static_cast<long>(d) * d;
   if (launch_split_terms(Q, terms, n, term_pre_scale(bf16), bf16, st) != hipSuccess) return LAROSA_EHIP;
   ContractionArgs a{};
   a.A = static_cast<const uint16_t*>(W); a.B = terms;
@@ -911,41 +800,23 @@ int larosa_residual_adapter(const float* Q_l, const float* Q_next, int d, larosa
   uint16_t* ta = static_cast<uint16_t*>(ws);
   uint16_t* tb16 = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + tb);
   const long n = static_cast<long>(d) * d;
+  const float pre = term_pre_scale(bf16);
+  if (launch_split_terms(Q_l, ta, n, pre, bf16, st) != hipSuccess) return LAROSA_EHIP;
+  if (launch_split_terms(Q_next, tb16, n, pre, bf16, st) != hipSuccess) return LAROSA_EHIP;
   ContractionArgs a{};
   a.A = ta; a.B = tb16;
   a.M = a.N = a.Kd = d;
   a.a_term_stride = a.b_term_stride = n;
-  const bool scaled = bf16 && terms_addressable(d, d) && (d >= kScaledAdapterMin || tuning().contraction_tiles != 0);
   // every product of terms whose combined weight is above the fp32 rounding of the full product
   static const int f16_pairs[3][2] = {{0, 0}, {0, 1}, {1, 0}};
   static const int bf16_pairs[6][2] = {{0, 0}, {0, 1}, {1, 0}, {1, 1}, {0, 2}, {2, 0}};
-  a.npairs = bf16 && !scaled ? 6 : 3;
+  a.npairs = bf16 ? 6 : 3;
   for (int i = 0; i < a.npairs; ++i) {
-    a.pa[i] = a.npairs == 6 ? bf16_pairs[i][0] : f16_pairs[i][0];
-    a.pb[i] = a.npairs == 6 ? bf16_pairs[i][1] : f16_pairs[i][1];
+    a.pa[i] = bf16 ? bf16_pairs[i][0] : f16_pairs[i][0];
+    a.pb[i] = bf16 ? bf16_pairs[i][1] : f16_pairs[i][1];
   }
   a.C16 = static_cast<uint16_t*>(A_out);
-  if (scaled) {
-    // each half of the workspace (3 terms) holds 2 terms, the exponents and their parts: 2 d^2 >= (5 + d / 128) d from d = 8 on
-    ScaleJob jobs[2]{};
-    for (int i = 0; i < 2; ++i) {
-      jobs[i].kind = kRotationColumns;
-      jobs[i].src = i ? Q_next : Q_l;
-      jobs[i].rows = jobs[i].cols = d;
-      jobs[i].pitch = d;
-      jobs[i].dst = i ? tb16 : ta;
-      jobs[i].exps = reinterpret_cast<int*>(jobs[i].dst + 2 * n);
-      jobs[i].part = reinterpret_cast<uint8_t*>(jobs[i].exps + d);
-    }
-    if (launch_scale(jobs, 2, st) != hipSuccess) return LAROSA_EHIP;
-    a.exp_m = jobs[0].exps; a.exp_n = jobs[1].exps;
-    a.ldc = d;
-  } else {
-    const float pre = term_pre_scale(bf16);
-    if (launch_split_terms(Q_l, ta, n, pre, bf16, st) != hipSuccess) return LAROSA_EHIP;
-    if (launch_split_terms(Q_next, tb16, n, pre, bf16, st) != hipSuccess) return LAROSA_EHIP;
-    a.post_scale = 1.0f / (pre * pre);
-  }
+  a.post_scale = 1.0f / (pre * pre);
   return launch_contraction(a, true, bf16, st) == hipSuccess ? LAROSA_OK : LAROSA_EHIP;
 }
 

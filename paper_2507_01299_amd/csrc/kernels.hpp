@@ -204,27 +204,8 @@ struct ContractionArgs {
   int symmetric;            // A == B, M == N: compute tiles on or above the diagonal, store both halves
   int tiles_m, tiles_n, tile0, tiles;           // filled in by launch_contraction
   long a_elements, b_elements;                  // extent of each operand over all its terms (filled in as well)
-  // bf16 on the f16 units, or null: exponent fields of the rows and columns of C by which the f16 operands are scaled; C16
-  // (bf16) then has rows of ldc elements, and C32, post_scale, accumulate and symmetric are not looked at
-  const int* exp_m;
-  const int* exp_n;
-  int ldc;
 };
 hipError_t launch_contraction(ContractionArgs a, bool a_kmajor, bool bf16, hipStream_t s);
-// An operand of that form: f16 terms of src [rows][cols] (rows of `pitch` elements), each line scaled by its own power of two.
-enum ScaleKind { kRotationColumns, kWeightColumns, kWeightRows };   // fp32, two terms, a line is a column; bf16, one term; a line is a row
-constexpr int kScaleRows = 128;                 // rows that share a set of partial exponents
-struct ScaleJob {
-  int kind;
-  const void* src;
-  int rows, cols;
-  long pitch;
-  uint8_t* part;            // columns: [ceil(rows / kScaleRows)][cols] scratch, 8-byte aligned
-  int* exps;                // out: the largest exponent field among each line's finite elements
-  uint16_t* dst;            // out: [terms][rows][cols]
-  int blocks_x;             // (filled in by launch_scale)
-};
-hipError_t launch_scale(const ScaleJob* jobs, int n, hipStream_t s);   // one or two
 // number of 16-bit terms an fp32 operand is split into (2 for f16, 3 for bf16)
 int contraction_terms(bool bf16);
 // dst[t][i] for t < terms: src[i] * pre_scale = sum_t dst[t][i] up to the last term's rounding

@@ -17,19 +17,15 @@
 //  * A rotation comes from an eigen-solver in fp32 or better; rounding it to 16 bits before the
 //    product would cost more than the 16-bit rounding of the folded weight itself.  It is therefore
 //    split into 2 (f16) or 3 (bf16) 16-bit terms whose sum carries the fp32 value, and the kernel
-//    adds the products of the listed term pairs into the same accumulators.  Larger bf16 products run on the f16 units
-//    all the same (BF16OnF16): two f16 terms carry the fp32 value too once every line of an operand is scaled by a power of two
-//    of its own, and a bf16 weight is an f16 number then.  A third of a fold's products and half of an adapter's go, for
-//    scaled copies of the operands (4096 x 28672: 2257 -> 1737 us, 240 of them copies).
-//  * The two terms of a fold go through k together (TWO): the weight's tile is loaded, and read from LDS, once for both, three
-//    operands a k-tile instead of four.  4096 x 28672 bf16 1737 -> 1640 us (1.37 PFLOP/s issued), 4096 x 22016 f16 1315 -> 1233,
-//    11008 x 4096 (W Q) f16 698 -> 646, 1024 x 16384 76 -> 72.
+//    adds the products of the listed term pairs into the same accumulators.
+//  * The two f16 terms of a fold go through k together (TWO): the weight's tile is loaded, and read from LDS, once for both, three
+//    operands a k-tile instead of four.  4096 x 22016 f16 1315 -> 1233 us, 11008 x 4096 (W Q) f16 698 -> 646, 1024 x 16384 76 -> 72.
 //  * X^T X is symmetric: only tiles on and above the diagonal are computed; a tile above it is stored twice.
 //  * Whole rounds of 256 tiles (one per compute unit) run in 256 x 256 tiles; what is left over runs as 128 x 128 or 64 x 64
 //    parts in a second launch when that is shorter than another round (launch_shape).
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
 // random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace): 4096 x
-// 28672 x 4096 bf16, in 3 terms 1.29 - 1.33 PFLOP/s, scaled in 2 1.37; f16 folds of a 4096-wide layer 1.23 - 1.25, its adapter 1.24;
+// 28672 x 4096 bf16, 3 terms, 1.29 - 1.33 PFLOP/s; f16 folds of a 4096-wide layer 1.23 - 1.25, its adapter 1.24;
 // second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 321 + 36 us = 1.04 (36 for the 16 tiles after
 // the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
 // 64 - 73 % of the cycles; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
@@ -68,11 +64,6 @@ template <> struct Mfma<BF16> {
                                                    0);
   }
 };
-
-// bf16 operands on the f16 units: each is held as f16 (a weight in one term, a rotation in two), every row of C and every
-// column of it with a power of two of its own (ContractionArgs::exp_m, exp_n), and C is stored as bf16.
-struct BF16OnF16 : BF16 {};
-template <> struct Mfma<BF16OnF16> : Mfma<F16> {};
 
 // Operand loads go through buffer resources that span the whole (multi-term) operand: rows past Kd and columns outside
 // the matrix only need the offset kOutside.
@@ -134,10 +125,6 @@ __device__ __forceinline__ TileAt tile_of(int number, int tiles_m, int tiles_n, 
     ++band;
   }
 }
-
-// A line of an operand whose largest finite element has exponent field E is multiplied by 2^(kExpTop - E), which brings
-// that element into [2^14, 2^15): below the f16 limit, and with 39 binary places between it and the smallest f16.
-constexpr int kExpTop = 141;
 
 constexpr int kBigTile = 256;      // tiles are numbered in this size; smaller workgroup tiles are parts of them
 
@@ -225,7 +212,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
         ta = tb = 0;
       }
     }
-    f_stage = f_stage == kStages - 1 ? 0 : f_stage + 1;
+    f_stage = TWO ? (f_stage == kStages - 1 ? 0 : f_stage + 1) : (f_stage + 1) & (kStages - 1);
     f_lds = lds_base + f_stage * kStageBytes + w * 1024;
   };
   auto fetch = [&]() {
@@ -301,7 +288,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
     tile_landed<(kStages - 2) * 2 * MI>();
     fetch();
     int stage = 0;
-  #pragma unroll
+#pragma unroll
     for (int r = 0; r < 2 * MI; ++r) read_piece(stage, 0, r, a0, b0);
     for (int it = 0; it < iters; ++it) {
       products(a0, b0, stage, 1, a1, b1, std::false_type{});
@@ -377,8 +364,6 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   const int mw = m0 + wm * W, nw = n0 + wn * W;  // first row and column of the wave's block
   const int rq = 4 * (lane >> 5), cl = lane & 31;
   const int M = a.M, N = a.N;
-  constexpr bool kScaled = std::is_same_v<T, BF16OnF16>;
-  const int ldc = kScaled ? a.ldc : a.N;
   uint16_t* const C16 = a.C16;
   float* const C32 = a.C32;
   const float post_scale = a.post_scale;
@@ -402,7 +387,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
       for (int p = 0; p < 32 * kLanes / 64; ++p) {
         const int r = p * (64 / kLanes) + lane / kLanes, c = lane % kLanes * 8;
         const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(strip) + r * kPitch16 + c);
-        if (row0 + r < M && col0 + c < N) *reinterpret_cast<uint4*>(C16 + static_cast<long>(row0 + r) * ldc + col0 + c) = v;
+        if (row0 + r < M && col0 + c < N) *reinterpret_cast<uint4*>(C16 + static_cast<long>(row0 + r) * N + col0 + c) = v;
       }
     } else {
       constexpr int kLanes = W / 4;
@@ -433,27 +418,12 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   }
   static_for<MI>([&](auto ic) {                  // block rows of the wave
     constexpr int i = decltype(ic)::value;
-    int em[kScaled ? 16 : 1];                    // exponents of the lane's 16 rows (M % 8 == 0: four are inside or none)
-    if constexpr (kScaled) {
-#pragma unroll
-      for (int r = 0; r < 16; r += 4) {
-        const int m = mw + i * 32 + 8 * (r >> 2) + rq;
-        const int4 e = m < M ? *reinterpret_cast<const int4*>(a.exp_m + m) : make_int4(0, 0, 0, 0);
-        em[r] = e.x;
-        em[r + 1] = e.y;
-        em[r + 2] = e.z;
-        em[r + 3] = e.w;
-      }
-    }
     static_for<MI>([&](auto jc) {
       constexpr int jj = decltype(jc)::value;
-      const int en = kScaled && nw + jj * 32 + cl < N ? a.exp_n[nw + jj * 32 + cl] - 2 * kExpTop : 0;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = 8 * (r >> 2) + rq + (r & 3), col = jj * 32 + cl;
-        if constexpr (kScaled)
-          reinterpret_cast<uint16_t*>(strip)[row * kPitch16 + col] = T::from_f32(__builtin_ldexpf(acc[i][jj][r], em[r] + en));
-        else if (C16) reinterpret_cast<uint16_t*>(strip)[row * kPitch16 + col] = T::from_f32(value(acc[i][jj][r], i, jj, r));
+        if (C16) reinterpret_cast<uint16_t*>(strip)[row * kPitch16 + col] = T::from_f32(value(acc[i][jj][r], i, jj, r));
         else strip[row * kPitch32 + col] = value(acc[i][jj][r], i, jj, r);
       }
     });
@@ -476,209 +446,7 @@ __global__ __launch_bounds__(256) void split_terms_kernel(const float* __restric
   }
 }
 
-// ---- operands of the scaled form (BF16OnF16), up to two matrices (ScaleJob) per launch.  Columns: a wave takes 16 bytes a
-// lane of a row, so 512 (bf16) or 256 (fp32) columns, and every fourth row of the workgroup's kScaleRows; one launch finds
-// the exponents of every block of rows (a byte each), the next combines them and scales, reading the matrix again.  Rows:
-// a wave per row, in the second launch alone.  Memory-bound; a launch costs a small fold as much as its products, hence
-// both matrices in each and no counters or maxima that had to be cleared first.
-__device__ __forceinline__ unsigned finite_exponent(float f) {   // exponent field, 0 for infinities and NaN
-  const unsigned e = (__float_as_uint(f) >> 23) & 255u;
-  return e == 255u ? 0u : e;
-}
-
-// the V values of a 16-byte piece as floats; V bytes as one load
-template <typename E> struct Piece;
-template <> struct Piece<float> {
-  static constexpr int V = 4;
-  static __device__ __forceinline__ void unpack(const uint4& v, float (&f)[4]) {
-    f[0] = __uint_as_float(v.x);
-    f[1] = __uint_as_float(v.y);
-    f[2] = __uint_as_float(v.z);
-    f[3] = __uint_as_float(v.w);
-  }
-  static __device__ __forceinline__ uint2 bytes(const uint8_t* p) { return make_uint2(*reinterpret_cast<const uint32_t*>(p), 0u); }
-};
-template <> struct Piece<uint16_t> {
-  static constexpr int V = 8;
-  static __device__ __forceinline__ void unpack(const uint4& v, float (&f)[8]) { unpack8<BF16>(v, f); }
-  static __device__ __forceinline__ uint2 bytes(const uint8_t* p) { return *reinterpret_cast<const uint2*>(p); }
-};
-
-// Non-temporal: a panel and its copy are more than the memory-side cache holds (4096 x 28672 with its rotation, both panels: exponents
-// 76 -> 56 us, scaling 108 -> 107; panels of an eighth of the size, which it does hold, were slower in all).
-__device__ __forceinline__ uint4 load_piece(const void* p) {
-  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(static_cast<const u32x4*>(p)));
-}
-
-// NT f16 terms of V scaled values to dst[term * stride ..]
-template <int NT, int V>
-__device__ __forceinline__ void store_terms(const float (&f)[V], const int (&shift)[V], uint16_t* dst, long stride) {
-  float r[V];
-#pragma unroll
-  for (int k = 0; k < V; ++k) r[k] = __builtin_ldexpf(f[k], shift[k]);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    uint32_t out[V / 2];
-#pragma unroll
-    for (int k = 0; k < V; k += 2) {
-      const uint16_t lo = F16::from_f32(r[k]), hi = F16::from_f32(r[k + 1]);
-      r[k] -= F16::to_f32(lo);
-      r[k + 1] -= F16::to_f32(hi);
-      out[k / 2] = lo | static_cast<uint32_t>(hi) << 16;
-    }
-    if constexpr (V == 8) *reinterpret_cast<uint4*>(dst + t * stride) = make_uint4(out[0], out[1], out[2], out[3]);
-    else *reinterpret_cast<uint2*>(dst + t * stride) = make_uint2(out[0], out[1]);
-  }
-}
-
-// part[block of rows][c] = largest exponent field among the finite elements of column c in it
-template <typename E>
-__device__ __forceinline__ void column_exponents(const ScaleJob& j, int block, int* lds) {
-  constexpr int V = Piece<E>::V;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int by = block / j.blocks_x, c0 = (block - by * j.blocks_x) * 64 * V;
-  const int c = c0 + lane * V;                   // cols % 8 == 0: a piece is inside or outside
-  unsigned e[V];
-#pragma unroll
-  for (int k = 0; k < V; ++k) e[k] = 0;
-  if (c < j.cols) {
-    const E* src = static_cast<const E*>(j.src) + c;
-    const int r0 = by * kScaleRows + w, r1 = min(j.rows, (by + 1) * kScaleRows);
-    for (int r = r0; r < r1; r += 4 * 8) {
-      uint4 v[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = load_piece(src + min(r + 4 * q, r1 - 1) * j.pitch);   // a row twice: no matter
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        float f[V];
-        Piece<E>::unpack(v[q], f);
-#pragma unroll
-        for (int k = 0; k < V; ++k) e[k] = max(e[k], finite_exponent(f[k]));
-      }
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < V; ++k) lds[w * (64 * V) + lane * V + k] = static_cast<int>(e[k]);
-  __syncthreads();
-  for (int i = threadIdx.x; i < 64 * V && c0 + i < j.cols; i += 256)
-    j.part[static_cast<long>(by) * j.cols + c0 + i] =
-        static_cast<uint8_t>(max(max(lds[i], lds[64 * V + i]), max(lds[128 * V + i], lds[192 * V + i])));
-}
-
-// dst[t][r][c], t < NT: the f16 terms of src[r][c] * 2^(kExpTop - exps[c]); the first block of rows stores exps
-template <typename E, int NT>
-__device__ __forceinline__ void scale_columns(const ScaleJob& j, int block, int* lds) {
-  constexpr int V = Piece<E>::V;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int by = block / j.blocks_x, c = (block - by * j.blocks_x) * 64 * V + lane * V;
-  const bool inside = c < j.cols;
-  unsigned e[V];
-#pragma unroll
-  for (int k = 0; k < V; ++k) e[k] = 0;
-  if (inside) {
-    const int parts = (j.rows + kScaleRows - 1) / kScaleRows;
-    for (int p = w; p < parts; p += 4 * 4) {
-      uint2 b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) b[q] = Piece<E>::bytes(j.part + static_cast<long>(min(p + 4 * q, parts - 1)) * j.cols + c);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int k = 0; k < V; ++k) e[k] = max(e[k], ((k < 4 ? b[q].x : b[q].y) >> (8 * (k & 3))) & 255u);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < V; ++k) lds[w * (64 * V) + lane * V + k] = static_cast<int>(e[k]);
-  __syncthreads();
-  if (!inside) return;
-  int shift[V];
-#pragma unroll
-  for (int k = 0; k < V; ++k) {
-    const int i = lane * V + k;
-    const int m = max(max(lds[i], lds[64 * V + i]), max(lds[128 * V + i], lds[192 * V + i]));
-    if (by == 0 && w == 0) j.exps[c + k] = m;
-    shift[k] = kExpTop - m;
-  }
-  const E* src = static_cast<const E*>(j.src) + c;
-  const int r0 = by * kScaleRows + w, r1 = min(j.rows, (by + 1) * kScaleRows);
-  for (int r = r0; r < r1; r += 4 * 4) {
-    uint4 v[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = load_piece(src + min(r + 4 * q, r1 - 1) * j.pitch);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (r + 4 * q >= r1) break;                // uniform over the wave
-      float f[V];
-      Piece<E>::unpack(v[q], f);
-      store_terms<NT>(f, shift, j.dst + static_cast<long>(r + 4 * q) * j.cols + c, static_cast<long>(j.rows) * j.cols);
-    }
-  }
-}
-
-// one f16 term of every row of a bf16 matrix, scaled by row (read twice, the second time from the caches)
-__device__ __forceinline__ void scale_row(const ScaleJob& j, int r) {
-  const int lane = threadIdx.x & 63;
-  if (r >= j.rows) return;
-  const uint16_t* row = static_cast<const uint16_t*>(j.src) + r * j.pitch;
-  unsigned e = 0;
-  for (int c = lane * 8; c < j.cols; c += 512) {
-    float f[8];
-    unpack8<BF16>(*reinterpret_cast<const uint4*>(row + c), f);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) e = max(e, finite_exponent(f[k]));
-  }
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) e = max(e, static_cast<unsigned>(__shfl_xor(static_cast<int>(e), d, kWave)));
-  if (lane == 0) j.exps[r] = static_cast<int>(e);
-  int shift[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) shift[k] = kExpTop - static_cast<int>(e);
-  for (int c = lane * 8; c < j.cols; c += 512) {
-    float f[8];
-    unpack8<BF16>(*reinterpret_cast<const uint4*>(row + c), f);
-    store_terms<1>(f, shift, j.dst + static_cast<long>(r) * j.cols + c, 0);
-  }
-}
-
-struct ScaleJobs { ScaleJob j[2]; int blocks[2]; };   // workgroups of each, 0: none
-
-__global__ __launch_bounds__(256) void column_exponents_kernel(ScaleJobs a) {
-  __shared__ int lds[4 * 512];
-  const bool second = static_cast<int>(blockIdx.x) >= a.blocks[0];
-  const ScaleJob& j = second ? a.j[1] : a.j[0];
-  const int block = static_cast<int>(blockIdx.x) - (second ? a.blocks[0] : 0);
-  if (j.kind == kRotationColumns) column_exponents<float>(j, block, lds);
-  else column_exponents<uint16_t>(j, block, lds);
-}
-
-__global__ __launch_bounds__(256) void scale_kernel(ScaleJobs a) {
-  __shared__ int lds[4 * 512];
-  const bool second = static_cast<int>(blockIdx.x) >= a.blocks[0];
-  const ScaleJob& j = second ? a.j[1] : a.j[0];
-  const int block = static_cast<int>(blockIdx.x) - (second ? a.blocks[0] : 0);
-  if (j.kind == kRotationColumns) scale_columns<float, 2>(j, block, lds);
-  else if (j.kind == kWeightColumns) scale_columns<uint16_t, 1>(j, block, lds);
-  else scale_row(j, block * 4 + static_cast<int>(threadIdx.x >> 6));
-}
-
 }  // namespace
-
-hipError_t launch_scale(const ScaleJob* jobs, int n, hipStream_t s) {
-  ScaleJobs find{}, scale{};
-  for (int i = 0; i < n; ++i) {
-    ScaleJob j = jobs[i];
-    const int width = j.kind == kRotationColumns ? 256 : 512;
-    j.blocks_x = (j.cols + width - 1) / width;
-    find.j[i] = scale.j[i] = j;
-    const int blocks = j.blocks_x * ((j.rows + kScaleRows - 1) / kScaleRows);
-    find.blocks[i] = j.kind == kWeightRows ? 0 : blocks;
-    scale.blocks[i] = j.kind == kWeightRows ? (j.rows + 3) / 4 : blocks;
-  }
-  if (const int g = find.blocks[0] + find.blocks[1]; g > 0)
-    hipLaunchKernelGGL(column_exponents_kernel, dim3(g), dim3(256), 0, s, find);
-  hipLaunchKernelGGL(scale_kernel, dim3(scale.blocks[0] + scale.blocks[1]), dim3(256), 0, s, scale);
-  return hipGetLastError();
-}
 
 int contraction_terms(bool bf16) { return bf16 ? 3 : 2; }
 
@@ -756,7 +524,6 @@ hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_contraction(ContractionArgs a, bool a_kmajor, bool bf16, hipStream_t s) {
-  if (a.exp_m) return a_kmajor ? launch_shape<BF16OnF16, true>(a, s) : launch_shape<BF16OnF16, false>(a, s);
   if (bf16) return a_kmajor ? launch_shape<BF16, true>(a, s) : launch_shape<BF16, false>(a, s);
   return a_kmajor ? launch_shape<F16, true>(a, s) : launch_shape<F16, false>(a, s);
 }

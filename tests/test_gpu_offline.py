@@ -370,10 +370,10 @@ def _spread(rng, lines, lo, hi):
 
 @pytest.mark.parametrize("tile", [1, 2])
 @pytest.mark.parametrize("d,other", [(8, 8), (264, 520), (520, 136)])
-def test_bf16_contractions_hold_any_exponents(gpu_device, tile, d, other):
-    """bf16 folds and adapters hold their operands as f16 scaled line by line (a forced tile takes small sizes there too):
-    lines whose magnitudes lie up to 2^120 apart, elements of a line up to 2^60 apart, a line of zeros, one of bf16
-    subnormals, infinities and NaN.  The bounds are those of the other tests here; they scale with each line's norm."""
+def test_bf16_contractions_over_wide_exponents(gpu_device, tile, d, other):
+    """bf16 folds and adapters whose lines' magnitudes lie up to 2^120 apart, elements of a line up to 2^60 apart, with a line of zeros,
+    one of bf16 subnormals, infinities and NaN.  The bounds are those of the other tests here; they scale with each line's norm, so
+    they say nothing of an entry that is small beside its line (the test of single products below does)."""
     from paper_2507_01299_amd import api
     rng = np.random.default_rng(d + other)
     print(f"bf16 exponents tile={tile} d={d} other={other}", flush=True)
@@ -417,11 +417,11 @@ def test_bf16_contractions_hold_any_exponents(gpu_device, tile, d, other):
 
 
 @pytest.mark.parametrize("d,other", [(2048, 8192 + 264), (2056, 7168 + 8)])
-def test_bf16_folds_in_panels(gpu_device, d, other):
-    """More columns (rows) than the workspace holds scaled copies of: panels of 7936 and 520 lines, 7168 and 8."""
+def test_wide_bf16_folds(gpu_device, d, other):
+    """Wide bf16 folds: drawn columns (rows), those around the border of two tiles and those at the end."""
     from paper_2507_01299_amd import api
     rng = np.random.default_rng(d)
-    print(f"bf16 panels d={d} other={other}", flush=True)
+    print(f"wide bf16 folds d={d} other={other}", flush=True)
     Q = _rotation32(d, 3)
     wb = O.encode16(synth.gaussian_weight(d, other, 5), "bf16")
     Qd, sc = torch.from_numpy(Q).cuda(), api.OfflineScratch(d, "bf16")
@@ -438,3 +438,62 @@ def test_bf16_folds_in_panels(gpu_device, d, other):
     at = torch.from_numpy(cols).cuda()
     _check_stored(to_bits(out[:, at].contiguous()), want, "bf16", "Q^T W", wn[None, :])
     _check_stored(to_bits(outT[at].contiguous()).T, want, "bf16", "W Q", wn[None, :])
+
+
+def _full_spread(rng, shape, lo):
+    """fp32 values of either sign with 24-bit mantissas and exponents from lo to 0, every line with one of magnitude 1 or more."""
+    v = (rng.uniform(1.0, 2.0, shape) * 2.0 ** rng.integers(lo, 1, shape) * rng.choice([-1.0, 1.0], shape)).astype(np.float32)
+    v[rng.integers(0, shape[0], shape[1]), np.arange(shape[1])] = np.float32(1.0 + 2.0 ** -23)
+    return v
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("d,other", [(8, 8), (264, 520), (2048, 256)])
+def test_bf16_contractions_hold_every_entry(gpu_device, tile, d, other):
+    """Results that are one product each show how an operand's entry is held, whatever its size beside the others of its line:
+    a line of the weight (or of one rotation) with one nonzero entry picks single entries of the rotation, a rotation with one
+    nonzero entry a line picks single entries of the weight.  The entries picked lie up to 2^60 below their line's largest.  A power of two times a
+    bf16 value is that value's bits; an fp32 entry times a power of two is its bf16 rounding; a product of two fp32 entries is off by the
+    fp32 additions of its terms (2^-22 of itself, 6 additions of 2^-25 and what lies below the last terms), then rounded once (2^-8, half a unit of bf16 at 1)."""
+    from paper_2507_01299_amd import api
+    rng = np.random.default_rng(1000 * d + other)
+    print(f"bf16 single products tile={tile} d={d} other={other}", flush=True)
+    sc = api.OfflineScratch(d, "bf16")
+    cols = np.arange(other)
+    api.set_tuning(10, tile)
+    try:
+        def folds(Q, wb):
+            Qd = torch.from_numpy(np.ascontiguousarray(Q)).cuda()
+            a = torch.full((d, other), 9.0, dtype=torch.bfloat16, device="cuda:0")
+            b = torch.full((other, d), 9.0, dtype=torch.bfloat16, device="cuda:0")
+            api.fold_input(Qd, to_dev(wb, "bf16"), a, "bf16", sc)
+            api.fold_output(to_dev(np.ascontiguousarray(wb.T), "bf16"), Qd, b, "bf16", sc)
+            return to_bits(a), to_bits(b).T
+
+        # single entries of the rotation
+        Q = _full_spread(rng, (d, d), -60)
+        pick = rng.integers(0, d, other)
+        wb = np.zeros((d, other), dtype=np.uint16)
+        wb[pick, cols] = O.encode16(2.0 ** rng.integers(-8, 9, other), "bf16")
+        want = O.encode16(Q[pick].astype(np.float64).T * O.decode16(wb[pick, cols], "bf16")[None, :], "bf16")
+        for what, got in zip(("Q^T W", "W Q"), folds(Q, wb)):
+            assert np.array_equal(got, want), (what, int((got != want).sum()))
+        # single entries of the weight: a signed permutation times powers of two
+        perm = rng.permutation(d)
+        P = np.zeros((d, d), dtype=np.float32)
+        P[perm, np.arange(d)] = 2.0 ** rng.integers(-8, 9, d) * rng.choice([-1.0, 1.0], d)
+        wb = O.encode16(_full_spread(rng, (d, other), -60).astype(np.float64), "bf16")
+        want = O.encode16(P[perm, np.arange(d)].astype(np.float64)[:, None] * O.decode16(wb[perm], "bf16"), "bf16")
+        for what, got in zip(("Q^T W", "W Q"), folds(P, wb)):
+            assert np.array_equal(got, want), (what, int((got != want).sum()))
+        # adapters, either rotation picking single entries of the other
+        S = np.zeros((d, d), dtype=np.float32)
+        S[perm, np.arange(d)] = _full_spread(rng, (1, d), 0)[0] * 2.0 ** rng.integers(-8, 9, d).astype(np.float32)
+        s = S[perm, np.arange(d)].astype(np.float64)
+        for Ql, Qn, want in ((S, Q, s[:, None] * Q[perm].astype(np.float64)), (Q, S, Q[perm].astype(np.float64).T * s[None, :])):
+            out = torch.full((d, d), 9.0, dtype=torch.bfloat16, device="cuda:0")
+            api.residual_adapter(torch.from_numpy(Ql).cuda(), torch.from_numpy(Qn).cuda(), out, "bf16", sc)
+            err = np.abs(O.decode16(to_bits(out), "bf16") - want)
+            assert np.all(err <= (2.0 ** -8 + 2.0 ** -22) * np.abs(want)), float((err / np.abs(want)).max())
+    finally:
+        api.set_tuning(10, 0)
