@@ -1,4 +1,4 @@
-// Stand-alone Top-K sparsifier kernel (Sec. 4.3, Eq. 8): one workgroup of 1024 lanes per token;
+// Stand-alone Top-K sparsifier kernel (Sec. 4.3, Eq. 8): one workgroup of 2, 8 or 16 waves per token;
 // the selection itself is in topk_core.hpp.
 #include <type_traits>
 
@@ -19,9 +19,10 @@ template <int NW> constexpr int kTopkKernelCopies = NW % 4 == 0 ? kTopkCopiesWid
 // Where the selected vector comes from (batched decoder layer): the plain vector, the context-length-1
 // attention output read straight from q|k|v (value head of the query head's group), or
 // R(SiLU(gate) * up) computed from gate|up.  The vector itself can be written out as well.
+// VALS: the kept values are written beside the index list.
 // RUN: the sum of squares of kSrcNorm is formed from the squares of runs of RUN elements, 64 runs by halves, the sums of
 // 64 runs one after the other -- whatever NW is, so that the choice of NW changes no bit.
-template <typename T, int NW, int E, int RUN>
+template <typename T, int NW, int E, int RUN, bool VALS>
 __global__ __launch_bounds__(NW * 64) void topk_kernel(const uint16_t* __restrict__ h, int d, int K,
                                                        int32_t* __restrict__ idx,
                                                        uint16_t* __restrict__ vals,
@@ -154,28 +155,23 @@ __global__ __launch_bounds__(NW * 64) void topk_kernel(const uint16_t* __restric
   LAROSA_STAMP(2);
 
   // The index list goes through LDS, so that memory sees whole lines: written from the lanes that hold the elements, a wave's
-// stores touch a line per lane or two (14336 wide, 8601 kept: whole kernel 8.2 -> 7.1 us, 28672: 15.5 -> 11.5).  Not kept: to a slot that nobody reads.
+  // stores touch a line per lane or two (14336 wide, 8601 kept: whole kernel 8.4 -> 7.0 us, 28672: 16.2 -> 11.3).  Values (VALS) are stored
+  // from the lanes in the same loop, ahead of the barrier, and a kernel without them holds no code for them (in a loop of their own
+  // after the list they cost 4104 wide 5.1 -> 5.4 us, now 4.95; 28672 21.9 -> 17.0, now 14.3).
   if (idx) {
-    constexpr int kList = NW * 64 * E;
-    __shared__ uint16_t list[kList + 64];
+    __shared__ uint16_t list[NW * 64 * E];
+    uint16_t* valb = VALS ? vals + static_cast<size_t>(b) * K : nullptr;
     unsigned pos = st.first;
 #pragma unroll
     for (int q = 0; q < E; ++q) {
-      const unsigned is = kept_bit(st, q);
-      list[is ? pos : static_cast<unsigned>(kList + (threadIdx.x & 63))] = static_cast<uint16_t>(base + q);
-      pos += is;
+      if (kept_bit(st, q)) {
+        if constexpr (VALS) valb[pos] = static_cast<uint16_t>(raw[q >> 1] >> (16 * (q & 1)));
+        list[pos++] = static_cast<uint16_t>(base + q);
+      }
     }
     __syncthreads();
     int32_t* idxb = idx + static_cast<size_t>(b) * K;
     for (int i = threadIdx.x; i < K; i += NW * 64) idxb[i] = list[i];
-  }
-  if (vals) {
-    uint16_t* valb = vals + static_cast<size_t>(b) * K;
-    unsigned pos = st.first;
-#pragma unroll
-    for (int q = 0; q < E; ++q) {
-      if (kept_bit(st, q)) valb[pos++] = static_cast<uint16_t>(raw[q >> 1] >> (16 * (q & 1)));
-    }
   }
   LAROSA_STAMP(3);
   if (masked) {
@@ -275,8 +271,14 @@ hipError_t launch_topk_t(const uint16_t* h, int B, int d, int K, int32_t* idx, u
   sc.head_magic = quotient_magic(sc.head_dim);
   sc.group_magic = quotient_magic(sc.group);
   auto launch = [&](auto nw, auto e, auto run) {
-    hipLaunchKernelGGL((topk_kernel<T, decltype(nw)::value, decltype(e)::value, decltype(run)::value>), dim3(B), dim3(64 * decltype(nw)::value),
-                       0, s, h, d, K, idx, vals, masked, sc);
+    constexpr int NW = decltype(nw)::value, E = decltype(e)::value, RUN = decltype(run)::value;
+    if constexpr (std::is_same_v<T, F16>) {      // (values are asked for through launch_topk alone, with the index list)
+      if (vals) {
+        hipLaunchKernelGGL((topk_kernel<T, NW, E, RUN, true>), dim3(B), dim3(64 * NW), 0, s, h, d, K, idx, vals, masked, sc);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((topk_kernel<T, NW, E, RUN, false>), dim3(B), dim3(64 * NW), 0, s, h, d, K, idx, nullptr, masked, sc);
     return hipGetLastError();
   };
 #define LAROSA_TOPK(NW, E, RUN) launch(std::integral_constant<int, NW>{}, std::integral_constant<int, E>{}, std::integral_constant<int, RUN>{})

@@ -89,6 +89,10 @@ def test_topk_where_its_workgroup_changes(api, dtype, d):
             want = O.topk_indices(hb[b], K)
             assert np.array_equal(idx.cpu().numpy()[b], want), (K, b)
             assert np.array_equal(to_bits(vals)[b], hb[b][want]), (K, b)
+        alone = torch.full((2, K), -1, dtype=torch.int32, device="cuda:0")   # a kernel of its own
+        api.topk(to_dev(hb, dtype), K, alone, dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(alone, idx), K
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
