@@ -511,9 +511,10 @@ hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
     // a fold's two term pairs: the rotation's first and second term with the weight
     bool two = a.npairs == 2 && (A_KMAJOR ? a.pa[0] == 0 && a.pa[1] == 1 && a.pb[0] == 0 && a.pb[1] == 0
                                           : a.pb[0] == 0 && a.pb[1] == 1 && a.pa[0] == 0 && a.pa[1] == 0);
-    hipError_t e;
     if constexpr (std::is_same_v<T, BF16>) two = false;   // (bf16 terms come in threes)
-    else if (two) e = launch_tiles<T, A_KMAJOR, 4, true>(a, 0, big, s);
+    hipError_t e = hipSuccess;
+    if constexpr (std::is_same_v<T, F16>)
+      if (two) e = launch_tiles<T, A_KMAJOR, 4, true>(a, 0, big, s);
     if (!two) e = launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s);
     if (e != hipSuccess) return e;
   }
