@@ -404,6 +404,9 @@ __global__ __launch_bounds__(RW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
   LAROSA_STAMP(6);
 }
 
+// Elements per lane in steps of the width.  The widest (64, inputs above 24576) does not fit 128 registers beside two workgroups
+// per compute unit and spills 50 of them: the o, gate|up and down launches behind an attention 28672 wide take 48.5 us, 67.7
+// before the keys were paired (f16; bf16 50.9, 54.8); 40.4 with an attention 24576 wide, which spills none.
 template <typename T, int RW>
 hipError_t launch_nv(const FusedArgs& a, hipStream_t st) {
   dim3 grid(a.g.G + a.side_G, a.g.B), block(RW * 64);

@@ -7,7 +7,8 @@
 //    operand reads from LDS feed sixteen instructions, two thirds of the LDS traffic per flop of the 128 x 64 quarters that
 //    eight waves would own.
 //  * Global loads go straight into LDS (16 bytes per lane, no staging registers) and run three 32-deep k-tiles ahead of
-//    the products: four stages of 32 KiB (the smallest tile: eight of 8 KiB, seven ahead), one barrier per k-tile, and the
+//    the products: four stages of 32 KiB (the smallest tile: eight of 8 KiB, seven ahead; both terms of an f16 fold together: three of
+//    48 KiB, two ahead), one barrier per k-tile, and the
 //    loads, the LDS reads and the products of a k-tile are issued in one fixed interleaved order.
 //  * Operands are stored k-major ([k][m], the layout of X, Q and W), the instruction wants 8 values along k per lane.
 //    The LDS tile keeps the memory's layout and the transposing LDS read does the rest: 16 lanes point at 4 rows x 16
@@ -25,10 +26,10 @@
 //    parts in a second launch when that is shorter than another round (launch_shape).
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
 // random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace): 4096 x
-// 28672 x 4096 bf16, 3 terms, 1.29 - 1.33 PFLOP/s; f16 folds of a 4096-wide layer 1.23 - 1.25, its adapter 1.24;
+// 28672 x 4096 bf16, 3 terms, 1.29 - 1.33 PFLOP/s; f16 folds of a 4096-wide layer 1.22 - 1.31, its adapter 1.23;
 // second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 321 + 36 us = 1.04 (36 for the 16 tiles after
 // the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
-// 64 - 73 % of the cycles; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
+// 69 - 79 % of the cycles in f16 folds, 64 - 73 % with a pass per term pair; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
 // staging registers, two LDS stages) kept them busy 34 % and gave the XCDs of a symmetric product uneven shares.
 #include <type_traits>
 

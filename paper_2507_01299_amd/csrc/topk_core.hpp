@@ -18,7 +18,7 @@
 //   3. a wave-level prefix sum of the ">T" and "==T" counts then gives every lane the number of kept
 //      elements before its own, so an index-ordered compaction keeps every key > T and the first
 //      r keys == T: ascending indices and the lower-index tie rule with no sort.
-// Three barriers in all (after the one that makes the cleared histograms and the vector visible).
+// Three barriers in all, four with kTopkCopiesWide (after the one that makes the cleared histograms and the vector visible).
 //
 // What bounds it: the instructions each wave executes one after the other (about 3 ns each with two waves per SIMD, whatever
 // they are), not LDS or memory.  So the keys are worked on in pairs, two to a register (packed 16-bit subtractions; the keys
