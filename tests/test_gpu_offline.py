@@ -497,3 +497,25 @@ def test_bf16_contractions_hold_every_entry(gpu_device, tile, d, other):
             assert np.all(err <= (2.0 ** -8 + 2.0 ** -22) * np.abs(want)), float((err / np.abs(want)).max())
     finally:
         api.set_tuning(10, 0)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_workspace_size_changes_no_bit(gpu_device, dtype):
+    """The same folds and adapter with the workspace made for them and with one made for a wider rotation (a program that keeps
+    one for a whole model)."""
+    from paper_2507_01299_amd import api
+    d, other = 1280, 5504
+    print(f"workspace sizes dtype={dtype} d={d} other={other}", flush=True)
+    Q, Qn = (torch.from_numpy(_rotation32(d, seed)).cuda() for seed in (3, 5))
+    W = to_dev(O.encode16(synth.gaussian_weight(d, other, 7), dtype), dtype)
+    Wt = W.t().contiguous()
+    outs = []
+    for width in (d, 4096):
+        sc = api.OfflineScratch(width, dtype)
+        a, b, c = torch.empty_like(W), torch.empty_like(Wt), torch.empty(d, d, dtype=W.dtype, device="cuda:0")
+        api.fold_input(Q, W, a, dtype, sc)
+        api.fold_output(Wt, Q, b, dtype, sc)
+        api.residual_adapter(Q, Qn, c, dtype, sc)
+        outs.append([to_bits(x) for x in (a, b, c)])
+    for what, x, y in zip(("Q^T W", "W Q", "Q_l^T Q_next"), *outs):
+        assert np.array_equal(x, y), (what, int((x != y).sum()))
