@@ -7,8 +7,7 @@
 //    operand reads from LDS feed sixteen instructions, two thirds of the LDS traffic per flop of the 128 x 64 quarters that
 //    eight waves would own.
 //  * Global loads go straight into LDS (16 bytes per lane, no staging registers) and run three 32-deep k-tiles ahead of
-//    the products: four stages of 32 KiB (the smallest tile: eight of 8 KiB, seven ahead; both terms of an f16 fold together: three of
-//    48 KiB, two ahead), one barrier per k-tile, and the
+//    the products: four stages of 32 KiB (both terms of an f16 fold together: three of 48 KiB, two ahead), one barrier per k-tile, and the
 //    loads, the LDS reads and the products of a k-tile are issued in one fixed interleaved order.
 //  * Operands are stored k-major ([k][m], the layout of X, Q and W), the instruction wants 8 values along k per lane.
 //    The LDS tile keeps the memory's layout and the transposing LDS read does the rest: 16 lanes point at 4 rows x 16
@@ -432,9 +431,195 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   });
 }
 
+// Few tiles: a workgroup owns a 64 x 64 tile, and its four waves share the k-tiles instead of the tile.  What bounds such
+// products is not the matrix cores but each wave's chain over k, so a wave takes every fourth k-tile through a ring of its own
+// in LDS, with no barrier until the four sums meet, and multiplies the whole 64 x 64 (with a 32 x 32 quarter per wave and a
+// barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 28).
+// Whole calls, us, quarters / shared k-tiles: second moment 5000 x 1024 f16 29.0 / 22.6, 2048 x 1024 (64 k-tiles) 14.8 / 12.6, fold
+// 4096 x 512 bf16 140.4 / 125, 2048 x 512 f16 32.3 / 26.0, adapter 512 bf16 (96) 23.0 / 20.8.  Short chains gain nothing from
+// it and pay for the four sums: second moment 512 x 512 (16 k-tiles) 6.9 / 7.1; so from 64 k-tiles on.
+constexpr int kSharedChain = 64;   // k-tiles of all term pairs from which the four waves share them
+constexpr int kSmallSide = 64;
+constexpr int kSmallStages = 4;    // k-tiles in a wave's ring
+constexpr int kSmallOperand = kSmallSide * kKTile * 2, kSmallStage = 2 * kSmallOperand, kSmallRing = kSmallStages * kSmallStage;
+constexpr int kSmallPitch = kSmallSide + 4;    // floats per row of a wave's sums
+
+template <typename T, bool A_KMAJOR>
+__global__ __launch_bounds__(256, 1) void small_contraction_kernel(ContractionArgs a) {
+  constexpr int kParts = kBigTile / kSmallSide;
+  constexpr int kLoads = kSmallStage / 1024;     // of a wave per k-tile
+  __shared__ __attribute__((aligned(1024))) char lds[4 * kSmallRing];
+  static_assert(4 * kSmallSide * kSmallPitch * 4 <= static_cast<int>(sizeof(lds)), "the sums reuse the rings");
+
+  const int per_xcd = (a.tiles + 7) >> 3;
+  const int local = static_cast<int>(blockIdx.x & 7) * per_xcd + static_cast<int>(blockIdx.x >> 3);
+  if (local >= a.tiles) return;
+  const TileAt at = tile_of(a.tile0 + local / (kParts * kParts), a.tiles_m, a.tiles_n, a.symmetric != 0);
+  const int part = local % (kParts * kParts);
+  const int m0 = at.m * kBigTile + part / kParts * kSmallSide, n0 = at.n * kBigTile + part % kParts * kSmallSide;
+  const int M = a.M, N = a.N, Kd = a.Kd;
+  if (m0 >= M || n0 >= N) return;                // a part of an edge tile that holds nothing (uniform)
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // ---- loads: wave-load q fills pieces 64 q .. + 63 of the operand's tile.  A k-major row is 128 bytes, two granules, which
+  // every second pair of rows exchanges: the four rows that half a wave's transposing read touches lie in different banks.
+  const u32x4 bufA = operand_buffer(a.A, a.a_elements);
+  const u32x4 bufB = operand_buffer(a.B, a.b_elements);
+  auto swap_of = [](int k) __attribute__((always_inline)) { return (k >> 1) & 1; };
+  uint32_t offA[4], offB[4];
+  int kA[4], kB[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = 8 * q + lane / 8, col = 8 * ((lane % 8) ^ (4 * swap_of(row)));
+    kB[q] = row;
+    offB[q] = n0 + col < N ? static_cast<uint32_t>((row * N + n0 + col) * 2) : kOutside;
+    if (A_KMAJOR) {
+      kA[q] = row;
+      offA[q] = m0 + col < M ? static_cast<uint32_t>((row * M + m0 + col) * 2) : kOutside;
+    } else {
+      // [row m][32 k values], pieces exchanged as in the large tiles
+      const int m = q * 16 + (lane >> 2);
+      kA[q] = 8 * ((lane & 3) ^ ((m >> 2) & 3));
+      offA[q] = m0 + m < M ? static_cast<uint32_t>(((m0 + m) * Kd + kA[q]) * 2) : kOutside;
+    }
+  }
+  const uint32_t ring = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)lds)) + w * kSmallRing;
+  const uint32_t stepA = static_cast<uint32_t>((A_KMAJOR ? kKTile * M : kKTile) * 2), stepB = static_cast<uint32_t>(kKTile * N * 2);
+  const int ktiles = (Kd + kKTile - 1) / kKTile;
+  const int iters = ktiles * a.npairs;           // k-tiles of all term pairs, one pass after the other
+  int f_pair = 0, f_tile = w, f_stage = 0;       // the k-tile to load next, the stage it goes to
+  auto fetch = [&]() __attribute__((always_inline)) {
+    while (f_tile >= ktiles && f_pair < a.npairs) { f_tile -= ktiles; ++f_pair; }   // (uniform)
+    const bool any = f_pair < a.npairs;          // past the last: zeros, so that every step waits for the same count
+    const int left = any ? Kd - f_tile * kKTile : 0;
+    const uint32_t ta = any ? static_cast<uint32_t>(a.pa[f_pair] * a.a_term_stride * 2) + f_tile * stepA : 0u;
+    const uint32_t tb = any ? static_cast<uint32_t>(a.pb[f_pair] * a.b_term_stride * 2) + f_tile * stepB : 0u;
+    const uint32_t to = ring + f_stage * kSmallStage;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) load_to_lds(bufA, to + q * 1024, (kA[q] < left ? offA[q] : kOutside) + ta);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) load_to_lds(bufB, to + kSmallOperand + q * 1024, (kB[q] < left ? offB[q] : kOutside) + tb);
+    f_tile += 4;
+    f_stage = (f_stage + 1) & (kSmallStages - 1);
+  };
+
+  // ---- operand reads, as in the large tiles with two granules per row
+  const int g = lane >> 4, j = lane & 15;
+  const int rowk = 8 * (g >> 1) + (j >> 2);
+  const int inrow = rowk * (kSmallSide * 2) + 32 * (g & 1) + 8 * (j & 3), swap = 64 * swap_of(rowk);
+  const lds_char* const mine = (const lds_char*)lds + w * kSmallRing;
+  auto read_k = [&](const lds_char* p) __attribute__((always_inline)) {
+    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)p));
+    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(p + 4 * kSmallSide * 2)));
+    return u32x4{lo.x, lo.y, hi.x, hi.y};
+  };
+  struct Operands { u32x4 a[2][2], b[2][2]; };   // [16-deep slice][32 rows or columns]
+  auto read = [&](Operands& o, int stage) __attribute__((always_inline)) {
+    const lds_char* p = mine + stage * kSmallStage;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int at16 = inrow + ((i * 64) ^ swap) + s * (16 * kSmallSide * 2);
+        o.b[s][i] = read_k(p + kSmallOperand + at16);
+        if constexpr (A_KMAJOR) o.a[s][i] = read_k(p + at16);
+        else o.a[s][i] = *(const __attribute__((address_space(3))) u32x4*)(p + (((i * 32 + (lane & 31)) * 64 + (((lane >> 5) ^ ((lane >> 2) & 3)) * 16)) ^ (32 * s)));
+      }
+  };
+  float16v acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][jj][r] = 0.0f;
+  auto multiply = [&](const Operands& o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) acc[i][jj] = Mfma<T>::run(o.a[s][i], o.b[s][jj], acc[i][jj]);
+  };
+
+  // ---- the operands of the wave's next k-tile are read while one is multiplied
+  Operands o0, o1;
+  for (int i = 0; i < kSmallStages; ++i) fetch();
+  int stage = 0;
+  auto step = [&](Operands& now, Operands& next) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // `now` is in registers: its stage takes the next loads
+    fetch();
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kSmallStages - 1) * kLoads) : "memory");   // the next k-tile has landed
+    stage = (stage + 1) & (kSmallStages - 1);
+    read(next, stage);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(now);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kSmallStages - 1) * kLoads) : "memory");
+  read(o0, 0);
+  for (int t = w; t < iters; t += 8) {           // two of the wave's k-tiles at a time (past the last: zeros)
+    step(o0, o1);
+    step(o1, o0);
+  }
+  // every load has landed and every wave has left its ring: the LDS is free for the sums
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+  // ---- the four waves' sums, in wave order.  Accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column
+  // l % 32 of its 32 x 32 block.
+  float* const sums = reinterpret_cast<float*>(lds);
+  constexpr int kCopy = kSmallSide * kSmallPitch;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        sums[w * kCopy + (i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kSmallPitch + jj * 32 + (lane & 31)] = acc[i][jj][r];
+  __syncthreads();
+  const bool mirror = a.symmetric != 0 && at.m != at.n;
+  const int tr = tid >> 4, tc = tid & 15;        // the thread's pieces: rows tr + 16 p, columns 4 tc .. + 3
+  auto store4 = [&](int row, int col, const float (&v)[4]) __attribute__((always_inline)) {
+    const long at4 = static_cast<long>(row) * N + col;
+    if (a.C16) *reinterpret_cast<uint2*>(a.C16 + at4) = pack4<T>(v);
+    else *reinterpret_cast<float4*>(a.C32 + at4) = make_float4(v[0], v[1], v[2], v[3]);
+  };
+  float v[4][4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int r = tr + 16 * p, row = m0 + r, col = n0 + 4 * tc;
+    float* const q = sums + r * kSmallPitch + 4 * tc;
+    float4 c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = *reinterpret_cast<const float4*>(q + k * kCopy);
+    const bool in = row < M && col < N;          // (N % 4 == 0: the four are inside together)
+    float4 old = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (a.accumulate != 0 && a.C32 && in) old = *reinterpret_cast<const float4*>(a.C32 + static_cast<long>(row) * N + col);
+    v[p][0] = old.x + (c[0].x + c[1].x + c[2].x + c[3].x) * a.post_scale;
+    v[p][1] = old.y + (c[0].y + c[1].y + c[2].y + c[3].y) * a.post_scale;
+    v[p][2] = old.z + (c[0].z + c[1].z + c[2].z + c[3].z) * a.post_scale;
+    v[p][3] = old.w + (c[0].w + c[1].w + c[2].w + c[3].w) * a.post_scale;
+    if (mirror) *reinterpret_cast<float4*>(q) = make_float4(v[p][0], v[p][1], v[p][2], v[p][3]);
+    if (in) store4(row, col, v[p]);
+  }
+  if (mirror) {                                  // uniform; below the diagonal: the transposed tile
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int c = tr + 16 * p;                 // column of the tile, row of the transposed one
+      float t[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = sums[(4 * tc + e) * kSmallPitch + c];
+      if (n0 + c < N && m0 + 4 * tc < M) store4(n0 + c, m0 + 4 * tc, t);
+    }
+  }
+}
+
 // fp32 -> NT 16-bit terms with x * pre_scale = t0 + t1 (+ t2) up to the last term's rounding.  HBM-bound, 4 bytes in and 2 NT
 // out per entry: eight entries a lane, so that every access moves 16 bytes (n is a multiple of 64; with one entry a lane 4096 x
-// 4096 in three terms took 49.8 us, 3.4 TB/s, now about 21).
+// 4096 in three terms took 49.8 us, 3.4 TB/s, now 28.8).
 template <typename T, int NT>
 __global__ __launch_bounds__(256) void split_terms_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long n,
                                                           float pre_scale) {
@@ -478,7 +663,9 @@ hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s
   if (grid > 0x7FFFFFFFL) return hipErrorInvalidValue;
   a.tile0 = static_cast<int>(first);
   a.tiles = static_cast<int>(parts);
-  hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TWO>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+  const bool shared = MI == 1 && (a.Kd + kKTile - 1) / kKTile * a.npairs >= kSharedChain;
+  if (shared) hipLaunchKernelGGL((small_contraction_kernel<T, A_KMAJOR>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TWO>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

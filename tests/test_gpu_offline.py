@@ -142,6 +142,38 @@ def test_residual_adapter_matches_oracle(api, dtype, d):
     assert np.abs(eye - np.eye(d)).max() <= 1e-5
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n", [2016, 2017, 2049, 2250])
+def test_products_of_few_tiles_and_long_sums(gpu_device, dtype, n):
+    """From 64 k-tiles of 32 on (2017 tokens are the first that need them) a tile's waves share them: one and two tiles of
+    256 x 256 (520 wide, so mirrored tiles as well), their last parts 8 wide, k-tiles that end short, counts that no wave's
+    share divides.  Folds and adapters reach the same length with their term pairs."""
+    from paper_2507_01299_amd import api
+    d = 520
+    print(f"few tiles n={n} dtype={dtype}", flush=True)
+    xb, x = _calibration(n, d, 41, dtype)
+    C = torch.full((d, d), 7.0, dtype=torch.float32, device="cuda:0")
+    for add in (False, True):
+        api.second_moment(to_dev(xb, dtype), C, dtype, accumulate=add)
+    torch.cuda.synchronize()
+    got, want = C.cpu().numpy().astype(np.float64), 2 * (x.T @ x)
+    sc = np.sqrt(np.diag(want))
+    assert np.all(np.abs(got - want) <= SM_TOL * sc[:, None] * sc[None, :] + 1e-30)
+    assert np.array_equal(got, got.T)
+    w = 1000 + n % 64 // 8 * 8                     # 32 k-tiles or more a pass, the last one short
+    Q, scr = _rotation32(w, 43), api.OfflineScratch(w, dtype)
+    Qd, wb = torch.from_numpy(Q).cuda(), O.encode16(synth.gaussian_weight(w, 72, 47), dtype)
+    w64, t = O.decode16(wb, dtype), api.torch_dtype(dtype)
+    out = torch.zeros(w, 72, dtype=t, device="cuda:0")
+    api.fold_input(Qd, to_dev(wb, dtype), out, dtype, scr)
+    outT = torch.zeros(72, w, dtype=t, device="cuda:0")
+    api.fold_output(to_dev(np.ascontiguousarray(wb.T), dtype), Qd, outT, dtype, scr)
+    torch.cuda.synchronize()
+    norms = np.linalg.norm(w64, axis=0)
+    _check_stored(to_bits(out), O.fold_input_side(Q.astype(np.float64), w64), dtype, "Q^T W", norms[None, :])
+    _check_stored(to_bits(outT), O.fold_output_side(w64.T, Q.astype(np.float64)), dtype, "W Q", norms[:, None])
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2])
 def test_contraction_tiles_and_left_over_tiles(gpu_device, tile):
     """Every workgroup tile, and the launch in two parts: 23 x 24 / 2 = 276 and 2 x 129 = 258 tiles of 256 x 256 are one
