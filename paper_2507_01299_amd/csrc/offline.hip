@@ -7,7 +7,8 @@
 //    operand reads from LDS feed sixteen instructions, two thirds of the LDS traffic per flop of the 128 x 64 quarters that
 //    eight waves would own.
 //  * Global loads go straight into LDS (16 bytes per lane, no staging registers) and run three 32-deep k-tiles ahead of
-//    the products: four stages of 32 KiB (both terms of an f16 fold together: three of 48 KiB, two ahead), one barrier per k-tile, and the
+//    the products: four stages of 32 KiB (the smallest tile: eight of 8 KiB, seven ahead; both terms of an f16 fold together: three of
+//    48 KiB, two ahead; three bf16 terms: five of 32 KiB, four ahead), one barrier per k-tile, and the
 //    loads, the LDS reads and the products of a k-tile are issued in one fixed interleaved order.
 //  * Operands are stored k-major ([k][m], the layout of X, Q and W), the instruction wants 8 values along k per lane.
 //    The LDS tile keeps the memory's layout and the transposing LDS read does the rest: 16 lanes point at 4 rows x 16
@@ -18,14 +19,16 @@
 //    product would cost more than the 16-bit rounding of the folded weight itself.  It is therefore
 //    split into 2 (f16) or 3 (bf16) 16-bit terms whose sum carries the fp32 value, and the kernel
 //    adds the products of the listed term pairs into the same accumulators.
-//  * The two f16 terms of a fold go through k together (TWO): the weight's tile is loaded, and read from LDS, once for both, three
-//    operands a k-tile instead of four.  4096 x 22016 f16 1315 -> 1233 us, 11008 x 4096 (W Q) f16 698 -> 646, 1024 x 16384 76 -> 72.
+//  * The terms of a fold go through k together (TERMS): the weight's tile is loaded, and read from LDS, once for all of them.
+//    Two f16 terms: three operands a k-tile instead of four; 4096 x 22016 1315 -> 1233 us, 11008 x 4096 (W Q) 698 -> 646, 1024 x
+//    16384 76 -> 72.  Three bf16 terms: four operands instead of six, k-tiles of 16 in five stages of 32 KiB, a barrier per 48
+//    products instead of 32; whole calls 4096 x 28672 2229 -> 2017 us, 14336 x 4096 (W Q) 1239 -> 1150 (with the split of the rotation).
 //  * X^T X is symmetric: only tiles on and above the diagonal are computed; a tile above it is stored twice.
 //  * Whole rounds of 256 tiles (one per compute unit) run in 256 x 256 tiles; what is left over runs as 128 x 128 or 64 x 64
 //    parts in a second launch when that is shorter than another round (launch_shape).
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
 // random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace): 4096 x
-// 28672 x 4096 bf16, 3 terms, 1.29 - 1.33 PFLOP/s; f16 folds of a 4096-wide layer 1.22 - 1.31, its adapter 1.23;
+// 28672 x 4096 bf16, 3 terms, 1.41 - 1.43 PFLOP/s (1.29 with a pass per term); f16 folds of a 4096-wide layer 1.22 - 1.31, its adapter 1.23;
 // second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 321 + 36 us = 1.04 (36 for the 16 tiles after
 // the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
 // 69 - 79 % of the cycles in f16 folds, 64 - 73 % with a pass per term pair; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
@@ -129,19 +132,21 @@ __device__ __forceinline__ TileAt tile_of(int number, int tiles_m, int tiles_n, 
 constexpr int kBigTile = 256;      // tiles are numbered in this size; smaller workgroup tiles are parts of them
 
 // A workgroup of 4 waves (2 x 2) owns a (64 MI) x (64 MI) tile of C, a wave (32 MI) x (32 MI) of it.
-// TWO: both term pairs of a fold in one pass over k.  The operand that has two terms (A if it is k-major, else B: the
-// rotation) brings both of a k-tile, the weight comes once for both: three operands are loaded and read from LDS where two
-// passes take four.
-template <typename T, bool A_KMAJOR, int MI, bool TWO>
+// TERMS > 1: all term pairs of a fold in one pass over k.  The operand that has terms (A if it is k-major, else B: the
+// rotation) brings those of a k-tile together, the weight comes once for all: three operands are loaded and read from LDS where
+// two passes take four, four where three passes take six (three terms: k-tiles of 16, so that five stages fit).
+template <typename T, bool A_KMAJOR, int MI, int TERMS>
 __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(ContractionArgs a) {
   constexpr int TC = 64 * MI;                    // tile side
-  constexpr int kOperandBytes = TC * kKTile * 2; // one operand of one stage
-  constexpr int kStageBytes = (TWO ? 3 : 2) * kOperandBytes;   // A, B, second term
+  constexpr int KT = TERMS == 3 ? 16 : kKTile;   // k rows of a k-tile
+  constexpr int kOperandBytes = TC * KT * 2;     // one operand of one stage
+  constexpr int kStageBytes = (TERMS + 1) * kOperandBytes;     // A, B, further terms
   constexpr int CPR = TC / 8;                    // 16-byte pieces per row of a k-major tile
   constexpr int RPI = 64 / CPR;                  // rows that one wave-load covers
   constexpr int GR = 2 * MI;                     // granules per row
-  constexpr int kStages = TWO ? 3 : kStagesOf<MI>;
-  static_assert(!TWO || MI == 4, "two terms at once: the large tile only");
+  constexpr int kStages = TERMS == 1 ? kStagesOf<MI> : TERMS == 2 ? 3 : 5;
+  static_assert(TERMS == 1 || MI == 4, "several terms at once: the large tile only");
+  constexpr int LQ = kOperandBytes / 4096;       // loads of a wave per operand and k-tile
   constexpr int kLoads = kStageBytes / 4096;     // of a wave per stage
   constexpr int kParts = 4 / MI;                 // a 256 x 256 tile is kParts x kParts tiles of this kernel
   __shared__ __attribute__((aligned(1024))) char lds[kStages * kStageBytes];
@@ -158,16 +163,16 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int wm = w >> 1, wn = w & 1;
 
-  const int ktiles = (a.Kd + kKTile - 1) / kKTile;
-  const int iters = TWO ? ktiles : ktiles * a.npairs;
+  const int ktiles = (a.Kd + KT - 1) / KT;
+  const int iters = TERMS > 1 ? ktiles : ktiles * a.npairs;
 
   // ---- loads, straight into LDS: wave-load q of wave w fills pieces 64 (4 q + w) .. + 63 of the operand's tile
   const u32x4 bufA = operand_buffer(a.A, a.a_elements);
   const u32x4 bufB = operand_buffer(a.B, a.b_elements);
-  uint32_t offA[MI], offB[MI];
-  int kA[MI], kB[MI];                            // k inside the tile of the lane's piece (its first k value)
+  uint32_t offA[LQ], offB[LQ];
+  int kA[LQ], kB[LQ];                            // k inside the tile of the lane's piece (its first k value)
 #pragma unroll
-  for (int q = 0; q < MI; ++q) {
+  for (int q = 0; q < LQ; ++q) {
     const int row = (4 * q + w) * RPI + lane / CPR, piece = lane % CPR;
     const int src = piece ^ (4 * granule_swizzle<GR>(row));
     kB[q] = row;
@@ -176,34 +181,34 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
       kA[q] = row;
       offA[q] = m0 + 8 * src < a.M ? static_cast<uint32_t>((row * a.M + m0 + 8 * src) * 2) : kOutside;
     } else {
-      // [row m][32 k values]: four 16-byte pieces per row, piece p of row m holds k values 8 (p ^ (m / 4 % 4)) ..
-      const int m = (4 * q + w) * 16 + (lane >> 2);
-      kA[q] = 8 * ((lane & 3) ^ ((m >> 2) & 3));
+      // [row m][KT k values]: piece p of the four (two) of 16 bytes of row m holds k values 8 (p ^ (m / 4 % 4)) .. (8 (p ^ (m / 8 % 2)) ..)
+      const int m = KT == 32 ? (4 * q + w) * 16 + (lane >> 2) : (4 * q + w) * 32 + (lane >> 1);
+      kA[q] = KT == 32 ? 8 * ((lane & 3) ^ ((m >> 2) & 3)) : 8 * ((lane & 1) ^ ((m >> 3) & 1));
       offA[q] = m0 + m < a.M ? static_cast<uint32_t>(((m0 + m) * a.Kd + kA[q]) * 2) : kOutside;
     }
   }
   const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_char*)lds));
   // The next k-tile to load: its first k, the stage it goes to and the byte offsets of its first element in the
   // operands.  Past the last tile f_k is 0: zeros are loaded, so that every step waits for the same count.
-  const uint32_t stepA = static_cast<uint32_t>((A_KMAJOR ? kKTile * a.M : kKTile) * 2), stepB = static_cast<uint32_t>(kKTile * a.N * 2);
+  const uint32_t stepA = static_cast<uint32_t>((A_KMAJOR ? KT * a.M : KT) * 2), stepB = static_cast<uint32_t>(KT * a.N * 2);
   int f_pair = 0, f_k = a.Kd, f_stage = 0;
   uint32_t ta = static_cast<uint32_t>(a.pa[0] * a.a_term_stride * 2), tb = static_cast<uint32_t>(a.pb[0] * a.b_term_stride * 2);
   uint32_t f_lds = lds_base + w * 1024;
   const uint32_t term2 = static_cast<uint32_t>((A_KMAJOR ? a.a_term_stride : a.b_term_stride) * 2);
-  auto fetch_piece = [&](int q) {                // q < MI: A, then B, then the second term of one of them
-    if (q >= 2 * MI) {
-      if (A_KMAJOR) load_to_lds(bufA, f_lds + 2 * kOperandBytes + (q - 2 * MI) * 4096, (kA[q & (MI - 1)] < f_k ? offA[q & (MI - 1)] : kOutside) + (ta + term2));
-      else load_to_lds(bufB, f_lds + 2 * kOperandBytes + (q - 2 * MI) * 4096, (kB[q & (MI - 1)] < f_k ? offB[q & (MI - 1)] : kOutside) + (tb + term2));
-    } else if (q < MI) load_to_lds(bufA, f_lds + q * 4096, (kA[q & (MI - 1)] < f_k ? offA[q & (MI - 1)] : kOutside) + ta);
-    else load_to_lds(bufB, f_lds + kOperandBytes + (q - MI) * 4096, (kB[q & (MI - 1)] < f_k ? offB[q & (MI - 1)] : kOutside) + tb);
+  auto fetch_piece = [&](int q) {                // operand q / LQ: A, B, the further terms of one of them
+    const int op = q / LQ, i = q % LQ;
+    const uint32_t to = f_lds + op * kOperandBytes + i * 4096;
+    const uint32_t term = op < 2 ? 0u : (op - 1) * term2;
+    if (op == 0 || (op > 1 && A_KMAJOR)) load_to_lds(bufA, to, (kA[i] < f_k ? offA[i] : kOutside) + (ta + term));
+    else load_to_lds(bufB, to, (kB[i] < f_k ? offB[i] : kOutside) + (tb + term));
   };
   auto fetch_next = [&]() {
-    f_k -= kKTile;
+    f_k -= KT;
     ta += stepA;
     tb += stepB;
     if (f_k <= 0) {                              // the next term pair (uniform, once per pass over k)
       ++f_pair;
-      if (!TWO && f_pair < a.npairs) {
+      if (TERMS == 1 && f_pair < a.npairs) {
         f_k = a.Kd;
         ta = static_cast<uint32_t>(a.pa[f_pair] * a.a_term_stride * 2);
         tb = static_cast<uint32_t>(a.pb[f_pair] * a.b_term_stride * 2);
@@ -212,7 +217,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
         ta = tb = 0;
       }
     }
-    f_stage = TWO ? (f_stage == kStages - 1 ? 0 : f_stage + 1) : (f_stage + 1) & (kStages - 1);
+    f_stage = TERMS > 1 ? (f_stage == kStages - 1 ? 0 : f_stage + 1) : (f_stage + 1) & (kStages - 1);
     f_lds = lds_base + f_stage * kStageBytes + w * 1024;
   };
   auto fetch = [&]() {
@@ -231,7 +236,8 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     adrA[i] = A_KMAJOR ? rowk * (TC * 2) + ((wm * MI + i) ^ sw) * 64 + inrow
-                       : (wm * MI * 32 + i * 32 + (lane & 31)) * 64 + (((lane >> 5) ^ ((lane >> 2) & 3)) * 16);
+                       : (wm * MI * 32 + i * 32 + (lane & 31)) * (2 * KT) +
+                             (((lane >> 5) ^ (KT == 32 ? (lane >> 2) & 3 : (lane >> 3) & 1)) * 16);
     adrB[i] = kOperandBytes + rowk * (TC * 2) + ((wn * MI + i) ^ sw) * 64 + inrow;
   }
   auto read_k = [&](int stage, int adr, int s) -> u32x4 {
@@ -282,7 +288,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
   // while its first half is multiplied, then one barrier, then the first half of tile it + 1 while the second half is
   // multiplied.  The barrier follows a wait for this wave's own loads of tile it + 1 (the kStages - 2 tiles of 2 MI loads
   // after it may be outstanding) and for its LDS reads of tile it, whose stage the loads issued next overwrite.
-  if constexpr (!TWO) {
+  if constexpr (TERMS == 1) {
     u32x4 a0[MI], b0[MI], a1[MI], b1[MI];
     for (int i = 0; i < kStages - 1; ++i) fetch();
     tile_landed<(kStages - 2) * 2 * MI>();
@@ -298,12 +304,12 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
       fetch_next();
     }
   } else {
-    // The same with four groups of products per k-tile: first term, second term of its first half, then of its second.
-    // The barrier stands before the last group, which reads the next tile's first operands; a tile's twelve loads are
-    // issued half in that group, half in the one after.
-    u32x4 p0[MI], p1[MI], s0[MI], s1[MI];        // first term, second term; the shared operand of each half
+    // The same with a group of products per term (two terms: of the tile's first half, then of its second).  The barrier stands
+    // before the last group, which reads the next tile's first operands; a tile's loads are issued half in that group, half in
+    // the one after.
+    u32x4 p0[MI], p1[MI], s0[MI], s1[MI];        // terms; the shared operand of each half (of each tile)
     auto read_term = [&](int st, int s, int term, int i) -> u32x4 {
-      return A_KMAJOR ? read_k(st + term * 2 * kOperandBytes, adrA[i], s) : read_k(st + term * kOperandBytes, adrB[i], s);
+      return A_KMAJOR ? read_k(st + (term ? term + 1 : 0) * kOperandBytes, adrA[i], s) : read_k(st + term * kOperandBytes, adrB[i], s);
     };
     auto read_shared = [&](int st, int s, int i) -> u32x4 {
       if constexpr (A_KMAJOR) return read_k(st, adrB[i], s);
@@ -318,9 +324,8 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
         __builtin_amdgcn_sched_barrier(0);
       });
     };
-    fetch();
-    fetch();
-    tile_landed<kLoads>();
+    for (int i = 0; i < kStages - 1; ++i) fetch();
+    tile_landed<(kStages - 2) * kLoads>();
 #pragma unroll
     for (int q = 0; q < kLoads / 2; ++q) fetch_piece(q);
     int stage = 0;
@@ -329,26 +334,52 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
       p0[i] = read_term(stage, 0, 0, i);
       s0[i] = read_shared(stage, 0, i);
     }
-    for (int it = 0; it < iters; ++it) {
-      group(p0, s0, [&](int x) __attribute__((always_inline)) {
-        if (x % 4 == 0) p1[x / 4] = read_term(stage, 0, 1, x / 4);
-        if (x % 2 == 1 && x / 2 < kLoads / 2) fetch_piece(kLoads / 2 + x / 2);
-      });
-      fetch_next();
-      group(p1, s0, [&](int x) __attribute__((always_inline)) {
-        if (x % 4 == 0) p0[x / 4] = read_term(stage, 1, 0, x / 4);
-        if (x % 4 == 2) s1[x / 4] = read_shared(stage, 1, x / 4);
-      });
-      group(p0, s1, [&](int x) __attribute__((always_inline)) {
-        if (x % 4 == 0) p1[x / 4] = read_term(stage, 1, 1, x / 4);
-      });
-      tile_landed<kLoads>();                     // of the three tiles under way, the youngest may be outstanding
-      stage = stage == (kStages - 1) * kStageBytes ? 0 : stage + kStageBytes;
-      group(p1, s1, [&](int x) __attribute__((always_inline)) {
-        if (x % 4 == 0) p0[x / 4] = read_term(stage, 0, 0, x / 4);
-        if (x % 4 == 2) s0[x / 4] = read_shared(stage, 0, x / 4);
-        if (x % 2 == 1 && x / 2 < kLoads / 2) fetch_piece(x / 2);
-      });
+    if constexpr (TERMS == 2) {
+      for (int it = 0; it < iters; ++it) {
+        group(p0, s0, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) p1[x / 4] = read_term(stage, 0, 1, x / 4);
+          if (x % 2 == 1 && x / 2 < kLoads / 2) fetch_piece(kLoads / 2 + x / 2);
+        });
+        fetch_next();
+        group(p1, s0, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) p0[x / 4] = read_term(stage, 1, 0, x / 4);
+          if (x % 4 == 2) s1[x / 4] = read_shared(stage, 1, x / 4);
+        });
+        group(p0, s1, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) p1[x / 4] = read_term(stage, 1, 1, x / 4);
+        });
+        tile_landed<(kStages - 2) * kLoads>();     // of the tiles under way, all but the next may be outstanding
+        stage = stage == (kStages - 1) * kStageBytes ? 0 : stage + kStageBytes;
+        group(p1, s1, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) p0[x / 4] = read_term(stage, 0, 0, x / 4);
+          if (x % 4 == 2) s0[x / 4] = read_shared(stage, 0, x / 4);
+          if (x % 2 == 1 && x / 2 < kLoads / 2) fetch_piece(x / 2);
+        });
+      }
+    } else {
+      // terms 0 and 2 of a tile sit in `p`, term 1 and the next tile's term 0 in `q`
+      auto tile = [&](u32x4 (&p)[MI], u32x4 (&q)[MI], u32x4 (&sh)[MI], u32x4 (&sh_next)[MI]) __attribute__((always_inline)) {
+        group(p, sh, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) q[x / 4] = read_term(stage, 0, 1, x / 4);
+          if (x % 4 == 1) fetch_piece(kLoads / 2 + x / 4);
+        });
+        fetch_next();
+        group(q, sh, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) p[x / 4] = read_term(stage, 0, 2, x / 4);
+        });
+        tile_landed<(kStages - 2) * kLoads>();
+        stage = stage == (kStages - 1) * kStageBytes ? 0 : stage + kStageBytes;
+        group(p, sh, [&](int x) __attribute__((always_inline)) {
+          if (x % 4 == 0) q[x / 4] = read_term(stage, 0, 0, x / 4);
+          if (x % 4 == 2) sh_next[x / 4] = read_shared(stage, 0, x / 4);
+          if (x % 4 == 1) fetch_piece(x / 4);
+        });
+      };
+      static_assert(TERMS != 3 || kLoads == 8, "four loads in a group");
+      for (int it = 0; it < iters; it += 2) {    // (an odd count: the last tile is zeros)
+        tile(p0, p1, s0, s1);
+        tile(p1, p0, s1, s0);
+      }
     }
   }
   // ---- store.  Accumulator register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of its 32 x 32
@@ -656,7 +687,7 @@ hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre
 namespace {
 
 // Tiles first .. first + count - 1 (numbered in 256 x 256 tiles) by workgroups of (64 MI) x (64 MI) tiles.
-template <typename T, bool A_KMAJOR, int MI, bool TWO = false>
+template <typename T, bool A_KMAJOR, int MI, int TERMS = 1>
 hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s) {
   const long parts = count * (4 / MI) * (4 / MI);
   const long grid = (parts + 7) / 8 * 8;
@@ -665,7 +696,7 @@ hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s
   a.tiles = static_cast<int>(parts);
   const bool shared = MI == 1 && (a.Kd + kKTile - 1) / kKTile * a.npairs >= kSharedChain;
   if (shared) hipLaunchKernelGGL((small_contraction_kernel<T, A_KMAJOR>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TWO>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TERMS>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -704,14 +735,11 @@ hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
     if (mi == 4) big = tiles;
   }
   if (big > 0) {
-    // a fold's two term pairs: the rotation's first and second term with the weight
-    bool two = a.npairs == 2 && (A_KMAJOR ? a.pa[0] == 0 && a.pa[1] == 1 && a.pb[0] == 0 && a.pb[1] == 0
-                                          : a.pb[0] == 0 && a.pb[1] == 1 && a.pa[0] == 0 && a.pa[1] == 0);
-    if constexpr (std::is_same_v<T, BF16>) two = false;   // (bf16 terms come in threes)
-    hipError_t e = hipSuccess;
-    if constexpr (std::is_same_v<T, F16>)
-      if (two) e = launch_tiles<T, A_KMAJOR, 4, true>(a, 0, big, s);
-    if (!two) e = launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s);
+    // a fold's term pairs: the rotation's terms, all of them, each with the weight
+    constexpr int kTerms = std::is_same_v<T, BF16> ? 3 : 2;
+    bool fold = a.npairs == kTerms;
+    for (int i = 0; fold && i < kTerms; ++i) fold = (A_KMAJOR ? a.pa[i] : a.pb[i]) == i && (A_KMAJOR ? a.pb[i] : a.pa[i]) == 0;
+    const hipError_t e = fold ? launch_tiles<T, A_KMAJOR, 4, kTerms>(a, 0, big, s) : launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s);
     if (e != hipSuccess) return e;
   }
   if (big == tiles) return hipSuccess;
