@@ -29,7 +29,7 @@
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
 // random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace): 4096 x
 // 28672 x 4096 bf16, 3 terms, 1.41 - 1.43 PFLOP/s (1.29 with a pass per term); f16 folds of a 4096-wide layer 1.22 - 1.31, its adapter 1.23;
-// second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 321 + 36 us = 1.04 (36 for the 16 tiles after
+// second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 313 - 333 + 29 us (29, 36 before the waves shared k-tiles, for the 16 tiles after
 // the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
 // 69 - 79 % of the cycles in f16 folds, 64 - 73 % with a pass per term pair; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
 // staging registers, two LDS stages) kept them busy 34 % and gave the XCDs of a symmetric product uneven shares.
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
 // Few tiles: a workgroup owns a 64 x 64 tile, and its four waves share the k-tiles instead of the tile.  What bounds such
 // products is not the matrix cores but each wave's chain over k, so a wave takes every fourth k-tile through a ring of its own
 // in LDS, with no barrier until the four sums meet, and multiplies the whole 64 x 64 (with a 32 x 32 quarter per wave and a
-// barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 28).
+// barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 29).
 // Whole calls, us, quarters / shared k-tiles: second moment 5000 x 1024 f16 29.0 / 22.6, 2048 x 1024 (64 k-tiles) 14.8 / 12.6, fold
 // 4096 x 512 bf16 140.4 / 125, 2048 x 512 f16 32.3 / 26.0, adapter 512 bf16 (96) 23.0 / 20.8.  Short chains gain nothing from
 // it and pay for the four sums: second moment 512 x 512 (16 k-tiles) 6.9 / 7.1; so from 64 k-tiles on.
