@@ -107,10 +107,10 @@ __device__ __forceinline__ void wave_lds_order() {
 // (workgroups b % 8) works on consecutive tiles: its 32 compute units on a patch of 4 x 8, sharing the panels of both
 // operands in their L2.  Symmetric products number the tiles on and above the diagonal only.
 struct TileAt { int m, n; };
-__device__ __forceinline__ TileAt tile_of(int number, int tiles_m, int tiles_n, bool symmetric) {
+__host__ __device__ __forceinline__ TileAt tile_of(int number, int tiles_m, int tiles_n, bool symmetric) {
   int band = 0;
   for (;;) {
-    const int rows = min(kBand, tiles_m - band * kBand);
+    const int left = tiles_m - band * kBand, rows = left < kBand ? left : kBand;
     const int first = symmetric ? band * kBand : 0;          // first column of the band
     const int head = symmetric ? rows * (rows - 1) / 2 : 0;  // tiles in the columns that meet the diagonal above its last row
     const int cols = tiles_n - first - (symmetric ? rows - 1 : 0);
@@ -466,9 +466,8 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
 // products is not the matrix cores but each wave's chain over k, so a wave takes every fourth k-tile through a ring of its own
 // in LDS, with no barrier until the four sums meet, and multiplies the whole 64 x 64 (with a 32 x 32 quarter per wave and a
 // barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 29).
-// Whole calls, us, quarters / shared k-tiles: second moment 5000 x 1024 f16 29.0 / 22.6, 2048 x 1024 (64 k-tiles) 14.8 / 12.6, fold
-// 4096 x 512 bf16 140.4 / 125, 2048 x 512 f16 32.3 / 26.0, adapter 512 bf16 (96) 23.0 / 20.8.  Short chains gain nothing from
-// it and pay for the four sums: second moment 512 x 512 (16 k-tiles) 6.9 / 7.1; so from 64 k-tiles on.
+// Whole calls, us, quarters / shared k-tiles: second moment 5000 x 1024 f16 29.0 / 22.6, 2048 x 1024 (64 k-tiles) 14.4 / 12.0, fold
+// 2048 x 512 f16 30.8 / 25.8, adapter 1024 bf16 46.8 / 38.4.  shares_chain says which products take it.
 constexpr int kSharedChain = 64;   // k-tiles of all term pairs from which the four waves share them
 constexpr int kSmallSide = 64;
 constexpr int kSmallStages = 4;    // k-tiles in a wave's ring
@@ -686,6 +685,30 @@ hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre
 
 namespace {
 
+// Whether 64 x 64 tiles of `count` (at most 32) tiles of 256 x 256 from number `first` run in the kernel whose waves share the
+// k-tiles.  It takes 128 KiB of LDS, one workgroup per compute unit where the other fits two, so it is for launches of one round:
+// no XCD's share of consecutive parts holds more than 32 (its compute units) that have anything to do.  Up to 16 tiles that is so;
+// above, the edges decide.  Whole calls, us, quarters / shared: second moment 2048 x 1536 (21 tiles) 17.6 / 21.8, 4800 x 1792 (28)
+// 33.8 / 38.9, fold f16 1024 x 2048 (32) 23.3 / 26.8, bf16 704 x 1400 (18 tiles, up to 36 parts an XCD) 23.4 / 28.8; W Q bf16 264 x 2504
+// (20 tiles, up to 28 parts) 87.7 / 53.1.  Two rounds pay only for sums so long that the shorter chain outweighs them: second moment 1536
+// wide of 16384 tokens (512 k-tiles) 117 / 108, of 32768 259 / 208, W Q bf16 256 x 8192 (768) 406 / 367; with more than 24 tiles of a
+// second moment later (1792 wide: 16384 tokens 102 / 108, 32768 207 / 206, 65536 469 / 399).
+bool shares_chain(const ContractionArgs& a, long first, long count) {
+  const int chain = (a.Kd + kKTile - 1) / kKTile * a.npairs;
+  if (chain < kSharedChain) return false;
+  if (count <= 16 || chain >= (a.symmetric != 0 && count > 24 ? 1024 : 512)) return true;
+  constexpr int kParts = kBigTile / kSmallSide, kTileParts = kParts * kParts;
+  const int share = static_cast<int>(count) * kTileParts / 8;    // parts of an XCD, in the kernels' numbering
+  int busy = 0;
+  for (int part = 0; part < share * 8; ++part) {
+    if (part % share == 0) busy = 0;
+    const TileAt at = tile_of(static_cast<int>(first) + part / kTileParts, a.tiles_m, a.tiles_n, a.symmetric != 0);
+    const int m0 = at.m * kBigTile + part % kTileParts / kParts * kSmallSide, n0 = at.n * kBigTile + part % kParts * kSmallSide;
+    if (m0 < a.M && n0 < a.N && ++busy > 32) return false;
+  }
+  return true;
+}
+
 // Tiles first .. first + count - 1 (numbered in 256 x 256 tiles) by workgroups of (64 MI) x (64 MI) tiles.
 template <typename T, bool A_KMAJOR, int MI, int TERMS = 1>
 hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s) {
@@ -694,8 +717,8 @@ hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s
   if (grid > 0x7FFFFFFFL) return hipErrorInvalidValue;
   a.tile0 = static_cast<int>(first);
   a.tiles = static_cast<int>(parts);
-  const bool shared = MI == 1 && (a.Kd + kKTile - 1) / kKTile * a.npairs >= kSharedChain;
-  if (shared) hipLaunchKernelGGL((small_contraction_kernel<T, A_KMAJOR>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
+  if (MI == 1 && shares_chain(a, first, count))
+    hipLaunchKernelGGL((small_contraction_kernel<T, A_KMAJOR>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TERMS>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   return hipGetLastError();
 }

@@ -174,6 +174,48 @@ def test_products_of_few_tiles_and_long_sums(gpu_device, dtype, n):
     _check_stored(to_bits(outT), O.fold_output_side(w64.T, Q.astype(np.float64)), dtype, "W Q", norms[:, None])
 
 
+@pytest.mark.parametrize("what,d,other,dtype", [
+    ("moment", 1536, 2048, "bf16"), ("moment", 1792, 2100, "f16"), ("moment", 5880, 2049, "bf16"), ("Q^T W", 1032, 904, "f16"),
+    ("Q^T W", 704, 1400, "bf16"), ("W Q", 1288, 1032, "f16"), ("adapter", 1280, 0, "bf16")])
+def test_products_of_more_than_one_round_of_small_tiles(gpu_device, what, d, other, dtype):
+    """17 to 32 tiles of 256 x 256 in parts of 64 are more than a workgroup per compute unit (of the chip, or of one eighth of it: 704
+    x 1400), which the kernel whose waves share the k-tiles would take in two rounds.  They keep the kernel whose waves each follow the
+    whole sum, whose order is that of the 128 x 128 tiles: the bits are the same, which sums in four parts do not give."""
+    from paper_2507_01299_amd import api
+    print(f"more than a round {what} d={d} other={other} dtype={dtype}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(d + other)
+    t = api.torch_dtype(dtype)
+
+    def normal(*shape, std=1.0):
+        return torch.randn(*shape, generator=g, device="cuda:0") * std
+
+    if what == "moment":
+        X, shape = normal(other, d).to(t), (d, d)
+    else:
+        Q, sc = normal(d, d, std=d ** -0.5), api.OfflineScratch(d, dtype)
+        shape = {"Q^T W": (d, other), "W Q": (other, d), "adapter": (d, d)}[what]
+        W = normal(d, d, std=d ** -0.5) if what == "adapter" else normal(*shape, std=0.02).to(t)
+    outs = []
+    for tile in (0, 1):
+        api.set_tuning(10, tile)
+        try:
+            out = torch.full(shape, 9.0, dtype=torch.float32 if what == "moment" else t, device="cuda:0")
+            if what == "moment":
+                api.second_moment(X, out, dtype)
+                api.second_moment(X, out, dtype, accumulate=True)
+            elif what == "Q^T W":
+                api.fold_input(Q, W, out, dtype, sc)
+            elif what == "W Q":
+                api.fold_output(W, Q, out, dtype, sc)
+            else:
+                api.residual_adapter(Q, W, out, dtype, sc)
+            torch.cuda.synchronize()
+        finally:
+            api.set_tuning(10, 0)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1]), int((outs[0] != outs[1]).sum())
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2])
 def test_contraction_tiles_and_left_over_tiles(gpu_device, tile):
     """Every workgroup tile, and the launch in two parts: 23 x 24 / 2 = 276 and 2 x 129 = 258 tiles of 256 x 256 are one
