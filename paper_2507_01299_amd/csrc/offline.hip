@@ -647,26 +647,34 @@ __global__ __launch_bounds__(256, 1) void small_contraction_kernel(ContractionAr
   }
 }
 
-// fp32 -> NT 16-bit terms with x * pre_scale = t0 + t1 (+ t2) up to the last term's rounding.  HBM-bound, 4 bytes in and 2 NT
-// out per entry: eight entries a lane, so that every access moves 16 bytes (n is a multiple of 64; with one entry a lane 4096 x
-// 4096 in three terms took 49.8 us, 3.4 TB/s, now 28.8).
-template <typename T, int NT>
-__global__ __launch_bounds__(256) void split_terms_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long n,
+// Bits of a 16-bit rounding as T::from_f32 gives them, for bf16 as a choice between two values: the branch around a NaN there is one more
+// serial step per rounding in a lane that has twelve of them.
+__device__ __forceinline__ uint32_t term_bits(F16, float f) { return F16::from_f32(f); }
+__device__ __forceinline__ uint32_t term_bits(BF16, float f) {
+  const uint32_t u = __float_as_uint(f), rounded = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16, nan = (u >> 16) | 0x40u;
+  return (u & 0x7FFFFFFFu) > 0x7F800000u ? nan : rounded;
+}
+
+// fp32 -> NT 16-bit terms with x * pre_scale = t0 + t1 (+ t2) up to the last term's rounding.  HBM-bound for wide rotations, 4 bytes in
+// and 2 NT out per entry (4096 x 4096 in three terms: 49.8 us with one entry a lane, 28.8 with eight), latency-bound for narrow ones, where
+// a lane's chain counts: bf16 fold 512 x 512 / adapter 256, whole calls, us: one entry 14.4 / 15.5, eight 15.0 / 16.7.  Four entries (16 bytes
+// in, n is a multiple of 64) are as fast as the better of the two: 14.4 / 15.6, adapter 4096 bf16 660 (eight: 659, one: 702).
+template <typename T, int NT, int THREADS>
+__global__ __launch_bounds__(THREADS) void split_terms_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long n,
                                                           float pre_scale) {
-  const long i = (static_cast<long>(blockIdx.x) * 256 + threadIdx.x) * 8;
+  const long i = (static_cast<long>(blockIdx.x) * THREADS + threadIdx.x) * 4;
   if (i >= n) return;
-  const float4 lo = *reinterpret_cast<const float4*>(src + i), hi = *reinterpret_cast<const float4*>(src + i + 4);
-  float r[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-  for (int k = 0; k < 8; ++k) r[k] *= pre_scale;
+  const float4 v = *reinterpret_cast<const float4*>(src + i);
+  float r[4] = {v.x * pre_scale, v.y * pre_scale, v.z * pre_scale, v.w * pre_scale};
 #pragma unroll
   for (int s = 0; s < NT; ++s) {
-    const uint4 b = pack8<T>(r);
-    *reinterpret_cast<uint4*>(dst + s * n + i) = b;
-    float f[8];
-    unpack8<T>(b, f);
+    uint32_t b[4];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r[k] -= f[k];
+    for (int k = 0; k < 4; ++k) {
+      b[k] = term_bits(T{}, r[k]);
+      r[k] -= T::to_f32(static_cast<uint16_t>(b[k]));
+    }
+    *reinterpret_cast<uint2*>(dst + s * n + i) = make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
   }
 }
 
@@ -674,12 +682,23 @@ __global__ __launch_bounds__(256) void split_terms_kernel(const float* __restric
 
 int contraction_terms(bool bf16) { return bf16 ? 3 : 2; }
 
+namespace {
+
+template <typename T, int NT, int THREADS>
+void launch_split(const float* src, uint16_t* dst, long n, float pre_scale, hipStream_t s) {
+  const unsigned grid = static_cast<unsigned>((n + 4 * THREADS - 1) / (4 * THREADS));
+  hipLaunchKernelGGL((split_terms_kernel<T, NT, THREADS>), dim3(grid), dim3(THREADS), 0, s, src, dst, n, pre_scale);
+}
+
+}  // namespace
+
 hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre_scale, bool bf16, hipStream_t s) {
-  const unsigned grid = static_cast<unsigned>((n + 2047) / 2048);
-  if (bf16)
-    hipLaunchKernelGGL((split_terms_kernel<BF16, 3>), dim3(grid), dim3(256), 0, s, src, dst, n, pre_scale);
-  else
-    hipLaunchKernelGGL((split_terms_kernel<F16, 2>), dim3(grid), dim3(256), 0, s, src, dst, n, pre_scale);
+  // One wave a workgroup up to 1024 x 1024: whole calls, us, with four waves / one: W Q 2048 x 1024 f16 24.8 / 23.3, bf16 33.6 / 31.4, Q^T W 1024 x
+  // 512 bf16 22.3 / 20.1 (level at other widths below; why the placement matters at 1024 was not found).  Above, four: adapter 2048 f16
+  // 74.5 / 75.8, Q^T W 1152 x 512 17.9 / 18.5.  (A run-time size would cost 0.4 us a launch for the implicit arguments.)
+  const bool narrow = n <= 1L << 20;
+  if (bf16) narrow ? launch_split<BF16, 3, 64>(src, dst, n, pre_scale, s) : launch_split<BF16, 3, 256>(src, dst, n, pre_scale, s);
+  else narrow ? launch_split<F16, 2, 64>(src, dst, n, pre_scale, s) : launch_split<F16, 2, 256>(src, dst, n, pre_scale, s);
   return hipGetLastError();
 }
 

@@ -574,6 +574,33 @@ def test_bf16_contractions_hold_every_entry(gpu_device, tile, d, other):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("d", [8, 1016, 1024, 1032])
+def test_terms_of_a_rotation_with_infinities_and_nan(gpu_device, dtype, d):
+    """The split of a rotation on both sides of the size where its launch changes, and one smaller than a workgroup.  Columns of Q with a
+    NaN (signalling, negative, all bits set: a rounding by addition alone would make infinities or zeros of them) or an infinity make
+    rows of Q^T W that are NaN throughout; the others are single entries of Q, times one: their own rounding."""
+    from paper_2507_01299_amd import api
+    print(f"terms with NaN dtype={dtype} d={d}", flush=True)
+    rng = np.random.default_rng(d)
+    Q = _full_spread(rng, (d, d), -4 if dtype == "f16" else -60) / (4.0 if dtype == "f16" else 1.0)
+    bad = [0x7F800001, 0xFF800001, 0x7FFFFFFF, 0xFFFFFFFF, 0x7F800000, 0xFF800000]
+    cols = rng.choice(d, len(bad), replace=False)
+    Q.view(np.uint32)[rng.integers(0, d, len(bad)), cols] = np.array(bad, dtype=np.uint32)
+    pick = rng.permutation(d)
+    wb = np.zeros((d, d), dtype=np.uint16)
+    wb[pick, np.arange(d)] = O.encode16(np.ones(d), dtype)
+    out = torch.full((d, d), 9.0, dtype=api.torch_dtype(dtype), device="cuda:0")
+    api.fold_input(torch.from_numpy(Q).cuda(), to_dev(wb, dtype), out, dtype, api.OfflineScratch(d, dtype))
+    got, clean = to_bits(out), np.setdiff1d(np.arange(d), cols)
+    assert np.isnan(O.decode16(got[cols], dtype)).all()
+    # f16: of 64 Q >= 1 the two terms leave out at most 2^-23 of the value, its last place is at least 2^-11 of it: on both sides of a
+    # tie 2 * 2^-23 / 2^-11 = 4.9e-4 of the entries may round the other way (below 2^-6 the second term would be subnormal)
+    want = O.encode16(Q[pick].astype(np.float64).T[clean], dtype)
+    step = np.abs(_ordered(got[clean]) - _ordered(want))
+    assert step.max() <= (1 if dtype == "f16" else 0) and (step != 0).mean() <= 1e-3
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_workspace_size_changes_no_bit(gpu_device, dtype):
     """The same folds and adapter with the workspace made for them and with one made for a wider rotation (a program that keeps
     one for a whole model)."""
