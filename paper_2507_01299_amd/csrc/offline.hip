@@ -750,6 +750,8 @@ double tile_rounds(long count, int mi) {
   return 0.1 + 0.16 * ((count + 15) / 16);
 }
 
+constexpr int kTogether = 112;     // k rows from which W Q takes three terms in one pass (launch_shape)
+
 template <typename T, bool A_KMAJOR>
 hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
   a.tiles_m = (a.M + kBigTile - 1) / kBigTile;
@@ -777,11 +779,19 @@ hipError_t launch_shape(ContractionArgs a, hipStream_t s) {
     if (mi == 4) big = tiles;
   }
   if (big > 0) {
-    // a fold's term pairs: the rotation's terms, all of them, each with the weight
+    // A fold's term pairs: the rotation's terms, all of them, each with the weight.  Short sums of three terms keep a pass per term when
+    // A is the weight: the longer start (four stages instead of three before the first product) is not won back.  W Q bf16, 65536 rows, us,
+    // a pass per term / together: 8 wide 31.8 / 32.3, 96 wide 36.6 / 36.8, 120 wide 39.2 / 38.7, 256 wide 53.7 / 52.0 (Q^T W 8 wide 26.3 / 25.9).
     constexpr int kTerms = std::is_same_v<T, BF16> ? 3 : 2;
     bool fold = a.npairs == kTerms;
     for (int i = 0; fold && i < kTerms; ++i) fold = (A_KMAJOR ? a.pa[i] : a.pb[i]) == i && (A_KMAJOR ? a.pb[i] : a.pa[i]) == 0;
-    const hipError_t e = fold ? launch_tiles<T, A_KMAJOR, 4, kTerms>(a, 0, big, s) : launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s);
+    hipError_t e;
+    if constexpr (!A_KMAJOR && kTerms == 2) {    // only folds come here
+      e = fold ? launch_tiles<T, A_KMAJOR, 4, kTerms>(a, 0, big, s) : hipErrorInvalidValue;
+    } else {
+      const bool together = fold && (A_KMAJOR || a.Kd >= kTogether);
+      e = together ? launch_tiles<T, A_KMAJOR, 4, kTerms>(a, 0, big, s) : launch_tiles<T, A_KMAJOR, 4>(a, 0, big, s);
+    }
     if (e != hipSuccess) return e;
   }
   if (big == tiles) return hipSuccess;

@@ -216,6 +216,30 @@ def test_products_of_more_than_one_round_of_small_tiles(gpu_device, what, d, oth
     assert torch.equal(outs[0], outs[1]), int((outs[0] != outs[1]).sum())
 
 
+@pytest.mark.parametrize("d", [8, 104, 112, 120])
+def test_wide_products_with_a_narrow_bf16_rotation(gpu_device, d):
+    """W Q of a weight with 33000 rows (129 tiles of 256 x 256, all in the large tile) by rotations on both sides of the width from which
+    the terms go through k together; below it they go one after the other as in every other tile: the same bits."""
+    from paper_2507_01299_amd import api
+    rows = 33000
+    print(f"narrow bf16 rotation d={d}", flush=True)
+    Q = _rotation32(d, 3)
+    wb = O.encode16(synth.gaussian_weight(rows, d, 5), "bf16")
+    w64, Qd, W = O.decode16(wb, "bf16"), torch.from_numpy(Q).cuda(), to_dev(wb, "bf16")
+    sc, outs = api.OfflineScratch(d, "bf16"), []
+    for tile in (0, 1):
+        api.set_tuning(10, tile)
+        try:
+            outs.append(torch.full((rows, d), 9.0, dtype=torch.bfloat16, device="cuda:0"))
+            api.fold_output(W, Qd, outs[-1], "bf16", sc)
+            torch.cuda.synchronize()
+        finally:
+            api.set_tuning(10, 0)
+    _check_stored(to_bits(outs[0]), O.fold_output_side(w64, Q.astype(np.float64)), "bf16", "W Q", np.linalg.norm(w64, axis=1)[:, None])
+    if d < 112:
+        assert torch.equal(outs[0], outs[1]), int((outs[0] != outs[1]).sum())
+
+
 @pytest.mark.parametrize("tile", [0, 1, 2])
 def test_contraction_tiles_and_left_over_tiles(gpu_device, tile):
     """Every workgroup tile, and the launch in two parts: 23 x 24 / 2 = 276 and 2 x 129 = 258 tiles of 256 x 256 are one
