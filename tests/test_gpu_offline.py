@@ -27,15 +27,17 @@ SM_TOL = 5e-5
 ULP_FRACTION = 0.02
 
 
-@pytest.fixture(scope="module", params=[0, 2], ids=["tiles-by-size", "tiles-256x256"])
+@pytest.fixture(params=[0, 2], ids=["tiles-by-size", "tiles-256x256"])
 def api(gpu_device, request):
-    """Every test runs with the workgroup tile chosen by size (64 or 128 wide at these sizes) and with the 256 x 256
-    tile that large products get forced on."""
+    """Every test that takes it runs with the workgroup tile chosen by size (64 or 128 wide at these sizes) and with the 256 x 256
+    tile that large products get forced on.  Function scope: the tests between that do not take it choose by size."""
     from paper_2507_01299_amd import api as A
     A.lib()
     A.set_tuning(10, request.param)
-    yield A
-    A.set_tuning(10, 0)
+    try:
+        yield A
+    finally:
+        A.set_tuning(10, 0)
 
 
 def _ordered(bits: np.ndarray) -> np.ndarray:
@@ -145,21 +147,39 @@ def test_residual_adapter_matches_oracle(api, dtype, d):
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("n", [2016, 2017, 2049, 2250])
 def test_products_of_few_tiles_and_long_sums(gpu_device, dtype, n):
-    """From 64 k-tiles of 32 on (2017 tokens are the first that need them) a tile's waves share them: one and two tiles of
-    256 x 256 (520 wide, so mirrored tiles as well), their last parts 8 wide, k-tiles that end short, counts that no wave's
-    share divides.  Folds and adapters reach the same length with their term pairs."""
+    """From 64 k-tiles of 32 on (2017 tokens are the first that need them) a tile's waves share them.  A second moment 520 wide is six
+    tiles of 256 x 256 (mirrored ones among them), their last parts 8 wide; folds of 1000 to 1032 x 72 are four or five, an adapter of 1000 or 1008
+    is sixteen; k-tiles that end short, counts that no wave's share divides.  Tiles of 128 add up each element in one chain, as parts of
+    64 do whose waves do not share: sums in four parts have other bits somewhere."""
     from paper_2507_01299_amd import api
     d = 520
     print(f"few tiles n={n} dtype={dtype}", flush=True)
     xb, x = _calibration(n, d, 41, dtype)
+    X = to_dev(xb, dtype)
     C = torch.full((d, d), 7.0, dtype=torch.float32, device="cuda:0")
     for add in (False, True):
-        api.second_moment(to_dev(xb, dtype), C, dtype, accumulate=add)
+        api.second_moment(X, C, dtype, accumulate=add)
     torch.cuda.synchronize()
     got, want = C.cpu().numpy().astype(np.float64), 2 * (x.T @ x)
     sc = np.sqrt(np.diag(want))
     assert np.all(np.abs(got - want) <= SM_TOL * sc[:, None] * sc[None, :] + 1e-30)
     assert np.array_equal(got, got.T)
+    one, chain = torch.empty_like(C), torch.empty_like(C)
+    api.second_moment(X, one, dtype)
+    api.set_tuning(10, 1)
+    try:
+        api.second_moment(X, chain, dtype)
+        torch.cuda.synchronize()
+    finally:
+        api.set_tuning(10, 0)
+    assert torch.equal(one, chain) == (n <= 2016)
+    # an infinity and a NaN reach their rows and columns and nothing else
+    X2, bad = X.clone(), torch.empty_like(C)
+    X2[5, 3], X2[n - 1, d - 1] = float("inf"), float("nan")
+    api.second_moment(X2, bad, dtype)
+    keep = [c for c in range(d) if c not in (3, d - 1)]
+    assert torch.equal(bad[keep][:, keep], one[keep][:, keep])
+    assert not torch.isfinite(bad[3]).any() and torch.isnan(bad[d - 1]).all() and torch.isnan(bad[:, d - 1]).all()
     w = 1000 + n % 64 // 8 * 8                     # 32 k-tiles or more a pass, the last one short
     Q, scr = _rotation32(w, 43), api.OfflineScratch(w, dtype)
     Qd, wb = torch.from_numpy(Q).cuda(), O.encode16(synth.gaussian_weight(w, 72, 47), dtype)
@@ -168,10 +188,14 @@ def test_products_of_few_tiles_and_long_sums(gpu_device, dtype, n):
     api.fold_input(Qd, to_dev(wb, dtype), out, dtype, scr)
     outT = torch.zeros(72, w, dtype=t, device="cuda:0")
     api.fold_output(to_dev(np.ascontiguousarray(wb.T), dtype), Qd, outT, dtype, scr)
+    Qn = _rotation32(w, 53)
+    ad = torch.zeros(w, w, dtype=t, device="cuda:0")
+    api.residual_adapter(Qd, torch.from_numpy(Qn).cuda(), ad, dtype, scr)
     torch.cuda.synchronize()
     norms = np.linalg.norm(w64, axis=0)
     _check_stored(to_bits(out), O.fold_input_side(Q.astype(np.float64), w64), dtype, "Q^T W", norms[None, :])
     _check_stored(to_bits(outT), O.fold_output_side(w64.T, Q.astype(np.float64)), dtype, "W Q", norms[:, None])
+    _check_stored(to_bits(ad), O.residual_adapter(Q.astype(np.float64), Qn.astype(np.float64)), dtype, "Q_l^T Q_next", 1.0)
 
 
 @pytest.mark.parametrize("what,d,other,dtype", [
@@ -619,7 +643,7 @@ def test_terms_of_a_rotation_with_infinities_and_nan(gpu_device, dtype, d):
     assert np.isnan(O.decode16(got[cols], dtype)).all()
     # f16: of 64 Q >= 1 the two terms leave out at most 2^-23 of the value, its last place is at least 2^-11 of it: on both sides of a
     # tie 2 * 2^-23 / 2^-11 = 4.9e-4 of the entries may round the other way (below 2^-6 the second term would be subnormal)
-    want = O.encode16(Q[pick].astype(np.float64).T[clean], dtype)
+    want = O.encode16(Q[pick][:, clean].T.astype(np.float64), dtype)
     step = np.abs(_ordered(got[clean]) - _ordered(want))
     assert step.max() <= (1 if dtype == "f16" else 0) and (step != 0).mean() <= 1e-3
 
