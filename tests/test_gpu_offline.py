@@ -198,6 +198,69 @@ def test_products_of_few_tiles_and_long_sums(gpu_device, dtype, n):
     _check_stored(to_bits(ad), O.residual_adapter(Q.astype(np.float64), Qn.astype(np.float64)), dtype, "Q_l^T Q_next", 1.0)
 
 
+@pytest.mark.parametrize("what,d,other,dtype", [("moment", 1288, 16400, "bf16"), ("W Q", 2504, 264, "f16"), ("W Q", 2504, 264, "bf16")])
+def test_shared_sums_of_17_to_32_tiles(gpu_device, what, d, other, dtype):
+    """More than 16 tiles whose waves share the k-tiles: a second moment of 21 tiles with 513 k-tiles (two rounds of workgroups), W Q of
+    20 tiles whose lower half is 8 rows high (one round)."""
+    from paper_2507_01299_amd import api
+    print(f"shared sums {what} d={d} other={other} dtype={dtype}", flush=True)
+    rng, outs = np.random.default_rng(d), []
+    xb = O.encode16(rng.standard_normal((other, d)), dtype)
+    x, X = O.decode16(xb, dtype), to_dev(xb, dtype)
+    Q = rng.standard_normal((d, d)).astype(np.float32) if what == "W Q" else None
+    for tile in (0, 1):
+        api.set_tuning(10, tile)
+        try:
+            if what == "moment":
+                outs.append(torch.full((d, d), 7.0, dtype=torch.float32, device="cuda:0"))
+                api.second_moment(X, outs[-1], dtype)
+            else:
+                outs.append(torch.zeros(other, d, dtype=X.dtype, device="cuda:0"))
+                api.fold_output(X, torch.from_numpy(Q).cuda(), outs[-1], dtype, api.OfflineScratch(d, dtype))
+            torch.cuda.synchronize()
+        finally:
+            api.set_tuning(10, 0)
+    assert not torch.equal(*outs)
+    if what == "moment":
+        got, want = outs[0].cpu().numpy().astype(np.float64), x.T @ x
+        sc = np.sqrt(np.diag(want))
+        assert np.all(np.abs(got - want) <= SM_TOL * sc[:, None] * sc[None, :])
+        assert np.array_equal(got, got.T)
+    else:
+        scale = np.linalg.norm(x, axis=1)[:, None] * np.linalg.norm(Q.astype(np.float64), axis=0)[None, :]
+        _check_stored(to_bits(outs[0]), O.fold_output_side(x, Q.astype(np.float64)), dtype, "W Q", scale)
+
+
+def test_tiles_left_over_from_whole_rounds_share_long_sums(gpu_device):
+    """A second moment 7944 wide is 32 x 33 / 2 = 528 tiles of 256 x 256: two rounds and 16 tiles left over, which are numbered from 512 on, some
+    of them above the diagonal, and share their 65 k-tiles.  Every element against one chain per element, the last columns and drawn ones
+    against 64 bits; accumulated to themselves."""
+    from paper_2507_01299_amd import api
+    n, d, dtype = 2049, 7944, "bf16"
+    print(f"left over tiles n={n} d={d}", flush=True)
+    rng = np.random.default_rng(61)
+    xb = O.encode16(rng.standard_normal((n, d), dtype=np.float32).astype(np.float64), dtype)
+    x, X, outs = O.decode16(xb, dtype), to_dev(xb, dtype), []
+    for tile in (0, 1):
+        api.set_tuning(10, tile)
+        try:
+            outs.append(torch.full((d, d), 7.0, dtype=torch.float32, device="cuda:0"))
+            for add in (False, True):
+                api.second_moment(X, outs[-1], dtype, accumulate=add)
+            torch.cuda.synchronize()
+        finally:
+            api.set_tuning(10, 0)
+    assert torch.equal(outs[0], outs[0].T)
+    diag = 2 * np.einsum("ij,ij->j", x, x)
+    sc = torch.from_numpy(np.sqrt(diag)).cuda()
+    assert bool(((outs[0] - outs[1]).abs().double() <= SM_TOL * sc[:, None] * sc[None, :]).all())
+    other = (outs[0] != outs[1]).nonzero()
+    assert len(other) and int(other.min()) >= 20 * 256 and bool(((other // 256)[:, 0] != (other // 256)[:, 1]).any())
+    cols = np.unique(np.concatenate([np.arange(d - 300, d), rng.choice(d, 40)]))
+    got = outs[0][:, torch.from_numpy(cols).cuda()].cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - 2 * (x.T @ x[:, cols])) <= SM_TOL * np.sqrt(diag[:, None] * diag[cols][None, :]))
+
+
 @pytest.mark.parametrize("what,d,other,dtype", [
     ("moment", 1536, 2048, "bf16"), ("moment", 1792, 2100, "f16"), ("moment", 5880, 2049, "bf16"), ("Q^T W", 1032, 904, "f16"),
     ("Q^T W", 704, 1400, "bf16"), ("W Q", 1288, 1032, "f16"), ("adapter", 1280, 0, "bf16")])
@@ -490,8 +553,8 @@ def _spread(rng, lines, lo, hi):
     return 2.0 ** rng.integers(lo, hi + 1, size=lines).astype(np.float64)
 
 
-@pytest.mark.parametrize("tile", [1, 2])
-@pytest.mark.parametrize("d,other", [(8, 8), (264, 520), (520, 136)])
+@pytest.mark.parametrize("tile", [0, 1, 2])
+@pytest.mark.parametrize("d,other", [(8, 8), (264, 520), (520, 136), (1000, 72)])
 def test_bf16_contractions_over_wide_exponents(gpu_device, tile, d, other):
     """bf16 folds and adapters whose lines' magnitudes lie up to 2^120 apart, elements of a line up to 2^60 apart, with a line of zeros,
     one of bf16 subnormals, infinities and NaN.  The bounds are those of the other tests here; they scale with each line's norm, so
