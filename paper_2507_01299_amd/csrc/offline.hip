@@ -468,6 +468,11 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
 // barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 29).
 // Whole calls, us, quarters / shared k-tiles: second moment 5000 x 1024 f16 29.0 / 22.6, 2048 x 1024 (64 k-tiles) 14.4 / 12.0, fold
 // 2048 x 512 f16 30.8 / 25.8, adapter 1024 bf16 46.8 / 38.4.  shares_chain says which products take it.
+// The line at 64 k-tiles is not one of speed: sharing is level at 16 k-tiles and faster from 24 on (second moment 512 wide, 512 / 768 / 1024 /
+// 2016 tokens: 6.90 / 8.03 / 9.08 / 13.7 in quarters, 7.01 / 7.77 / 8.47 / 11.4 shared).  Sums on the matrix cores are not symmetric under
+// negation, and sums in four parts are two to five times less so (entries of Q^T W that round the other way for -Q, quarters / shared:
+// f16 256 x 704 4 / 11, 1024 x 1024 92 / 191, bf16 2048 x 256 11 / 60): at 16 or 24 the flipped eigenvectors of a 256-wide layer reach its output's last
+// bits at batch 1, where they did not before.
 constexpr int kSharedChain = 64;   // k-tiles of all term pairs from which the four waves share them
 constexpr int kSmallSide = 64;
 constexpr int kSmallStages = 4;    // k-tiles in a wave's ring
@@ -743,7 +748,9 @@ hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s
 }
 
 // Time of `count` 256 x 256 tiles on the chip by workgroup tiles of 64 mi, in rounds (the time of one 256 x 256 tile per
-// compute unit), from the rates measured on products that fill the chip: 1.25 / 0.9 / 0.5 PFLOP/s for 256 / 128 / 64.
+// compute unit).  Whole calls by tiles of 64 / 128 / 256, us, Q^T W 2048 deep, f16: 16 tiles 26.9 / 44.5 / 88.1, 32 41.3 / 46.6 / 87.7, 40 59.4 /
+// 46.7 / 86.8, 64 70.8 / 52.6 / 89.7, 128 128 / 81.2 / 98.2, 136 145 / 112 / 97.6, 256 244 / 151 / 127; the lines that follow, 32 and 128 tiles, are the same for
+// bf16, W Q and adapters.  (Second moments of 129 to about 200 tiles would take less in tiles of 128: 136 tiles, 2048 tokens 58.6 / 67.3.)
 double tile_rounds(long count, int mi) {
   if (mi == 4) return static_cast<double>((count + 255) / 256);
   if (mi == 2) return count <= 64 ? 0.5 : 0.7 * ((count + 127) / 128);   // one, two workgroups per compute unit

@@ -447,8 +447,10 @@ def test_eigenvector_signs_do_not_reach_the_layer_output(api, monkeypatch, dtype
     Flipping the sign of a column of Q negates channel i of h and row i of Q^T W together, the Top-K
     compares magnitudes, and negation is exact in every format used: with an explicit rotation the layer
     output must keep its bits; with the rotations absorbed the input and output live in the rotated basis,
-    so both simply carry the signs of the attention basis (to the bit at batch 1; within one unit in the
-    last place on a few entries in the batched path, see below).  The whole product-side pipeline (second
+    so both simply carry the signs of the attention basis.  The layer's own batch-1 kernels give that to the bit, batched
+    ones within one unit in the last place on a few entries (see below).  The folds run on the matrix cores, whose sums are not
+    symmetric under negation (the test below): at this width and seed none of the few entries that round the
+    other way reaches a batch-1 output, in wider layers some do.  The whole product-side pipeline (second
     moments, eigen-solver, folds, adapters, layer) is run twice, the second time with the solver's columns
     multiplied by seeded signs."""
     from paper_2507_01299_amd import offline
@@ -519,6 +521,29 @@ def test_eigenvector_signs_do_not_reach_the_layer_output(api, monkeypatch, dtype
     same(flip["explicit"][0], plain["explicit"][0], "explicit form: output changed with the signs")
     same(flip["absorbed"][0], plain["absorbed"][0].float() * sa, "absorbed form: output is not the signed one")
     assert float(plain["absorbed"][0].float().abs().max()) > 0.0
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("d,other", [(256, 704), (1024, 1024), (2048, 4352)])
+def test_folds_by_a_negated_rotation(gpu_device, dtype, d, other):
+    """Q^T W and W Q by -Q are those by Q with the other sign, up to the rounding of the sums: tiles of 64 in quarters, the same with
+    shared k-tiles, whole rounds of 256 x 256.  Up to 1 in 2000 entries rounds the other way (f16 4096 x 4096: 8563 of 16.8 million)."""
+    from paper_2507_01299_amd import api
+    print(f"negated rotation dtype={dtype} d={d} other={other}", flush=True)
+    Q = _rotation32(d, 3)
+    wb = O.encode16(synth.gaussian_weight(d, other, 5), dtype)
+    W, WT, sc = to_dev(wb, dtype), to_dev(np.ascontiguousarray(wb.T), dtype), api.OfflineScratch(d, dtype)
+    outs = []
+    for sign in (1.0, -1.0):
+        Qd, a, b = torch.from_numpy(Q * np.float32(sign)).cuda(), torch.zeros_like(W), torch.zeros_like(WT)
+        api.fold_input(Qd, W, a, dtype, sc)
+        api.fold_output(WT, Qd, b, dtype, sc)
+        outs.append((to_bits(a), to_bits(b)))
+    norms = np.linalg.norm(O.decode16(wb, dtype), axis=0)
+    for (plain, flipped), what, scale in zip(zip(*outs), ("Q^T W", "W Q"), (norms[None, :], norms[:, None])):
+        frac, _ = _check_stored(flipped, -O.decode16(plain, dtype), dtype, what, scale)
+        # either sum is within about sqrt(2 d) 2^-24 of exact, relative to the entry's norm; a rounding step is 2^-11 of it or more
+        assert frac <= 2 * np.sqrt(2 * d) * 2.0 ** -24 / 2.0 ** -11
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
