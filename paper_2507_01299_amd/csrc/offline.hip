@@ -22,16 +22,18 @@
 //  * The terms of a fold go through k together (TERMS): the weight's tile is loaded, and read from LDS, once for all of them.
 //    Two f16 terms: three operands a k-tile instead of four; 4096 x 22016 1315 -> 1233 us, 11008 x 4096 (W Q) 698 -> 646, 1024 x
 //    16384 76 -> 72.  Three bf16 terms: four operands instead of six, k-tiles of 16 in five stages of 32 KiB, a barrier per 48
-//    products instead of 32; whole calls 4096 x 28672 2229 -> 2017 us, 14336 x 4096 (W Q) 1239 -> 1150 (with the split of the rotation).
+//    products instead of 32; whole calls 4096 x 28672 2229 -> 2000 us, 14336 x 4096 (W Q) 1239 -> 1145 (with the split of the rotation).
 //  * X^T X is symmetric: only tiles on and above the diagonal are computed; a tile above it is stored twice.
 //  * Whole rounds of 256 tiles (one per compute unit) run in 256 x 256 tiles; what is left over runs as 128 x 128 or 64 x 64
 //    parts in a second launch when that is shorter than another round (launch_shape).
 // What bounds it: the matrix cores at the clock that the card's power allows.  A loop of nothing but these instructions on
 // random operands reaches 1.63 PFLOP/s here (2.37 on zeros).  Issued in whole rounds (kernel trace): 4096 x
-// 28672 x 4096 bf16, 3 terms, 1.41 - 1.43 PFLOP/s (1.29 with a pass per term); f16 folds of a 4096-wide layer 1.22 - 1.31, its adapter 1.23;
-// second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB, 736 -> 313 - 333 + 29 us (29, 36 before the waves shared k-tiles, for the 16 tiles after
-// the last whole round; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy
-// 69 - 79 % of the cycles in f16 folds, 64 - 73 % with a pass per term pair; LDS bank conflicts are under 1 % of its active cycles.  The design before (8 waves of 128 x 64,
+// 28672 x 4096 bf16, 3 terms, 1.43 PFLOP/s (2016 us; 1.29 with a pass per term); f16 folds of a 4096-wide layer 1.21 - 1.29, its adapter 1.22;
+// second moment of 5000 x 8192 bf16, whose two rounds also store 268 MB: 311 us in the first traced passes, 350 - 399 once the card is warm, and
+// 26 - 35 for the 16 tiles left over (36 - 38 before the waves shared k-tiles); untraced the whole call takes 327 (736 before the
+// large tile; C stored in 16-byte pieces through LDS instead of from registers saved 45).  The matrix cores are busy 81 % of the cycles with three
+// bf16 terms together, 69 - 79 % in f16 folds, 73 % in its adapter's passes, 59 % in the two rounds of that second moment, 20 % in parts of 64 that share
+// the k-tiles (a chain's latency); LDS bank conflicts are under 1 % of the large tile's active cycles.  The design before (8 waves of 128 x 64,
 // staging registers, two LDS stages) kept them busy 34 % and gave the XCDs of a symmetric product uneven shares.
 #include <type_traits>
 
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(256, MI == 4 ? 1 : 2) void contraction_kernel(Contr
 // Few tiles: a workgroup owns a 64 x 64 tile, and its four waves share the k-tiles instead of the tile.  What bounds such
 // products is not the matrix cores but each wave's chain over k, so a wave takes every fourth k-tile through a ring of its own
 // in LDS, with no barrier until the four sums meet, and multiplies the whole 64 x 64 (with a 32 x 32 quarter per wave and a
-// barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 29).
+// barrier per k-tile, 16 tiles of 256 x 256 left over from a second moment of 5000 x 8192 took 36 us, 0.23 us a k-tile; now 26 - 32).
 // Whole calls, us, quarters / shared k-tiles: second moment 5000 x 1024 f16 29.0 / 22.6, 2048 x 1024 (64 k-tiles) 14.4 / 12.0, fold
 // 2048 x 512 f16 30.8 / 25.8, adapter 1024 bf16 46.8 / 38.4.  shares_chain says which products take it.
 // The line at 64 k-tiles is not one of speed: sharing is level at 16 k-tiles and faster from 24 on (second moment 512 wide, 512 / 768 / 1024 /
@@ -661,7 +663,7 @@ __device__ __forceinline__ uint32_t term_bits(BF16, float f) {
 }
 
 // fp32 -> NT 16-bit terms with x * pre_scale = t0 + t1 (+ t2) up to the last term's rounding.  HBM-bound for wide rotations, 4 bytes in
-// and 2 NT out per entry (4096 x 4096 in three terms: 49.8 us with one entry a lane, 28.8 with eight), latency-bound for narrow ones, where
+// and 2 NT out per entry (4096 x 4096 in three terms: 49.8 us with one entry a lane, 28.8 with eight, 27.7 with four), latency-bound for narrow ones, where
 // a lane's chain counts: bf16 fold 512 x 512 / adapter 256, whole calls, us: one entry 14.4 / 15.5, eight 15.0 / 16.7.  Four entries (16 bytes
 // in, n is a multiple of 64) are as fast as the better of the two: 14.4 / 15.6, adapter 4096 bf16 660 (eight: 659, one: 702).
 template <typename T, int NT, int THREADS>
