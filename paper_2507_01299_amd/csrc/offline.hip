@@ -700,10 +700,11 @@ void launch_split(const float* src, uint16_t* dst, long n, float pre_scale, hipS
 }  // namespace
 
 hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre_scale, bool bf16, hipStream_t s) {
-  // One wave a workgroup up to 1024 x 1024: whole calls, us, with four waves / one: W Q 2048 x 1024 f16 24.8 / 23.3, bf16 33.6 / 31.4, Q^T W 1024 x
-  // 512 bf16 22.3 / 20.1 (level at other widths below; why the placement matters at 1024 was not found).  Above, four: adapter 2048 f16
-  // 74.5 / 75.8, Q^T W 1152 x 512 17.9 / 18.5.  (A run-time size would cost 0.4 us a launch for the implicit arguments.)
-  const bool narrow = n <= 1L << 20;
+  // Narrow rotations: one wave a workgroup.  Whole calls, us, four waves / one: f16 Q^T W 256 x 2048 8.3 / 8.1, level at 512; bf16 W Q 2048 x 1024
+  // 33.6 / 31.5, Q^T W 1024 x 512 22.3 / 20.1 (why the placement matters at 1024 was not found), level at other widths.  f16 above 512: adapter
+  // 976 26.7 / 27.3, Q^T W 768 x 600 14.9 / 15.2, 1152 x 512 17.9 / 18.5, W Q 992 x 600 17.0 / 17.4, against W Q 2048 x 1024 24.8 / 23.2 alone.  (A
+  // run-time size would cost 0.4 us a launch for the implicit arguments.)
+  const bool narrow = n <= (bf16 ? 1L << 20 : 1L << 18);
   if (bf16) narrow ? launch_split<BF16, 3, 64>(src, dst, n, pre_scale, s) : launch_split<BF16, 3, 256>(src, dst, n, pre_scale, s);
   else narrow ? launch_split<F16, 2, 64>(src, dst, n, pre_scale, s) : launch_split<F16, 2, 256>(src, dst, n, pre_scale, s);
   return hipGetLastError();
