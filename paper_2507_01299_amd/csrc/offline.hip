@@ -726,10 +726,11 @@ bool shares_chain(const ContractionArgs& a, long first, long count) {
   if (count <= 16 || chain >= (a.symmetric != 0 && count > 24 ? 1024 : 512)) return true;
   constexpr int kParts = kBigTile / kSmallSide, kTileParts = kParts * kParts;
   const int share = static_cast<int>(count) * kTileParts / 8;    // parts of an XCD, in the kernels' numbering
-  int busy = 0;
-  for (int part = 0; part < share * 8; ++part) {
-    if (part % share == 0) busy = 0;
-    const TileAt at = tile_of(static_cast<int>(first) + part / kTileParts, a.tiles_m, a.tiles_n, a.symmetric != 0);
+  TileAt at{};
+  for (int part = 0, of_share = 0, busy = 0; part < share * 8; ++part, ++of_share) {
+    if (of_share == share) of_share = busy = 0;
+    // (once per tile: tile_of walks the bands before it, of which tall products have many)
+    if (part % kTileParts == 0) at = tile_of(static_cast<int>(first) + part / kTileParts, a.tiles_m, a.tiles_n, a.symmetric != 0);
     const int m0 = at.m * kBigTile + part % kTileParts / kParts * kSmallSide, n0 = at.n * kBigTile + part % kParts * kSmallSide;
     if (m0 < a.M && n0 < a.N && ++busy > 32) return false;
   }
