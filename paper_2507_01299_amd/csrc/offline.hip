@@ -666,10 +666,16 @@ __device__ __forceinline__ uint32_t term_bits(BF16, float f) {
 // and 2 NT out per entry (4096 x 4096 in three terms: 49.8 us with one entry a lane, 28.8 with eight, 27.7 with four), latency-bound for narrow ones, where
 // a lane's chain counts: bf16 fold 512 x 512 / adapter 256, whole calls, us: one entry 14.4 / 15.5, eight 15.0 / 16.7.  Four entries (16 bytes
 // in, n is a multiple of 64) are as fast as the better of the two: 14.4 / 15.6, adapter 4096 bf16 660 (eight: 659, one: 702).
-template <typename T, int NT, int THREADS>
-__global__ __launch_bounds__(THREADS) void split_terms_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long n,
+// DEALT: pieces of 256 entries, a wave's, go round the eight XCDs one by one (workgroup b runs on XCD b % 8), not four at a time: of a
+// rotation 1024 wide each XCD then writes one column panel of 256 and can find it in its own L2.  Whole calls, us, four at a time / dealt: f16 W Q 2048 x
+// 1024 24.9 / 23.0, Q^T W 1024 x 512 16.4 / 14.9, W Q 264 x 2048 27.1 / 23.8 (one entry a lane, which dealt them too: 23.6, 17.6, 31.5); elsewhere between
+// 3 % faster and 1.5 % slower (Q^T W 1536 x 512 22.1 / 22.5).
+template <typename T, int NT, int WAVES, bool DEALT>
+__global__ __launch_bounds__(WAVES * 64) void split_terms_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, long n,
                                                           float pre_scale) {
-  const long i = (static_cast<long>(blockIdx.x) * THREADS + threadIdx.x) * 4;
+  const long b = blockIdx.x, wave = threadIdx.x >> 6;
+  const long piece = DEALT ? (b >> 3) * (8 * WAVES) + wave * 8 + (b & 7) : b * WAVES + wave;
+  const long i = piece * 256 + (threadIdx.x & 63) * 4;
   if (i >= n) return;
   const float4 v = *reinterpret_cast<const float4*>(src + i);
   float r[4] = {v.x * pre_scale, v.y * pre_scale, v.z * pre_scale, v.w * pre_scale};
@@ -691,22 +697,24 @@ int contraction_terms(bool bf16) { return bf16 ? 3 : 2; }
 
 namespace {
 
-template <typename T, int NT, int THREADS>
+template <typename T, int NT, int WAVES, bool DEALT>
 void launch_split(const float* src, uint16_t* dst, long n, float pre_scale, hipStream_t s) {
-  const unsigned grid = static_cast<unsigned>((n + 4 * THREADS - 1) / (4 * THREADS));
-  hipLaunchKernelGGL((split_terms_kernel<T, NT, THREADS>), dim3(grid), dim3(THREADS), 0, s, src, dst, n, pre_scale);
+  constexpr long kRound = 256L * WAVES * (DEALT ? 8 : 1);        // entries of the workgroups that share out a run of pieces
+  const unsigned grid = static_cast<unsigned>((n + kRound - 1) / kRound * (DEALT ? 8 : 1));
+  hipLaunchKernelGGL((split_terms_kernel<T, NT, WAVES, DEALT>), dim3(grid), dim3(64 * WAVES), 0, s, src, dst, n, pre_scale);
 }
 
 }  // namespace
 
 hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre_scale, bool bf16, hipStream_t s) {
-  // Narrow rotations: one wave a workgroup.  Whole calls, us, four waves / one: f16 Q^T W 256 x 2048 8.3 / 8.1, level at 512; bf16 W Q 2048 x 1024
-  // 33.6 / 31.5, Q^T W 1024 x 512 22.3 / 20.1 (why the placement matters at 1024 was not found), level at other widths.  f16 above 512: adapter
-  // 976 26.7 / 27.3, Q^T W 768 x 600 14.9 / 15.2, 1152 x 512 17.9 / 18.5, W Q 992 x 600 17.0 / 17.4, against W Q 2048 x 1024 24.8 / 23.2 alone.  (A
-  // run-time size would cost 0.4 us a launch for the implicit arguments.)
-  const bool narrow = n <= (bf16 ? 1L << 20 : 1L << 18);
-  if (bf16) narrow ? launch_split<BF16, 3, 64>(src, dst, n, pre_scale, s) : launch_split<BF16, 3, 256>(src, dst, n, pre_scale, s);
-  else narrow ? launch_split<F16, 2, 64>(src, dst, n, pre_scale, s) : launch_split<F16, 2, 256>(src, dst, n, pre_scale, s);
+  // Up to 512 x 512 one wave a workgroup (f16 Q^T W 256 x 2048, four waves / one: 8.3 / 8.1 us a call, level at 512), above four, whose launch is
+  // shorter (f16 adapter 976 26.7 / 27.3, W Q 992 x 600 17.0 / 17.4).  Dealt above 512 x 512, but for bf16 only up to 1024 x 1024: Q^T W
+  // 1536 x 512 28.5 four at a time, 29.0 dealt, 3072 x 512 80.3 / 81.0 (f16 22.3 / 22.3, 54.7 / 54.7, W Q 2048 x 512 25.3 / 24.4).
+  // (A run-time size would cost 0.4 us a launch for the implicit arguments.)
+  if (n <= 1L << 18) bf16 ? launch_split<BF16, 3, 1, false>(src, dst, n, pre_scale, s) : launch_split<F16, 2, 1, false>(src, dst, n, pre_scale, s);
+  else if (!bf16) launch_split<F16, 2, 4, true>(src, dst, n, pre_scale, s);
+  else if (n <= 1L << 20) launch_split<BF16, 3, 4, true>(src, dst, n, pre_scale, s);
+  else launch_split<BF16, 3, 4, false>(src, dst, n, pre_scale, s);
   return hipGetLastError();
 }
 
