@@ -728,9 +728,15 @@ namespace {
 // (20 tiles, up to 28 parts) 87.7 / 53.1.  Two rounds pay only for sums so long that the shorter chain outweighs them: second moment 1536
 // wide of 16384 tokens (512 k-tiles) 117 / 108, of 32768 259 / 208, W Q bf16 256 x 8192 (768) 406 / 367; with more than 24 tiles of a
 // second moment later (1792 wide: 16384 tokens 102 / 108, 32768 207 / 206, 65536 469 / 399).
+// W Q of up to 16 tiles reads its weight along k, 64 bytes a row and k-tile.  Where rows are no whole number of those, pieces straddle cache lines, and
+// sharing gains only if the XCDs' equal shares of the parts end with the tiles' columns (columns in fours).  Quarters / shared: bf16 1280 x 680
+// 19.6 / 20.5, 768 x 1096 27.3 / 29.7, f16 768 x 1048 19.5 / 20.6, 200 x 2312 34.7 / 36.5; in fours 520 x 904 bf16 23.0 / 21.5, 520 x 1016 f16 18.1 /
+// 17.2, 200 x 2008 31.0 / 26.6; whole pieces 1280 x 704 bf16 19.4 / 17.7, 200 x 1088 f16 19.2 / 17.3.  Q^T W of such sizes gains or is level.
+template <bool A_KMAJOR>
 bool shares_chain(const ContractionArgs& a, long first, long count) {
   const int chain = (a.Kd + kKTile - 1) / kKTile * a.npairs;
   if (chain < kSharedChain) return false;
+  if (!A_KMAJOR && count <= 16 && a.Kd % kKTile != 0 && a.tiles_n % 4 != 0) return false;
   if (count <= 16 || chain >= (a.symmetric != 0 && count > 24 ? 1024 : 512)) return true;
   constexpr int kParts = kBigTile / kSmallSide, kTileParts = kParts * kParts;
   const int share = static_cast<int>(count) * kTileParts / 8;    // parts of an XCD, in the kernels' numbering
@@ -753,7 +759,7 @@ hipError_t launch_tiles(ContractionArgs a, long first, long count, hipStream_t s
   if (grid > 0x7FFFFFFFL) return hipErrorInvalidValue;
   a.tile0 = static_cast<int>(first);
   a.tiles = static_cast<int>(parts);
-  if (MI == 1 && shares_chain(a, first, count))
+  if (MI == 1 && shares_chain<A_KMAJOR>(a, first, count))
     hipLaunchKernelGGL((small_contraction_kernel<T, A_KMAJOR>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((contraction_kernel<T, A_KMAJOR, MI, TERMS>), dim3(static_cast<unsigned>(grid)), dim3(256), 0, s, a);
   return hipGetLastError();

@@ -303,6 +303,30 @@ def test_products_of_more_than_one_round_of_small_tiles(gpu_device, what, d, oth
     assert torch.equal(outs[0], outs[1]), int((outs[0] != outs[1]).sum())
 
 
+@pytest.mark.parametrize("d,rows,dtype,shares", [
+    (680, 1280, "bf16", False), (696, 72, "bf16", False), (1048, 768, "f16", False), (2312, 200, "bf16", False),
+    (704, 1280, "bf16", True), (904, 520, "bf16", True), (1016, 1000, "f16", True), (1056, 264, "f16", True), (2008, 200, "f16", True)])
+def test_products_that_read_the_weight_along_k(gpu_device, d, rows, dtype, shares):
+    """W Q of few tiles shares long sums only where its rows are whole 64-byte pieces or the tiles' columns come in fours; otherwise
+    each element is one chain, with the bits of tiles of 128."""
+    from paper_2507_01299_amd import api
+    print(f"along k d={d} rows={rows} dtype={dtype}", flush=True)
+    Q = _rotation32(d, 3)
+    wb = O.encode16(synth.gaussian_weight(rows, d, 5), dtype)
+    w64, Qd, W = O.decode16(wb, dtype), torch.from_numpy(Q).cuda(), to_dev(wb, dtype)
+    sc, outs = api.OfflineScratch(d, dtype), []
+    for tile in (0, 1):
+        api.set_tuning(10, tile)
+        try:
+            outs.append(torch.full((rows, d), 9.0, dtype=W.dtype, device="cuda:0"))
+            api.fold_output(W, Qd, outs[-1], dtype, sc)
+            torch.cuda.synchronize()
+        finally:
+            api.set_tuning(10, 0)
+    _check_stored(to_bits(outs[0]), O.fold_output_side(w64, Q.astype(np.float64)), dtype, "W Q", np.linalg.norm(w64, axis=1)[:, None])
+    assert torch.equal(outs[0], outs[1]) == (not shares)
+
+
 @pytest.mark.parametrize("d", [8, 104, 112, 120])
 def test_wide_products_with_a_narrow_bf16_rotation(gpu_device, d):
     """W Q of a weight with 33000 rows (129 tiles of 256 x 256, all in the large tile) by rotations on both sides of the width from which
