@@ -708,12 +708,13 @@ void launch_split(const float* src, uint16_t* dst, long n, float pre_scale, hipS
 
 hipError_t launch_split_terms(const float* src, uint16_t* dst, long n, float pre_scale, bool bf16, hipStream_t s) {
   // Up to 512 x 512 one wave a workgroup (f16 Q^T W 256 x 2048, four waves / one: 8.3 / 8.1 us a call, level at 512), above four, whose launch is
-  // shorter (f16 adapter 976 26.7 / 27.3, W Q 992 x 600 17.0 / 17.4).  Dealt above 512 x 512, but for bf16 only up to 1024 x 1024: Q^T W
-  // 1536 x 512 28.5 four at a time, 29.0 dealt, 3072 x 512 80.3 / 81.0 (f16 22.3 / 22.3, 54.7 / 54.7, W Q 2048 x 512 25.3 / 24.4).
+  // shorter (f16 adapter 976 26.7 / 27.3, W Q 992 x 600 17.0 / 17.4).  Dealt above 512 x 512, but for bf16 only up to 1448 x 1448: Q^T W
+  // 1536 x 512 28.5 four at a time, 29.0 dealt, 3072 x 512 80.3 / 81.0 (f16 22.3 / 22.3, 54.7 / 54.7, W Q 2048 x 512 25.3 / 24.4), against means over 16
+  // allocations of W Q 520 x 1288 38.6 / 38.2, 560 x 1288 40.6 / 38.3, 520 x 1352 46.4 / 45.9 and Q^T W 1280 x 512 26.1 / 26.3.
   // (A run-time size would cost 0.4 us a launch for the implicit arguments.)
   if (n <= 1L << 18) bf16 ? launch_split<BF16, 3, 1, false>(src, dst, n, pre_scale, s) : launch_split<F16, 2, 1, false>(src, dst, n, pre_scale, s);
   else if (!bf16) launch_split<F16, 2, 4, true>(src, dst, n, pre_scale, s);
-  else if (n <= 1L << 20) launch_split<BF16, 3, 4, true>(src, dst, n, pre_scale, s);
+  else if (n <= 1L << 21) launch_split<BF16, 3, 4, true>(src, dst, n, pre_scale, s);
   else launch_split<BF16, 3, 4, false>(src, dst, n, pre_scale, s);
   return hipGetLastError();
 }

@@ -734,9 +734,9 @@ def test_bf16_contractions_hold_every_entry(gpu_device, tile, d, other):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("d", [8, 24, 512, 520, 1024, 1032])
+@pytest.mark.parametrize("d", [8, 24, 512, 520, 1024, 1032, 1448, 1456])
 def test_terms_of_a_rotation_with_infinities_and_nan(gpu_device, dtype, d):
-    """The split of a rotation on both sides of the sizes where its launch changes (512 wide, for bf16 1024 as well), and ones smaller than a workgroup.  Columns of Q with a
+    """The split of a rotation on both sides of the sizes where its launch changes (512 wide, for bf16 1448 as well), and ones smaller than a workgroup.  Columns of Q with a
     NaN (signalling, negative, all bits set: a rounding by addition alone would make infinities or zeros of them) or an infinity make
     rows of Q^T W that are NaN throughout; the others are single entries of Q, times one: their own rounding."""
     from paper_2507_01299_amd import api
